@@ -7,7 +7,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libchunkflow.so")
 HOST_SOURCES = ["planner.cpp"]
-HIP_SOURCES = ["api.hip", "attn_simple.hip", "attn_mfma_fwd.hip", "attn_mfma_bwd.hip"]
+HIP_SOURCES = ["api.hip", "attn_simple.hip", "attn_fp32.hip", "attn_mfma_fwd.hip", "attn_mfma_bwd.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed-fp32 VALU forms are switched off for all device code.
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",

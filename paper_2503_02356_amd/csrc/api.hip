@@ -66,6 +66,19 @@ bool mfma_shape(const cf_attn_fwd_params &p)
 // The MFMA kernels take the row maximum before scaling, which needs a positive scale.
 bool use_mfma(const cf_attn_fwd_params &p) { return mfma_shape(p) && p.softmax_scale > 0.f; }
 
+// The fp32 matrix kernels: every fp32 shape, any scale.  They address the 32 rows of a block with 32-bit byte offsets.
+bool use_f32(const cf_attn_fwd_params &p)
+{
+    constexpr int64_t kMostStride = 1 << 25;         // elements: 31 rows x 4 bytes stay below 2^32
+    return p.dtype == CF_FP32 && !(p.flags & CF_FLAG_SCALAR_KERNELS) && p.q_stride_tok < kMostStride && p.kv_stride_tok < kMostStride;
+}
+bool use_f32(const cf_attn_bwd_params &b) { return use_f32(b.f) && b.do_stride_tok < (1 << 25); }
+
+hipError_t fwd_one(const cf_attn_fwd_params &p, hipStream_t s)
+{
+    return use_mfma(p) ? cf::launch_mfma_fwd(p, s) : use_f32(p) ? cf::launch_f32_fwd(p, s) : cf::launch_simple_fwd(p, s);
+}
+
 int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
 int64_t delta_bytes(const cf_attn_fwd_params &p) { return round_up((int64_t)p.n_q_heads * p.n_tokens * 4, 256); }
@@ -102,7 +115,7 @@ extern "C" int cf_attn_fwd(const cf_attn_fwd_params *p, void *hip_stream)
 {
     if (int rc = check_fwd(p, "cf_attn_fwd", false)) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const hipError_t e = use_mfma(*p) ? cf::launch_mfma_fwd(*p, s) : cf::launch_simple_fwd(*p, s);
+    const hipError_t e = fwd_one(*p, s);
     return e == hipSuccess ? CF_OK : hip_fail("cf_attn_fwd", e);
 }
 
@@ -163,6 +176,8 @@ int bwd_one(const cf_attn_bwd_params *b, const cf::BwdWorkspace &ws, hipStream_t
     hipError_t e = hipSuccess;
     if (use_mfma(b->f)) {
         e = cf::launch_mfma_bwd(*b, ws, s);          // its dQ kernel forms delta itself
+    } else if (use_f32(*b)) {
+        e = cf::launch_f32_bwd(*b, s);               // so does every workgroup of this one
     } else {
         e = cf::launch_delta(*b, ws, s);
         if (e != hipSuccess) return hip_fail(who, e);
@@ -260,7 +275,7 @@ extern "C" int cf_attn_fwd_batch(const cf_attn_fwd_params *params, int32_t n, vo
             e = cf::launch_mfma_fwd_batch(chunks, j - i, s);
         } else {
             j = i + 1;
-            e = use_mfma(params[i]) ? cf::launch_mfma_fwd(params[i], s) : cf::launch_simple_fwd(params[i], s);
+            e = fwd_one(params[i], s);
         }
         if (e != hipSuccess) return hip_fail(who, e);
         i = j;

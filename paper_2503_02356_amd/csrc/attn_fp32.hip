@@ -1,0 +1,418 @@
+// fp32 attention for one chunk on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: fp32 operands and sums, 64 FLOP
+// per clock and SIMD, 32 clocks each), head_dim 64 and 128, any softmax scale.
+//
+// What bounds it: large calls the fp32 matrix rate (157 TFLOP/s) and how evenly the units below fill 256 compute units;
+// small ones the serial chain of a wavefront (a 16 x 16 block of pairs is D / 4 dependent MFMAs per product) and the
+// latency of its loads.  The unit of work is therefore small and split as far as it goes: ONE workgroup of 16 wavefronts
+// owns 16 query rows of a head (forward, dQ) or 16 key rows of a key/value head (dK/dV), its wavefronts take every 16th
+// block of the other side, and their partial results meet in LDS at the end in a fixed order: no atomics, every result
+// has one writer and is bitwise reproducible.  (32-row units on 32x32x2 MFMAs would leave half the chip idle on a
+// 700-row slice of 6 heads: 132 workgroups.)
+// Operands go straight from global memory into registers: a wavefront's blocks are its own, so LDS tiles would not be
+// shared.  What the 16 wavefronts share, the owned rows, is kept in LDS in operand order.
+//
+// Everything is computed with the owned row on the lane axis, as in the bf16 kernels:
+//   forward  S^T = K Q^T              O^T  += V^T P^T           lane % 16 = query
+//   dQ       S^T, dP^T = V dO^T       dQ^T += K^T dS^T          lane % 16 = query
+//   dK/dV    S = Q K^T, dP = dO V^T   dV^T += dO^T P, dK^T += Q^T dS   lane % 16 = key
+// so that P and dS feed the second product from the registers the first one left them in: register i of a 16 x 16
+// result holds row 4 * quarter + i (quarter = lane / 16), which is exactly the contraction index that a lane of that
+// quarter supplies in step i.  The order of the contraction over d, and of the columns of a result, is free: both are
+// chosen so that every global access is a float4.
+//
+// The backward is ONE launch: every workgroup forms delta = <dO, O> of the rows it meets itself (128 FMAs a row next to
+// the MFMAs of four products), so that neither half waits for the other.
+//
+// Measured, forward + backward of a whole step: 13 calls of 1286 tokens, 1 head, D = 64: 762 us -> 122 us; 6 / 2 heads,
+// D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 1.24 ms (before: one wavefront per row, scalar loads; attn_simple.hip).
+#include <hip/hip_runtime.h>
+
+#include "kernels.h"
+#include "mfma_common.h"
+
+namespace cf {
+namespace {
+
+#define CF_GLOBAL __attribute__((address_space(1)))
+
+constexpr int NW = 16;           // wavefronts per workgroup
+constexpr int RB = 16;           // rows per block
+constexpr float kLog2e = 1.44269504088896340736f;
+constexpr float kLn2 = 0.69314718055994530942f;
+
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+template <int D>
+struct Shape {
+    static constexpr int J = D / 16;         // float4 pieces of a row that a lane holds (quarter rows)
+    static constexpr int NC = D / 64;        // 64-wide column groups of a result
+    static constexpr int OS = D + 4;         // row stride of a partial result in LDS (spreads float4 rows over the banks)
+    static constexpr int PART = RB * OS;     // floats of one wavefront's partial result
+    static constexpr int OPERAND = RB * D * 4;   // bytes of 16 staged rows
+};
+template <int D>
+using Acc = f32x4[D / 16];                   // [4 * c + e], register i: column 64 c + 4 * (4 * quarter + i) + e
+
+// Combines over the four lanes that hold the same owned row (lane % 16).
+__device__ __forceinline__ float max_over_quarters(float x)
+{
+    const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return max_with_other_half(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float sum_over_quarters(float x)
+{
+    const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return sum_with_other_half(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+// This lane's quarter of a row: floats 16 j + 4 * quarter + 0..3.
+template <int D>
+__device__ __forceinline__ void load_row(const float *row, int quarter, f32x4 (&f)[D / 16])
+{
+#pragma unroll
+    for (int j = 0; j < D / 16; ++j) f[j] = *(const f32x4 *)(row + 16 * j + 4 * quarter);
+}
+// The 16 owned rows into LDS, in operand order: piece c (floats 4 c .. 4 c + 3) of row r at [c * 16 + r].
+template <int D>
+__device__ __forceinline__ void stage_rows(const float *base, int64_t stride, int row0, int last_row, f32x4 *dst)
+{
+    for (int t = threadIdx.x; t < RB * D / 4; t += NW * 64) {
+        const int r = t / (D / 4), c = t % (D / 4);
+        dst[c * RB + r] = *(const f32x4 *)(base + (int64_t)min(row0 + r, last_row) * stride + c * 4);
+    }
+}
+// rows (A operand, from registers) x owned rows (B operand, from LDS), contraction over d.
+template <int D>
+__device__ __forceinline__ f32x4 row_product(const f32x4 (&a)[D / 16], const f32x4 *b, int lane)
+{
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < D / 16; ++j) {
+        const f32x4 bj = b[j * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = mfma_f32(a[j][e], bj[e], acc);
+    }
+    return acc;
+}
+// Column operands of a 16-row block: whole rows per 16 lanes, step i of the contraction over the rows takes rows
+// 4 * quarter + i, which is where register i of the other operand stands; lane % 16 = m holds columns 64 c + 4 m + e.
+// Rows past last_row (relative to the block's first row, `block`) re-read last_row; the other operand is 0 there.
+// (A scalar base that is known to be global memory and a 32-bit lane offset: a flat load would also wait for LDS.)
+template <int D>
+__device__ __forceinline__ void load_columns(const float *block, unsigned row_bytes, int last_row, int lane, f32x4 (&x)[4][D / 64])
+{
+    const int quarter = lane >> 4, m = lane & 15;
+    const CF_GLOBAL char *base = (const CF_GLOBAL char *)uniform(block);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int c = 0; c < D / 64; ++c)
+            x[i][c] = *(const CF_GLOBAL f32x4 *)(base + ((unsigned)min(4 * quarter + i, last_row) * row_bytes + 16 * m + 256 * c));
+}
+// acc^T += X^T w
+template <int D>
+__device__ __forceinline__ void add_column_product(const f32x4 (&x)[4][D / 64], const f32x4 &w, Acc<D> &acc)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int c = 0; c < D / 64; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[4 * c + e] = mfma_f32(x[i][c][e], w[i], acc[4 * c + e]);
+}
+// A wavefront's transposed result (lane % 16 = owned row) into its part of the LDS scratch.
+template <int D>
+__device__ __forceinline__ void write_part(const Acc<D> &acc, float *part, int lane)
+{
+    const int quarter = lane >> 4, r = lane & 15;
+#pragma unroll
+    for (int c = 0; c < D / 64; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *(f32x4 *)(part + r * Shape<D>::OS + 64 * c + 16 * quarter + 4 * i) =
+                f32x4{acc[4 * c][i], acc[4 * c + 1][i], acc[4 * c + 2][i], acc[4 * c + 3][i]};
+}
+template <int D>
+__device__ __forceinline__ f32x4 sum_parts(const float *parts, int n, int row, int c)
+{
+    f32x4 s = *(const f32x4 *)(parts + row * Shape<D>::OS + c * 4);
+    for (int w = 1; w < n; ++w) s += *(const f32x4 *)(parts + w * Shape<D>::PART + row * Shape<D>::OS + c * 4);
+    return s;
+}
+
+template <int D>
+__global__ __launch_bounds__(NW * 64) void f32_fwd_kernel(cf_attn_fwd_params p)
+{
+    using S = Shape<D>;
+    __shared__ f32x4 qs[S::J * 64];
+    __shared__ __attribute__((aligned(16))) float parts[NW * S::PART];
+    __shared__ float m_s[NW][RB], l_s[NW][RB];
+    const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
+    const int G = p.n_q_heads / p.n_kv_heads, kh = blockIdx.x % p.n_kv_heads, h = kh * G + blockIdx.x / p.n_kv_heads % G;
+    TileLocation loc;
+    if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, RB, blockIdx.x / p.n_q_heads, loc)) return;
+    const int lq = uniform(loc.len), lk = uniform(loc.other_len), off = lk - lq, q0 = uniform(loc.tile_in_seg) * RB;
+    const int rows = min(RB, lq - q0), n_kb = (q0 + rows + off + RB - 1) / RB;
+    const float *q = (const float *)p.q + (int64_t)loc.begin * p.q_stride_tok + (int64_t)h * p.q_stride_head;
+    const float *k = (const float *)p.k + (int64_t)loc.other_begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head;
+    const float *v = (const float *)p.v + (int64_t)loc.other_begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head;
+    const float c2 = p.softmax_scale * kLog2e;
+    const unsigned kv_row_bytes = (unsigned)p.kv_stride_tok * 4;
+    const int amax = q0 + col + off;                 // last visible key of this lane's row
+
+    f32x4 kf[S::J];
+    if (wave < n_kb) load_row<D>(k + (int64_t)min(wave * RB + col, lk - 1) * p.kv_stride_tok, quarter, kf);
+    stage_rows<D>(q, p.q_stride_tok, q0, lq - 1, qs);
+    __syncthreads();
+
+    Acc<D> o;
+#pragma unroll
+    for (int x = 0; x < D / 16; ++x) o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;
+    for (int kb = wave; kb < n_kb; kb += NW) {
+        f32x4 s = row_product<D>(kf, qs, lane);
+        __builtin_amdgcn_sched_barrier(0);           // V takes the registers of K: with both held D = 128 spills
+        f32x4 x[4][S::NC];
+        load_columns<D>(v + (int64_t)(kb * RB) * p.kv_stride_tok, kv_row_bytes, lk - 1 - kb * RB, lane, x);
+        if (kb + NW < n_kb) load_row<D>(k + (int64_t)min((kb + NW) * RB + col, lk - 1) * p.kv_stride_tok, quarter, kf);
+        const int lim = amax - kb * RB - 4 * quarter;    // key 4 * quarter + i of the block is masked iff i > lim
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] = i > lim ? -INFINITY : s[i] * c2;
+        const float m_new = fmaxf(m, max_over_quarters(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))));
+        const float ref = m_new == -INFINITY ? 0.f : m_new;     // no visible key yet: every exponential is 0
+        const float alpha = __builtin_amdgcn_exp2f(m - ref);
+        m = m_new;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] = __builtin_amdgcn_exp2f(s[i] - ref);
+        l = l * alpha + ((s[0] + s[1]) + (s[2] + s[3]));
+#pragma unroll
+        for (int x = 0; x < D / 16; ++x) o[x] *= alpha;
+        add_column_product<D>(x, s, o);
+    }
+    l = sum_over_quarters(l);
+    if (quarter == 0) {
+        m_s[wave][col] = m;
+        l_s[wave][col] = l;
+    }
+    if (wave < n_kb) write_part<D>(o, parts + wave * S::PART, lane);
+    __syncthreads();
+
+    // O = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w over the wavefronts that had a block
+    const int n = min(NW, n_kb);
+    for (int t = threadIdx.x; t < rows * (D / 4); t += NW * 64) {
+        const int r = t / (D / 4), c = t % (D / 4);
+        float M = m_s[0][r], L = 0.f;
+        for (int w = 1; w < n; ++w) M = fmaxf(M, m_s[w][r]);
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < n; ++w) {
+            const float g = __builtin_amdgcn_exp2f(m_s[w][r] - M);
+            L += g * l_s[w][r];
+            a += g * *(const f32x4 *)(parts + w * S::PART + r * S::OS + c * 4);
+        }
+        *(f32x4 *)((float *)p.o + (int64_t)(loc.begin + q0 + r) * p.o_stride_tok + (int64_t)h * p.o_stride_head + c * 4) = a * (1.f / L);
+        if (c == 0) p.lse[(int64_t)h * p.n_tokens + loc.begin + q0 + r] = M * kLn2 + logf(L);
+    }
+}
+
+// dQ of 16 query rows of one head.
+template <int D>
+__device__ __forceinline__ void f32_dq_body(const cf_attn_bwd_params &b, int id, char *smem)
+{
+    using S = Shape<D>;
+    const cf_attn_fwd_params &p = b.f;
+    f32x4 *qs = (f32x4 *)smem, *dos = (f32x4 *)(smem + S::OPERAND);
+    float *del_s = (float *)(smem + 2 * S::OPERAND);
+    float *parts = (float *)smem;                    // takes the place of the operands once all wavefronts are done
+    const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
+    const int G = p.n_q_heads / p.n_kv_heads, kh = id % p.n_kv_heads, h = kh * G + id / p.n_kv_heads % G;
+    TileLocation loc;
+    if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, RB, id / p.n_q_heads, loc)) return;
+    const int lq = uniform(loc.len), lk = uniform(loc.other_len), off = lk - lq, q0 = uniform(loc.tile_in_seg) * RB;
+    const int rows = min(RB, lq - q0), n_kb = (q0 + rows + off + RB - 1) / RB;
+    const float *k = (const float *)p.k + (int64_t)loc.other_begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head;
+    const float *v = (const float *)p.v + (int64_t)loc.other_begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head;
+    const float *d_o = (const float *)b.d_o + (int64_t)loc.begin * b.do_stride_tok + (int64_t)h * b.do_stride_head;
+    const float *o = (const float *)p.o + (int64_t)loc.begin * p.o_stride_tok + (int64_t)h * p.o_stride_head;
+    stage_rows<D>((const float *)p.q + (int64_t)loc.begin * p.q_stride_tok + (int64_t)h * p.q_stride_head, p.q_stride_tok, q0, lq - 1, qs);
+    stage_rows<D>(d_o, b.do_stride_tok, q0, lq - 1, dos);
+    static_assert(NW == RB, "a wavefront forms one row's delta");
+    {
+        const int r = wave, row = min(q0 + r, lq - 1), c = lane;
+        float s = 0.f;
+        if (c < D / 4) {
+            const f32x4 x = *(const f32x4 *)(d_o + (int64_t)row * b.do_stride_tok + c * 4), y = *(const f32x4 *)(o + (int64_t)row * p.o_stride_tok + c * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_fmaf(x[e], y[e], s);
+        }
+        for (int x = 32; x > 0; x >>= 1) s += __shfl_xor(s, x);
+        if (c == 0) del_s[r] = s;
+    }
+    const float lse2 = p.lse[(int64_t)h * p.n_tokens + loc.begin + min(q0 + col, lq - 1)] * kLog2e;
+    const float c2 = p.softmax_scale * kLog2e;
+    const unsigned kv_row_bytes = (unsigned)p.kv_stride_tok * 4;
+    const int amax = q0 + col + off;
+    __syncthreads();
+    const float dlt = del_s[col];
+
+    Acc<D> dq;
+#pragma unroll
+    for (int x = 0; x < D / 16; ++x) dq[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int kb = wave; kb < n_kb; kb += NW) {
+        const int row = min(kb * RB + col, lk - 1);
+        f32x4 kf[S::J], vf[S::J];
+        load_row<D>(k + (int64_t)row * p.kv_stride_tok, quarter, kf);
+        load_row<D>(v + (int64_t)row * p.kv_stride_tok, quarter, vf);
+        const f32x4 s = row_product<D>(kf, qs, lane);
+        f32x4 x[4][S::NC];
+        load_columns<D>(k + (int64_t)(kb * RB) * p.kv_stride_tok, kv_row_bytes, lk - 1 - kb * RB, lane, x);
+        f32x4 dp = row_product<D>(vf, dos, lane);
+        const int lim = amax - kb * RB - 4 * quarter;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float pv = i > lim ? 0.f : __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], c2, -lse2));
+            dp[i] = pv * (dp[i] - dlt);
+        }
+        add_column_product<D>(x, dp, dq);
+    }
+    __syncthreads();                                 // the operands have been read for the last time
+    if (wave < n_kb) write_part<D>(dq, parts + wave * S::PART, lane);
+    __syncthreads();
+    const int n = min(NW, n_kb);
+    for (int t = threadIdx.x; t < rows * (D / 4); t += NW * 64) {
+        const int r = t / (D / 4), c = t % (D / 4);
+        *(f32x4 *)((float *)b.d_q + (int64_t)(loc.begin + q0 + r) * b.dq_stride_tok + (int64_t)h * b.dq_stride_head + c * 4) =
+            sum_parts<D>(parts, n, r, c) * p.softmax_scale;
+    }
+}
+
+// dK, dV of 16 key rows of one key/value head: (query head of the group, 16-row query block) pairs dealt over the
+// wavefronts.
+template <int D>
+__device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id, char *smem, float (*stat)[2 * RB])
+{
+    using S = Shape<D>;
+    const cf_attn_fwd_params &p = b.f;
+    f32x4 *ks = (f32x4 *)smem, *vs = (f32x4 *)(smem + S::OPERAND);
+    float *parts = (float *)smem;
+    const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
+    const int G = p.n_q_heads / p.n_kv_heads, kh = id % p.n_kv_heads;
+    TileLocation loc;
+    if (!locate_tile(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, RB, id / p.n_kv_heads, loc)) return;
+    const int lk = uniform(loc.len), lq = uniform(loc.other_len), off = lk - lq;
+    // (tiles are numbered from a segment's end; its FIRST key tiles are seen by the most rows: start with those)
+    const int k0 = ((lk + RB - 1) / RB - 1 - uniform(loc.tile_in_seg)) * RB, rows = min(RB, lk - k0);
+    const int qb_first = max(0, k0 - off) / RB, n_qb = (lq + RB - 1) / RB - qb_first;
+    if (n_qb <= 0) return;
+    const int n_items = G * n_qb;
+    stage_rows<D>((const float *)p.k + (int64_t)loc.begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head, p.kv_stride_tok, k0, lk - 1, ks);
+    stage_rows<D>((const float *)p.v + (int64_t)loc.begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head, p.kv_stride_tok, k0, lk - 1, vs);
+    const float c2 = p.softmax_scale * kLog2e;
+    const unsigned q_row_bytes = (unsigned)p.q_stride_tok * 4, do_row_bytes = (unsigned)b.do_stride_tok * 4;
+    float *st = stat[wave];                          // this wavefront's LSE (log2) and delta by query row
+    __syncthreads();
+
+    Acc<D> dk, dv;
+#pragma unroll
+    for (int x = 0; x < D / 16; ++x) dk[x] = dv[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int n = wave; n < n_items; n += NW) {
+        const int g = n / n_qb, q0 = (qb_first + n - g * n_qb) * RB, h = kh * G + g;
+        const float *q = (const float *)p.q + (int64_t)(loc.other_begin + q0) * p.q_stride_tok + (int64_t)h * p.q_stride_head;
+        const float *d_o = (const float *)b.d_o + (int64_t)(loc.other_begin + q0) * b.do_stride_tok + (int64_t)h * b.do_stride_head;
+        const int last = lq - 1 - q0, row = min(col, last);      // relative to the block's first row
+        f32x4 a[S::J];
+        load_row<D>(d_o + (int64_t)row * b.do_stride_tok, quarter, a);
+        const float *orow = (const float *)p.o + (int64_t)(loc.other_begin + q0 + row) * p.o_stride_tok + (int64_t)h * p.o_stride_head;
+        float dlt = 0.f;
+#pragma unroll
+        for (int j = 0; j < S::J; ++j) {
+            const f32x4 y = *(const f32x4 *)(orow + 16 * j + 4 * quarter);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dlt = __builtin_fmaf(a[j][e], y[e], dlt);
+        }
+        dlt = sum_over_quarters(dlt);
+        const float lse = p.lse[(int64_t)h * p.n_tokens + loc.other_begin + q0 + row];
+        if (quarter == 0) {
+            st[col] = col <= last ? lse * kLog2e : INFINITY;         // rows past the end: P = 0
+            st[RB + col] = dlt;
+        }
+        __builtin_amdgcn_wave_barrier();
+        f32x4 dp = row_product<D>(a, vs, lane);
+        load_row<D>(q + (int64_t)row * p.q_stride_tok, quarter, a);
+        f32x4 x[4][S::NC];
+        load_columns<D>(d_o, do_row_bytes, last, lane, x);
+        f32x4 s = row_product<D>(a, ks, lane);
+        const int lim = k0 + col - off - q0 - 4 * quarter;           // query 4 * quarter + i of the block is masked iff i < lim
+        const f32x4 l4 = *(const f32x4 *)(st + 4 * quarter), d4 = *(const f32x4 *)(st + RB + 4 * quarter);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s[i] = lim > i ? 0.f : __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], c2, -l4[i]));
+            dp[i] = s[i] * (dp[i] - d4[i]);
+        }
+        __builtin_amdgcn_wave_barrier();                             // st is rewritten by the next item
+        f32x4 y[4][S::NC];
+        load_columns<D>(q, q_row_bytes, last, lane, y);
+        add_column_product<D>(x, s, dv);
+        add_column_product<D>(y, dp, dk);
+    }
+    const int n = min(NW, n_items);
+    auto add_rows = [&](const Acc<D> &acc, float *g, float scale) {
+        __syncthreads();
+        if (wave < n_items) write_part<D>(acc, parts + wave * S::PART, lane);
+        __syncthreads();
+        for (int t = threadIdx.x; t < rows * (D / 4); t += NW * 64) {
+            const int r = t / (D / 4), c = t % (D / 4);
+            f32x4 *dst = (f32x4 *)(g + (int64_t)(loc.begin + k0 + r) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head + c * 4);
+            *dst += sum_parts<D>(parts, n, r, c) * scale;
+        }
+    };
+    add_rows(dv, b.d_v, 1.f);
+    add_rows(dk, b.d_k, p.softmax_scale);
+}
+
+template <int D>
+__global__ __launch_bounds__(NW * 64) void f32_bwd_kernel(cf_attn_bwd_params b, int dkv_blocks)
+{
+    using S = Shape<D>;
+    constexpr int OPERANDS = 2 * S::OPERAND + RB * 4, PARTS = NW * S::PART * 4;
+    __shared__ __attribute__((aligned(16))) char smem[OPERANDS > PARTS ? OPERANDS : PARTS];
+    __shared__ __attribute__((aligned(16))) float stat[NW][2 * RB];
+    if ((int)blockIdx.x < dkv_blocks) f32_dkv_body<D>(b, blockIdx.x, smem, stat);
+    else f32_dq_body<D>(b, blockIdx.x - dkv_blocks, smem);
+}
+
+// Upper bounds on block counts: sum_g ceil(L_g / 16) <= total / 16 + n_segments.
+int64_t row_blocks(int64_t total, int n_segments) { return total / RB + n_segments; }
+
+template <int D>
+hipError_t run_fwd(const cf_attn_fwd_params &p, hipStream_t s)
+{
+    const int64_t blocks = row_blocks(p.n_tokens, p.n_segments) * p.n_q_heads;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    const ProfileHook hook = take_profile_hook();
+    if (hook.start) (void)hipEventRecord(hook.start, s);
+    f32_fwd_kernel<D><<<dim3((unsigned)blocks), NW * 64, 0, s>>>(p);
+    const hipError_t e = hipGetLastError();
+    if (hook.stop) (void)hipEventRecord(hook.stop, s);
+    return e;
+}
+
+template <int D>
+hipError_t run_bwd(const cf_attn_bwd_params &b, hipStream_t s)
+{
+    const cf_attn_fwd_params &p = b.f;
+    const int64_t dkv = row_blocks(p.n_kv_tokens, p.n_segments) * p.n_kv_heads, dq = row_blocks(p.n_tokens, p.n_segments) * p.n_q_heads;
+    if (dkv + dq > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    const ProfileHook hook = take_profile_hook();
+    if (hook.start) (void)hipEventRecord(hook.start, s);
+    f32_bwd_kernel<D><<<dim3((unsigned)(dkv + dq)), NW * 64, 0, s>>>(b, (int)dkv);
+    const hipError_t e = hipGetLastError();
+    if (hook.stop) (void)hipEventRecord(hook.stop, s);
+    return e;
+}
+
+}  // namespace
+
+hipError_t launch_f32_fwd(const cf_attn_fwd_params &p, hipStream_t s) { return p.head_dim == 64 ? run_fwd<64>(p, s) : run_fwd<128>(p, s); }
+hipError_t launch_f32_bwd(const cf_attn_bwd_params &b, hipStream_t s) { return b.f.head_dim == 64 ? run_bwd<64>(b, s) : run_bwd<128>(b, s); }
+
+}  // namespace cf

@@ -1,6 +1,6 @@
 // Plain scalar attention kernels for one chunk: fp32 arithmetic, fp32 or bf16 storage.
-// One wavefront per query row (forward, dQ) or per key row (dK/dV).  They serve the fp32
-// configuration and every shape the MFMA kernels do not cover.
+// One wavefront per query row (forward, dQ) or per key row (dK/dV).  They serve the cross-check flag and
+// whatever the matrix kernels do not cover.
 //
 // Math (paper sections 2.1, 2.2, 4.2 give the masking and the state dependency; the formulas are
 // the standard softmax-attention gradient):

@@ -25,6 +25,10 @@ struct ProfileHook {
 };
 ProfileHook take_profile_hook();
 
+// fp32 matrix kernels, head_dim 64 and 128; the backward is one launch and needs no scratch.
+hipError_t launch_f32_fwd(const cf_attn_fwd_params &p, hipStream_t s);
+hipError_t launch_f32_bwd(const cf_attn_bwd_params &p, hipStream_t s);
+
 // Plain scalar kernels: any supported head_dim, fp32 or bf16 storage, fp32 arithmetic.
 hipError_t launch_simple_fwd(const cf_attn_fwd_params &p, hipStream_t s);
 hipError_t launch_simple_bwd(const cf_attn_bwd_params &p, const BwdWorkspace &ws, hipStream_t s);
