@@ -61,7 +61,7 @@ int check_fwd(const cf_attn_fwd_params *p, const char *who, bool sizes_only)
 // Shapes the MFMA kernels cover (decides the workspace size, so it may only look at sizes, dtype, flags).
 bool mfma_shape(const cf_attn_fwd_params &p)
 {
-    return p.dtype == CF_BF16 && p.head_dim == 128 && !(p.flags & CF_FLAG_SCALAR_KERNELS);
+    return p.dtype == CF_BF16 && !(p.flags & CF_FLAG_SCALAR_KERNELS);
 }
 // The MFMA kernels take the row maximum before scaling, which needs a positive scale.
 bool use_mfma(const cf_attn_fwd_params &p) { return mfma_shape(p) && p.softmax_scale > 0.f; }
@@ -261,10 +261,10 @@ extern "C" int cf_attn_fwd_batch(const cf_attn_fwd_params *params, int32_t n, vo
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     int32_t i = 0;
     while (i < n) {
-        // a run of chunks the MFMA kernel covers with the same head counts becomes one launch
+        // a run of chunks the MFMA kernel covers with the same heads becomes one launch
         int32_t j = i;
         while (j < n && j - i < cf::CF_FWD_BATCH_MAX && use_mfma(params[j]) && params[j].n_q_heads == params[i].n_q_heads &&
-               params[j].n_kv_heads == params[i].n_kv_heads)
+               params[j].n_kv_heads == params[i].n_kv_heads && params[j].head_dim == params[i].head_dim)
             ++j;
         hipError_t e;
         if (j - i >= 2) {
@@ -308,7 +308,7 @@ extern "C" int cf_attn_bwd_batch(const cf_attn_bwd_params *params, int32_t n, vo
     while (i < n) {
         int32_t j = i;
         while (j < n && j - i < cf::CF_BWD_BATCH_MAX && use_mfma(params[j].f) && params[j].f.n_q_heads == params[i].f.n_q_heads &&
-               params[j].f.n_kv_heads == params[i].f.n_kv_heads)
+               params[j].f.n_kv_heads == params[i].f.n_kv_heads && params[j].f.head_dim == params[i].f.head_dim)
             ++j;
         if (j - i >= 2) {
             int order[cf::CF_BWD_BATCH_MAX];

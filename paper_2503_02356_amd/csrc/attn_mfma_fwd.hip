@@ -1,4 +1,4 @@
-// bf16 MFMA forward kernel for one chunk, head_dim 128 (paper sections 2.1, 2.2, 4.2: causal mask per
+// bf16 MFMA forward kernel for one chunk, head_dim 64 and 128 (paper sections 2.1, 2.2, 4.2: causal mask per
 // packed sequence; a dependent chunk's queries also read the retained key/value prefix).
 //
 // One workgroup = 4 wavefronts; each wavefront owns a unit = 32 consecutive query rows of one query head.  A tile
@@ -22,14 +22,20 @@ namespace {
 
 constexpr int BM = 128;        // query rows per workgroup
 constexpr int BN = 64;         // key rows per tile
-constexpr int D = 128;
-constexpr int TILE_BYTES = BN * 256;          // one swizzled K or V tile (see mfma_common.h)
-constexpr int STAGE_BYTES = 2 * TILE_BYTES;   // K then V
 constexpr float kLazy = 8.f;                  // log2 units a row maximum may exceed the running reference before O is rescaled
 
+template <int D>
+struct Stage {
+    static constexpr int tile_bytes = BN * 2 * D;    // one swizzled K or V tile (see mfma_common.h)
+    static constexpr int bytes = 2 * tile_bytes;     // K then V
+};
+
 // id: index of the workgroup among those of this chunk
+// D = 64: the second product takes P as bf16 value plus bf16 rounding residual (two MFMAs; P keeps 16 bits).
+template <int D>
 __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, char *stage_a, char *stage_b)
 {
+    constexpr int KS = D / 16, DB = D / 32, TILE_BYTES = Stage<D>::tile_bytes;
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int half = lane >> 5, col = lane & 31;
 
@@ -75,22 +81,22 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     const int64_t kv_row_bytes = p.kv_stride_tok * 2;
     const char *kbase = uniform((const char *)p.k + ((int64_t)k_seg0 * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2);
     const char *vbase = uniform((const char *)p.v + ((int64_t)k_seg0 * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2);
-    TileDma<BN> dma;
+    TileDma<BN, D> dma;
     dma.init(kv_row_bytes);
 
     // Q^T fragments: lane (col, half) holds row iq, d = 16*ks + 8*half + 0..7.
-    bf16x8 qf[8];
+    bf16x8 qf[KS];
     {
         const int row = q_seg0 + min(iq, lq - 1);
         const char *qrow = (const char *)p.q + ((int64_t)row * p.q_stride_tok + (int64_t)h * p.q_stride_head) * 2;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qf[ks] = *(const bf16x8 *)(qrow + ks * 32 + half * 16);
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8 *)(qrow + ks * 32 + half * 16);
     }
-    const LaneOffsets lo = lane_offsets();
+    const LaneOffsets<D> lo = lane_offsets<D>();
 
-    f32x16 o_acc[4];
+    f32x16 o_acc[DB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < DB; ++i)
 #pragma unroll
         for (int j = 0; j < 16; ++j) o_acc[i][j] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;            // running max (log2 units) and this lane's partial row sum
@@ -113,18 +119,18 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
             // All 16 K fragments are requested before the first MFMA: the LDS latency is paid once per tile,
             // not once per MFMA (the matrix unit then consumes them in arrival order).
             f32x16 s[2];
-            bf16x8 ka[2][8];
+            bf16x8 ka[2][KS];
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks)
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb) ka[mb][ks] = lds_read_b128(stage + mb * 8192 + lo.row_unit[ks]);
+                for (int mb = 0; mb < 2; ++mb) ka[mb][ks] = lds_read_b128(stage + mb * (TILE_BYTES / 2) + lo.row_unit[ks]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
                 for (int j = 0; j < 16; ++j) s[mb][j] = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < 8; ++ks)
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
                 for (int mb = 0; mb < 2; ++mb) s[mb] = mfma32(ka[mb][ks], qf[ks], s[mb]);
             // ---- causal mask, only on tiles that cross this wavefront's diagonal
@@ -156,7 +162,7 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
                 m_run = m_new;
                 l_run *= alpha;
 #pragma unroll
-                for (int db = 0; db < 4; ++db)
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
                     for (int j = 0; j < 16; ++j) o_acc[db][j] *= alpha;
             }
@@ -178,10 +184,18 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
                     // register 8*tq + j of block mb is key mb*32 + 16*tq + (j/4)*8 + 4*half + j%4
                     const bf16x8 pb = pack8(s[mb][8 * tq + 0], s[mb][8 * tq + 1], s[mb][8 * tq + 2], s[mb][8 * tq + 3],
                                             s[mb][8 * tq + 4], s[mb][8 * tq + 5], s[mb][8 * tq + 6], s[mb][8 * tq + 7]);
-                    const char *va = vst + mb * 8192 + tq * 4096;
+                    bf16x8 pl;
+                    if (D == 64) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        o_acc[j] = mfma32(lds_read_tr_pair(va + lo.tr_lo[j], va + lo.tr_hi[j]), pb, o_acc[j]);
+                        for (int e = 0; e < 8; ++e) pl[e] = (__bf16)(s[mb][8 * tq + e] - (float)pb[e]);
+                    }
+                    const char *va = vst + mb * (TILE_BYTES / 2) + tq * (TILE_BYTES / 4);
+#pragma unroll
+                    for (int j = 0; j < DB; ++j) {
+                        const bf16x8 a = lds_read_tr_pair(va + lo.tr_lo[j], va + lo.tr_hi[j]);
+                        o_acc[j] = mfma32(a, pb, o_acc[j]);
+                        if (D == 64) o_acc[j] = mfma32(a, pl, o_acc[j]);
+                    }
                 }
         }
         wait_lds_dma();
@@ -196,21 +210,22 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     const float l_tot = sum_with_other_half(l_run);
     // O rows leave through this wavefront's part of the (now idle) stage buffers, whole rows per store instruction.
     // The scale of a padding row (l_tot = 0 cannot happen: every real row sees its own key) is never stored.
-    char *scratch = (wave < 2 ? stage_a : stage_b) + (wave & 1) * kRowScratchBytes;
-    store_rows_bf16(o_acc, 1.f / l_tot, scratch, lq - wq0, [&](int r) {
+    char *scratch = (wave < 2 ? stage_a : stage_b) + (wave & 1) * RowScratch<D>::bytes;
+    store_rows_bf16<D>(o_acc, 1.f / l_tot, scratch, lq - wq0, [&](int r) {
         return (char *)p.o + ((int64_t)(q_seg0 + wq0 + r) * p.o_stride_tok + (int64_t)h * p.o_stride_head) * 2;
     });
     if (iq < lq && half == 0)
         p.lse[(int64_t)h * p.n_tokens + q_seg0 + iq] = m_run * 0.69314718055994530942f + __logf(l_tot);
 }
 
+template <int D>
 __global__ __launch_bounds__(256, 2) void mfma_fwd_kernel(cf_attn_fwd_params p)
 {
     // Two separate arrays (not one array with two halves): the compiler must see that the direct-to-LDS
     // loads of the next tile cannot alias the reads of the current one, or it waits for them too early.
-    __shared__ __attribute__((aligned(16))) char stage_a[STAGE_BYTES];
-    __shared__ __attribute__((aligned(16))) char stage_b[STAGE_BYTES];
-    fwd_body(p, blockIdx.x, stage_a, stage_b);
+    __shared__ __attribute__((aligned(16))) char stage_a[Stage<D>::bytes];
+    __shared__ __attribute__((aligned(16))) char stage_b[Stage<D>::bytes];
+    fwd_body<D>(p, blockIdx.x, stage_a, stage_b);
 }
 
 // Several chunks in one launch: workgroups [first_block[c], first_block[c+1]) belong to chunk c.  The host
@@ -221,14 +236,15 @@ struct FwdBatch {
     int first_block[CF_FWD_BATCH_MAX + 1];
     cf_attn_fwd_params p[CF_FWD_BATCH_MAX];
 };
+template <int D>
 __global__ __launch_bounds__(256, 2) void mfma_fwd_batch_kernel(FwdBatch b)
 {
-    __shared__ __attribute__((aligned(16))) char stage_a[STAGE_BYTES];
-    __shared__ __attribute__((aligned(16))) char stage_b[STAGE_BYTES];
+    __shared__ __attribute__((aligned(16))) char stage_a[Stage<D>::bytes];
+    __shared__ __attribute__((aligned(16))) char stage_b[Stage<D>::bytes];
     const int id = blockIdx.x;
     int c = 0;
     while (c + 1 < b.n && id >= b.first_block[c + 1]) ++c;
-    fwd_body(b.p[c], id - b.first_block[c], stage_a, stage_b);
+    fwd_body<D>(b.p[c], id - b.first_block[c], stage_a, stage_b);
 }
 
 // Upper bound on the number of 128-row tiles: sum_g ceil(Lq_g / BM) <= T / BM + n_segments.
@@ -252,7 +268,8 @@ hipError_t launch_mfma_fwd_batch(const cf_attn_fwd_params *const *chunks, int n,
         if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     }
     b.first_block[n] = (int)total;
-    mfma_fwd_batch_kernel<<<dim3((unsigned)total), 256, 0, s>>>(b);
+    if (chunks[0]->head_dim == 64) mfma_fwd_batch_kernel<64><<<dim3((unsigned)total), 256, 0, s>>>(b);
+    else mfma_fwd_batch_kernel<128><<<dim3((unsigned)total), 256, 0, s>>>(b);
     return hipGetLastError();
 }
 
@@ -262,7 +279,8 @@ hipError_t launch_mfma_fwd(const cf_attn_fwd_params &p, hipStream_t s)
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const ProfileHook hook = take_profile_hook();
     if (hook.start) (void)hipEventRecord(hook.start, s);
-    mfma_fwd_kernel<<<dim3((unsigned)blocks), 256, 0, s>>>(p);
+    if (p.head_dim == 64) mfma_fwd_kernel<64><<<dim3((unsigned)blocks), 256, 0, s>>>(p);
+    else mfma_fwd_kernel<128><<<dim3((unsigned)blocks), 256, 0, s>>>(p);
     const hipError_t e = hipGetLastError();
     if (hook.stop) (void)hipEventRecord(hook.stop, s);
     return e;

@@ -36,7 +36,7 @@ hipError_t launch_simple_bwd(const cf_attn_bwd_params &p, const BwdWorkspace &ws
 // delta[h][t] = sum_d dO[t][h][d] * O[t][h][d].
 hipError_t launch_delta(const cf_attn_bwd_params &p, const BwdWorkspace &ws, hipStream_t s);
 
-// bf16 MFMA kernels, head_dim 128.
+// bf16 MFMA kernels, head_dim 64 and 128 (one head_dim per batch).
 hipError_t launch_mfma_fwd(const cf_attn_fwd_params &p, hipStream_t s);
 // Forward of 1..CF_FWD_BATCH_MAX chunks as one launch, workgroups dealt in the order of `chunks`.
 constexpr int CF_FWD_BATCH_MAX = 16;
