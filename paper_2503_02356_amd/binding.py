@@ -147,14 +147,16 @@ class Plan:
         self.group_chunk_ptr = arr(v.group_chunk_ptr, n_g + 1, np.int64)
         self.group_chunks = arr(v.group_chunks, n_c, np.int64)
         self.group_seq_id = arr(v.group_seq_id, n_g, np.int64)
+        self._seg_ptr, self._segments = self.chunk_seg_ptr.tolist(), None
 
     def chunk_cu_seqlens(self, c):
-        a = int(self.chunk_seg_ptr[c]) + c
-        return self.cu_seqlens[a:a + int(self.chunk_seg_ptr[c + 1] - self.chunk_seg_ptr[c]) + 1]
+        a, b = self._seg_ptr[c], self._seg_ptr[c + 1]
+        return self.cu_seqlens[a + c:b + c + 1]
 
     def chunk_segments(self, c):
-        a, b = int(self.chunk_seg_ptr[c]), int(self.chunk_seg_ptr[c + 1])
-        return [(int(self.seg_seq_id[s]), int(self.seg_seq_start[s]), int(self.seg_len[s])) for s in range(a, b)]
+        if self._segments is None:        # all segments as plain numbers, converted once
+            self._segments = list(zip(self.seg_seq_id.tolist(), self.seg_seq_start.tolist(), self.seg_len.tolist()))
+        return self._segments[self._seg_ptr[c]:self._seg_ptr[c + 1]]
 
     def group(self, g):
         return [int(x) for x in self.group_chunks[int(self.group_chunk_ptr[g]):int(self.group_chunk_ptr[g + 1])]]
@@ -162,7 +164,10 @@ class Plan:
     def schedule(self, K):
         ops, n = C.POINTER(SchedOp)(), C.c_int64()
         _check(lib().cf_build_schedule(self._h, int(K), C.byref(ops), C.byref(n)))
-        return [(ops[i].op, ops[i].chunk) for i in range(n.value)]
+        if n.value == 0:
+            return []
+        rec = np.ctypeslib.as_array(C.cast(ops, C.POINTER(C.c_int64)), shape=(n.value, 2))     # (op and 0, chunk) per op
+        return list(zip((rec[:, 0] & 0xffffffff).tolist(), rec[:, 1].tolist()))
 
     def schedule_stats(self, K):
         """cf_schedule_stats as a dict."""
@@ -241,16 +246,26 @@ def _stream():
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+def _address(a):
+    """Address of a contiguous numpy array's data (a.ctypes and __array_interface__ build objects for it, which takes
+    longer than the calls it is for; a buffer needs a writable array with at least one element)."""
+    try:
+        return C.addressof(C.c_char.from_buffer(a))
+    except (TypeError, ValueError):
+        return a.__array_interface__["data"][0]
+
+
 def cf_attn_q_tiles(cu_q, cu_k):
     """Host table of the chunk's 128-row query tiles, heaviest first: int32 array [n_tiles, 8] with the columns
     of cf_q_tile (q_begin, q_len, k_begin, k_len, tile, segment, 0, 0).  cu_q, cu_k: host int arrays."""
     a = np.ascontiguousarray(cu_q, dtype=np.int32)
     b = np.ascontiguousarray(cu_k, dtype=np.int32)
-    n = _check(lib().cf_attn_q_tiles(a.ctypes.data_as(C.c_void_p), b.ctypes.data_as(C.c_void_p), len(a) - 1, None, 0))
-    out = np.zeros((n, 8), dtype=np.int32)
-    _check(lib().cf_attn_q_tiles(a.ctypes.data_as(C.c_void_p), b.ctypes.data_as(C.c_void_p), len(a) - 1,
-                                 out.ctypes.data_as(C.c_void_p), n))
-    return out
+    n_seg = len(a) - 1
+    # an upper bound on the tile count, so that one call does it (more than the tokens need is refused above anyway)
+    room = max(0, int(a[-1]) - int(a[0])) // 128 + max(0, n_seg) if len(a) else 0
+    out = np.empty((room, 8), dtype=np.int32)
+    n = _check(lib().cf_attn_q_tiles(_address(a), _address(b), n_seg, _address(out), room))
+    return out[:n]
 
 
 def make_fwd_params(q, k, v, o, lse, cu_q, cu_k, scale, flags=0, q_tiles=None):

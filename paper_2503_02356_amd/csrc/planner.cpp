@@ -38,6 +38,14 @@ struct cf_plan {
     std::vector<int64_t> group_chunk_ptr{0}, group_chunks, group_seq_id;
     std::vector<cf_sched_op> sched;
 
+    void reserve(size_t segments, size_t chunks)
+    {
+        seg_seq_id.reserve(segments), seg_seq_start.reserve(segments), seg_len.reserve(segments);
+        cu_seqlens.reserve(segments + chunks);
+        chunk_seg_ptr.reserve(chunks + 1), chunk_tokens.reserve(chunks), chunk_prefix_len.reserve(chunks);
+        chunk_group.reserve(chunks), chunk_idx_in_group.reserve(chunks), group_chunks.reserve(chunks);
+    }
+
     // Appends one chunk made of the given (sequence, start, length) segments to group `group`.
     void add_chunk(int32_t group, int32_t idx_in_group, int64_t prefix,
                    const std::vector<int64_t> &ids, const std::vector<int64_t> &starts,
@@ -68,37 +76,86 @@ struct PackItem {
     bool is_tail;
 };
 
-// One packing attempt: items in `order` (longest first) each go to the least-loaded bin, ties to the lowest bin
-// index; a tail only goes to a bin that holds no tail yet (a chunk then depends on at most one split sequence).
-// Fails as soon as an item does not fit its bin, or a tail finds no tail-free bin.
-static bool try_pack(const std::vector<PackItem> &order, int64_t n_bins, int64_t cap,
-                     std::vector<std::vector<int64_t>> &bins)
+// Least-loaded-bin queue: a binary heap of (load << 32 | bin), smallest first (ties: lowest bin).  Placing an item raises
+// the smallest entry, so the heap is repaired once from the top instead of by a pop and a push.
+class BinHeap {
+public:
+    explicit BinHeap(int64_t n_bins) : e_((size_t)n_bins), n_((size_t)n_bins)
+    {
+        for (size_t b = 0; b < e_.size(); ++b) e_[b] = b;          // equal loads in bin order are a heap
+    }
+    uint64_t top() const { return e_[0]; }
+    void raise_top(uint64_t entry) { sift_down(0, entry); }
+    // the entry `from` (anywhere in the heap) becomes the larger `to`
+    void raise(uint64_t from, uint64_t to)
+    {
+        size_t i = 0;
+        while (e_[i] != from) ++i;
+        sift_down(i, to);
+    }
+
+private:
+    void sift_down(size_t i, uint64_t x)
+    {
+        for (size_t c; (c = 2 * i + 1) < n_; i = c) {
+            c += c + 1 < n_ && e_[c + 1] < e_[c];
+            if (x <= e_[c]) break;
+            e_[i] = e_[c];
+        }
+        e_[i] = x;
+    }
+    std::vector<uint64_t> e_;
+    size_t n_;
+};
+
+// One packing attempt: items in `order` (indices into items, longest first) each go to the least-loaded bin, ties to the
+// lowest bin index; a tail only goes to a bin that holds no tail yet (a chunk then depends on at most one split sequence).
+// Fails as soon as an item does not fit its bin, or a tail finds no tail-free bin.  bin_of[item] = the bin.
+// (n_bins <= number of items < 2^31 and loads <= 2^31 - 1, so both halves of a heap entry hold their number.)
+static bool try_pack(const std::vector<PackItem> &items, const std::vector<int32_t> &order, int64_t n_bins, int64_t cap,
+                     std::vector<int32_t> &bin_of)
 {
-    using Entry = std::pair<int64_t, int64_t>;  // (load, bin): the smallest pair is the target bin
-    std::priority_queue<Entry, std::vector<Entry>, std::greater<Entry>> heap;
+    BinHeap heap(n_bins);
+    std::vector<char> has_tail;
     std::vector<int64_t> load((size_t)n_bins, 0);
-    std::vector<char> has_tail((size_t)n_bins, 0);
-    for (int64_t b = 0; b < n_bins; ++b) heap.push({0, b});
-    bins.assign((size_t)n_bins, {});
-    for (size_t n = 0; n < order.size(); ++n) {
-        const PackItem &it = order[n];
-        int64_t b = -1;
+    for (int32_t n : order) {
+        const PackItem &it = items[(size_t)n];
+        int64_t b;
         if (!it.is_tail) {
-            while (heap.top().first != load[(size_t)heap.top().second]) heap.pop();   // entries a tail made stale
-            b = heap.top().second;
-            heap.pop();
+            b = (int64_t)(heap.top() & 0xffffffffu);
         } else {
+            if (has_tail.empty()) has_tail.assign((size_t)n_bins, 0);
+            b = -1;
             for (int64_t x = 0; x < n_bins; ++x)
                 if (!has_tail[(size_t)x] && (b < 0 || load[(size_t)x] < load[(size_t)b])) b = x;
             if (b < 0) return false;
             has_tail[(size_t)b] = 1;
         }
-        if (load[(size_t)b] + it.len > cap) return false;
-        load[(size_t)b] += it.len;
-        bins[(size_t)b].push_back((int64_t)n);
-        heap.push({load[(size_t)b], b});
+        const int64_t before = load[(size_t)b], after = before + it.len;
+        if (after > cap) return false;
+        load[(size_t)b] = after;
+        bin_of[(size_t)n] = (int32_t)b;
+        const uint64_t entry = (uint64_t)after << 32 | (uint64_t)b;
+        if (!it.is_tail) heap.raise_top(entry);
+        else heap.raise((uint64_t)before << 32 | (uint64_t)b, entry);
     }
     return true;
+}
+
+// Indices of the items, longest first, equal lengths in item order: a radix sort over the length's bits (least
+// significant digit first, 11 bits at a time).
+static std::vector<int32_t> longest_first(const std::vector<PackItem> &items, int64_t longest)
+{
+    std::vector<int32_t> order(items.size()), next(items.size());
+    std::iota(order.begin(), order.end(), 0);
+    for (int shift = 0; shift == 0 || longest >> shift; shift += 11) {
+        size_t at[2049] = {0};
+        for (int32_t n : order) ++at[2048 - (items[(size_t)n].len >> shift & 2047)];       // bucket 1 + (2047 - digit)
+        for (int d = 1; d < 2049; ++d) at[d] += at[d - 1];
+        for (int32_t n : order) next[at[2047 - (items[(size_t)n].len >> shift & 2047)]++] = n;
+        order.swap(next);
+    }
+    return order;
 }
 
 extern "C" int cf_build_chunks_ex(const int64_t *seq_lens, int64_t n_seqs, int64_t chunk_size, uint32_t flags,
@@ -148,28 +205,35 @@ extern "C" int cf_build_chunks_ex(const int64_t *seq_lens, int64_t n_seqs, int64
             p->group_chunk_ptr.push_back((int64_t)p->group_chunks.size());
         }
         if (!items.empty()) {
-            std::vector<PackItem> order = items;     // items are in sequence order: a stable sort keeps it among equals
-            std::stable_sort(order.begin(), order.end(),
-                             [](const PackItem &a, const PackItem &b) { return a.len > b.len; });
+            const std::vector<int32_t> order = longest_first(items, C);
             // Bin counts below ceil(tokens / C) cannot hold the tokens, so every attempt there fails:
             // starting at that count gives the same answer as starting at 1.
-            std::vector<std::vector<int64_t>> bins;
+            std::vector<int32_t> bin_of(items.size());
             int64_t n_bins = std::max<int64_t>(1, (item_tokens + C - 1) / C);
-            while (!try_pack(order, n_bins, C, bins)) ++n_bins;
+            while (!try_pack(items, order, n_bins, C, bin_of)) ++n_bins;
+            // The members of a bin in sequence order: items are in sequence order, so dealing them out keeps it.
+            std::vector<int64_t> at((size_t)n_bins + 1, 0);
+            for (int32_t b : bin_of) ++at[(size_t)b + 1];
+            for (int64_t b = 0; b < n_bins; ++b) at[(size_t)b + 1] += at[(size_t)b];
+            std::vector<int32_t> member(items.size());
+            {
+                std::vector<int64_t> next(at.begin(), at.end() - 1);
+                for (size_t n = 0; n < items.size(); ++n) member[(size_t)next[(size_t)bin_of[n]]++] = (int32_t)n;
+            }
             // A chunk that holds a tail is the last chunk of that sequence's group; it is inserted into the
             // group lists afterwards (group_chunks is laid out group by group).
             std::vector<std::vector<int64_t>> extra(p->group_seq_id.size());
             std::vector<int64_t> packed_chunks;
-            for (auto &members : bins) {
-                if (members.empty()) continue;
-                std::sort(members.begin(), members.end(),
-                          [&](int64_t a, int64_t b) { return order[(size_t)a].seq < order[(size_t)b].seq; });
-                std::vector<int64_t> ids, starts;
-                std::vector<int32_t> lens;
+            p->reserve(p->seg_len.size() + items.size(), p->chunk_tokens.size() + (size_t)n_bins);
+            std::vector<int64_t> ids, starts;
+            std::vector<int32_t> lens;
+            for (int64_t b = 0; b < n_bins; ++b) {
+                if (at[(size_t)b] == at[(size_t)b + 1]) continue;
+                ids.clear(), starts.clear(), lens.clear();
                 int64_t prefix = 0;
                 int32_t group = -1, idx = 0;
-                for (int64_t n : members) {
-                    const PackItem &it = order[(size_t)n];
+                for (int64_t m = at[(size_t)b]; m < at[(size_t)b + 1]; ++m) {
+                    const PackItem &it = items[(size_t)member[(size_t)m]];
                     ids.push_back(it.seq);
                     starts.push_back(it.start);
                     lens.push_back(it.len);
@@ -509,21 +573,38 @@ extern "C" int64_t cf_attn_q_tiles(const int32_t *cu_q, const int32_t *cu_k, int
     if (capacity < n_tiles) return cf::fail(CF_EINVAL, "cf_attn_q_tiles: capacity %lld < %lld tiles", (long long)capacity,
                                             (long long)n_tiles);
     try {
-        std::vector<std::pair<int64_t, int64_t>> order;   // (-steps, index): ascending pairs = longest first, then list order
-        order.reserve((size_t)n_tiles);
-        int64_t n = 0;
+        // Longest first, equal lengths in list order.  A tile's length in key steps is known as it is made, so the
+        // tiles are counted per length and written straight to their places (the lengths of a chunk span little more
+        // than twice its tile count; where they do not, as behind a long prefix, only the span that occurs is counted).
+        auto steps_of = [&](int64_t lq, int64_t lk, int64_t t) {
+            const int64_t keys = std::min((t + 1) * kRows, lq) + (lk - lq);   // keys the tile's last row sees
+            return (keys + kKeysPerStep - 1) / kKeysPerStep;
+        };
+        int64_t lo = INT64_MAX, hi = 0;
         for (int32_t g = 0; g < n_segments; ++g) {
             const int64_t lq = cu_q[g + 1] - cu_q[g], lk = cu_k[g + 1] - cu_k[g];
-            for (int64_t t = 0; t * kRows < lq; ++t, ++n) {
-                const int64_t keys = std::min((t + 1) * kRows, lq) + (lk - lq);   // keys the tile's last row sees
-                order.push_back({-((keys + kKeysPerStep - 1) / kKeysPerStep), n});
-                out[n] = cf_q_tile{cu_q[g], (int32_t)lq, cu_k[g], (int32_t)lk, (int32_t)t, g, {0, 0}};
-            }
+            lo = std::min(lo, steps_of(lq, lk, 0));
+            hi = std::max(hi, steps_of(lq, lk, (lq + kRows - 1) / kRows - 1));
         }
-        std::sort(order.begin(), order.end());
-        std::vector<cf_q_tile> sorted((size_t)n_tiles);
-        for (int64_t i = 0; i < n_tiles; ++i) sorted[(size_t)i] = out[order[(size_t)i].second];
-        std::copy(sorted.begin(), sorted.end(), out);
+        auto for_each_tile = [&](auto &&visit) {
+            for (int32_t g = 0; g < n_segments; ++g) {
+                const int64_t lq = cu_q[g + 1] - cu_q[g], lk = cu_k[g + 1] - cu_k[g];
+                for (int64_t t = 0; t * kRows < lq; ++t)
+                    visit(steps_of(lq, lk, t), cf_q_tile{cu_q[g], (int32_t)lq, cu_k[g], (int32_t)lk, (int32_t)t, g, {0, 0}});
+            }
+        };
+        if (hi - lo <= 8 * n_tiles + 4096) {
+            std::vector<int32_t> at((size_t)(hi - lo) + 2, 0);
+            for_each_tile([&](int64_t steps, const cf_q_tile &) { ++at[(size_t)(hi - steps) + 1]; });
+            for (size_t d = 1; d < at.size(); ++d) at[d] += at[d - 1];
+            for_each_tile([&](int64_t steps, const cf_q_tile &tile) { out[at[(size_t)(hi - steps)]++] = tile; });
+        } else {                                     // few tiles of very different lengths
+            std::vector<std::pair<int64_t, cf_q_tile>> all;
+            all.reserve((size_t)n_tiles);
+            for_each_tile([&](int64_t steps, const cf_q_tile &tile) { all.push_back({steps, tile}); });
+            std::stable_sort(all.begin(), all.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+            for (int64_t i = 0; i < n_tiles; ++i) out[i] = all[(size_t)i].second;
+        }
     } catch (const std::bad_alloc &) {
         return cf::fail(CF_ENOMEM, "cf_attn_q_tiles: out of host memory");
     }
