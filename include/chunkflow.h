@@ -315,6 +315,18 @@ int cf_attn_fwd_batch(const cf_attn_fwd_params *params, int32_t n, void *hip_str
 int cf_attn_bwd_batch(const cf_attn_bwd_params *params, int32_t n, void *hip_stream);
 
 /*
+ * n calls, in order, on one stream: calls[i].backward ? cf_attn_bwd(calls[i].params) : cf_attn_fwd(calls[i].params),
+ * with params a cf_attn_bwd_params resp. cf_attn_fwd_params.  The same launches as n separate calls; what is saved is
+ * the caller's way into the library (for a caller in an interpreted language longer than the launch itself).
+ * Stops at the first call that fails and returns its error.  n < 0, NULL calls with n > 0 -> CF_EINVAL.
+ */
+typedef struct {
+    const void *params;
+    int32_t backward, reserved;
+} cf_attn_call;
+int cf_attn_calls(const cf_attn_call *calls, int64_t n, void *hip_stream);
+
+/*
  * Measurement aid (not part of the paper's method): when both events (hipEvent_t, created by the
  * caller with timing enabled) are non-NULL, the NEXT cf_attn_fwd / cf_attn_bwd call on this thread
  * records `start` right before and `stop` right after its main kernel (forward: the attention

@@ -21,7 +21,7 @@ CF_PLAN_MERGE_TAILS = 1
 
 EXPORTS = ["cf_last_error", "cf_version", "cf_build_chunks", "cf_build_chunks_ex", "cf_attn_q_tiles", "cf_plan_free", "cf_plan_get",
            "cf_build_schedule", "cf_schedule_stats", "cf_attn_fwd", "cf_attn_bwd_workspace_bytes", "cf_attn_bwd", "cf_attn_fwd_batch", "cf_attn_bwd_batch",
-           "cf_count_pairs", "cf_profile_next_call", "cf_attn_bwd_static", "cf_sim_1f1b", "cf_sim_1f1b_sequences"]
+           "cf_attn_calls", "cf_count_pairs", "cf_profile_next_call", "cf_attn_bwd_static", "cf_sim_1f1b", "cf_sim_1f1b_sequences"]
 
 
 class CfError(RuntimeError):
@@ -74,6 +74,10 @@ class AttnBwdParams(C.Structure):
                 ("workspace", C.c_void_p), ("workspace_bytes", C.c_int64)]
 
 
+class AttnCall(C.Structure):
+    _fields_ = [("params", C.c_void_p), ("backward", C.c_int32), ("reserved", C.c_int32)]
+
+
 _lib = None
 
 
@@ -102,6 +106,7 @@ def lib():
         L.cf_attn_bwd_static.argtypes = [C.POINTER(AttnBwdParams), C.c_void_p]
         L.cf_attn_fwd_batch.argtypes = [C.POINTER(AttnFwdParams), C.c_int32, C.c_void_p]
         L.cf_attn_bwd_batch.argtypes = [C.POINTER(AttnBwdParams), C.c_int32, C.c_void_p]
+        L.cf_attn_calls.argtypes = [C.POINTER(AttnCall), C.c_int64, C.c_void_p]
         L.cf_schedule_stats.argtypes = [C.c_void_p, C.c_int32, C.POINTER(SchedStats)]
         L.cf_profile_next_call.argtypes = [C.c_void_p, C.c_void_p]
         L.cf_count_pairs.argtypes = [C.c_void_p, C.c_void_p, C.c_int32]
@@ -337,6 +342,18 @@ def cf_attn_fwd_batch(params_arr, stream=None):
 def cf_attn_bwd_batch(params_arr, stream=None):
     n = len(params_arr) if params_arr is not None else 0
     _check(lib().cf_attn_bwd_batch(params_arr, n, stream if stream is not None else _stream()))
+
+
+def make_calls(ops):
+    """The argument of cf_attn_calls: ops is an iterable of (is_backward, parameter struct)."""
+    ops = list(ops)
+    arr = (AttnCall * len(ops))(*[AttnCall(C.addressof(params), int(bool(bwd)), 0) for bwd, params in ops])
+    arr._keepalive = ops
+    return arr
+
+
+def cf_attn_calls(calls, stream=None):
+    _check(lib().cf_attn_calls(calls, len(calls), stream if stream is not None else _stream()))
 
 
 def cf_attn_bwd(params, stream=None):

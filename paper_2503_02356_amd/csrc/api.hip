@@ -325,3 +325,14 @@ extern "C" int cf_attn_bwd_batch(const cf_attn_bwd_params *params, int32_t n, vo
     }
     return CF_OK;
 }
+
+extern "C" int cf_attn_calls(const cf_attn_call *calls, int64_t n, void *hip_stream)
+{
+    if (n < 0 || (n > 0 && !calls)) return cf::fail(CF_EINVAL, "cf_attn_calls: bad argument");
+    for (int64_t i = 0; i < n; ++i) {
+        const int rc = calls[i].backward ? cf_attn_bwd(static_cast<const cf_attn_bwd_params *>(calls[i].params), hip_stream)
+                                         : cf_attn_fwd(static_cast<const cf_attn_fwd_params *>(calls[i].params), hip_stream);
+        if (rc) return rc;
+    }
+    return CF_OK;
+}

@@ -49,6 +49,7 @@ struct Shape {
     static constexpr int OS = D + 4;         // row stride of a partial result in LDS (spreads float4 rows over the banks)
     static constexpr int PART = RB * OS;     // floats of one wavefront's partial result
     static constexpr int OPERAND = RB * D * 4;   // bytes of 16 staged rows
+    static constexpr bool BOTH_MEET = D == 64;   // LDS holds the partial results of dK and dV at once
 };
 template <int D>
 using Acc = f32x4[D / 16];                   // [4 * c + e], register i: column 64 c + 4 * (4 * quarter + i) + e
@@ -170,10 +171,14 @@ __global__ __launch_bounds__(NW * 64) void f32_fwd_kernel(cf_attn_fwd_params p)
     for (int x = 0; x < D / 16; ++x) o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;
     for (int kb = wave; kb < n_kb; kb += NW) {
-        f32x4 s = row_product<D>(kf, qs, lane);
-        __builtin_amdgcn_sched_barrier(0);           // V takes the registers of K: with both held D = 128 spills
         f32x4 x[4][S::NC];
-        load_columns<D>(v + (int64_t)(kb * RB) * p.kv_stride_tok, kv_row_bytes, lk - 1 - kb * RB, lane, x);
+        auto load_v = [&] { load_columns<D>(v + (int64_t)(kb * RB) * p.kv_stride_tok, kv_row_bytes, lk - 1 - kb * RB, lane, x); };
+        if (D == 64) load_v();
+        f32x4 s = row_product<D>(kf, qs, lane);
+        if (D != 64) {
+            __builtin_amdgcn_sched_barrier(0);       // V takes the registers of K: with both held D = 128 spills
+            load_v();
+        }
         if (kb + NW < n_kb) load_row<D>(k + (int64_t)min((kb + NW) * RB + col, lk - 1) * p.kv_stride_tok, quarter, kf);
         const int lim = amax - kb * RB - 4 * quarter;    // key 4 * quarter + i of the block is masked iff i > lim
 #pragma unroll
@@ -262,9 +267,11 @@ __device__ __forceinline__ void f32_dq_body(const cf_attn_bwd_params &b, int id,
         f32x4 kf[S::J], vf[S::J];
         load_row<D>(k + (int64_t)row * p.kv_stride_tok, quarter, kf);
         load_row<D>(v + (int64_t)row * p.kv_stride_tok, quarter, vf);
-        const f32x4 s = row_product<D>(kf, qs, lane);
         f32x4 x[4][S::NC];
-        load_columns<D>(k + (int64_t)(kb * RB) * p.kv_stride_tok, kv_row_bytes, lk - 1 - kb * RB, lane, x);
+        auto load_k = [&] { load_columns<D>(k + (int64_t)(kb * RB) * p.kv_stride_tok, kv_row_bytes, lk - 1 - kb * RB, lane, x); };
+        if (D == 64) load_k();
+        const f32x4 s = row_product<D>(kf, qs, lane);
+        if (D != 64) load_k();
         f32x4 dp = row_product<D>(vf, dos, lane);
         const int lim = amax - kb * RB - 4 * quarter;
 #pragma unroll
@@ -319,8 +326,14 @@ __device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id
         const float *q = (const float *)p.q + (int64_t)(loc.other_begin + q0) * p.q_stride_tok + (int64_t)h * p.q_stride_head;
         const float *d_o = (const float *)b.d_o + (int64_t)(loc.other_begin + q0) * b.do_stride_tok + (int64_t)h * b.do_stride_head;
         const int last = lq - 1 - q0, row = min(col, last);      // relative to the block's first row
-        f32x4 a[S::J];
+        // At D = 64 (almost) everything an item reads is requested at once (one latency; short calls are made of those); at
+        // D = 128 there are registers for one or two operands at a time.
+        f32x4 a[S::J], qa[S::J], x[4][S::NC], y[4][S::NC];
         load_row<D>(d_o + (int64_t)row * b.do_stride_tok, quarter, a);
+        auto load_q_row = [&] { load_row<D>(q + (int64_t)row * p.q_stride_tok, quarter, qa); };
+        auto load_do_columns = [&] { load_columns<D>(d_o, do_row_bytes, last, lane, x); };
+        auto load_q_columns = [&] { load_columns<D>(q, q_row_bytes, last, lane, y); };
+        if (D == 64) load_q_row(), load_do_columns();
         const float *orow = (const float *)p.o + (int64_t)(loc.other_begin + q0 + row) * p.o_stride_tok + (int64_t)h * p.o_stride_head;
         float dlt = 0.f;
 #pragma unroll
@@ -337,10 +350,9 @@ __device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id
         }
         __builtin_amdgcn_wave_barrier();
         f32x4 dp = row_product<D>(a, vs, lane);
-        load_row<D>(q + (int64_t)row * p.q_stride_tok, quarter, a);
-        f32x4 x[4][S::NC];
-        load_columns<D>(d_o, do_row_bytes, last, lane, x);
-        f32x4 s = row_product<D>(a, ks, lane);
+        if (D == 64) load_q_columns();
+        else load_q_row(), load_do_columns();
+        f32x4 s = row_product<D>(qa, ks, lane);
         const int lim = k0 + col - off - q0 - 4 * quarter;           // query 4 * quarter + i of the block is masked iff i < lim
         const f32x4 l4 = *(const f32x4 *)(st + 4 * quarter), d4 = *(const f32x4 *)(st + RB + 4 * quarter);
 #pragma unroll
@@ -349,31 +361,33 @@ __device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id
             dp[i] = s[i] * (dp[i] - d4[i]);
         }
         __builtin_amdgcn_wave_barrier();                             // st is rewritten by the next item
-        f32x4 y[4][S::NC];
-        load_columns<D>(q, q_row_bytes, last, lane, y);
+        if (D != 64) load_q_columns();
         add_column_product<D>(x, s, dv);
         add_column_product<D>(y, dp, dk);
     }
+    // At D = 64 both results meet in LDS together, at D = 128 there is room for one after the other.
     const int n = min(NW, n_items);
-    auto add_rows = [&](const Acc<D> &acc, float *g, float scale) {
+    constexpr int TOGETHER = S::BOTH_MEET ? 2 : 1;
+    for (int first = 0; first < 2; first += TOGETHER) {
         __syncthreads();
-        if (wave < n_items) write_part<D>(acc, parts + wave * S::PART, lane);
-        __syncthreads();
-        for (int t = threadIdx.x; t < rows * (D / 4); t += NW * 64) {
-            const int r = t / (D / 4), c = t % (D / 4);
-            f32x4 *dst = (f32x4 *)(g + (int64_t)(loc.begin + k0 + r) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head + c * 4);
-            *dst += sum_parts<D>(parts, n, r, c) * scale;
+        if (wave < n_items) {
+            if (first == 0) write_part<D>(dv, parts + wave * S::PART, lane);
+            if (first + TOGETHER == 2) write_part<D>(dk, parts + ((TOGETHER - 1) * NW + wave) * S::PART, lane);
         }
-    };
-    add_rows(dv, b.d_v, 1.f);
-    add_rows(dk, b.d_k, p.softmax_scale);
+        __syncthreads();
+        for (int t = threadIdx.x; t < TOGETHER * rows * (D / 4); t += NW * 64) {
+            const int which = first + t / (rows * (D / 4)), r = t / (D / 4) % rows, c = t % (D / 4);
+            f32x4 *dst = (f32x4 *)((which ? b.d_k : b.d_v) + (int64_t)(loc.begin + k0 + r) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head + c * 4);
+            *dst += sum_parts<D>(parts + (which - first) * NW * S::PART, n, r, c) * (which ? p.softmax_scale : 1.f);
+        }
+    }
 }
 
 template <int D>
 __global__ __launch_bounds__(NW * 64) void f32_bwd_kernel(cf_attn_bwd_params b, int dkv_blocks)
 {
     using S = Shape<D>;
-    constexpr int OPERANDS = 2 * S::OPERAND + RB * 4, PARTS = NW * S::PART * 4;
+    constexpr int OPERANDS = 2 * S::OPERAND + RB * 4, PARTS = (S::BOTH_MEET ? 2 : 1) * NW * S::PART * 4;
     __shared__ __attribute__((aligned(16))) char smem[OPERANDS > PARTS ? OPERANDS : PARTS];
     __shared__ __attribute__((aligned(16))) float stat[NW][2 * RB];
     if ((int)blockIdx.x < dkv_blocks) f32_dkv_body<D>(b, blockIdx.x, smem, stat);

@@ -309,6 +309,14 @@ struct TileLocation {
 __device__ __forceinline__ bool locate_tile(const int32_t *cu, const int32_t *cu_other, int n_seg, int tile, int rank,
                                             TileLocation &out)
 {
+    if (n_seg == 1) {                                // one slice of one sequence: nothing to search
+        out.seg = 0;
+        out.begin = cu[0], out.len = cu[1] - cu[0];
+        out.other_begin = cu_other[0], out.other_len = cu_other[1] - cu_other[0];
+        const int n = (out.len + tile - 1) / tile;
+        out.tile_in_seg = n - 1 - rank;
+        return rank < n;
+    }
     const int lane = threadIdx.x & 63;
     for (int base = 0; base < n_seg; base += 64) {
         const int gi = n_seg - 1 - (base + lane);

@@ -191,6 +191,7 @@ class ChunkAttention:
             self.fwd_batch = B.params_array([self.chunks[c]["fwd"] for c in self.forward_order()])
             self.bwd_batch = B.params_array([self.chunks[c]["bwd"] for c in self.backward_order()])
         self.total_pairs = sum(ch["pairs"] for ch in placed_chunks)
+        self._calls = {}          # launch orders as the library takes them, by what they are (see _launch_order)
         return self
 
     # ------------------------------------------------------------------ launches
@@ -207,13 +208,9 @@ class ChunkAttention:
         return [c for g in self.groups() for c in reversed(self.plan.group(g))]
 
     def _launch(self, ops):
-        """ops: iterable of (is_backward, chunk id) in issue order.  One stream: plain launches on the current
-        stream.  Several: every side stream first waits for what the current stream has queued, and the current
-        stream waits for all of them at the end, so callers see ordinary stream semantics."""
-        if not self.streams:
-            for bwd, c in ops:
-                (B.cf_attn_bwd if bwd else B.cf_attn_fwd)(self.chunks[c]["bwd" if bwd else "fwd"])
-            return
+        """ops: list of (is_backward, chunk id) in issue order, dealt over the side streams: every side stream first
+        waits for what the current stream has queued, and the current stream waits for all of them at the end, so
+        callers see ordinary stream semantics."""
         cur = torch.cuda.current_stream()
         start = torch.cuda.Event()
         start.record(cur)
@@ -228,23 +225,33 @@ class ChunkAttention:
             done.record(st)
             cur.wait_event(done)
 
+    def _launch_order(self, key, make_ops):
+        """Launches an order of (is_backward, chunk id) that follows from the plan alone.  One stream: plain launches on
+        the current stream, one cf_attn_fwd / cf_attn_bwd call per op, in a list that is laid out once, like the plan."""
+        if self.streams:
+            self._launch(make_ops())
+            return
+        if key not in self._calls:
+            self._calls[key] = B.make_calls((bwd, self.chunks[c]["bwd" if bwd else "fwd"]) for bwd, c in make_ops())
+        B.cf_attn_calls(self._calls[key])
+
     def run_forward(self, fused=None):
         """fused: None = as constructed; True needs fused_launch=True at construction."""
         if self.fused_launch if fused is None else fused:
             B.cf_attn_fwd_batch(self.fwd_batch)
         else:
-            self._launch((False, c) for c in self.forward_order())      # ascending inside each group
+            self._launch_order("fwd", lambda: [(False, c) for c in self.forward_order()])      # ascending inside each group
 
     def run_backward(self, fused=None):
         if self.fused_launch if fused is None else fused:
             B.cf_attn_bwd_batch(self.bwd_batch)
         else:
-            self._launch((True, c) for c in self.backward_order())      # descending inside each group
+            self._launch_order("bwd", lambda: [(True, c) for c in self.backward_order()])      # descending inside each group
 
     def run_schedule(self, K):
         """Algorithm 2 with K kept chunks: chunks marked FWD_DISCARD run forward (their K/V state is
         what later chunks need) and run forward again right before their backward."""
-        self._launch((op == B.CF_OP_BWD, c) for op, c in self.plan.schedule(K) if self.chunks[c] is not None)
+        self._launch_order(int(K), lambda: [(op == B.CF_OP_BWD, c) for op, c in self.plan.schedule(K) if self.chunks[c] is not None])
 
     def capture_step(self, K=None):
         """One whole step (zeroing of the gradients, forward, backward; Algorithm 2 with K kept chunks when K is
