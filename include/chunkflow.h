@@ -302,11 +302,11 @@ int cf_attn_bwd_static(const cf_attn_bwd_params *p, void *hip_stream);
  * Whole-plan launches: several chunks in one call.  The results are those of calling cf_attn_fwd /
  * cf_attn_bwd for params[0], params[1], ... in that order on the stream (dK/dV that several chunks share --
  * the chunks of one long sequence, section 4.2 -- accumulate in exactly that order).  What changes is the
- * launch shape: for a run of consecutive chunks that take the bf16 head_dim-128 path with equal head counts
- * (up to 16 forward, 8 backward), the forward kernels -- and in the backward the dQ kernels, which touch
- * nothing another chunk's backward writes -- become ONE launch whose workgroups are dealt heaviest chunk
- * first, so that the last, partly filled wave of workgroups of a big chunk is filled by the next chunk's
- * instead of leaving compute units idle.  The dK/dV kernels still run chunk by chunk.
+ * launch shape: a run of consecutive chunks on the same matrix kernels (dtype, head counts, head_dim; up to 16
+ * forward, 8 backward) that do not touch each other's results becomes ONE launch per kernel, whose workgroups are
+ * dealt heaviest chunk first: the last, partly filled wave of workgroups of a big chunk is filled by the next
+ * chunk's, and small chunks fill the GPU together.  In the backward, chunks that add to the same dK/dV rows share
+ * the dQ launch only (bf16) or no launch (fp32).
  *   params  host array [n]; for the backward every chunk needs a workspace of its OWN (they are in use at
  *           the same time; overlapping workspaces -> CF_EINVAL)
  * Errors: as the single-chunk calls, checked for every chunk before anything is enqueued; n == 0 is a no-op.
@@ -316,9 +316,12 @@ int cf_attn_bwd_batch(const cf_attn_bwd_params *params, int32_t n, void *hip_str
 
 /*
  * n calls, in order, on one stream: calls[i].backward ? cf_attn_bwd(calls[i].params) : cf_attn_fwd(calls[i].params),
- * with params a cf_attn_bwd_params resp. cf_attn_fwd_params.  The same launches as n separate calls; what is saved is
- * the caller's way into the library (for a caller in an interpreted language longer than the launch itself).
- * Stops at the first call that fails and returns its error.  n < 0, NULL calls with n > 0 -> CF_EINVAL.
+ * with params a cf_attn_bwd_params resp. cf_attn_fwd_params.  Results as of n separate calls, which this saves the way
+ * into the library (for a caller in an interpreted language longer than the launch itself); calls next to each other
+ * that do not touch each other's results -- backward ones with workspaces of their own among them -- share launches as
+ * in cf_attn_fwd_batch / cf_attn_bwd_batch.  (cu_seqlens and q_tiles are descriptors: no call of the list writes them.)
+ * Stops at the first call that fails and returns its error; the calls before it have been enqueued.  n < 0, NULL calls
+ * with n > 0 -> CF_EINVAL.
  */
 typedef struct {
     const void *params;

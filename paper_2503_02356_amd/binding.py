@@ -344,6 +344,9 @@ def cf_attn_bwd_batch(params_arr, stream=None):
     _check(lib().cf_attn_bwd_batch(params_arr, n, stream if stream is not None else _stream()))
 
 
+BWD_TOGETHER = 8          # backward calls that cf_attn_calls puts into one launch at most
+
+
 def make_calls(ops):
     """The argument of cf_attn_calls: ops is an iterable of (is_backward, parameter struct)."""
     ops = list(ops)

@@ -142,16 +142,16 @@ __device__ __forceinline__ f32x4 sum_parts(const float *parts, int n, int row, i
 }
 
 template <int D>
-__global__ __launch_bounds__(NW * 64) void f32_fwd_kernel(cf_attn_fwd_params p)
+__device__ __forceinline__ void f32_fwd_body(const cf_attn_fwd_params &p, int id)
 {
     using S = Shape<D>;
     __shared__ f32x4 qs[S::J * 64];
     __shared__ __attribute__((aligned(16))) float parts[NW * S::PART];
     __shared__ float m_s[NW][RB], l_s[NW][RB];
     const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
-    const int G = p.n_q_heads / p.n_kv_heads, kh = blockIdx.x % p.n_kv_heads, h = kh * G + blockIdx.x / p.n_kv_heads % G;
+    const int G = p.n_q_heads / p.n_kv_heads, kh = id % p.n_kv_heads, h = kh * G + id / p.n_kv_heads % G;
     TileLocation loc;
-    if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, RB, blockIdx.x / p.n_q_heads, loc)) return;
+    if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, RB, id / p.n_q_heads, loc)) return;
     const int lq = uniform(loc.len), lk = uniform(loc.other_len), off = lk - lq, q0 = uniform(loc.tile_in_seg) * RB;
     const int rows = min(RB, lq - q0), n_kb = (q0 + rows + off + RB - 1) / RB;
     const float *q = (const float *)p.q + (int64_t)loc.begin * p.q_stride_tok + (int64_t)h * p.q_stride_head;
@@ -217,6 +217,40 @@ __global__ __launch_bounds__(NW * 64) void f32_fwd_kernel(cf_attn_fwd_params p)
         *(f32x4 *)((float *)p.o + (int64_t)(loc.begin + q0 + r) * p.o_stride_tok + (int64_t)h * p.o_stride_head + c * 4) = a * (1.f / L);
         if (c == 0) p.lse[(int64_t)h * p.n_tokens + loc.begin + q0 + r] = M * kLn2 + logf(L);
     }
+}
+
+template <int D>
+__global__ __launch_bounds__(NW * 64) void f32_fwd_kernel(cf_attn_fwd_params p) { f32_fwd_body<D>(p, blockIdx.x); }
+
+// Several chunks in one launch: workgroups [first_block[c], first_block[c + 1]) belong to chunk c.
+template <typename Params, int MAX>
+struct Batch {
+    int n;
+    int first_block[MAX + 1], dkv_blocks[MAX];
+    Params p[MAX];
+    __device__ __forceinline__ int chunk_of(int id) const
+    {
+        int c = 0;
+        while (c + 1 < n && id >= first_block[c + 1]) ++c;
+        return c;
+    }
+    bool append(const Params &chunk, int64_t dkv, int64_t others)
+    {
+        if (first_block[n] + dkv + others > 0x7fffffffLL) return false;
+        p[n] = chunk;
+        dkv_blocks[n] = (int)dkv;
+        first_block[n + 1] = first_block[n] + (int)(dkv + others);
+        ++n;
+        return true;
+    }
+};
+using FwdBatch = Batch<cf_attn_fwd_params, CF_FWD_BATCH_MAX>;
+using BwdBatch = Batch<cf_attn_bwd_params, CF_BWD_BATCH_MAX>;
+template <int D>
+__global__ __launch_bounds__(NW * 64) void f32_fwd_batch_kernel(FwdBatch q)
+{
+    const int c = q.chunk_of(blockIdx.x);
+    f32_fwd_body<D>(q.p[c], blockIdx.x - q.first_block[c]);
 }
 
 // dQ of 16 query rows of one head.
@@ -384,23 +418,33 @@ __device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id
 }
 
 template <int D>
-__global__ __launch_bounds__(NW * 64) void f32_bwd_kernel(cf_attn_bwd_params b, int dkv_blocks)
+__device__ __forceinline__ void f32_bwd_body(const cf_attn_bwd_params &b, int id, int dkv_blocks)
 {
     using S = Shape<D>;
     constexpr int OPERANDS = 2 * S::OPERAND + RB * 4, PARTS = (S::BOTH_MEET ? 2 : 1) * NW * S::PART * 4;
     __shared__ __attribute__((aligned(16))) char smem[OPERANDS > PARTS ? OPERANDS : PARTS];
     __shared__ __attribute__((aligned(16))) float stat[NW][2 * RB];
-    if ((int)blockIdx.x < dkv_blocks) f32_dkv_body<D>(b, blockIdx.x, smem, stat);
-    else f32_dq_body<D>(b, blockIdx.x - dkv_blocks, smem);
+    if (id < dkv_blocks) f32_dkv_body<D>(b, id, smem, stat);
+    else f32_dq_body<D>(b, id - dkv_blocks, smem);
+}
+template <int D>
+__global__ __launch_bounds__(NW * 64) void f32_bwd_kernel(cf_attn_bwd_params b, int dkv_blocks) { f32_bwd_body<D>(b, blockIdx.x, dkv_blocks); }
+template <int D>
+__global__ __launch_bounds__(NW * 64) void f32_bwd_batch_kernel(BwdBatch q)
+{
+    const int c = q.chunk_of(blockIdx.x);
+    f32_bwd_body<D>(q.p[c], blockIdx.x - q.first_block[c], q.dkv_blocks[c]);
 }
 
 // Upper bounds on block counts: sum_g ceil(L_g / 16) <= total / 16 + n_segments.
 int64_t row_blocks(int64_t total, int n_segments) { return total / RB + n_segments; }
+int64_t query_blocks(const cf_attn_fwd_params &p) { return row_blocks(p.n_tokens, p.n_segments) * p.n_q_heads; }
+int64_t key_blocks(const cf_attn_fwd_params &p) { return row_blocks(p.n_kv_tokens, p.n_segments) * p.n_kv_heads; }
 
 template <int D>
 hipError_t run_fwd(const cf_attn_fwd_params &p, hipStream_t s)
 {
-    const int64_t blocks = row_blocks(p.n_tokens, p.n_segments) * p.n_q_heads;
+    const int64_t blocks = query_blocks(p);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const ProfileHook hook = take_profile_hook();
     if (hook.start) (void)hipEventRecord(hook.start, s);
@@ -413,8 +457,7 @@ hipError_t run_fwd(const cf_attn_fwd_params &p, hipStream_t s)
 template <int D>
 hipError_t run_bwd(const cf_attn_bwd_params &b, hipStream_t s)
 {
-    const cf_attn_fwd_params &p = b.f;
-    const int64_t dkv = row_blocks(p.n_kv_tokens, p.n_segments) * p.n_kv_heads, dq = row_blocks(p.n_tokens, p.n_segments) * p.n_q_heads;
+    const int64_t dkv = key_blocks(b.f), dq = query_blocks(b.f);
     if (dkv + dq > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const ProfileHook hook = take_profile_hook();
     if (hook.start) (void)hipEventRecord(hook.start, s);
@@ -428,5 +471,32 @@ hipError_t run_bwd(const cf_attn_bwd_params &b, hipStream_t s)
 
 hipError_t launch_f32_fwd(const cf_attn_fwd_params &p, hipStream_t s) { return p.head_dim == 64 ? run_fwd<64>(p, s) : run_fwd<128>(p, s); }
 hipError_t launch_f32_bwd(const cf_attn_bwd_params &b, hipStream_t s) { return b.f.head_dim == 64 ? run_bwd<64>(b, s) : run_bwd<128>(b, s); }
+
+
+hipError_t launch_f32_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s)
+{
+    if (n < 1 || n > CF_FWD_BATCH_MAX) return hipErrorInvalidValue;
+    FwdBatch q;
+    q.n = q.first_block[0] = 0;
+    for (int c = 0; c < n; ++c)
+        if (!q.append(*chunks[c], 0, query_blocks(*chunks[c]))) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)q.first_block[n]);
+    if (chunks[0]->head_dim == 64) f32_fwd_batch_kernel<64><<<grid, NW * 64, 0, s>>>(q);
+    else f32_fwd_batch_kernel<128><<<grid, NW * 64, 0, s>>>(q);
+    return hipGetLastError();
+}
+
+hipError_t launch_f32_bwd_batch(const cf_attn_bwd_params *const *chunks, int n, hipStream_t s)
+{
+    if (n < 1 || n > CF_BWD_BATCH_MAX) return hipErrorInvalidValue;
+    BwdBatch q;
+    q.n = q.first_block[0] = 0;
+    for (int c = 0; c < n; ++c)
+        if (!q.append(*chunks[c], key_blocks(chunks[c]->f), query_blocks(chunks[c]->f))) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)q.first_block[n]);
+    if (chunks[0]->f.head_dim == 64) f32_bwd_batch_kernel<64><<<grid, NW * 64, 0, s>>>(q);
+    else f32_bwd_batch_kernel<128><<<grid, NW * 64, 0, s>>>(q);
+    return hipGetLastError();
+}
 
 }  // namespace cf

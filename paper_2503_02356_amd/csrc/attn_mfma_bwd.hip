@@ -23,6 +23,7 @@
 //              It also computes delta = <dO, O> (which the dK/dV kernel, launched after it, reads).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -44,8 +45,8 @@ constexpr int BKV = 128;                              // key rows per workgroup,
 // key/value head.  A key tile seen by few query tiles keeps all G heads of the group in ONE item (one
 // prologue, one epilogue, one set of atomic updates instead of G); a tile seen by many query tiles is split
 // over up to G items so that no workgroup runs much longer than `target` tile iterations: half of what a workgroup slot
-// gets on average (two workgroups on each of 256 compute units), so that small chunks spread over the whole chip and
-// large ones end evenly, but at most kSplitTarget.
+// gets on average (two workgroups on each of 256 compute units; `slots` of them when several chunks share a launch), so
+// that small chunks spread over the whole chip and large ones end evenly, but at most kSplitTarget.
 // The list is ordered by DESCENDING duration (heads x query tiles; a counting sort): workgroups start in list
 // order, and starting the longest first is what keeps the last compute units from running one long item alone
 // (a packed 8K chunk has ~500 items of 7 to 130 iterations for 256 compute units).
@@ -54,11 +55,11 @@ constexpr int kSplitTarget = 48;
 constexpr int kSlots = 512;
 constexpr int kDurationBuckets = 256;
 
-// Runs in ONE workgroup of 256 threads: as a kernel of its own (whole-plan launches) or as the first workgroup of the dQ
-// launch, which the dK/dV kernel follows anyway (no launch of its own on the per-chunk path).
+// Runs in ONE workgroup of 256 threads: among the first of the dQ launch, which the dK/dV kernel follows anyway (no launch
+// of its own).
 // Segment bounds pass through LDS 256 at a time (one coalesced load instead of a chain of dependent ones); a wavefront
 // takes every fourth segment, its lanes the key tiles.
-__device__ __forceinline__ void build_dkv_worklist(const cf_attn_fwd_params &p, int *wl, int capacity)
+__device__ __forceinline__ void build_dkv_worklist(const cf_attn_fwd_params &p, int *wl, int capacity, int slots)
 {
     __shared__ int bucket[kDurationBuckets];        // items per duration, then the next free slot of each duration
     __shared__ int seg_lq[256], seg_lk[256];
@@ -89,7 +90,7 @@ __device__ __forceinline__ void build_dkv_worklist(const cf_attn_fwd_params &p, 
     for_each_tile([&](int, int, int n_qt) { mine += n_qt; });
     atomicAdd(&total, mine);
     __syncthreads();
-    const int target = max(2, min(kSplitTarget, (int)((int64_t)total * p.n_q_heads / (2 * kSlots))));
+    const int target = max(2, min(kSplitTarget, (int)((int64_t)total * p.n_q_heads / (2 * slots))));
     auto for_each_item = [&](auto &&visit) {
         for_each_tile([&](int seg, int kt0, int n_qt) {
             const int sp = min(G, (G * n_qt + target - 1) / target);
@@ -116,10 +117,6 @@ __device__ __forceinline__ void build_dkv_worklist(const cf_attn_fwd_params &p, 
         if (slot < capacity) items[slot] = item;     // (capacity is an upper bound on the item count; see dkv_worklist_capacity)
     });
     if (tid == 0) wl[0] = min(n_items, capacity);
-}
-__global__ __launch_bounds__(256) void dkv_worklist_kernel(cf_attn_fwd_params p, int *wl, int capacity)
-{
-    build_dkv_worklist(p, wl, capacity);
 }
 
 // One stage: Q tile, dO tile, LSE[64] (log2 units), -delta[64] (the dQ kernel stores it negated).  Two stages also hold the end-of-kernel transpose
@@ -430,6 +427,33 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(cf_attn_bwd_params b, 
     dkv_body<D, FUSED_HEADS>(b, delta, blockIdx.x, wl, st0, st1);
 }
 
+// Several chunks' backward in one launch: workgroups [first_block[c], first_block[c + 1]) belong to chunk c.
+struct BwdBatch {
+    int n;
+    int first_block[CF_BWD_BATCH_MAX + 1];
+    int capacity[CF_BWD_BATCH_MAX], slots[CF_BWD_BATCH_MAX];     // of the work list that is built (see there)
+    float *delta[CF_BWD_BATCH_MAX];
+    int *wl[CF_BWD_BATCH_MAX];                                   // nullptr: no list (one workgroup per key tile)
+    cf_attn_bwd_params b[CF_BWD_BATCH_MAX];
+};
+__device__ __forceinline__ int chunk_of(const BwdBatch &q, int id)
+{
+    int c = 0;
+    while (c + 1 < q.n && id >= q.first_block[c + 1]) ++c;
+    return c;
+}
+
+// Chunks whose dK/dV rows are disjoint.  Their lists follow each other, each longest first: the last workgroups of one
+// chunk run beside the first of the next.
+template <int D>
+__global__ __launch_bounds__(256, 2) void mfma_dkv_batch_kernel(BwdBatch q)
+{
+    __shared__ __attribute__((aligned(16))) char st0[DkvStage<D>::bytes];
+    __shared__ __attribute__((aligned(16))) char st1[DkvStage<D>::bytes];
+    const int c = chunk_of(q, blockIdx.x);
+    dkv_body<D, false>(q.b[c], q.delta[c], blockIdx.x - q.first_block[c], q.wl[c], st0, st1);
+}
+
 // =====================================================================================================
 // dQ
 // =====================================================================================================
@@ -656,7 +680,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(cf_attn_bwd_params b, f
     // The list builder is workgroup 0: it starts with the first wave of workgroups and is long done when the
     // launch ends (as the last workgroup it would start last and could be what the launch ends with).
     if (wl != nullptr && blockIdx.x == 0) {
-        build_dkv_worklist(b.f, wl, capacity);
+        build_dkv_worklist(b.f, wl, capacity, kSlots);
         return;
     }
     // Two separate arrays (not one array with two halves): the compiler must see that the direct-to-LDS
@@ -666,23 +690,21 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(cf_attn_bwd_params b, f
     dq_body<D>(b, delta, (int)blockIdx.x - (wl != nullptr ? 1 : 0), stage_a, stage_b);
 }
 
-// Several chunks in one launch (workgroups [first_block[c], first_block[c+1]) belong to chunk c, heaviest chunk
-// first): dQ and delta of a chunk depend on nothing another chunk's backward writes, so the last, partly filled
-// wave of workgroups of a big chunk can be filled by the next chunk's.
-struct DqBatch {
-    int n;
-    int first_block[CF_BWD_BATCH_MAX + 1];
-    float *delta[CF_BWD_BATCH_MAX];
-    cf_attn_bwd_params b[CF_BWD_BATCH_MAX];
-};
+// Several chunks, heaviest first: dQ and delta of a chunk depend on nothing another chunk's backward writes, so the last,
+// partly filled wave of workgroups of a big chunk can be filled by the next chunk's.  The first q.n workgroups build the
+// chunks' dK/dV work lists.
 template <int D>
-__global__ __launch_bounds__(256, 2) void mfma_dq_batch_kernel(DqBatch q)
+__global__ __launch_bounds__(256, 2) void mfma_dq_batch_kernel(BwdBatch q)
 {
+    if ((int)blockIdx.x < q.n) {
+        const int c = blockIdx.x;
+        if (q.wl[c] != nullptr) build_dkv_worklist(q.b[c].f, q.wl[c], q.capacity[c], q.slots[c]);
+        return;
+    }
     __shared__ __attribute__((aligned(16))) char stage_a[KvStage<D>::bytes];
     __shared__ __attribute__((aligned(16))) char stage_b[KvStage<D>::bytes];
-    int c = 0;
-    while (c + 1 < q.n && (int)blockIdx.x >= q.first_block[c + 1]) ++c;
-    dq_body<D>(q.b[c], q.delta[c], blockIdx.x - q.first_block[c], stage_a, stage_b);
+    const int id = (int)blockIdx.x - q.n, c = chunk_of(q, id);
+    dq_body<D>(q.b[c], q.delta[c], id - q.first_block[c], stage_a, stage_b);
 }
 
 // Launch geometry of one chunk's backward.
@@ -729,35 +751,63 @@ hipError_t run_bwd(const cf_attn_bwd_params &b, const BwdWorkspace &ws, hipStrea
     return e != hipSuccess ? e : launch_dkv<D>(b, ws, g, take_profile_hook(), s);
 }
 
+// Adds a chunk's part to a batch launch.
+bool append(BwdBatch &q, const cf_attn_bwd_params &b, const BwdWorkspace &ws, const BwdShape &g, int64_t blocks)
+{
+    const int i = q.n;
+    if (q.first_block[i] + blocks > 0x7fffffffLL - CF_BWD_BATCH_MAX) return false;
+    q.first_block[i + 1] = q.first_block[i] + (int)blocks;
+    q.capacity[i] = (int)ws.worklist_items;
+    q.delta[i] = ws.delta;
+    q.wl[i] = g.fused ? nullptr : ws.worklist;
+    q.b[i] = b;
+    ++q.n;
+    return true;
+}
+
 template <int D>
-hipError_t run_bwd_batch(const cf_attn_bwd_params *const *chunks, const BwdWorkspace *ws, const int *dq_order, int n, hipStream_t s)
+hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
 {
     BwdShape g[CF_BWD_BATCH_MAX];
-    hipError_t e;
+    int order[CF_BWD_BATCH_MAX];
+    int64_t tokens[CF_BWD_BATCH_MAX] = {};           // of the dK/dV launch that a chunk goes into (index: its first chunk)
+    int first_of[CF_BWD_BATCH_MAX];
     for (int c = 0; c < n; ++c) {
-        g[c] = bwd_shape(chunks[c]->f, ws[c]);
+        g[c] = bwd_shape(chunks[c].b->f, chunks[c].ws);
         if (!g[c].ok) return hipErrorInvalidConfiguration;
-        if (g[c].fused) continue;
-        dkv_worklist_kernel<<<1, 256, 0, s>>>(chunks[c]->f, ws[c].worklist, (int)ws[c].worklist_items);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        first_of[c] = c > 0 && chunks[c].dkv_with_previous && !g[c].fused && !g[c - 1].fused ? first_of[c - 1] : c;
+        tokens[first_of[c]] += chunks[c].b->f.n_tokens;
+        order[c] = c;
     }
-    DqBatch q;
-    q.n = n;
-    int64_t total = 0;
+    // heaviest first: work ~ queries x keys
+    std::stable_sort(order, order + n, [&](int x, int y) {
+        const cf_attn_fwd_params &a = chunks[x].b->f, &b = chunks[y].b->f;
+        return (int64_t)a.n_tokens * a.n_kv_tokens > (int64_t)b.n_tokens * b.n_kv_tokens;
+    });
+    BwdBatch q;
+    q.n = q.first_block[0] = 0;
     for (int i = 0; i < n; ++i) {
-        const int c = dq_order[i];
-        q.first_block[i] = (int)total;
-        q.delta[i] = ws[c].delta;
-        q.b[i] = *chunks[c];
-        total += g[c].dq_blocks;
-        if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+        const int c = order[i];
+        q.slots[i] = (int)max((int64_t)1, kSlots * (int64_t)chunks[c].b->f.n_tokens / tokens[first_of[c]]);
+        if (!append(q, *chunks[c].b, chunks[c].ws, g[c], g[c].dq_blocks)) return hipErrorInvalidConfiguration;
     }
-    q.first_block[n] = (int)total;
-    mfma_dq_batch_kernel<D><<<dim3((unsigned)total), 256, 0, s>>>(q);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    for (int c = 0; c < n; ++c)
-        if ((e = launch_dkv<D>(*chunks[c], ws[c], g[c], ProfileHook(), s)) != hipSuccess) return e;
-    return hipSuccess;
+    mfma_dq_batch_kernel<D><<<dim3((unsigned)(q.first_block[n] + n)), 256, 0, s>>>(q);
+    hipError_t e = hipGetLastError();
+    for (int first = 0, end; first < n && e == hipSuccess; first = end) {
+        for (end = first + 1; end < n && first_of[end] == first;) ++end;
+        if (end == first + 1) {
+            e = launch_dkv<D>(*chunks[first].b, chunks[first].ws, g[first], ProfileHook(), s);
+            continue;
+        }
+        q.n = 0;
+        for (int i = 0; i < n; ++i) {
+            const int c = order[i];
+            if (first_of[c] == first && !append(q, *chunks[c].b, chunks[c].ws, g[c], g[c].dkv_blocks)) return hipErrorInvalidConfiguration;
+        }
+        mfma_dkv_batch_kernel<D><<<dim3((unsigned)q.first_block[q.n]), 256, 0, s>>>(q);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 }  // namespace
@@ -773,14 +823,10 @@ hipError_t launch_mfma_bwd(const cf_attn_bwd_params &b, const BwdWorkspace &ws, 
     return b.f.head_dim == 64 ? run_bwd<64>(b, ws, s) : run_bwd<128>(b, ws, s);
 }
 
-// Backward of 1..CF_BWD_BATCH_MAX chunks of one head_dim: work lists, ONE dQ launch over all chunks (dealt in the order of
-// `dq_order`, indices into chunks), then the dK/dV kernels chunk by chunk in the order of `chunks`, which is therefore
-// the order in which a shared dK/dV state accumulates.
-hipError_t launch_mfma_bwd_batch(const cf_attn_bwd_params *const *chunks, const BwdWorkspace *ws, const int *dq_order, int n,
-                                 hipStream_t s)
+hipError_t launch_mfma_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
 {
     if (n < 1 || n > CF_BWD_BATCH_MAX) return hipErrorInvalidValue;
-    return chunks[0]->f.head_dim == 64 ? run_bwd_batch<64>(chunks, ws, dq_order, n, s) : run_bwd_batch<128>(chunks, ws, dq_order, n, s);
+    return chunks[0].b->f.head_dim == 64 ? run_bwd_batch<64>(chunks, n, s) : run_bwd_batch<128>(chunks, n, s);
 }
 
 }  // namespace cf

@@ -28,6 +28,9 @@ ProfileHook take_profile_hook();
 // fp32 matrix kernels, head_dim 64 and 128; the backward is one launch and needs no scratch.
 hipError_t launch_f32_fwd(const cf_attn_fwd_params &p, hipStream_t s);
 hipError_t launch_f32_bwd(const cf_attn_bwd_params &p, hipStream_t s);
+// Several chunks of one head_dim as one launch (limits as for the bf16 kernels below); the backward's d_k / d_v disjoint.
+hipError_t launch_f32_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s);
+hipError_t launch_f32_bwd_batch(const cf_attn_bwd_params *const *chunks, int n, hipStream_t s);
 
 // Plain scalar kernels: any supported head_dim, fp32 or bf16 storage, fp32 arithmetic.
 hipError_t launch_simple_fwd(const cf_attn_fwd_params &p, hipStream_t s);
@@ -42,10 +45,14 @@ hipError_t launch_mfma_fwd(const cf_attn_fwd_params &p, hipStream_t s);
 constexpr int CF_FWD_BATCH_MAX = 16;
 hipError_t launch_mfma_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s);
 hipError_t launch_mfma_bwd(const cf_attn_bwd_params &p, const BwdWorkspace &ws, hipStream_t s);
-// Backward of 1..CF_BWD_BATCH_MAX chunks: one dQ launch (workgroups dealt in the order dq_order, indices into
-// chunks), then the dK/dV kernels in the order of `chunks`.
+// Backward of 1..CF_BWD_BATCH_MAX chunks: one dQ launch, then the dK/dV kernels, one launch per run of chunks that go with
+// their predecessor.
 constexpr int CF_BWD_BATCH_MAX = 8;
-hipError_t launch_mfma_bwd_batch(const cf_attn_bwd_params *const *chunks, const BwdWorkspace *ws, const int *dq_order,
-                                 int n, hipStream_t s);
+struct BwdBatchChunk {
+    const cf_attn_bwd_params *b;
+    BwdWorkspace ws;
+    bool dkv_with_previous;      // its d_k / d_v rows are no other chunk's of the same dK/dV launch
+};
+hipError_t launch_mfma_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s);
 
 }  // namespace cf

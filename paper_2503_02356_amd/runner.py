@@ -33,7 +33,7 @@ class ChunkAttention:
         self.plan, self.Hq, self.Hkv, self.D = plan, n_q_heads, n_kv_heads, head_dim
         self.n_streams = max(1, int(n_streams))
         # fused_launch: run_forward / run_backward hand the whole plan to cf_attn_fwd_batch / cf_attn_bwd_batch
-        # (one workspace per chunk); otherwise one cf_attn_fwd / cf_attn_bwd call per chunk.
+        # (one workspace per chunk); otherwise a list of one cf_attn_fwd / cf_attn_bwd call per chunk to cf_attn_calls.
         self.fused_launch = bool(fused_launch)
         # tile_tables: give every chunk's calls the table of cf_attn_q_tiles (built on the host when the plan is
         # placed: it only depends on the chunk's cu_seqlens), so that the kernels start their heaviest tiles first
@@ -170,8 +170,11 @@ class ChunkAttention:
                                           self.scale, self.flags, q_tiles=ch.get("q_tiles"))
             ws_bytes = max(ws_bytes, B.cf_attn_bwd_workspace_bytes(ch["fwd"]))
             self.chunks.append(ch)
-        # one backward workspace per stream: calls on different streams overlap
-        self.workspaces = [torch.empty(ws_bytes, dtype=torch.uint8, device=dev) for _ in range(self.n_streams)]
+        # Calls in flight together need a backward workspace each: one per stream, and on a single stream as many in turn
+        # as backward calls share a launch.
+        self.workspaces = [torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
+                           for _ in range(0 if self.fused_launch else self.n_streams if self.n_streams > 1 else
+                                          min(B.BWD_TOGETHER, len(self.chunks)))]
         self.streams = [torch.cuda.Stream(device=dev) for _ in range(self.n_streams)] if self.n_streams > 1 else []
         # groups go, in plan order, to the stream with the least work so far (work = unmasked pairs)
         load, lane_of = [0] * self.n_streams, {}
@@ -185,8 +188,11 @@ class ChunkAttention:
             if self.fused_launch:       # the chunks of a fused call are in flight together: a workspace each
                 need = B.cf_attn_bwd_workspace_bytes(ch["fwd"])
                 ch["workspace"] = torch.empty(need, dtype=torch.uint8, device=dev)
-            ch["bwd"] = B.make_bwd_params(ch["fwd"], ch["d_o"], ch["d_q"], ch["dk"], ch["dv"],
-                                          ch.get("workspace", self.workspaces[ch["lane"]]))
+        for i, c in enumerate(self.backward_order()):
+            ch = self.chunks[c]
+            turn = ch["lane"] if self.n_streams > 1 else i % max(1, len(self.workspaces))
+            ws = ch["workspace"] if self.fused_launch else self.workspaces[turn]
+            ch["bwd"] = B.make_bwd_params(ch["fwd"], ch["d_o"], ch["d_q"], ch["dk"], ch["dv"], ws)
         if self.fused_launch:
             self.fwd_batch = B.params_array([self.chunks[c]["fwd"] for c in self.forward_order()])
             self.bwd_batch = B.params_array([self.chunks[c]["bwd"] for c in self.backward_order()])
@@ -226,8 +232,8 @@ class ChunkAttention:
             cur.wait_event(done)
 
     def _launch_order(self, key, make_ops):
-        """Launches an order of (is_backward, chunk id) that follows from the plan alone.  One stream: plain launches on
-        the current stream, one cf_attn_fwd / cf_attn_bwd call per op, in a list that is laid out once, like the plan."""
+        """Launches an order of (is_backward, chunk id) that follows from the plan alone.  One stream: on the current
+        stream, one cf_attn_fwd / cf_attn_bwd call per op, in a list that is laid out once, like the plan."""
         if self.streams:
             self._launch(make_ops())
             return

@@ -1,7 +1,10 @@
 """GPU parity at the sizes where a kernel or a dispatch rule changes its path: edges of tiles, remainders, the smallest
 calls.  Reference: the fp64 oracle's unsplit attention; tolerances: tests/parity.py (per data type)."""
+import numpy as np
 import pytest
+import torch
 
+from paper_2503_02356_amd import binding as B
 from tests import parity as P
 
 pytestmark = pytest.mark.gpu
@@ -19,3 +22,63 @@ def test_fp32_blocks(D, lens, C, Hq, Hkv, scale):
     got, _ = P.run_gpu(lens, C, Hq, Hkv, D, "fp32", seed=31, scale=scale)
     ref = P.run_oracle(lens, Hq, Hkv, D, "fp32", seed=31, scale=scale)
     P.check(got, ref, "fp32", f"lens={lens} C={C} D={D} scale={scale}")
+
+
+@pytest.mark.parametrize("flags", [0, B.CF_FLAG_DKV_SINGLE_WRITER])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("lens,C,Hq,Hkv", [
+    ([1], 8, 1, 1),                                        # one row, one key: one wavefront of four has keys
+    ([31, 32, 33, 63, 64, 65, 127, 128, 129], 642, 4, 2),  # around a wavefront's keys, a query tile, a key tile
+    ([1 + i % 3 for i in range(300)], 600, 2, 1),          # more segments than the work list is built from at once
+    ([700], 70, 7, 1),                                     # slices that start inside a sequence's first 128 positions
+    ([2500], 1300, 8, 1),                                  # key tiles whose query heads are split over work items
+])
+def test_bf16_blocks(D, lens, C, Hq, Hkv, flags):
+    got, _ = P.run_gpu(lens, C, Hq, Hkv, D, "bf16", seed=32, flags=flags)
+    ref = P.run_oracle(lens, Hq, Hkv, D, "bf16", seed=32)
+    P.check(got, ref, "bf16", f"lens={lens[:9]} C={C} D={D} flags={flags}")
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("fp32", 64), ("fp32", 128)])
+def test_calls_that_share_launches(dtype, D):
+    """A list of calls (more than one launch holds; slices of one sequence, whose gradients meet, among them) against the
+    same calls one at a time: O, LSE, dQ bit for bit; dK/dV too in fp32, in bf16 (atomic adds) to fp32 rounding."""
+    lens = [500, 40, 130, 77, 9, 128, 33, 100, 64, 90, 41, 127, 5, 120, 88, 110, 101, 99, 97, 95]
+    got, eng = P.run_gpu(lens, 130, 4, 2, D, dtype, seed=33)
+    assert len(eng.chunks) > 16
+    P.check(got, P.run_oracle(lens, 4, 2, D, dtype, seed=33), dtype, "calls")
+    eng.zero_grads()
+    for c in eng.forward_order():
+        B.cf_attn_fwd(eng.chunks[c]["fwd"])
+    for c in eng.backward_order():
+        B.cf_attn_bwd(eng.chunks[c]["bwd"])
+    one = eng.results()
+    for sid in got:
+        for n in P.NAMES:
+            a, b = got[sid][n], one[sid][n]
+            if n in ("dk", "dv") and dtype == "bf16":      # at most 40 additions, each rounded to 2^-24 of a partial sum (up to 4x the result)
+                assert np.abs(a - b).max() <= 40 * 2.0 ** -24 * max(1.0, np.abs(b).max()) * 4, (sid, n)
+            else:
+                assert np.array_equal(a, b), (sid, n)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_calls_that_depend_on_each_other(dtype):
+    """The second forward takes the first one's output as its queries; the list stops at a call that is refused."""
+    dt, T, H, D = torch.bfloat16 if dtype == "bf16" else torch.float32, 200, 2, 128
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    rand = lambda: torch.randn(T, H, D, device="cuda:0", generator=gen).to(dt)
+    q, k, v, cu = rand(), rand(), rand(), torch.tensor([0, 77, T], dtype=torch.int32, device="cuda:0")
+    o = [torch.zeros_like(q) for _ in range(3)]
+    lse = [torch.zeros(H, T, device="cuda:0") for _ in range(3)]
+    f = [B.make_fwd_params(a, k, v, o[i], lse[i], cu, cu, 0.09) for i, a in enumerate((q, o[0], q))]
+    for p in f[:2]:
+        B.cf_attn_fwd(p)
+    want = o[1].clone()
+    o[0].zero_(), o[1].zero_()
+    f[2].n_segments = 0
+    B.cf_attn_calls(B.make_calls([]))
+    with pytest.raises(B.CfError):
+        B.cf_attn_calls(B.make_calls((False, p) for p in f))
+    torch.cuda.synchronize()
+    assert torch.equal(o[1], want) and not o[2].any()
