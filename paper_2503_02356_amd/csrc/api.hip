@@ -63,16 +63,18 @@ bool mfma_shape(const cf_attn_fwd_params &p)
 {
     return p.dtype == CF_BF16 && !(p.flags & CF_FLAG_SCALAR_KERNELS);
 }
-// The MFMA kernels take the row maximum before scaling, which needs a positive scale.
-bool use_mfma(const cf_attn_fwd_params &p) { return mfma_shape(p) && p.softmax_scale > 0.f; }
+// The matrix kernels address the rows of a block with 32-bit byte offsets: 63 rows x 2 bytes (bf16) and 31 rows x 4 bytes
+// (fp32) of this many elements stay below 2^32.  Wider strides go to the scalar kernels.
+constexpr int64_t kMostStride = 1 << 25;
+bool narrow(const cf_attn_fwd_params &p) { return p.q_stride_tok < kMostStride && p.kv_stride_tok < kMostStride; }
 
-// The fp32 matrix kernels: every fp32 shape, any scale.  They address the 32 rows of a block with 32-bit byte offsets.
-bool use_f32(const cf_attn_fwd_params &p)
-{
-    constexpr int64_t kMostStride = 1 << 25;         // elements: 31 rows x 4 bytes stay below 2^32
-    return p.dtype == CF_FP32 && !(p.flags & CF_FLAG_SCALAR_KERNELS) && p.q_stride_tok < kMostStride && p.kv_stride_tok < kMostStride;
-}
-bool use_f32(const cf_attn_bwd_params &b) { return use_f32(b.f) && b.do_stride_tok < (1 << 25); }
+// The MFMA kernels take the row maximum before scaling, which needs a positive scale.
+bool use_mfma(const cf_attn_fwd_params &p) { return mfma_shape(p) && p.softmax_scale > 0.f && narrow(p); }
+bool use_mfma(const cf_attn_bwd_params &b) { return use_mfma(b.f) && b.do_stride_tok < kMostStride; }
+
+// The fp32 matrix kernels: every fp32 shape, any scale.
+bool use_f32(const cf_attn_fwd_params &p) { return p.dtype == CF_FP32 && !(p.flags & CF_FLAG_SCALAR_KERNELS) && narrow(p); }
+bool use_f32(const cf_attn_bwd_params &b) { return use_f32(b.f) && b.do_stride_tok < kMostStride; }
 
 hipError_t fwd_one(const cf_attn_fwd_params &p, hipStream_t s)
 {
@@ -87,6 +89,9 @@ int64_t worklist_bytes(const cf_attn_fwd_params &p)
 {
     return mfma_shape(p) ? 256 + cf::dkv_worklist_capacity(p) * 16 : 0;
 }
+// The least scratch a backward runs in.  At head_dim 64 that is delta alone: with no room for a work list the dK/dV kernel
+// takes one workgroup per key tile and kv head, as under CF_FLAG_DKV_SINGLE_WRITER.
+int64_t least_scratch(const cf_attn_fwd_params &p) { return delta_bytes(p) + (p.head_dim == 64 ? 0 : worklist_bytes(p)); }
 
 int hip_fail(const char *who, hipError_t e)
 {
@@ -155,12 +160,13 @@ int carve_workspace(const cf_attn_fwd_params &p, void *base, int64_t bytes, cons
                     cf::BwdWorkspace *ws)
 {
     if (!base || !aligned(base, 256)) return cf::fail(CF_EINVAL, "%s: %s must be non-NULL and 256-byte aligned", who, what);
-    const int64_t need = delta_bytes(p) + worklist_bytes(p);
+    const int64_t need = least_scratch(p);
     if (bytes < need)
         return cf::fail(CF_EINVAL, "%s: %s has %lld bytes, %lld needed", who, what, (long long)bytes, (long long)need);
+    const bool listed = mfma_shape(p) && bytes >= delta_bytes(p) + worklist_bytes(p);
     ws->delta = static_cast<float *>(base);
-    ws->worklist = mfma_shape(p) ? reinterpret_cast<int *>(static_cast<char *>(base) + delta_bytes(p)) : nullptr;
-    ws->worklist_items = mfma_shape(p) ? cf::dkv_worklist_capacity(p) : 0;
+    ws->worklist = listed ? reinterpret_cast<int *>(static_cast<char *>(base) + delta_bytes(p)) : nullptr;
+    ws->worklist_items = listed ? cf::dkv_worklist_capacity(p) : 0;
     return CF_OK;
 }
 
@@ -174,7 +180,7 @@ int check_bwd(const cf_attn_bwd_params *b, const char *who, cf::BwdWorkspace *ws
 int bwd_one(const cf_attn_bwd_params *b, const cf::BwdWorkspace &ws, hipStream_t s, const char *who)
 {
     hipError_t e = hipSuccess;
-    if (use_mfma(b->f)) {
+    if (use_mfma(*b)) {
         e = cf::launch_mfma_bwd(*b, ws, s);          // its dQ kernel forms delta itself
     } else if (use_f32(*b)) {
         e = cf::launch_f32_bwd(*b, s);               // so does every workgroup of this one
@@ -201,7 +207,7 @@ constexpr int kWindow = 64;      // calls looked at together
 enum Path { kScalar, kMfma, kF32 };
 Path path_of(const Call &c)
 {
-    return use_mfma(*c.f) ? kMfma : (c.b ? use_f32(*c.b) : use_f32(*c.f)) ? kF32 : kScalar;
+    return (c.b ? use_mfma(*c.b) : use_mfma(*c.f)) ? kMfma : (c.b ? use_f32(*c.b) : use_f32(*c.f)) ? kF32 : kScalar;
 }
 bool same_kernel(const Call &a, const Call &c)
 {
@@ -369,7 +375,7 @@ extern "C" int cf_attn_bwd_static(const cf_attn_bwd_params *b, void *hip_stream)
     const char *who = "cf_attn_bwd_static";
     if (int rc = check_bwd_tensors(b, who)) return rc;
     // the size check comes before any HIP call: an oversized chunk is refused on any host
-    const int64_t need = delta_bytes(b->f) + worklist_bytes(b->f);
+    const int64_t need = least_scratch(b->f);
     if (need > (int64_t)CF_STATIC_SCRATCH_BYTES)
         return cf::fail(CF_EINVAL, "%s: this chunk needs %lld bytes of scratch, the static buffer holds %lld "
                         "(use cf_attn_bwd with a workspace)", who, (long long)need, (long long)CF_STATIC_SCRATCH_BYTES);

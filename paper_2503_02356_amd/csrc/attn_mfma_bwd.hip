@@ -720,7 +720,8 @@ BwdShape bwd_shape(const cf_attn_fwd_params &p, const BwdWorkspace &ws)
     const int64_t kv_tiles = (int64_t)p.n_kv_tokens / BKV + p.n_segments;
     const int64_t q_tiles = p.q_tiles ? (int64_t)p.n_q_tiles : (int64_t)p.n_tokens / BM + p.n_segments;
     // Fusing the heads of a group into one workgroup needs enough key tiles to fill 256 CUs several times.
-    g.fused = kv_tiles * p.n_kv_heads >= 4096 || (p.flags & CF_FLAG_DKV_SINGLE_WRITER);
+    // (no work list: the scratch has no room for one)
+    g.fused = kv_tiles * p.n_kv_heads >= 4096 || (p.flags & CF_FLAG_DKV_SINGLE_WRITER) || ws.worklist == nullptr;
     g.dq_blocks = q_tiles * p.n_q_heads;
     g.dkv_blocks = (g.fused ? kv_tiles : ws.worklist_items) * p.n_kv_heads;
     g.ok = g.dkv_blocks <= 0x7fffffffLL && g.dq_blocks < 0x7fffffffLL && ws.worklist_items <= 0x7fffffffLL;

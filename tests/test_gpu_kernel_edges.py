@@ -82,3 +82,50 @@ def test_calls_that_depend_on_each_other(dtype):
         B.cf_attn_calls(B.make_calls((False, p) for p in f))
     torch.cuda.synchronize()
     assert torch.equal(o[1], want) and not o[2].any()
+
+
+def _backward(q, k, v, d_o, flags=0, workspace_bytes=None):
+    """-> o, lse, dq, dk, dv of one packed chunk of two segments."""
+    (T, H, D), Hkv, dev = q.shape, k.shape[1], q.device
+    o, dq, lse = torch.empty_like(d_o.contiguous()), torch.empty_like(d_o.contiguous()), torch.zeros(H, T, device=dev)
+    dkv = torch.zeros(2, T, Hkv, D, device=dev)
+    cu = torch.tensor([0, T // 3, T], dtype=torch.int32, device=dev)
+    fp = B.make_fwd_params(q, k, v, o, lse, cu, cu, D ** -0.5, flags)
+    B.cf_attn_fwd(fp)
+    ws = torch.empty(workspace_bytes or B.cf_attn_bwd_workspace_bytes(fp), dtype=torch.uint8, device=dev)
+    B.cf_attn_bwd(B.make_bwd_params(fp, d_o, dq, dkv[0], dkv[1], ws))
+    torch.cuda.synchronize()
+    return o, lse, dq, dkv[0], dkv[1]
+
+
+def test_d64_backward_without_room_for_a_work_list():
+    """bf16, head_dim 64, a workspace that holds delta and nothing else: the single-writer kernel, bit for bit."""
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    rand = lambda h: torch.randn(600, h, 64, device="cuda:0", generator=gen).bfloat16()
+    t = rand(4), rand(2), rand(2), rand(4)
+    least = (4 * 600 * 4 + 255) // 256 * 256
+    for a, b in zip(_backward(*t, workspace_bytes=least), _backward(*t, flags=B.CF_FLAG_DKV_SINGLE_WRITER)):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("wide", ["q", "kv", "do"])
+def test_strides_beyond_32_bit_offsets(wide):
+    """64 rows of 2^25 bf16 elements span 4 GiB, more than the matrix kernels' row offsets: the results of the scalar
+    kernels (of each pass that the wide tensor is an input of), bit for bit."""
+    gen = torch.Generator(device="cuda:0").manual_seed(6)
+    T, D, stride = 70, 64, 1 << 25
+    rand = lambda: torch.randn(T, 1, D, device="cuda:0", generator=gen).bfloat16()
+    q, k, v, d_o = rand(), rand(), rand(), rand()
+    room = torch.empty((T - 1) * stride + 2 * D, dtype=torch.bfloat16, device="cuda:0")
+
+    def spread(x, at):
+        y = room[at:].as_strided((T, 1, D), (stride, D, 1))
+        return y.copy_(x)
+    want = _backward(q, k, v, d_o, flags=B.CF_FLAG_SCALAR_KERNELS)
+    got = _backward(spread(q, 0) if wide == "q" else q, spread(k, 0) if wide == "kv" else k, spread(v, D) if wide == "kv" else v,
+                    spread(d_o, 0) if wide == "do" else d_o)
+    for n, a, b in zip(("o", "lse", "dq", "dk", "dv"), got, want):
+        if wide == "do":        # its forward ran on the matrix kernels: bf16 results within their rounding
+            assert (a.double() - b.double()).norm() <= 5e-3 * b.double().norm(), n
+        else:
+            assert torch.equal(a, b), n

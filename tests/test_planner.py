@@ -5,6 +5,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import chunking as CK
 from paper_2503_02356_amd import binding as B
@@ -262,6 +263,16 @@ def test_static_scratch_backward_refuses_oversized_chunks_on_the_host():
     with pytest.raises(B.CfError) as e:
         B.cf_attn_bwd_static(bp, ctypes.c_void_p(0))
     assert e.value.code == B.CF_EINVAL and "static buffer" in str(e.value)
+    # at head_dim 64 delta alone decides: 64 * 65536 * 4 bytes just fit (without a GPU the call gets as far as the HIP error)
+    bp.f.head_dim, bp.f.n_tokens, bp.f.n_kv_tokens = 64, 65537, 65537
+    with pytest.raises(B.CfError) as e:
+        B.cf_attn_bwd_static(bp, ctypes.c_void_p(0))
+    assert e.value.code == B.CF_EINVAL
+    if not torch.cuda.is_available():
+        bp.f.n_tokens = bp.f.n_kv_tokens = 65536
+        with pytest.raises(B.CfError) as e:
+            B.cf_attn_bwd_static(bp, ctypes.c_void_p(0))
+        assert e.value.code == B.CF_EHIP
     hdr = open(os.path.join(ROOT, "include", "chunkflow.h")).read()
     assert re.search(r"#define\s+CF_STATIC_SCRATCH_BYTES\s+\(16\s*<<\s*20\)", hdr)
 
