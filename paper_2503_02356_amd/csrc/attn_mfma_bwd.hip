@@ -135,9 +135,10 @@ struct DkvStage {
 // (A operands from LDS rows resp. transposing LDS reads; lane = key, so P and dS are B operands where they stand).
 // Two workgroups share a compute unit, one wavefront of each on a SIMD, with nothing to wait for in each other: while
 // one multiplies the other does its arithmetic.
-// RESIDUAL tile pairs (those made of a sequence's first 128 positions: query rows at positions < 128 x key tile 0; at
-// D = 64 all of them) feed the MFMAs the bf16 values of P and dS AND their bf16 rounding residuals: rows that see few
-// keys have large P and dS, whose rounding would be the largest error in dK/dV.
+// RESIDUAL tile pairs (those made of a sequence's first 128 positions: query rows at positions < 128 x key tile 0) feed the
+// MFMAs the bf16 values of P and dS AND their bf16 rounding residuals: rows that see few keys have large P and dS, whose
+// rounding would be the largest error in dK/dV.  At D = 64 P and dS enter every product with all their 24 bits instead, as
+// three bf16 operands.
 template <int D, bool FUSED_HEADS>
 __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const float *__restrict__ delta, int id,
                                          const int *__restrict__ wl, char *st0, char *st1)
@@ -184,7 +185,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     if (qt_first >= qt_end) return;                  // whole workgroup leaves before any barrier
     const int n_tiles = n_heads * (qt_end - qt_first);   // (head, query tile) pairs, head by head
     // query tiles below qt_head are RESIDUAL ones for this key tile
-    const int qt_head = D == 64 ? qt_end : kt0 == 0 && off < 128 ? (128 - off + BQ - 1) / BQ : 0;
+    const int qt_head = kt0 == 0 && off < 128 ? (128 - off + BQ - 1) / BQ : 0;
 
     const int kw0 = kt0 + 32 * wave;                 // first key of this wavefront (segment-local)
     const bool wave_active = kw0 < lk;
@@ -325,22 +326,20 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
                         accumulate_in_place<D>(x ? dk[j] : dv[j], lds_read_tr_pair(rows + at.tr_lo(j), rows + at.tr_hi(j)), w);
                 }
         }
-        // dV_w^T += dO^T P, then dK_w^T += Q^T dS.  D = 64 takes the residual of every block along, fragment by fragment,
-        // on the operands that are there (a pass of its own, as D = 128 makes for the few blocks that need one, reads them
-        // twice: 1.00 ms against 0.95 ms a step of 16 / 4 heads, 17.3k tokens).
-        bf16x8 w[4], wl;
+        // dV_w^T += dO^T P, then dK_w^T += Q^T dS.  D = 64 splits each fragment of P and dS (three operands) where it is used.
+        bf16x8 w[4], ws[3];
         if (D != 64) w[0] = pack(s, 0), w[1] = pack(s, 1), w[2] = pack(dp, 0), w[3] = pack(dp, 1);
 #pragma unroll
         for (int m = 0; m < 4 * DB; ++m) {
             __builtin_amdgcn_sched_barrier(0);
             const int j = m % DB, g = m / DB, x = g / 2, n = 2 * KS + m;
-            if (D == 64 && j == 0) {
-                w[g] = pack(x ? dp : s, g % 2);
+            if (D == 64) {
+                if (j == 0) split_exact(x ? dp : s, 8 * (g % 2), ws);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) wl[e] = (__bf16)((x ? dp[8 * (g % 2) + e] : s[8 * (g % 2) + e]) - (float)w[g][e]);
+                for (int t = 0; t < 3; ++t) accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n & 3], ws[t]);
+            } else {
+                accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n & 3], w[g]);
             }
-            accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n & 3], w[g]);
-            if (D == 64) accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n & 3], wl);
             fetch(n + 4);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -348,7 +347,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     auto do_tile = [&](int t, const char *stage, char *next_stage) {
         if (t + 1 < n_tiles) issue_tile(next_stage);
         if (wave_active) {
-            const bool residual = D == 64 || cur_qt < qt_head;
+            const bool residual = cur_qt < qt_head;
 #pragma unroll 1
             for (int mb = 0; mb < 2; ++mb) {
                 do_block(mb, stage, residual);
@@ -466,8 +465,8 @@ struct KvStage {
 };
 
 // A workgroup whose 128-row tile starts a sequence (rows at positions < 128: a "head" tile) feeds the dQ product the
-// bf16 rounding residual of dS besides dS, as the dK/dV kernel does for these rows (at D = 64 every workgroup does).  It
-// also replaces delta of its rows: delta = <dO, O> is computed from the ROUNDED O, and for rows that see few keys
+// bf16 rounding residual of dS besides dS, as the dK/dV kernel does for these rows (at D = 64 every workgroup feeds it all
+// 24 bits of dS, as three operands).  It also replaces delta of its rows: delta = <dO, O> is computed from the ROUNDED O, and for rows that see few keys
 // (large P, large |O|) that rounding would be the largest error of the whole backward pass (it lands in dK
 // of the first keys of each sequence).  It first runs over its (at most 4) key tiles once to form delta = sum_j P_j dP_j,
 // which needs no O, stores it for the dK/dV kernel, then runs again for dQ.
@@ -635,14 +634,18 @@ __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__re
                     // dQ^T += K^T dS^T : contraction over these 32 keys in 2 groups of 16
 #pragma unroll
                     for (int tq = 0; tq < 2; ++tq) {
-                        const bf16x8 dsb = pack8(dp[8 * tq + 0], dp[8 * tq + 1], dp[8 * tq + 2], dp[8 * tq + 3],
-                                                 dp[8 * tq + 4], dp[8 * tq + 5], dp[8 * tq + 6], dp[8 * tq + 7]);
+                        bf16x8 dsb[3];
+                        if (D == 64) split_exact(dp, 8 * tq, dsb);
+                        else dsb[0] = pack8(dp[8 * tq + 0], dp[8 * tq + 1], dp[8 * tq + 2], dp[8 * tq + 3],
+                                            dp[8 * tq + 4], dp[8 * tq + 5], dp[8 * tq + 6], dp[8 * tq + 7]);
 #pragma unroll
-                        for (int j = 0; j < DB; ++j) dq[j] = mfma32(kt[tq][j], dsb, dq[j]);
-                        if (D == 64 || head) {   // add the bf16 rounding residual of dS
+                        for (int x = 0; x < (D == 64 ? 3 : 1); ++x)
+#pragma unroll
+                            for (int j = 0; j < DB; ++j) dq[j] = mfma32(kt[tq][j], dsb[x], dq[j]);
+                        if (D != 64 && head) {   // add the bf16 rounding residual of dS
                             bf16x8 dl;
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) dl[e] = (__bf16)(dp[8 * tq + e] - (float)dsb[e]);
+                            for (int e = 0; e < 8; ++e) dl[e] = (__bf16)(dp[8 * tq + e] - (float)dsb[0][e]);
 #pragma unroll
                             for (int j = 0; j < DB; ++j) dq[j] = mfma32(kt[tq][j], dl, dq[j]);
                         }

@@ -22,7 +22,10 @@ namespace {
 
 constexpr int BM = 128;        // query rows per workgroup
 constexpr int BN = 64;         // key rows per tile
-constexpr float kLazy = 8.f;                  // log2 units a row maximum may exceed the running reference before O is rescaled
+// Log2 units a row maximum may exceed the running reference before O is rescaled.  D = 64: none, so that no exponent that
+// counts is far from zero, where its rounding would be the largest error of the row sum.
+template <int D>
+constexpr float kLazy = D == 64 ? 0.f : 8.f;
 
 template <int D>
 struct Stage {
@@ -31,7 +34,8 @@ struct Stage {
 };
 
 // id: index of the workgroup among those of this chunk
-// D = 64: the second product takes P as bf16 value plus bf16 rounding residual (two MFMAs; P keeps 16 bits).
+// D = 64 keeps what the scalar kernels keep in fp32: the second product takes P with all its 24 bits, as three bf16 operands
+// (three MFMAs), exponentials and row sums are formed so that the errors of O and LSE against fp64 are no larger than theirs.
 template <int D>
 __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, char *stage_a, char *stage_b)
 {
@@ -99,8 +103,11 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     for (int i = 0; i < DB; ++i)
 #pragma unroll
         for (int j = 0; j < 16; ++j) o_acc[i][j] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;            // running max (log2 units) and this lane's partial row sum
-    const float c2 = p.softmax_scale * 1.44269504088896340736f;
+    // Exponentials: D = 128 in log2 units, the scale folded into them (exp2(s c2 - m), m in those units); D = 64 in the natural
+    // units of the scores, exp2((s c2 - m) log2e), where the rounding of log2e only acts on the distance to the maximum.
+    constexpr float kLog2e = 1.44269504088896340736f, kUnit = D == 64 ? kLog2e : 1.f;
+    const float c2 = p.softmax_scale * (D == 64 ? 1.f : kLog2e);
+    float m_run = -INFINITY, l_run = 0.f;            // running max (those units) and this lane's partial row sum
 
     auto issue_tile = [&](int tile_start, char *stage) {
         dma.issue(kbase + (int64_t)tile_start * kv_row_bytes, lk - 1 - tile_start, stage);
@@ -155,10 +162,10 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
             // 2^kLazy; until then P = exp2(s - m_run) <= 2^kLazy, exact enough in the fp32 sums and in bf16 alike,
             // and O needs no rescale.  The final division by l_tot and the LSE absorb whatever reference was used.
             const float mx2 = mx * c2;
-            const bool grow = mx2 > m_run + kLazy;        // first tile: m_run = -inf
+            const bool grow = mx2 > m_run + kLazy<D>;        // first tile: m_run = -inf
             if (__builtin_amdgcn_ballot_w64(grow) != 0) {
                 const float m_new = grow ? mx2 : m_run;
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // first tile: exp2(-inf) = 0
+                const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * kUnit);   // first tile: exp2(-inf) = 0
                 m_run = m_new;
                 l_run *= alpha;
 #pragma unroll
@@ -166,15 +173,21 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
 #pragma unroll
                     for (int j = 0; j < 16; ++j) o_acc[db][j] *= alpha;
             }
-            float rs = 0.f;
+            // (the row sum in short chains: rounding grows with a chain's length)
+            constexpr int CHAINS = D == 64 ? 8 : 1;
+            float rs[CHAINS] = {};
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    s[mb][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][i], c2, -m_run));
-                    rs += s[mb][i];
+                    s[mb][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][i], c2, -m_run) * kUnit);
+                    rs[i % CHAINS] += s[mb][i];
                 }
-            l_run += rs;
+#pragma unroll
+            for (int n = CHAINS / 2; n > 0; n /= 2)
+#pragma unroll
+                for (int i = 0; i < n; ++i) rs[i] += rs[i + n];
+            l_run += rs[0];
             // ---- O^T += V^T P^T : contraction over the 64 keys in 4 groups of 16
             const char *vst = stage + TILE_BYTES;
 #pragma unroll
@@ -182,19 +195,16 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
 #pragma unroll
                 for (int tq = 0; tq < 2; ++tq) {
                     // register 8*tq + j of block mb is key mb*32 + 16*tq + (j/4)*8 + 4*half + j%4
-                    const bf16x8 pb = pack8(s[mb][8 * tq + 0], s[mb][8 * tq + 1], s[mb][8 * tq + 2], s[mb][8 * tq + 3],
-                                            s[mb][8 * tq + 4], s[mb][8 * tq + 5], s[mb][8 * tq + 6], s[mb][8 * tq + 7]);
-                    bf16x8 pl;
-                    if (D == 64) {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) pl[e] = (__bf16)(s[mb][8 * tq + e] - (float)pb[e]);
-                    }
+                    bf16x8 pb[3];
+                    if (D == 64) split_exact(s[mb], 8 * tq, pb);
+                    else pb[0] = pack8(s[mb][8 * tq + 0], s[mb][8 * tq + 1], s[mb][8 * tq + 2], s[mb][8 * tq + 3],
+                                       s[mb][8 * tq + 4], s[mb][8 * tq + 5], s[mb][8 * tq + 6], s[mb][8 * tq + 7]);
                     const char *va = vst + mb * (TILE_BYTES / 2) + tq * (TILE_BYTES / 4);
 #pragma unroll
                     for (int j = 0; j < DB; ++j) {
                         const bf16x8 a = lds_read_tr_pair(va + lo.tr_lo[j], va + lo.tr_hi[j]);
-                        o_acc[j] = mfma32(a, pb, o_acc[j]);
-                        if (D == 64) o_acc[j] = mfma32(a, pl, o_acc[j]);
+#pragma unroll
+                        for (int t = 0; t < (D == 64 ? 3 : 1); ++t) o_acc[j] = mfma32(a, pb[t], o_acc[j]);
                     }
                 }
         }
@@ -215,7 +225,7 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
         return (char *)p.o + ((int64_t)(q_seg0 + wq0 + r) * p.o_stride_tok + (int64_t)h * p.o_stride_head) * 2;
     });
     if (iq < lq && half == 0)
-        p.lse[(int64_t)h * p.n_tokens + q_seg0 + iq] = m_run * 0.69314718055994530942f + __logf(l_tot);
+        p.lse[(int64_t)h * p.n_tokens + q_seg0 + iq] = m_run * (D == 64 ? 1.f : 0.69314718055994530942f) + __logf(l_tot);
 }
 
 template <int D>

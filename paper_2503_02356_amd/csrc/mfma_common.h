@@ -73,6 +73,26 @@ __device__ __forceinline__ bf16x8 pack8(float a0, float a1, float a2, float a3, 
     return r;
 }
 
+// Eight fp32 values as three bf16 operands: x = w[0] + w[1] + w[2] exactly (8 of the 24 significant bits each, taken off by
+// truncation), so that three MFMAs multiply the fp32 value and not its rounding.
+__device__ __forceinline__ void split_exact(const f32x16 &f, int first, bf16x8 (&w)[3])
+{
+    i32x4 u[3];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float x0 = f[first + 2 * e], x1 = f[first + 2 * e + 1];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const unsigned b0 = __float_as_uint(x0), b1 = __float_as_uint(x1);
+            u[t][e] = __builtin_amdgcn_perm(b1, b0, 0x07060302);      // the upper halves of both
+            x0 -= __uint_as_float(b0 & 0xffff0000u);
+            x1 -= __uint_as_float(b1 & 0xffff0000u);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t) w[t] = __builtin_bit_cast(bf16x8, u[t]);
+}
+
 // Swizzled LDS tile with rows of 2 D bytes (D bf16) and no padding: the 16-byte unit u of row r lives at unit
 // u ^ swz(r).  LDS has 64 four-byte banks; a 16-byte row read (ds_read_b128) is served 16 lanes per clock and a
 // transposing 8-byte read (ds_read_b64_tr_b16) 32 lanes per clock.  swz() maps 16 consecutive rows to 16 different

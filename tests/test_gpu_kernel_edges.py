@@ -39,6 +39,17 @@ def test_bf16_blocks(D, lens, C, Hq, Hkv, flags):
     P.check(got, ref, "bf16", f"lens={lens[:9]} C={C} D={D} flags={flags}")
 
 
+@pytest.mark.parametrize("dtype,D", [("bf16", 64)])
+@pytest.mark.parametrize("lens,C,Hq,Hkv", [([300, 41, 700, 64, 9, 150], 256, 4, 2), ([40] * 30 + [130] * 5, 600, 2, 2)])
+def test_errors_are_no_larger_than_the_scalar_kernels(dtype, D, lens, C, Hq, Hkv):
+    """Shapes whose P, dS and sums are fp32 in the scalar kernels: relative 2-norm error against the fp64 oracle, per tensor.
+    5 %: how far the errors of two sums of equal precision over these few thousand elements may lie apart."""
+    ref = P.run_oracle(lens, Hq, Hkv, D, dtype, seed=34)
+    here, scalar = (P.errors(P.run_gpu(lens, C, Hq, Hkv, D, dtype, seed=34, flags=f)[0], ref) for f in (0, B.CF_FLAG_SCALAR_KERNELS))
+    for n in P.NAMES:
+        assert here[n][1] <= 1.05 * scalar[n][1], (n, here[n], scalar[n])
+
+
 @pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("fp32", 64), ("fp32", 128)])
 def test_calls_that_share_launches(dtype, D):
     """A list of calls (more than one launch holds; slices of one sequence, whose gradients meet, among them) against the
