@@ -39,7 +39,7 @@ def test_bf16_blocks(D, lens, C, Hq, Hkv, flags):
     P.check(got, ref, "bf16", f"lens={lens[:9]} C={C} D={D} flags={flags}")
 
 
-@pytest.mark.parametrize("dtype,D", [("bf16", 64)])
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp32", 64), ("fp32", 128)])
 @pytest.mark.parametrize("lens,C,Hq,Hkv", [([300, 41, 700, 64, 9, 150], 256, 4, 2), ([40] * 30 + [130] * 5, 600, 2, 2)])
 def test_errors_are_no_larger_than_the_scalar_kernels(dtype, D, lens, C, Hq, Hkv):
     """Shapes whose P, dS and sums are fp32 in the scalar kernels: relative 2-norm error against the fp64 oracle, per tensor.
