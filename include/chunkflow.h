@@ -180,11 +180,12 @@ int cf_sim_1f1b(cf_plan *plan, int32_t K, int32_t n_stages, uint32_t flags, cf_p
 enum { CF_BF16 = 0, CF_FP32 = 1 };
 /* flags: CF_FLAG_SCALAR_KERNELS runs the plain scalar kernels even where an MFMA kernel exists
  * (same results up to rounding; for cross-checks).
- * CF_FLAG_DKV_SINGLE_WRITER (backward, bf16): every dK/dV row is updated by ONE workgroup that loops
+ * CF_FLAG_DKV_SINGLE_WRITER (backward, bf16 head_dim 128): every dK/dV row is updated by ONE workgroup that loops
  * over the query heads of its key/value head, with a plain read-modify-write -- dK/dV are then bitwise reproducible
  * from run to run.  Without the flag the library takes that mode only when a launch has enough key tiles to fill
  * the GPU that way (>= 4096 key-tile x kv-head pairs: long prefixes) and otherwise splits the query heads of a
- * group over workgroups that meet in dK/dV through fp32 atomic adds (faster on short chunks; last bits vary). */
+ * group over workgroups that meet in dK/dV through fp32 atomic adds (faster on short chunks; last bits vary).
+ * bf16 head_dim 64 and fp32: always one writer per dK/dV row, reproducible with or without the flag. */
 enum { CF_FLAG_SCALAR_KERNELS = 1, CF_FLAG_DKV_SINGLE_WRITER = 2 };
 
 /*
@@ -259,11 +260,10 @@ int cf_attn_fwd(const cf_attn_fwd_params *p, void *hip_stream);
  * dependent chunk they point at the base of the sequence's gradient state, so that rows [0,P)
  * collect the contributions of later chunks when the group's chunks run in descending order; the
  * caller zeroes them once per long sequence / per packed chunk.  Launches on one stream are
- * ordered; in bf16 several workgroups of one launch may add to a d_k/d_v element (fp32 atomic adds, see
+ * ordered; in bf16 at head_dim 128 several workgroups of one launch may add to a d_k/d_v element (fp32 atomic adds, see
  * CF_FLAG_DKV_SINGLE_WRITER).
  * workspace: device scratch of at least cf_attn_bwd_workspace_bytes(&f) bytes, 256-byte aligned;
- * contents need not be initialised and are not preserved.  (bf16 at head_dim 64 also runs in
- * n_q_heads * n_tokens * 4 bytes rounded up to 256, every d_k/d_v element then with a single writer.)
+ * contents need not be initialised and are not preserved.
  */
 typedef struct {
     cf_attn_fwd_params f;
@@ -289,7 +289,7 @@ int cf_attn_bwd(const cf_attn_bwd_params *p, void *hip_stream);
  * CF_STATIC_SCRATCH_BYTES that is part of the library's device code (one copy per GPU, held until the process
  * ends).  The call allocates and frees nothing (no hipMalloc / hipFree, no allocating library routine) and, like
  * cf_attn_bwd, only enqueues kernels on the stream.
- *   - A chunk whose least workspace (see above) exceeds CF_STATIC_SCRATCH_BYTES -> CF_EINVAL (decided on the
+ *   - A chunk whose cf_attn_bwd_workspace_bytes exceeds CF_STATIC_SCRATCH_BYTES -> CF_EINVAL (decided on the
  *     host before any HIP call; n_q_heads * n_tokens * 4 bytes dominate: 64 heads x 32768 tokens need 8.3 MiB).
  *   - Every call on a GPU uses that GPU's one buffer, which keeps the previous call's contents; nothing in it
  *     has to start at zero (each call overwrites what it reads).  Calls that OVERLAP on one GPU (two streams,

@@ -4,14 +4,14 @@
 //
 // Two kernels, no dQ atomics:
 //
-//  dkv kernel  A workgroup (4 wavefronts) owns 128 consecutive key rows of one segment, a wavefront 32 of them: their
-//              dV^T and dK^T (fp32) and K, V operands stay in its registers for the whole kernel.  It loops over the
-//              64-row query tiles that can see its keys, for one or several query heads of its key/value head; Q and
-//              dO tiles go straight from global memory into two XOR-swizzled LDS stages (row reads and transposing
-//              reads are both free of bank conflicts).
+//  dkv kernel  A workgroup (4 wavefronts) owns 128 (D = 64: 32) consecutive key rows of one segment, a wavefront 32 of them:
+//              their dV^T and dK^T (fp32) and K, V operands stay in its registers for the whole kernel.  It loops over
+//              the 64-row (D = 64: 128-row) query tiles that can see its keys, for one or several query heads of its
+//              key/value head; Q and dO tiles go straight from global memory into two XOR-swizzled LDS stages (row
+//              reads and transposing reads are both free of bank conflicts).
 //              FUSED_HEADS = true : one workgroup per key tile and key/value head loops over ALL query heads
 //                  of the group and is the only writer of its dK/dV rows (plain read-modify-write, bitwise
-//                  reproducible).  Used when the launch has enough key tiles to fill the GPU.
+//                  reproducible).  Used when the launch has enough key tiles to fill the GPU, and always at D = 64.
 //              FUSED_HEADS = false: a work list built on the device cuts the (key tile, query heads) work into
 //                  items of similar length, longest first; the items of one key/value head meet in dK/dV
 //                  through fp32 atomic adds (once per workgroup, at the end).
@@ -37,8 +37,21 @@ constexpr float kLog2e = 1.44269504088896340736f;
 // =====================================================================================================
 // dK / dV
 // =====================================================================================================
-constexpr int BQ = 64;                                // query rows per tile (two 32-row blocks)
-constexpr int BKV = 128;                              // key rows per workgroup, 32 per wavefront
+// How the four wavefronts of a workgroup divide a tile: KW groups of 32 keys, QW wavefronts each that take every QW-th 32-row
+// block of the query tile (their partial results meet in LDS at the end, in a fixed order).
+// D = 128: 128 keys per workgroup; query heads are split over work items where that fills the chip, through atomic adds.
+// D = 64: every dK/dV row has one writer, so no workgroup may share its keys with another: few keys and a long query tile
+// shorten the chain that one workgroup is.  Step of 16 / 4 heads, 16.7k tokens: 0.99 ms with 32 keys x 128 rows a tile, 1.03
+// with 64 x 128, 1.06 with 64 x 64, 1.32 with 128 x 64 (0.95 with split heads and atomic adds).
+template <int D>
+struct DkvShape {
+    static constexpr int KW = D == 64 ? 1 : 4, QW = 4 / KW;
+    static constexpr int BKV = 32 * KW;               // key rows per workgroup
+    static constexpr int BQ = D == 64 ? 128 : 64;    // query rows per tile
+    static constexpr int BLOCKS = BQ / 32 / QW;       // of a tile, per wavefront
+    static_assert(BLOCKS == 1 || BLOCKS == 2, "do_tile");
+};
+constexpr int BQ = DkvShape<128>::BQ, BKV = DkvShape<128>::BKV;
 
 // ---- work list of the dK/dV kernel (not used in the fused mode) -------------------------------------------
 // One item = (segment, key tile, first head of the group's share, number of heads): the workgroups of one
@@ -123,12 +136,13 @@ __device__ __forceinline__ void build_dkv_worklist(const cf_attn_fwd_params &p, 
 // scratch (32 rows of D floats per wavefront).
 template <int D>
 struct DkvStage {
+    static constexpr int BQ = DkvShape<D>::BQ;
     static constexpr int tile_bytes = BQ * 2 * D, bytes = 2 * tile_bytes + 2 * BQ * 4;
     static constexpr int scratch_bytes = 32 * D * 4;
     static_assert(bytes >= 2 * scratch_bytes, "two wavefronts turn their results around in a stage");
 };
 
-// A workgroup owns 128 key rows, a wavefront 32 of them: K_w, V_w (operands) and dV_w^T, dK_w^T (fp32) stay in its
+// A wavefront owns 32 key rows: K_w, V_w (operands) and dV_w^T, dK_w^T (fp32) stay in its
 // registers for the whole kernel, 192 of them at D = 128.  Per 32-row block of queries:
 //     S = Q K_w^T    P = exp2(S c - LSE)    dP' = dO V_w^T - delta (the accumulator starts at -delta)    dS = P dP'
 //     dV_w^T += dO^T P      dK_w^T += Q^T dS
@@ -145,8 +159,10 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
 {
     using Stage = DkvStage<D>;
     constexpr int KS = D / 16, DB = D / 32, BLOCK = 32 * 2 * D;
+    constexpr int QW = DkvShape<D>::QW, BQ = DkvShape<D>::BQ, BKV = DkvShape<D>::BKV;
+    static_assert(FUSED_HEADS || QW == 1, "atomic updates are made by the wavefront that owns the keys");
     const cf_attn_fwd_params &p = b.f;
-    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), key_wave = wave / QW, query_wave = wave % QW;
     const int half = lane >> 5, col = lane & 31;
 
     // Block id -> (item, key/value head); the key/value head varies fastest (XCD L2 locality, see forward).
@@ -187,7 +203,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     // query tiles below qt_head are RESIDUAL ones for this key tile
     const int qt_head = kt0 == 0 && off < 128 ? (128 - off + BQ - 1) / BQ : 0;
 
-    const int kw0 = kt0 + 32 * wave;                 // first key of this wavefront (segment-local)
+    const int kw0 = kt0 + 32 * key_wave;                 // first key of this wavefront (segment-local)
     const bool wave_active = kw0 < lk;
     const float c2 = scalar(p.softmax_scale * kLog2e);
 
@@ -207,6 +223,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
 #pragma unroll
         for (int j = 0; j < 16; ++j) dv[i][j] = dk[i][j] = 0.f;
     BlockAddress<D> at;                              // of the block in use
+    at.flip(query_wave * BLOCK);
 
     // Tile staging: Q and dO rows, LSE and -delta go straight from global memory into an LDS stage; once they have landed,
     // wavefront 0 turns LSE into log2 units (+inf for rows past the segment, so that P = 0).  What the copies need of the
@@ -222,10 +239,11 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
         dma.init(b.do_stride_tok * 2, wave, lane_);
         dma.issue(uniform((const char *)b.d_o + (row0 * b.do_stride_tok + (int64_t)h * b.do_stride_head) * 2), lq - 1 - q0,
                   stage + Stage::tile_bytes);
-        if (wave < 2)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(TileDma<BQ, D>::descriptor((const char *)uniform((wave == 0 ? p.lse : delta) + (int64_t)h * p.n_tokens + row0)),
-                                                     (CF_LDS void *)(stage + 2 * Stage::tile_bytes + wave * BQ * 4), 4,
-                                                     min(lane_, lq - 1 - q0) * 4, 0, 0, 0);
+        constexpr int PER = BQ / 64;                 // wavefronts that fetch LSE resp. -delta, 64 rows each
+        if (wave < 2 * PER)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(TileDma<BQ, D>::descriptor((const char *)uniform((wave < PER ? p.lse : delta) + (int64_t)h * p.n_tokens + row0)),
+                                                     (CF_LDS void *)(stage + 2 * Stage::tile_bytes + wave * 256), 4,
+                                                     min(wave % PER * 64 + lane_, lq - 1 - q0) * 4, 0, 0, 0);
         if (++nx_qt == qt_end) {
             nx_qt = qt_first;
             ++nx_h;
@@ -233,10 +251,10 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     };
     auto finish_tile = [&](char *stage, int rows) {  // rows: of the segment, in this tile
         wait_lds_dma();
-        if (wave == 0) {
-            const int lane_ = fresh_lane();
-            float *l = (float *)(stage + 2 * Stage::tile_bytes) + lane_;
-            *l = lane_ < rows ? *l * kLog2e : INFINITY;
+        if (wave < BQ / 64) {
+            const int row = wave * 64 + fresh_lane();
+            float *l = (float *)(stage + 2 * Stage::tile_bytes) + row;
+            *l = row < rows ? *l * kLog2e : INFINITY;
         }
     };
     issue_tile(st0);
@@ -246,7 +264,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     int cur_qt = qt_first;                           // query tile of the stage in use
     auto do_block = [&](int mb, const char *stage, bool residual) {
         const int q0 = cur_qt * BQ + mb * 32;
-        if (q0 + 31 + off < kw0) return;             // no row of the block sees a key of this wavefront
+        if (q0 + 31 + off < kw0 || (D == 64 && q0 >= lq)) return;     // no row of the block sees a key of this wavefront
         const char *qs = stage, *dos = stage + Stage::tile_bytes;
         const float *stats = (const float *)(stage + 2 * Stage::tile_bytes) + mb * 32 + (fresh_lane() >> 5) * 4;
         // The A operands of the block's four products pass through a ring of four fragments, each requested four MFMAs
@@ -277,7 +295,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
         }
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
-            const f32x4 d4 = *(const f32x4 *)(stats + 64 + g4 * 8);
+            const f32x4 d4 = *(const f32x4 *)(stats + BQ + g4 * 8);
 #pragma unroll
             for (int j = 0; j < 4; ++j) dp[g4 * 4 + j] = d4[j];
         }
@@ -349,9 +367,9 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
         if (wave_active) {
             const bool residual = cur_qt < qt_head;
 #pragma unroll 1
-            for (int mb = 0; mb < 2; ++mb) {
-                do_block(mb, stage, residual);
-                at.flip(BLOCK);
+            for (int i = 0; i < DkvShape<D>::BLOCKS; ++i) {
+                do_block(query_wave + i * QW, stage, residual);
+                if (DkvShape<D>::BLOCKS == 2) at.flip(QW * BLOCK);
             }
         }
         if (++cur_qt == qt_end) cur_qt = qt_first;
@@ -369,14 +387,20 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     // lane-per-row update would touch 64 cache lines per instruction.
     //   FUSED_HEADS : this workgroup is the only writer of these rows in this launch: plain load, add, store.
     //   otherwise   : the query heads of a group add into the same rows: fp32 atomic adds.
+    // QW > 1: the partial results of a key group's wavefronts are added in their order, each of them writes every QW-th group of 8 rows.
     const int rows_valid = min(32, lk - kw0);        // <= 0: this wavefront has no real keys
-    if (rows_valid <= 0) return;
+    if (QW == 1 && rows_valid <= 0) return;
 #pragma unroll
     for (int j = 0; j < DB; ++j) {
         accumulator_done(dv[j]);
         accumulator_done(dk[j]);
     }
-    float *tr = (float *)((wave < 2 ? st0 : st1) + (wave & 1) * Stage::scratch_bytes);
+    auto scratch_of = [&](int w) { return (float *)((w < 2 ? st0 : st1) + (w & 1) * Stage::scratch_bytes); };
+    auto meet = [] {
+        if (QW == 1) __builtin_amdgcn_wave_barrier();
+        else __syncthreads();
+    };
+    float *tr = scratch_of(wave);
     const int end_lane = fresh_lane(), end_half = end_lane >> 5, end_col = end_lane & 31;
     auto add_rows = [&](const f32x16 (&acc)[DB], float scale, float *g) {
 #pragma unroll
@@ -388,16 +412,20 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
                 for (int e = 0; e < 4; ++e) a[e] = acc[j][g4 * 4 + e] * scale;
                 *(f32x4 *)(tr + end_col * D + (((j * 8 + g4 * 2 + end_half) ^ (end_col & 15)) << 2)) = a;
             }
-        __builtin_amdgcn_wave_barrier();
+        meet();
         g += (int64_t)(k_seg0 + kw0) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head;
         // 8 rows per step: all LDS reads first, then the global updates (one LDS latency per step)
-        for (int r0 = 0; r0 < rows_valid; r0 += 8) {
+        for (int r0 = 8 * query_wave; r0 < rows_valid; r0 += 8 * QW) {
             float v[8][D / 64];
 #pragma unroll
             for (int e = 0; e < 8; ++e)
 #pragma unroll
-                for (int c = 0; c < D / 64; ++c)
-                    v[e][c] = tr[(r0 + e) * D + (((16 * c + (end_lane >> 2)) ^ ((r0 + e) & 15)) << 2) + (end_lane & 3)];
+                for (int c = 0; c < D / 64; ++c) {
+                    const int at_ = (r0 + e) * D + (((16 * c + (end_lane >> 2)) ^ ((r0 + e) & 15)) << 2) + (end_lane & 3);
+                    v[e][c] = scratch_of(key_wave * QW)[at_];
+#pragma unroll
+                    for (int w = 1; w < QW; ++w) v[e][c] += scratch_of(key_wave * QW + w)[at_];
+                }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 if (r0 + e < rows_valid) {
@@ -410,7 +438,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
                 }
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        meet();
     };
     add_rows(dv, 1.f, b.d_v);
     add_rows(dk, p.softmax_scale, b.d_k);
@@ -450,7 +478,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_batch_kernel(BwdBatch q)
     __shared__ __attribute__((aligned(16))) char st0[DkvStage<D>::bytes];
     __shared__ __attribute__((aligned(16))) char st1[DkvStage<D>::bytes];
     const int c = chunk_of(q, blockIdx.x);
-    dkv_body<D, false>(q.b[c], q.delta[c], blockIdx.x - q.first_block[c], q.wl[c], st0, st1);
+    dkv_body<D, D == 64>(q.b[c], q.delta[c], blockIdx.x - q.first_block[c], q.wl[c], st0, st1);
 }
 
 // =====================================================================================================
@@ -682,7 +710,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(cf_attn_bwd_params b, f
 {
     // The list builder is workgroup 0: it starts with the first wave of workgroups and is long done when the
     // launch ends (as the last workgroup it would start last and could be what the launch ends with).
-    if (wl != nullptr && blockIdx.x == 0) {
+    if (D == 128 && wl != nullptr && blockIdx.x == 0) {
         build_dkv_worklist(b.f, wl, capacity, kSlots);
         return;
     }
@@ -701,7 +729,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_batch_kernel(BwdBatch q)
 {
     if ((int)blockIdx.x < q.n) {
         const int c = blockIdx.x;
-        if (q.wl[c] != nullptr) build_dkv_worklist(q.b[c].f, q.wl[c], q.capacity[c], q.slots[c]);
+        if (D == 128 && q.wl[c] != nullptr) build_dkv_worklist(q.b[c].f, q.wl[c], q.capacity[c], q.slots[c]);
         return;
     }
     __shared__ __attribute__((aligned(16))) char stage_a[KvStage<D>::bytes];
@@ -720,11 +748,11 @@ BwdShape bwd_shape(const cf_attn_fwd_params &p, const BwdWorkspace &ws)
 {
     BwdShape g;
     // Upper bounds on tile counts: sum_g ceil(L_g / tile) <= total / tile + n_segments.
-    const int64_t kv_tiles = (int64_t)p.n_kv_tokens / BKV + p.n_segments;
+    const int64_t kv_tiles = (int64_t)p.n_kv_tokens / (p.head_dim == 64 ? DkvShape<64>::BKV : BKV) + p.n_segments;
     const int64_t q_tiles = p.q_tiles ? (int64_t)p.n_q_tiles : (int64_t)p.n_tokens / BM + p.n_segments;
-    // Fusing the heads of a group into one workgroup needs enough key tiles to fill 256 CUs several times.
-    // (no work list: the scratch has no room for one)
-    g.fused = kv_tiles * p.n_kv_heads >= 4096 || (p.flags & CF_FLAG_DKV_SINGLE_WRITER) || ws.worklist == nullptr;
+    // Fusing the heads of a group into one workgroup needs enough key tiles to fill 256 CUs several times.  At D = 64 dK/dV rows
+    // always have one writer (and no work list).
+    g.fused = kv_tiles * p.n_kv_heads >= 4096 || (p.flags & CF_FLAG_DKV_SINGLE_WRITER) || p.head_dim == 64;
     g.dq_blocks = q_tiles * p.n_q_heads;
     g.dkv_blocks = (g.fused ? kv_tiles : ws.worklist_items) * p.n_kv_heads;
     g.ok = g.dkv_blocks <= 0x7fffffffLL && g.dq_blocks < 0x7fffffffLL && ws.worklist_items <= 0x7fffffffLL;
@@ -736,7 +764,7 @@ hipError_t launch_dkv(const cf_attn_bwd_params &b, const BwdWorkspace &ws, const
 {
     if (hook.start) (void)hipEventRecord(hook.start, s);
     if (g.fused) mfma_dkv_kernel<D, true><<<dim3((unsigned)g.dkv_blocks), 256, 0, s>>>(b, ws.delta, nullptr);
-    else mfma_dkv_kernel<D, false><<<dim3((unsigned)g.dkv_blocks), 256, 0, s>>>(b, ws.delta, ws.worklist);
+    else if constexpr (D == 128) mfma_dkv_kernel<D, false><<<dim3((unsigned)g.dkv_blocks), 256, 0, s>>>(b, ws.delta, ws.worklist);
     const hipError_t e = hipGetLastError();
     if (hook.stop) (void)hipEventRecord(hook.stop, s);
     return e;
@@ -779,7 +807,7 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
     for (int c = 0; c < n; ++c) {
         g[c] = bwd_shape(chunks[c].b->f, chunks[c].ws);
         if (!g[c].ok) return hipErrorInvalidConfiguration;
-        first_of[c] = c > 0 && chunks[c].dkv_with_previous && !g[c].fused && !g[c - 1].fused ? first_of[c - 1] : c;
+        first_of[c] = c > 0 && chunks[c].dkv_with_previous && (D == 64 || (!g[c].fused && !g[c - 1].fused)) ? first_of[c - 1] : c;
         tokens[first_of[c]] += chunks[c].b->f.n_tokens;
         order[c] = c;
     }

@@ -73,6 +73,26 @@ def test_calls_that_share_launches(dtype, D):
                 assert np.array_equal(a, b), (sid, n)
 
 
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp32", 64), ("fp32", 128)])
+@pytest.mark.parametrize("lens,C,Hq,Hkv", [
+    ([1100, 31, 33, 64, 65, 127, 129, 4, 300], 500, 8, 2),     # keys and rows around a workgroup's, slices of one sequence, head groups
+    ([2300], 2300, 8, 1),                                      # many query tiles per key tile: work that invites a split over heads
+])
+def test_gradients_repeat_bitwise(dtype, D, lens, C, Hq, Hkv):
+    """One writer per dK/dV row without any flag: a second pass, and the same calls one at a time, give the same bits."""
+    got, eng = P.run_gpu(lens, C, Hq, Hkv, D, dtype, seed=35)
+
+    def again(backward):
+        eng.zero_grads()
+        backward()
+        return eng.results()
+    for backward in (eng.run_backward, lambda: [B.cf_attn_bwd(eng.chunks[c]["bwd"]) for c in eng.backward_order()]):
+        r = again(backward)
+        for sid in got:
+            for n in ("dq", "dk", "dv"):
+                assert np.array_equal(got[sid][n], r[sid][n]), (sid, n)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 def test_calls_that_depend_on_each_other(dtype):
     """The second forward takes the first one's output as its queries; the list stops at a call that is refused."""
@@ -110,7 +130,8 @@ def _backward(q, k, v, d_o, flags=0, workspace_bytes=None):
 
 
 def test_d64_backward_without_room_for_a_work_list():
-    """bf16, head_dim 64, a workspace that holds delta and nothing else: the single-writer kernel, bit for bit."""
+    """bf16, head_dim 64, a workspace that holds delta and nothing else (all that is asked for): the single-writer kernel, bit
+    for bit."""
     gen = torch.Generator(device="cuda:0").manual_seed(5)
     rand = lambda h: torch.randn(600, h, 64, device="cuda:0", generator=gen).bfloat16()
     t = rand(4), rand(2), rand(2), rand(4)
