@@ -87,6 +87,8 @@ int64_t delta_bytes(const cf_attn_fwd_params &p) { return round_up((int64_t)p.n_
 // counters (256 bytes) + 16-byte items; head_dim 64 has no work list
 bool has_worklist(const cf_attn_fwd_params &p) { return mfma_shape(p) && p.head_dim == 128; }
 int64_t worklist_bytes(const cf_attn_fwd_params &p) { return has_worklist(p) ? 256 + cf::dkv_worklist_capacity(p) * 16 : 0; }
+// The least scratch a backward runs in: with room for the coarse list only, its work is cut less finely.
+int64_t least_scratch(const cf_attn_fwd_params &p) { return delta_bytes(p) + (has_worklist(p) ? 256 + cf::dkv_worklist_least(p) * 16 : 0); }
 
 int hip_fail(const char *who, hipError_t e)
 {
@@ -155,12 +157,12 @@ int carve_workspace(const cf_attn_fwd_params &p, void *base, int64_t bytes, cons
                     cf::BwdWorkspace *ws)
 {
     if (!base || !aligned(base, 256)) return cf::fail(CF_EINVAL, "%s: %s must be non-NULL and 256-byte aligned", who, what);
-    const int64_t need = delta_bytes(p) + worklist_bytes(p);
+    const int64_t need = least_scratch(p);
     if (bytes < need)
         return cf::fail(CF_EINVAL, "%s: %s has %lld bytes, %lld needed", who, what, (long long)bytes, (long long)need);
     ws->delta = static_cast<float *>(base);
     ws->worklist = has_worklist(p) ? reinterpret_cast<int *>(static_cast<char *>(base) + delta_bytes(p)) : nullptr;
-    ws->worklist_items = has_worklist(p) ? cf::dkv_worklist_capacity(p) : 0;
+    ws->worklist_items = has_worklist(p) ? std::min(cf::dkv_worklist_capacity(p), (bytes - delta_bytes(p) - 256) / 16) : 0;
     return CF_OK;
 }
 
@@ -369,7 +371,7 @@ extern "C" int cf_attn_bwd_static(const cf_attn_bwd_params *b, void *hip_stream)
     const char *who = "cf_attn_bwd_static";
     if (int rc = check_bwd_tensors(b, who)) return rc;
     // the size check comes before any HIP call: an oversized chunk is refused on any host
-    const int64_t need = delta_bytes(b->f) + worklist_bytes(b->f);
+    const int64_t need = least_scratch(b->f);
     if (need > (int64_t)CF_STATIC_SCRATCH_BYTES)
         return cf::fail(CF_EINVAL, "%s: this chunk needs %lld bytes of scratch, the static buffer holds %lld "
                         "(use cf_attn_bwd with a workspace)", who, (long long)need, (long long)CF_STATIC_SCRATCH_BYTES);

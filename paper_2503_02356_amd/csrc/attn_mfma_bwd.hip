@@ -54,19 +54,33 @@ struct DkvShape {
 constexpr int BQ = DkvShape<128>::BQ, BKV = DkvShape<128>::BKV;
 
 // ---- work list of the dK/dV kernel (not used in the fused mode) -------------------------------------------
-// One item = (segment, key tile, first head of the group's share, number of heads): the workgroups of one
-// key/value head.  A key tile seen by few query tiles keeps all G heads of the group in ONE item (one
-// prologue, one epilogue, one set of atomic updates instead of G); a tile seen by many query tiles is split
-// over up to G items so that no workgroup runs much longer than `target` tile iterations: half of what a workgroup slot
-// gets on average (two workgroups on each of 256 compute units; `slots` of them when several chunks share a launch), so
-// that small chunks spread over the whole chip and large ones end evenly, but at most kSplitTarget.
-// The list is ordered by DESCENDING duration (heads x query tiles; a counting sort): workgroups start in list
-// order, and starting the longest first is what keeps the last compute units from running one long item alone
-// (a packed 8K chunk has ~500 items of 7 to 130 iterations for 256 compute units).
-// Workspace layout (ints): [0] = number of items, [64 ...] = the items; an item is int4 {segment, kt0, g0, n_heads}.
-constexpr int kSplitTarget = 48;
-constexpr int kSlots = 512;
+// One item = (segment, key tile, range of its (head of the group, query tile) pairs, head by head): the workgroups of one
+// key/value head.  A key tile seen by few query tiles keeps all its pairs in ONE item (one prologue, one epilogue, one set of
+// atomic updates); one with more pairs than the target is cut into equal items.  Where the cuts lie:
+//   A launch ends with its longest item.  A workgroup that has a compute unit to itself takes 2.2 us per pair, one of two 3.6:
+//   an item of 1.6 times what a workgroup slot gets on average (`fair`; 512 slots, `slots` of them when several chunks share
+//   a launch) still ends with the rest, and every item more costs a prologue and an epilogue (some 14 us of its slot).
+//   fair <= kFineMost (few rounds of items): items of `fair` pairs.  Beyond it (long sequences, whose items end evenly
+//   anyway, and whose extra atomic updates cost more than they balance): whole heads, items of half the average but at most
+//   kSplitTarget pairs, except where a whole head is more than `fair`.
+// dK/dV of one packed call, 28 / 4 heads, 8192 tokens around 600: 143 us; items of half the average (twice as many) 196, of
+// 1.0 / 2.0 times the average 177 / 147; 4 / 4 heads, 4000 tokens in one sequence: 70 us, whole heads 147.
+// The list is ordered by DESCENDING duration (pairs; a counting sort): workgroups start in list order, and starting the
+// longest first is what keeps the last compute units from running one long item alone.
+// Workspace layout (ints): [0] = number of items, [64 ...] = the items; an item is int4 {segment, kt0, first pair, pairs}.
+constexpr int kSlots = 512, kSplitTarget = 48, kFineMost = 64, kFineLeast = 3;
+constexpr int kFairNum = 8, kFairDen = 5;             // 1.6
 constexpr int kDurationBuckets = 256;
+
+// sum over segments of ceil(Lk / 128) <= n_kv_tokens / 128 + n_segments
+__host__ __device__ inline int64_t key_tiles_most(const cf_attn_fwd_params &p) { return (int64_t)p.n_kv_tokens / BKV + p.n_segments; }
+// Items of `fair` pairs: one per key tile and, beyond that, as many as one key/value head's pairs hold `fair`, which is at least
+// 1.6 / kSlots of the pairs of all.  Whole heads: G per key tile.
+__host__ __device__ inline int64_t dkv_items_most(const cf_attn_fwd_params &p)
+{
+    const int64_t tiles = key_tiles_most(p), G = p.n_q_heads / p.n_kv_heads, cuts = kSlots * kFairDen / kFairNum / p.n_kv_heads + 1;
+    return tiles * G > tiles + cuts ? tiles * G : tiles + cuts;
+}
 
 // Runs in ONE workgroup of 256 threads: among the first of the dQ launch, which the dK/dV kernel follows anyway (no launch
 // of its own).
@@ -103,31 +117,51 @@ __device__ __forceinline__ void build_dkv_worklist(const cf_attn_fwd_params &p, 
     for_each_tile([&](int, int, int n_qt) { mine += n_qt; });
     atomicAdd(&total, mine);
     __syncthreads();
-    const int target = max(2, min(kSplitTarget, (int)((int64_t)total * p.n_q_heads / (2 * slots))));
+    const int64_t all_pairs = (int64_t)total * p.n_q_heads;
+    const int64_t share = (all_pairs * kFairNum + (int64_t)kFairDen * slots - 1) / ((int64_t)kFairDen * slots);
+    const int fair = (int)max((int64_t)kFineLeast, min(share, (int64_t)1 << 30));
+    const int target = fair <= kFineMost ? fair : (int)min((int64_t)kSplitTarget, all_pairs / (2 * slots));
+    bool cut_heads = true;                           // items may end inside a head's query tiles
     auto for_each_item = [&](auto &&visit) {
         for_each_tile([&](int seg, int kt0, int n_qt) {
-            const int sp = min(G, (G * n_qt + target - 1) / target);
+            const int pairs = G * n_qt;
+            if (pairs <= target) {
+                visit(i32x4{seg, kt0, 0, pairs}, min(pairs, kDurationBuckets - 1));
+                return;
+            }
+            const int want = (pairs + target - 1) / target, fairly = (pairs + fair - 1) / fair;
+            const bool heads = !cut_heads || (fair > kFineMost && fairly <= min(G, want));
+            // equal shares of the heads or of the pairs, the first few with one more
+            const int sp = heads ? min(G, want) : fairly, whole = heads ? G : pairs, unit = heads ? n_qt : 1;
+            const int base = whole / sp, longer = whole - base * sp;
             for (int s = 0; s < sp; ++s) {
-                const int g0 = s * G / sp, g1 = (s + 1) * G / sp;
-                visit(i32x4{seg, kt0, g0, g1 - g0}, min((g1 - g0) * n_qt, kDurationBuckets - 1));
+                const int n = (base + (s < longer)) * unit;
+                visit(i32x4{seg, kt0, (s * base + min(s, longer)) * unit, n}, min(n, kDurationBuckets - 1));
             }
         });
     };
-    for_each_item([&](i32x4, int duration) { atomicAdd(&bucket[duration], 1); });
-    __syncthreads();
-    if (tid == 0) {                                  // longest first: slots are handed out from the top bucket down
-        int next = 0;
-        for (int d = kDurationBuckets - 1; d >= 0; --d) {
-            const int n = bucket[d];
-            bucket[d] = next;
-            next += n;
+    for (;;) {
+        for_each_item([&](i32x4, int duration) { atomicAdd(&bucket[duration], 1); });
+        __syncthreads();
+        if (tid == 0) {                              // longest first: slots are handed out from the top bucket down
+            int next = 0;
+            for (int d = kDurationBuckets - 1; d >= 0; --d) {
+                const int n = bucket[d];
+                bucket[d] = next;
+                next += n;
+            }
+            n_items = next;
         }
-        n_items = next;
+        __syncthreads();
+        if (n_items <= capacity || !cut_heads) break;
+        cut_heads = false;                           // (at most G items per key tile: what every scratch has room for)
+        __syncthreads();
+        bucket[tid] = 0;                             // (for_each_item's first barrier comes before its first visit)
     }
     i32x4 *items = (i32x4 *)(wl + 64);
     for_each_item([&](i32x4 item, int duration) {    // (its first barrier comes after the slots are laid out)
         const int slot = atomicAdd(&bucket[duration], 1);
-        if (slot < capacity) items[slot] = item;     // (capacity is an upper bound on the item count; see dkv_worklist_capacity)
+        if (slot < capacity) items[slot] = item;     // (it always is: a scratch has room for G items per key tile)
     });
     if (tid == 0) wl[0] = min(n_items, capacity);
 }
@@ -171,7 +205,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     const int G = p.n_q_heads / p.n_kv_heads;
     const int kh = id % p.n_kv_heads;
     id /= p.n_kv_heads;
-    int seg, kt0, g0 = 0, n_heads = G;
+    int seg, kt0, first_pair = 0, n_pairs = 0;
     if (FUSED_HEADS) {
         TileLocation loc;
         if (!locate_tile(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, BKV, id, loc)) return;
@@ -185,21 +219,23 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
         const i32x4 item = items[id];
         seg = item[0];
         kt0 = item[1];
-        g0 = uniform(item[2]);
-        n_heads = uniform(item[3]);
+        first_pair = uniform(item[2]);
+        n_pairs = uniform(item[3]);
     }
     // (seg, kt0 are the same in every lane, but values that leave locate_tile's search loop do not look that way to
     // the compiler: say so, or everything derived from them lives in vector registers.)
     seg = uniform(seg);
     kt0 = uniform(kt0);
-    const int h_first = kh * G + g0;
     const int q_seg0 = p.cu_seqlens_q[seg], lq = p.cu_seqlens_q[seg + 1] - q_seg0;
     const int k_seg0 = p.cu_seqlens_k[seg], lk = p.cu_seqlens_k[seg + 1] - k_seg0;
     const int off = lk - lq;
     const int qt_first = max(0, kt0 - off) / BQ;     // first query tile with a row that sees any key of this tile
     const int qt_end = (lq + BQ - 1) / BQ;
     if (qt_first >= qt_end) return;                  // whole workgroup leaves before any barrier
-    const int n_tiles = n_heads * (qt_end - qt_first);   // (head, query tile) pairs, head by head
+    if (FUSED_HEADS) n_pairs = G * (qt_end - qt_first);
+    const int n_tiles = n_pairs;                     // (head, query tile) pairs, head by head
+    const int head_first = FUSED_HEADS ? 0 : first_pair / (qt_end - qt_first);
+    const int qt_start = qt_first + first_pair - head_first * (qt_end - qt_first);
     // query tiles below qt_head are RESIDUAL ones for this key tile
     const int qt_head = kt0 == 0 && off < 128 ? (128 - off + BQ - 1) / BQ : 0;
 
@@ -229,7 +265,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     // wavefront 0 turns LSE into log2 units (+inf for rows past the segment, so that P = 0).  What the copies need of the
     // lane is made anew per tile: every register counts (a spilled one would be reloaded behind the copies in flight,
     // and the wait for it would be a wait for them).
-    int nx_h = h_first, nx_qt = qt_first;            // the tile the next copy fetches (advances by additions only)
+    int nx_h = kh * G + head_first, nx_qt = qt_start;            // the tile the next copy fetches (advances by additions only)
     auto issue_tile = [&](char *stage) {
         const int h = nx_h, q0 = nx_qt * BQ, lane_ = fresh_lane();
         const int64_t row0 = q_seg0 + q0;
@@ -258,10 +294,10 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
         }
     };
     issue_tile(st0);
-    finish_tile(st0, lq - qt_first * BQ);
+    finish_tile(st0, lq - qt_start * BQ);
     __syncthreads();
 
-    int cur_qt = qt_first;                           // query tile of the stage in use
+    int cur_qt = qt_start;                           // query tile of the stage in use
     auto do_block = [&](int mb, const char *stage, bool residual) {
         const int q0 = cur_qt * BQ + mb * 32;
         if (q0 + 31 + off < kw0 || (D == 64 && q0 >= lq)) return;     // no row of the block sees a key of this wavefront
@@ -844,11 +880,8 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
 
 }  // namespace
 
-int64_t dkv_worklist_capacity(const cf_attn_fwd_params &p)
-{
-    // sum over segments of ceil(Lk / 128) <= n_kv_tokens / 128 + n_segments key tiles, each split in at most G items
-    return ((int64_t)p.n_kv_tokens / BKV + p.n_segments) * (p.n_q_heads / p.n_kv_heads);
-}
+int64_t dkv_worklist_least(const cf_attn_fwd_params &p) { return key_tiles_most(p) * (p.n_q_heads / p.n_kv_heads); }
+int64_t dkv_worklist_capacity(const cf_attn_fwd_params &p) { return dkv_items_most(p); }
 
 hipError_t launch_mfma_bwd(const cf_attn_bwd_params &b, const BwdWorkspace &ws, hipStream_t s)
 {

@@ -15,8 +15,10 @@ struct BwdWorkspace {
     int *worklist;
     int64_t worklist_items;
 };
-// Upper bound on the dK/dV work items of a launch (one item = a key tile and a set of query heads of one group).
+// Upper bound on the dK/dV work items of one key/value head (one item = a key tile and some of its (query head, query tile)
+// pairs), and the room that the list needs at least (it is cut less finely then).
 int64_t dkv_worklist_capacity(const cf_attn_fwd_params &p);
+int64_t dkv_worklist_least(const cf_attn_fwd_params &p);
 
 // One-shot event pair recorded around the main kernel of the next launch on this thread (see
 // cf_profile_next_call); both NULL when unset.

@@ -129,6 +129,54 @@ def _backward(q, k, v, d_o, flags=0, workspace_bytes=None):
     return o, lse, dq, dkv[0], dkv[1]
 
 
+@pytest.mark.parametrize("lens,prefix,Hq,Hkv,least", [
+    ([900, 300, 2100, 37, 128, 640, 1500, 555, 1000, 64, 968], 0, 28, 4, False),   # a packed chunk of 8192 tokens
+    ([4000], 0, 4, 4, False),                              # one head per group: nothing to split but its query tiles
+    ([130], 3000, 8, 2, False), ([16384], 0, 8, 1, False), # a short slice behind a prefix; whole heads
+    ([4000], 0, 4, 4, True), ([1] * 300, 0, 2, 1, True),   # a scratch with room for G items per key tile only
+])
+def test_dkv_work_list(lens, prefix, Hq, Hkv, least):
+    """The list a bf16 backward leaves in its scratch: every (head, query tile) pair of every key tile in exactly one item, longest
+    items first, no item longer than 1.6 times a slot's share (512 slots) nor more items than that asks for."""
+    T, Tk, G, D = sum(lens), sum(lens) + prefix, Hq // Hkv, 128
+    t = lambda n, h: torch.randn(n, h, D, device="cuda:0").bfloat16()
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cu_k = cu + (np.arange(len(cu)) > 0) * np.int32(prefix)
+    dev = lambda a: torch.from_numpy(a).to("cuda:0")
+    q, k = t(T, Hq), t(Tk, Hkv)
+    f = B.make_fwd_params(q, k, k, torch.empty_like(q), torch.empty(Hq, T, device="cuda:0"), dev(cu), dev(cu_k), D ** -0.5)
+    delta = (Hq * T * 4 + 255) // 256 * 256
+    n_bytes = B.cf_attn_bwd_workspace_bytes(f)
+    if least:
+        n_bytes = min(n_bytes, delta + 256 + 16 * G * (Tk // 128 + len(lens)))
+    ws = torch.zeros(n_bytes, dtype=torch.uint8, device="cuda:0")
+    dk, dv = torch.zeros(Tk, Hkv, D, device="cuda:0"), torch.zeros(Tk, Hkv, D, device="cuda:0")
+    B.cf_attn_fwd(f)
+    B.cf_attn_bwd(B.make_bwd_params(f, q, torch.empty_like(q), dk, dv, ws))
+    wl = ws[delta:].cpu().numpy().view(np.int32)
+    items = wl[64:64 + 4 * wl[0]].reshape(-1, 4).tolist()
+
+    pairs = {}
+    for g, lq in enumerate(lens):
+        off = int(cu_k[g + 1] - cu_k[g]) - lq
+        for kt in range(0, lq + off, 128):
+            n = -(-lq // 64) - max(0, kt - off) // 64
+            if n > 0:
+                pairs[g, kt] = G * n
+    seen = {}
+    for g, kt, first, n in sorted(items):
+        assert n > 0 and first == seen.get((g, kt), 0)
+        seen[g, kt] = first + n
+    assert seen == pairs
+    length = [min(n, 255) for *_, n in items]
+    assert length == sorted(length, reverse=True)
+    fair = max(3, -(-sum(pairs.values()) * Hkv * 8 // (5 * 512)))
+    if not least:
+        assert max(n for *_, n in items) <= fair
+        if fair <= 64:
+            assert len(items) <= len(pairs) + 320 // Hkv + 1
+
+
 def test_d64_backward_without_room_for_a_work_list():
     """bf16, head_dim 64, a workspace that holds delta and nothing else (all that is asked for): the single-writer kernel, bit
     for bit."""
