@@ -199,6 +199,8 @@ enum { CF_FLAG_SCALAR_KERNELS = 1, CF_FLAG_DKV_SINGLE_WRITER = 2 };
  *                     whose rows [P,P+T) the caller filled with this chunk's keys/values.
  * Query head h reads key/value head h / (n_q_heads / n_kv_heads).
  * dtype CF_BF16: q,k,v,o are bf16, arithmetic accumulates in fp32.  CF_FP32: all fp32.
+ * Infinities and NaNs in an input reach only the rows that see it, except in bf16 at head_dim 128, whose kernels
+ * multiply a hidden pair of a block by zero: there rows of the same 64-row block may become NaN too.
  * cu_seqlens are NOT validated (they live on the device): the caller guarantees they are
  * non-decreasing, start at 0, end at n_tokens (q) / n_kv_tokens (k) and satisfy Lk_g >= Lq_g.
  */

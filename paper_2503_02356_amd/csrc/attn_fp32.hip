@@ -31,6 +31,7 @@
 
 #include "kernels.h"
 #include "mfma_common.h"
+#include "scalar_rows.h"
 
 namespace cf {
 namespace {
@@ -152,6 +153,22 @@ __device__ __forceinline__ f32x4 sum_parts(const float *parts, int n, int row, i
     return s;
 }
 
+// The last step of every kernel gives D / 4 consecutive lanes of a wavefront one row: visit(first lane of the row), by the whole
+// wavefront, for every row that one of `lanes` has a part of.  (Rows whose result is not finite: see scalar_rows.h.)
+template <int D>
+__device__ __forceinline__ unsigned long long lanes_of_row(int lane) { return ((1ull << (D / 4)) - 1) << (lane / (D / 4) * (D / 4)); }
+template <int D, typename Visit>
+__device__ __forceinline__ void for_rows_of(unsigned long long lanes, Visit visit)
+{
+    static_assert(RB * (D / 4) <= NW * 64, "one step");
+    while (lanes != 0) {
+        const int first = __ffsll((long long)lanes) - 1;
+        lanes &= ~lanes_of_row<D>(first);
+        visit(first / (D / 4) * (D / 4));
+    }
+}
+__device__ __forceinline__ bool finite(const f32x4 &x) { return cf::finite((x[0] + x[1]) + (x[2] + x[3])); }
+
 template <int D>
 __device__ __forceinline__ void f32_fwd_body(const cf_attn_fwd_params &p, int id)
 {
@@ -214,9 +231,9 @@ __device__ __forceinline__ void f32_fwd_body(const cf_attn_fwd_params &p, int id
     __syncthreads();
 
     // O = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w over the wavefronts that had a block
-    const int n = min(NW, n_kb);
-    for (int t = threadIdx.x; t < rows * (D / 4); t += NW * 64) {
-        const int r = t / (D / 4), c = t % (D / 4);
+    const int n = min(NW, n_kb), r = threadIdx.x / (D / 4), c = threadIdx.x % (D / 4);
+    bool bad = false;
+    if (r < rows) {
         float M = m_s[0][r], L = 0.f;
         for (int w = 1; w < n; ++w) M = fmaxf(M, m_s[w][r]);
         f32x4 a = {0.f, 0.f, 0.f, 0.f};
@@ -225,9 +242,16 @@ __device__ __forceinline__ void f32_fwd_body(const cf_attn_fwd_params &p, int id
             L += g * l_s[w][r];
             a += g * *(const f32x4 *)(parts + w * S::PART + r * S::OS + c * 4);
         }
-        *(f32x4 *)((float *)p.o + (int64_t)(loc.begin + q0 + r) * p.o_stride_tok + (int64_t)h * p.o_stride_head + c * 4) = a * (1.f / L);
+        a *= 1.f / L;
+        bad = !finite(a);
+        *(f32x4 *)((float *)p.o + (int64_t)(loc.begin + q0 + r) * p.o_stride_tok + (int64_t)h * p.o_stride_head + c * 4) = a;
         if (c == 0) p.lse[(int64_t)h * p.n_tokens + loc.begin + q0 + r] = M * kLn2 + logf(L);
     }
+    for_rows_of<D>(__ballot(bad), [&](int first) {
+        const int row = q0 + (wave * 64 + first) / (D / 4);
+        const float *qr = q + (int64_t)row * p.q_stride_tok;
+        scalar_fwd_row<float, D, 4>(p, SegmentRows{loc.begin, lq, loc.other_begin, lk}, loc.begin + row, h, [&](int x) { return qr[x]; });
+    });
 }
 
 template <int D>
@@ -363,12 +387,19 @@ __device__ __forceinline__ void f32_dq_body(const cf_attn_bwd_params &b, int id,
     __syncthreads();                                 // the operands have been read for the last time
     if (wave < n_kb) write_part<D>(dq, parts + wave * S::PART, lane);
     __syncthreads();
-    const int n = min(NW, n_kb);
-    for (int t = threadIdx.x; t < rows * (D / 4); t += NW * 64) {
-        const int r = t / (D / 4), c = t % (D / 4);
-        *(f32x4 *)((float *)b.d_q + (int64_t)(loc.begin + q0 + r) * b.dq_stride_tok + (int64_t)h * b.dq_stride_head + c * 4) =
-            sum_parts<D>(parts, n, r, c) * p.softmax_scale;
+    const int n = min(NW, n_kb), r = threadIdx.x / (D / 4), c = threadIdx.x % (D / 4);
+    bool bad = false;
+    if (r < rows) {
+        const f32x4 a = sum_parts<D>(parts, n, r, c) * p.softmax_scale;
+        bad = !finite(a);
+        *(f32x4 *)((float *)b.d_q + (int64_t)(loc.begin + q0 + r) * b.dq_stride_tok + (int64_t)h * b.dq_stride_head + c * 4) = a;
     }
+    for_rows_of<D>(__ballot(bad), [&](int first) {
+        const int row = loc.begin + q0 + (wave * 64 + first) / (D / 4);
+        const SegmentRows g{loc.begin, lq, loc.other_begin, lk};
+        const float *qr = row_of<float>(p.q, row, p.q_stride_tok, h, p.q_stride_head), *dr = row_of<float>(b.d_o, row, b.do_stride_tok, h, b.do_stride_head);
+        scalar_dq_row<float, D, 4>(b, g, row, h, [&](int x) { return qr[x]; }, [&](int x) { return dr[x]; }, scalar_delta<float, D>(b, g, row, h));
+    });
 }
 
 // dK, dV of 16 key rows of one key/value head: (query head of the group, 16-row query block) pairs dealt over the
@@ -429,7 +460,7 @@ __device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id
         __builtin_amdgcn_wave_barrier();
         f32x4 dp = row_product<D>(a, vs, lane);
         if (D == 64) load_q_columns();
-        else load_q_row(), load_do_columns();
+        else load_q_row();
         f32x4 s = row_product<D>(qa, ks, lane);
         const int lim = k0 + col - off - q0 - 4 * quarter;           // query 4 * quarter + i of the block is masked iff i < lim
         const f32x4 l4 = *(const f32x4 *)(st + 4 * quarter);
@@ -444,13 +475,16 @@ __device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id
 #pragma unroll
         for (int i = 0; i < 4; ++i) dp[i] = s[i] * (dp[i] - d4[i]);
         __builtin_amdgcn_wave_barrier();                             // st is rewritten by the next item
-        if (D != 64) load_q_columns();
+        if (D != 64) load_do_columns(), load_q_columns();     // (before S: 30 registers spilled)
         add_column_product<D>(x, s, dv);
         add_column_product<D>(y, dp, dk);
     }
     // At D = 64 both results meet in LDS together, at D = 128 there is room for one after the other.
     const int n = min(NW, n_items);
     constexpr int TOGETHER = S::BOTH_MEET ? 2 : 1;
+    static_assert(TOGETHER * RB * (D / 4) <= NW * 64, "one step");
+    const int t = threadIdx.x, r = t / (D / 4) % rows, c = t % (D / 4);
+    unsigned long long left_out[2 / TOGETHER];       // lanes whose row is not finite
     for (int first = 0; first < 2; first += TOGETHER) {
         __syncthreads();
         if (wave < n_items) {
@@ -458,12 +492,28 @@ __device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id
             if (first + TOGETHER == 2) write_part<D>(dk, parts + ((TOGETHER - 1) * NW + wave) * S::PART, lane);
         }
         __syncthreads();
-        for (int t = threadIdx.x; t < TOGETHER * rows * (D / 4); t += NW * 64) {
-            const int which = first + t / (rows * (D / 4)), r = t / (D / 4) % rows, c = t % (D / 4);
-            f32x4 *dst = (f32x4 *)((which ? b.d_k : b.d_v) + (int64_t)(loc.begin + k0 + r) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head + c * 4);
-            *dst += sum_parts<D>(parts + (which - first) * NW * S::PART, n, r, c) * (which ? p.softmax_scale : 1.f);
-        }
+        const int which = first + t / (rows * (D / 4));
+        const bool mine = t < TOGETHER * rows * (D / 4);
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+        if (mine) a = sum_parts<D>(parts + (which - first) * NW * S::PART, n, r, c) * (which ? p.softmax_scale : 1.f);
+        const unsigned long long bad = __ballot(!finite(a));
+        left_out[first / TOGETHER] = bad;
+        if (mine && (bad & lanes_of_row<D>(lane)) == 0)
+            *(f32x4 *)((which ? b.d_k : b.d_v) + (int64_t)(loc.begin + k0 + r) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head + c * 4) += a;
     }
+    for (int pass = 0; pass < 2 / TOGETHER; ++pass)
+        for_rows_of<D>(left_out[pass], [&](int at) {
+            const int first = wave * 64 + at, krow = loc.begin + k0 + first / (D / 4) % rows;
+            const bool is_k = pass + first / (rows * (D / 4)) != 0;
+            const SegmentRows g{loc.other_begin, lq, loc.begin, lk};
+            const float *kr = row_of<float>(p.k, krow, p.kv_stride_tok, kh, p.kv_stride_head), *vr = row_of<float>(p.v, krow, p.kv_stride_tok, kh, p.kv_stride_head);
+            float gk[D / 64], gv[D / 64];
+            scalar_dkv_row<float, D, 4>(b, g, krow, kh, [&](int x) { return kr[x]; }, [&](int x) { return vr[x]; },
+                                        [&](int row, int h) { return scalar_delta<float, D>(b, g, row, h); }, gk, gv);
+            float *dst = (is_k ? b.d_k : b.d_v) + (int64_t)krow * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head;
+#pragma unroll
+            for (int x = 0; x < D / 64; ++x) dst[lane + 64 * x] += is_k ? gk[x] * p.softmax_scale : gv[x];
+        });
 }
 
 template <int D>

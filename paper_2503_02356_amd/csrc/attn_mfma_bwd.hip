@@ -28,6 +28,7 @@
 
 #include "kernels.h"
 #include "mfma_common.h"
+#include "scalar_rows.h"
 
 namespace cf {
 namespace {
@@ -438,7 +439,8 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     };
     float *tr = scratch_of(wave);
     const int end_lane = fresh_lane(), end_half = end_lane >> 5, end_col = end_lane & 31;
-    auto add_rows = [&](const f32x16 (&acc)[DB], float scale, float *g) {
+    unsigned not_finite[2] = {0, 0};                 // rows of dV and dK that this wavefront has left out (D = 64; see scalar_rows.h)
+    auto add_rows = [&](const f32x16 (&acc)[DB], float scale, float *g, unsigned &left_out) {
 #pragma unroll
         for (int j = 0; j < DB; ++j)
 #pragma unroll
@@ -464,7 +466,9 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
                 }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                if (r0 + e < rows_valid) {
+                const bool leave = D == 64 && __ballot(!finite(v[e][0])) != 0;
+                if (leave && r0 + e < rows_valid) left_out |= 1u << (r0 + e);
+                if (!leave && r0 + e < rows_valid) {
                     float *row = g + (int64_t)(r0 + e) * b.dkv_stride_tok + end_lane;
 #pragma unroll
                     for (int c = 0; c < D / 64; ++c) {
@@ -476,8 +480,22 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
         }
         meet();
     };
-    add_rows(dv, 1.f, b.d_v);
-    add_rows(dk, p.softmax_scale, b.d_k);
+    add_rows(dv, 1.f, b.d_v, not_finite[0]);
+    add_rows(dk, p.softmax_scale, b.d_k, not_finite[1]);
+    if (D == 64) {
+        for (unsigned rows = not_finite[0] | not_finite[1]; rows != 0; rows &= rows - 1) {
+            const int r = __builtin_ctz(rows), krow = k_seg0 + kw0 + r;
+            const unsigned short *kr = row_of<unsigned short>(p.k, krow, p.kv_stride_tok, kh, p.kv_stride_head);
+            const unsigned short *vr = row_of<unsigned short>(p.v, krow, p.kv_stride_tok, kh, p.kv_stride_head);
+            float gk[1], gv[1];
+            scalar_dkv_row<unsigned short, 64, 4>(b, SegmentRows{q_seg0, lq, k_seg0, lk}, krow, kh, [&](int x) { return ld(kr + x); },
+                                               [&](int x) { return ld(vr + x); },
+                                               [&](int row, int h) { return -delta[(int64_t)h * p.n_tokens + row]; }, gk, gv);
+            const int64_t at = (int64_t)krow * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head + end_lane;
+            if (not_finite[0] >> r & 1) b.d_v[at] += gv[0];
+            if (not_finite[1] >> r & 1) b.d_k[at] += gk[0] * p.softmax_scale;
+        }
+    }
 }
 
 template <int D, bool FUSED_HEADS>
@@ -690,8 +708,9 @@ __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__re
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], c2, -lse2));
-                        if (need_mask && mb * 32 + (i >> 2) * 8 + (i & 3) > lim) pv = 0.f;
-                        if (DELTA_PASS) dsum += pv * dp[i];
+                        const bool hidden = need_mask && mb * 32 + (i >> 2) * 8 + (i & 3) > lim;
+                        if (hidden) pv = 0.f;
+                        if (DELTA_PASS) dsum += D == 64 && hidden ? 0.f : pv * dp[i];     // (dP of a hidden pair may be anything)
                         else dp[i] = pv * (dp[i] - dlt);
                     }
                     if (DELTA_PASS) continue;
@@ -737,6 +756,15 @@ __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__re
         store_rows_bf16<D>(dq, p.softmax_scale, scratch, lq - wq0, [&](int r) {
             return (char *)b.d_q + ((int64_t)(q_seg0 + wq0 + r) * b.dq_stride_tok + (int64_t)h * b.dq_stride_head) * 2;
         });
+        if (D == 64) {
+            for_rows_not_finite<D>(dq, p.softmax_scale, lq - wq0, [&](int r) {
+                const int row = q_seg0 + wq0 + r;
+                const unsigned short *qr = row_of<unsigned short>(p.q, row, p.q_stride_tok, h, p.q_stride_head);
+                const unsigned short *dr = row_of<unsigned short>(b.d_o, row, b.do_stride_tok, h, b.do_stride_head);
+                scalar_dq_row<unsigned short, 64, 4>(b, SegmentRows{q_seg0, lq, k_seg0, lk}, row, h, [&](int x) { return ld(qr + x); },
+                                                  [&](int x) { return ld(dr + x); }, __shfl(dlt, r));
+            });
+        }
     }
 }
 

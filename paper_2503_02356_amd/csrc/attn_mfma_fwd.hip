@@ -16,6 +16,7 @@
 
 #include "kernels.h"
 #include "mfma_common.h"
+#include "scalar_rows.h"
 
 namespace cf {
 namespace {
@@ -226,6 +227,13 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     });
     if (iq < lq && half == 0)
         p.lse[(int64_t)h * p.n_tokens + q_seg0 + iq] = m_run * (D == 64 ? 1.f : 0.69314718055994530942f) + __logf(l_tot);
+    if (D == 64) {
+        for_rows_not_finite<D>(o_acc, 1.f / l_tot, lq - wq0, [&](int r) {
+            const int row = q_seg0 + wq0 + r;
+            const unsigned short *qr = row_of<unsigned short>(p.q, row, p.q_stride_tok, h, p.q_stride_head);
+            scalar_fwd_row<unsigned short, 64, 4>(p, SegmentRows{q_seg0, lq, k_seg0, lk}, row, h, [&](int x) { return ld(qr + x); });
+        });
+    }
 }
 
 template <int D>

@@ -10,32 +10,12 @@
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
+#include "scalar_rows.h"
 
 namespace cf {
 namespace {
 
 constexpr int kWaves = 4;  // wavefronts per workgroup
-
-__device__ inline float ld(const float *p) { return *p; }
-__device__ inline float ld(const unsigned short *p) { return __uint_as_float(((unsigned)*p) << 16); }
-__device__ inline void st(float *p, float x) { *p = x; }
-__device__ inline void st(unsigned short *p, float x)
-{  // round to nearest even bf16
-    unsigned u = __float_as_uint(x);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    *p = (unsigned short)(u >> 16);
-}
-
-__device__ inline float wave_max(float x)
-{
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-    return x;
-}
-__device__ inline float wave_sum(float x)
-{
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return x;
-}
 
 // Largest g in [0, n) with cu[g] <= row  (cu non-decreasing, cu[0] = 0, zero-length segments skipped).
 __device__ inline int find_segment(const int32_t *cu, int n, int row)
@@ -48,6 +28,16 @@ __device__ inline int find_segment(const int32_t *cu, int n, int row)
     return lo;
 }
 
+__device__ inline SegmentRows segment_rows(const cf_attn_fwd_params &p, int g)
+{
+    const int q0 = p.cu_seqlens_q[g], k0 = p.cu_seqlens_k[g];
+    return {q0, p.cu_seqlens_q[g + 1] - q0, k0, p.cu_seqlens_k[g + 1] - k0};
+}
+__device__ inline SegmentRows segment_of_query(const cf_attn_fwd_params &p, int row)
+{
+    return segment_rows(p, find_segment(p.cu_seqlens_q, p.n_segments, row));
+}
+
 template <typename T, int D>
 __global__ __launch_bounds__(kWaves * 64) void simple_fwd_kernel(cf_attn_fwd_params p)
 {
@@ -55,45 +45,12 @@ __global__ __launch_bounds__(kWaves * 64) void simple_fwd_kernel(cf_attn_fwd_par
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int row = blockIdx.x * kWaves + wave;
     if (row >= p.n_tokens) return;  // whole wavefront leaves together; no barrier below
-    const int h = blockIdx.y, kh = h / (p.n_q_heads / p.n_kv_heads);
-    const int g = find_segment(p.cu_seqlens_q, p.n_segments, row);
-    const int q0 = p.cu_seqlens_q[g], lq = p.cu_seqlens_q[g + 1] - q0;
-    const int k0 = p.cu_seqlens_k[g], lk = p.cu_seqlens_k[g + 1] - k0;
-    const int n_vis = lk - lq + (row - q0) + 1;
-    const T *q = (const T *)p.q + (int64_t)row * p.q_stride_tok + (int64_t)h * p.q_stride_head;
-    const T *kb = (const T *)p.k + (int64_t)kh * p.kv_stride_head;
-    const T *vb = (const T *)p.v + (int64_t)kh * p.kv_stride_head;
-    constexpr int DPL = D / 64;
-    for (int t = 0; t < DPL; ++t) sq[wave][lane + 64 * t] = ld(q + lane + 64 * t);
+    const int h = blockIdx.y;
+    const SegmentRows g = segment_of_query(p, row);
+    const T *q = row_of<T>(p.q, row, p.q_stride_tok, h, p.q_stride_head);
+    for (int t = 0; t < D / 64; ++t) sq[wave][lane + 64 * t] = ld(q + lane + 64 * t);
     __builtin_amdgcn_wave_barrier();
-    float m = -INFINITY, z = 0.f, acc[DPL];
-    for (int t = 0; t < DPL; ++t) acc[t] = 0.f;
-    for (int j0 = 0; j0 < n_vis; j0 += 64) {
-        const int j = j0 + lane;
-        float s = -INFINITY;
-        if (j < n_vis) {
-            const T *kj = kb + (int64_t)(k0 + j) * p.kv_stride_tok;
-            float d = 0.f;
-            for (int x = 0; x < D; ++x) d += sq[wave][x] * ld(kj + x);
-            s = d * p.softmax_scale;
-        }
-        const float m_new = fmaxf(m, wave_max(s));
-        const float pr = (j < n_vis) ? expf(s - m_new) : 0.f;
-        const float corr = expf(m - m_new);  // m = -inf on the first block gives 0
-        z = z * corr + wave_sum(pr);
-        for (int t = 0; t < DPL; ++t) acc[t] *= corr;
-        const int cnt = min(64, n_vis - j0);
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float pj = __shfl(pr, jj);
-            const T *vj = vb + (int64_t)(k0 + j0 + jj) * p.kv_stride_tok;
-            for (int t = 0; t < DPL; ++t) acc[t] += pj * ld(vj + lane + 64 * t);
-        }
-        m = m_new;
-    }
-    T *o = (T *)p.o + (int64_t)row * p.o_stride_tok + (int64_t)h * p.o_stride_head;
-    const float inv = 1.f / z;
-    for (int t = 0; t < DPL; ++t) st(o + lane + 64 * t, acc[t] * inv);
-    if (lane == 0) p.lse[(int64_t)h * p.n_tokens + row] = m + logf(z);
+    scalar_fwd_row<T, D, 0>(p, g, row, h, [&](int x) { return sq[wave][x]; });
 }
 
 template <typename T, int D>
@@ -104,47 +61,17 @@ __global__ __launch_bounds__(kWaves * 64) void simple_dq_kernel(cf_attn_bwd_para
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int row = blockIdx.x * kWaves + wave;
     if (row >= p.n_tokens) return;
-    const int h = blockIdx.y, kh = h / (p.n_q_heads / p.n_kv_heads);
-    const int g = find_segment(p.cu_seqlens_q, p.n_segments, row);
-    const int q0 = p.cu_seqlens_q[g], lq = p.cu_seqlens_q[g + 1] - q0;
-    const int k0 = p.cu_seqlens_k[g], lk = p.cu_seqlens_k[g + 1] - k0;
-    const int n_vis = lk - lq + (row - q0) + 1;
-    const T *q = (const T *)p.q + (int64_t)row * p.q_stride_tok + (int64_t)h * p.q_stride_head;
-    const T *d_o = (const T *)b.d_o + (int64_t)row * b.do_stride_tok + (int64_t)h * b.do_stride_head;
-    const T *kb = (const T *)p.k + (int64_t)kh * p.kv_stride_head;
-    const T *vb = (const T *)p.v + (int64_t)kh * p.kv_stride_head;
-    constexpr int DPL = D / 64;
-    for (int t = 0; t < DPL; ++t) {
+    const int h = blockIdx.y;
+    const SegmentRows g = segment_of_query(p, row);
+    const T *q = row_of<T>(p.q, row, p.q_stride_tok, h, p.q_stride_head);
+    const T *d_o = row_of<T>(b.d_o, row, b.do_stride_tok, h, b.do_stride_head);
+    for (int t = 0; t < D / 64; ++t) {
         sq[wave][lane + 64 * t] = ld(q + lane + 64 * t);
         sdo[wave][lane + 64 * t] = ld(d_o + lane + 64 * t);
     }
     __builtin_amdgcn_wave_barrier();
-    const float lse = p.lse[(int64_t)h * p.n_tokens + row];
-    const float dl = delta[(int64_t)h * p.n_tokens + row];
-    float acc[DPL];
-    for (int t = 0; t < DPL; ++t) acc[t] = 0.f;
-    for (int j0 = 0; j0 < n_vis; j0 += 64) {
-        const int j = j0 + lane;
-        float ds = 0.f;
-        if (j < n_vis) {
-            const T *kj = kb + (int64_t)(k0 + j) * p.kv_stride_tok;
-            const T *vj = vb + (int64_t)(k0 + j) * p.kv_stride_tok;
-            float s = 0.f, dp = 0.f;
-            for (int x = 0; x < D; ++x) {
-                s += sq[wave][x] * ld(kj + x);
-                dp += sdo[wave][x] * ld(vj + x);
-            }
-            ds = expf(s * p.softmax_scale - lse) * (dp - dl);
-        }
-        const int cnt = min(64, n_vis - j0);
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float dj = __shfl(ds, jj);
-            const T *kj = kb + (int64_t)(k0 + j0 + jj) * p.kv_stride_tok;
-            for (int t = 0; t < DPL; ++t) acc[t] += dj * ld(kj + lane + 64 * t);
-        }
-    }
-    T *dq = (T *)b.d_q + (int64_t)row * b.dq_stride_tok + (int64_t)h * b.dq_stride_head;
-    for (int t = 0; t < DPL; ++t) st(dq + lane + 64 * t, acc[t] * p.softmax_scale);
+    scalar_dq_row<T, D, 0>(b, g, row, h, [&](int x) { return sq[wave][x]; }, [&](int x) { return sdo[wave][x]; },
+                        delta[(int64_t)h * p.n_tokens + row]);
 }
 
 // One wavefront per (key row, key/value head): the only writer of that row of dK and dV.
@@ -156,51 +83,19 @@ __global__ __launch_bounds__(kWaves * 64) void simple_dkv_kernel(cf_attn_bwd_par
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int krow = blockIdx.x * kWaves + wave;
     if (krow >= p.n_kv_tokens) return;
-    const int kh = blockIdx.y, G = p.n_q_heads / p.n_kv_heads;
-    const int g = find_segment(p.cu_seqlens_k, p.n_segments, krow);
-    const int q0 = p.cu_seqlens_q[g], lq = p.cu_seqlens_q[g + 1] - q0;
-    const int k0 = p.cu_seqlens_k[g], lk = p.cu_seqlens_k[g + 1] - k0;
-    const int j = krow - k0, prefix = lk - lq;
-    const int i_first = j > prefix ? j - prefix : 0;  // first query row that sees this key
-    const T *kj = (const T *)p.k + (int64_t)krow * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head;
-    const T *vj = (const T *)p.v + (int64_t)krow * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head;
+    const int kh = blockIdx.y, seg = find_segment(p.cu_seqlens_k, p.n_segments, krow);
+    const SegmentRows g = segment_rows(p, seg);
+    const T *k = row_of<T>(p.k, krow, p.kv_stride_tok, kh, p.kv_stride_head);
+    const T *v = row_of<T>(p.v, krow, p.kv_stride_tok, kh, p.kv_stride_head);
     constexpr int DPL = D / 64;
     for (int t = 0; t < DPL; ++t) {
-        sk[wave][lane + 64 * t] = ld(kj + lane + 64 * t);
-        sv[wave][lane + 64 * t] = ld(vj + lane + 64 * t);
+        sk[wave][lane + 64 * t] = ld(k + lane + 64 * t);
+        sv[wave][lane + 64 * t] = ld(v + lane + 64 * t);
     }
     __builtin_amdgcn_wave_barrier();
     float dk[DPL], dv[DPL];
-    for (int t = 0; t < DPL; ++t) dk[t] = dv[t] = 0.f;
-    for (int h = kh * G; h < (kh + 1) * G; ++h) {
-        const T *qb = (const T *)p.q + (int64_t)h * p.q_stride_head;
-        const T *dob = (const T *)b.d_o + (int64_t)h * b.do_stride_head;
-        for (int i0 = i_first; i0 < lq; i0 += 64) {
-            const int i = i0 + lane;
-            float pr = 0.f, ds = 0.f;
-            if (i < lq) {
-                const T *qi = qb + (int64_t)(q0 + i) * p.q_stride_tok;
-                const T *doi = dob + (int64_t)(q0 + i) * b.do_stride_tok;
-                float s = 0.f, dp = 0.f;
-                for (int x = 0; x < D; ++x) {
-                    s += ld(qi + x) * sk[wave][x];
-                    dp += ld(doi + x) * sv[wave][x];
-                }
-                pr = expf(s * p.softmax_scale - p.lse[(int64_t)h * p.n_tokens + q0 + i]);
-                ds = pr * (dp - delta[(int64_t)h * p.n_tokens + q0 + i]);
-            }
-            const int cnt = min(64, lq - i0);
-            for (int ii = 0; ii < cnt; ++ii) {
-                const float pi = __shfl(pr, ii), di = __shfl(ds, ii);
-                const T *qi = qb + (int64_t)(q0 + i0 + ii) * p.q_stride_tok;
-                const T *doi = dob + (int64_t)(q0 + i0 + ii) * b.do_stride_tok;
-                for (int t = 0; t < DPL; ++t) {
-                    dv[t] += pi * ld(doi + lane + 64 * t);
-                    dk[t] += di * ld(qi + lane + 64 * t);
-                }
-            }
-        }
-    }
+    scalar_dkv_row<T, D, 0>(b, g, krow, kh, [&](int x) { return sk[wave][x]; }, [&](int x) { return sv[wave][x]; },
+                         [&](int row, int h) { return delta[(int64_t)h * p.n_tokens + row]; }, dk, dv);
     float *gk = b.d_k + (int64_t)krow * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head;
     float *gv = b.d_v + (int64_t)krow * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head;
     for (int t = 0; t < DPL; ++t) {

@@ -300,6 +300,22 @@ __device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[D / 32], flo
     }
 }
 
+// visit(r), by the whole wavefront, for every row r < rows_valid of a 32 x D block (a lane owns row lane % 32, as above) whose
+// results, scaled, are not finite.
+template <int D, typename Visit>
+__device__ __forceinline__ void for_rows_not_finite(const f32x16 (&acc)[D / 32], float scale, int rows_valid, Visit visit)
+{
+    float zero = scale * 0.f;                        // stays 0 while everything is finite
+#pragma unroll
+    for (int j = 0; j < D / 32; ++j)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) zero = __builtin_fmaf(acc[j][i], 0.f, zero);
+    const unsigned long long lanes = __ballot(zero != 0.f);
+    unsigned rows = (unsigned)lanes | (unsigned)(lanes >> 32);
+    if (rows_valid < 32) rows &= (1u << rows_valid) - 1;
+    for (; rows != 0; rows &= rows - 1) visit(__builtin_ctz(rows));
+}
+
 // Lane l and lane l ^ 32 combine a value without going through LDS: v_permlane32_swap with both operands = x
 // returns (x of the lower half, x of the upper half) in every lane (checked on the device with a probe).
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));

@@ -129,6 +129,41 @@ def _backward(q, k, v, d_o, flags=0, workspace_bytes=None):
     return o, lse, dq, dkv[0], dkv[1]
 
 
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp32", 64), ("fp32", 128)])
+@pytest.mark.parametrize("lens,prefix,where", [
+    ([150, 200], 0, 70), ([150, 200], 0, 149), ([150, 200], 0, 155),      # in a block's middle, a segment's last row, another's first ones
+    ([90], 100, 130), ([300], 0, 299),
+])
+def test_infinities_and_nans_reach_only_the_rows_that_see_them(dtype, D, lens, prefix, where):
+    """An infinity in V, a NaN in K, Q or dO, at row `where` of the keys (queries: of the same token): the scalar kernels never
+    read a pair that the mask hides, so what is finite there has to be finite here, and agree."""
+    dt, T, Hq, Hkv = torch.bfloat16 if dtype == "bf16" else torch.float32, sum(lens), 4, 2
+    gen = torch.Generator(device="cuda:0").manual_seed(8)
+    rand = lambda n, h: torch.randn(n, h, D, device="cuda:0", generator=gen).to(dt)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    cu_k = cu + (np.arange(len(cu)) > 0) * np.int32(prefix)
+    cu, cu_k = (torch.from_numpy(a).to("cuda:0") for a in (cu, cu_k))
+    clean = rand(T, Hq), rand(T + prefix, Hkv), rand(T + prefix, Hkv), rand(T, Hq)
+    for n, value in ((1, float("nan")), (2, float("inf")), (0, float("nan")), (3, float("nan")), (3, float("-inf"))):
+        q, k, v, d_o = t = [x.clone() for x in clean]
+        t[n][where - (prefix if n in (0, 3) else 0), 1, 5] = value
+        res = []
+        for flags in (0, B.CF_FLAG_SCALAR_KERNELS):
+            o, dq, lse = torch.empty_like(q), torch.empty_like(q), torch.empty(Hq, T, device="cuda:0")
+            dk, dv = torch.zeros(T + prefix, Hkv, D, device="cuda:0"), torch.zeros(T + prefix, Hkv, D, device="cuda:0")
+            f = B.make_fwd_params(q, k, v, o, lse, cu, cu_k, D ** -0.5, flags)
+            B.cf_attn_fwd(f)
+            ws = torch.empty(B.cf_attn_bwd_workspace_bytes(f), dtype=torch.uint8, device="cuda:0")
+            B.cf_attn_bwd(B.make_bwd_params(f, d_o, dq, dk, dv, ws))
+            torch.cuda.synchronize()
+            res.append((o, lse, dq, dk, dv))
+        for name, a, b in zip(P.NAMES, *res):
+            fine = torch.isfinite(b)
+            assert torch.equal(torch.isfinite(a), fine), (n, value, name)
+            d, r = (a[fine].double() - b[fine].double()).norm(), b[fine].double().norm()
+            assert d <= P.TOL[dtype][1] * r, (n, value, name, float(d / r))
+
+
 @pytest.mark.parametrize("lens,prefix,Hq,Hkv,least", [
     ([900, 300, 2100, 37, 128, 640, 1500, 555, 1000, 64, 968], 0, 28, 4, False),   # a packed chunk of 8192 tokens
     ([4000], 0, 4, 4, False),                              # one head per group: nothing to split but its query tiles
