@@ -1,5 +1,6 @@
 """Builds libchunkflow.so (host planner + HIP kernels for gfx950) in-tree with hipcc."""
 import os
+import re
 import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -12,10 +13,27 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed-fp32 VALU forms are switched off for all device code.
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
              "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
+RESOURCE_REPORT = "-Rpass-analysis=kernel-resource-usage"
 
 
 def _stale(obj, deps):
     return not os.path.exists(obj) or any(os.path.getmtime(d) > os.path.getmtime(obj) for d in deps)
+
+
+def spilled_accumulators(report):
+    """Kernels of a compiler resource report that update accumulators in place behind the compiler's back (the dK/dV kernels
+    at head_dim 128; mfma_common.h, accumulate_in_place) and spill: a spilled accumulator would be stored while its last
+    MFMA is still running.  -> [(kernel, what)]"""
+    bad, kernel = [], None
+    for line in report.splitlines():
+        m = re.search(r"remark: [^:]*?(Function Name|VGPRs Spill|ScratchSize \[bytes/lane\]): (\S+)", line)
+        if m is None:
+            continue
+        if m[1] == "Function Name":
+            kernel = m[2]
+        elif "mfma_dkv" in kernel and "ILi128E" in kernel and int(m[2]) != 0:
+            bad.append((kernel, f"{m[1]}: {m[2]}"))
+    return bad
 
 
 def build(force=True, verbose=False):
@@ -33,7 +51,7 @@ def build(force=True, verbose=False):
         if not force and not _stale(obj, [path] + headers):
             continue
         if src.endswith(".hip"):
-            cmd = [HIPCC] + HIP_FLAGS + inc + ["-c", path, "-o", obj]
+            cmd = [HIPCC] + HIP_FLAGS + [RESOURCE_REPORT, "-fno-caret-diagnostics"] + inc + ["-c", path, "-o", obj]
         else:
             cmd = [HIPCC, "-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra"] + inc + ["-x", "c++", "-c", path, "-o", obj]
         if verbose:
@@ -42,9 +60,13 @@ def build(force=True, verbose=False):
     failed = []
     for src, pr in procs:
         out, _ = pr.communicate()
-        out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
+        spilled = spilled_accumulators(out)
+        out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l and RESOURCE_REPORT not in l)
         if pr.returncode != 0:
             failed.append(f"--- {src}\n{out}")
+        elif spilled:
+            os.remove(os.path.join(bdir, src + ".o"))
+            failed.append(f"--- {src}: kernels with in-place accumulators may not spill: {spilled}")
         elif verbose and out.strip():
             print(out)
     if failed:
