@@ -67,14 +67,21 @@ bool mfma_shape(const cf_attn_fwd_params &p)
 // (fp32) of this many elements stay below 2^32.  Wider strides go to the scalar kernels.
 constexpr int64_t kMostStride = 1 << 25;
 bool narrow(const cf_attn_fwd_params &p) { return p.q_stride_tok < kMostStride && p.kv_stride_tok < kMostStride; }
+// Their launches give every segment workgroups of its own: hundreds of thousands of segments can be more than one launch
+// holds, and go to the scalar kernels (a row per wavefront).  (bf16 at head_dim 128 never had that way out.)
+bool launchable_mfma(const cf_attn_fwd_params &p, bool backward)
+{
+    return p.head_dim == 128 || cf::mfma_launch_size(p, backward) <= cf::kMostWorkItems;
+}
+bool launchable_f32(const cf_attn_fwd_params &p, bool backward) { return cf::f32_launch_size(p, backward) <= cf::kMostWorkItems; }
 
 // The MFMA kernels take the row maximum before scaling, which needs a positive scale.
-bool use_mfma(const cf_attn_fwd_params &p) { return mfma_shape(p) && p.softmax_scale > 0.f && narrow(p); }
-bool use_mfma(const cf_attn_bwd_params &b) { return use_mfma(b.f) && b.do_stride_tok < kMostStride; }
+bool use_mfma(const cf_attn_fwd_params &p) { return mfma_shape(p) && p.softmax_scale > 0.f && narrow(p) && launchable_mfma(p, false); }
+bool use_mfma(const cf_attn_bwd_params &b) { return use_mfma(b.f) && b.do_stride_tok < kMostStride && launchable_mfma(b.f, true); }
 
 // The fp32 matrix kernels: every fp32 shape, any scale.
-bool use_f32(const cf_attn_fwd_params &p) { return p.dtype == CF_FP32 && !(p.flags & CF_FLAG_SCALAR_KERNELS) && narrow(p); }
-bool use_f32(const cf_attn_bwd_params &b) { return use_f32(b.f) && b.do_stride_tok < kMostStride; }
+bool use_f32(const cf_attn_fwd_params &p) { return p.dtype == CF_FP32 && !(p.flags & CF_FLAG_SCALAR_KERNELS) && narrow(p) && launchable_f32(p, false); }
+bool use_f32(const cf_attn_bwd_params &b) { return use_f32(b.f) && b.do_stride_tok < kMostStride && launchable_f32(b.f, true); }
 
 hipError_t fwd_one(const cf_attn_fwd_params &p, hipStream_t s)
 {
@@ -205,6 +212,7 @@ Path path_of(const Call &c)
 {
     return (c.b ? use_mfma(*c.b) : use_mfma(*c.f)) ? kMfma : (c.b ? use_f32(*c.b) : use_f32(*c.f)) ? kF32 : kScalar;
 }
+int64_t launch_size(const Call &c) { return path_of(c) == kMfma ? cf::mfma_launch_size(*c.f, c.b != nullptr) : cf::f32_launch_size(*c.f, c.b != nullptr); }
 bool same_kernel(const Call &a, const Call &c)
 {
     return !a.b == !c.b && path_of(a) != kScalar && path_of(a) == path_of(c) && a.f->head_dim == c.f->head_dim &&
@@ -312,8 +320,11 @@ int launch_calls(const Call *calls, int n, hipStream_t s, const char *who)
         const int launches = (end - i + most - 1) / most, size = (end - i + launches - 1) / launches;
         while (i < end) {
             t[i] = touched(calls[i]);
+            int64_t work_items = launch_size(calls[i]);
             int j = i + 1;
             for (; j < end && j - i < size; ++j) {
+                work_items += launch_size(calls[j]);
+                if (work_items > cf::kMostWorkItems) break;
                 t[j] = touched(calls[j]);
                 bool apart = true;
                 for (int a = i; a < j && apart; ++a)

@@ -540,10 +540,12 @@ int64_t row_blocks(int64_t total, int n_segments) { return total / RB + n_segmen
 int64_t query_blocks(const cf_attn_fwd_params &p) { return row_blocks(p.n_tokens, p.n_segments) * p.n_q_heads; }
 int64_t key_blocks(const cf_attn_fwd_params &p) { return row_blocks(p.n_kv_tokens, p.n_segments) * p.n_kv_heads; }
 
+int64_t launch_blocks(const cf_attn_fwd_params &p, bool backward) { return query_blocks(p) + (backward ? key_blocks(p) : 0); }
+
 template <int D>
 hipError_t run_fwd(const cf_attn_fwd_params &p, hipStream_t s)
 {
-    const int64_t blocks = query_blocks(p);
+    const int64_t blocks = launch_blocks(p, false);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const ProfileHook hook = take_profile_hook();
     if (hook.start) (void)hipEventRecord(hook.start, s);
@@ -557,7 +559,7 @@ template <int D>
 hipError_t run_bwd(const cf_attn_bwd_params &b, hipStream_t s)
 {
     const int64_t dkv = key_blocks(b.f), dq = query_blocks(b.f);
-    if (dkv + dq > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    if (launch_blocks(b.f, true) > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const ProfileHook hook = take_profile_hook();
     if (hook.start) (void)hipEventRecord(hook.start, s);
     f32_bwd_kernel<D><<<dim3((unsigned)(dkv + dq)), NW * 64, 0, s>>>(b, (int)dkv);
@@ -568,9 +570,10 @@ hipError_t run_bwd(const cf_attn_bwd_params &b, hipStream_t s)
 
 }  // namespace
 
+int64_t f32_launch_size(const cf_attn_fwd_params &p, bool backward) { return launch_blocks(p, backward) * NW * 64; }
+
 hipError_t launch_f32_fwd(const cf_attn_fwd_params &p, hipStream_t s) { return p.head_dim == 64 ? run_fwd<64>(p, s) : run_fwd<128>(p, s); }
 hipError_t launch_f32_bwd(const cf_attn_bwd_params &b, hipStream_t s) { return b.f.head_dim == 64 ? run_bwd<64>(b, s) : run_bwd<128>(b, s); }
-
 
 hipError_t launch_f32_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s)
 {

@@ -808,16 +808,18 @@ struct BwdShape {
     int64_t dq_blocks, dkv_blocks;
     bool ok;
 };
+// Upper bounds on tile counts: sum_g ceil(L_g / tile) <= total / tile + n_segments.
+int64_t kv_tiles_most(const cf_attn_fwd_params &p) { return (int64_t)p.n_kv_tokens / (p.head_dim == 64 ? DkvShape<64>::BKV : BKV) + p.n_segments; }
+int64_t q_tiles_most(const cf_attn_fwd_params &p) { return p.q_tiles ? (int64_t)p.n_q_tiles : (int64_t)p.n_tokens / BM + p.n_segments; }
+
 BwdShape bwd_shape(const cf_attn_fwd_params &p, const BwdWorkspace &ws)
 {
     BwdShape g;
-    // Upper bounds on tile counts: sum_g ceil(L_g / tile) <= total / tile + n_segments.
-    const int64_t kv_tiles = (int64_t)p.n_kv_tokens / (p.head_dim == 64 ? DkvShape<64>::BKV : BKV) + p.n_segments;
-    const int64_t q_tiles = p.q_tiles ? (int64_t)p.n_q_tiles : (int64_t)p.n_tokens / BM + p.n_segments;
+    const int64_t kv_tiles = kv_tiles_most(p);
     // Fusing the heads of a group into one workgroup needs enough key tiles to fill 256 CUs several times.  At D = 64 dK/dV rows
     // always have one writer (and no work list).
     g.fused = kv_tiles * p.n_kv_heads >= 4096 || (p.flags & CF_FLAG_DKV_SINGLE_WRITER) || p.head_dim == 64;
-    g.dq_blocks = q_tiles * p.n_q_heads;
+    g.dq_blocks = q_tiles_most(p) * p.n_q_heads;
     g.dkv_blocks = (g.fused ? kv_tiles : ws.worklist_items) * p.n_kv_heads;
     g.ok = g.dkv_blocks <= 0x7fffffffLL && g.dq_blocks < 0x7fffffffLL && ws.worklist_items <= 0x7fffffffLL;
     return g;
@@ -907,6 +909,12 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
 }
 
 }  // namespace
+
+int64_t mfma_bwd_blocks(const cf_attn_fwd_params &p)
+{
+    const int64_t items = p.head_dim == 64 ? 0 : dkv_items_most(p);
+    return std::max(q_tiles_most(p) * p.n_q_heads + 1, std::max(kv_tiles_most(p), items) * p.n_kv_heads);
+}
 
 int64_t dkv_worklist_least(const cf_attn_fwd_params &p) { return key_tiles_most(p) * (p.n_q_heads / p.n_kv_heads); }
 int64_t dkv_worklist_capacity(const cf_attn_fwd_params &p) { return dkv_items_most(p); }

@@ -273,6 +273,8 @@ int64_t fwd_blocks(const cf_attn_fwd_params &p)
 
 }  // namespace
 
+int64_t mfma_launch_size(const cf_attn_fwd_params &p, bool backward) { return (backward ? mfma_bwd_blocks(p) : fwd_blocks(p)) * 256; }
+
 hipError_t launch_mfma_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s)
 {
     if (n < 1 || n > CF_FWD_BATCH_MAX) return hipErrorInvalidValue;

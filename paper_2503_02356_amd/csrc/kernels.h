@@ -27,6 +27,12 @@ struct ProfileHook {
 };
 ProfileHook take_profile_hook();
 
+// Work-items of the largest launch that a call makes on these kernels; one launch holds fewer than 2^32 (a HIP limit).
+int64_t f32_launch_size(const cf_attn_fwd_params &p, bool backward);
+int64_t mfma_launch_size(const cf_attn_fwd_params &p, bool backward);
+int64_t mfma_bwd_blocks(const cf_attn_fwd_params &p);
+constexpr int64_t kMostWorkItems = 0xffffffffLL;
+
 // fp32 matrix kernels, head_dim 64 and 128; the backward is one launch and needs no scratch.
 hipError_t launch_f32_fwd(const cf_attn_fwd_params &p, hipStream_t s);
 hipError_t launch_f32_bwd(const cf_attn_bwd_params &p, hipStream_t s);

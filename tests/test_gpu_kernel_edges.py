@@ -223,6 +223,34 @@ def test_d64_backward_without_room_for_a_work_list():
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("dtype,T,Hq,n_calls", [("fp32", 70000, 64, 1), ("bf16", 270000, 64, 1), ("fp32", 30000, 64, 3), ("bf16", 100000, 64, 3)])
+def test_more_segments_than_one_launch_holds(dtype, T, Hq, n_calls):
+    """One-token sequences, D = 64: more workgroups than one launch holds (2^32 work-items), in one call or in calls that would
+    share a launch.  O = V, LSE = the scaled score, dQ = dK = 0, dV = dO of the head group, all but exactly."""
+    dt, D, dev = torch.bfloat16 if dtype == "bf16" else torch.float32, 64, "cuda:0"
+    gen = torch.Generator(device=dev).manual_seed(9)
+    rand = lambda h: torch.randn(T, h, D, device=dev, generator=gen).to(dt)
+    cu = torch.arange(T + 1, dtype=torch.int32, device=dev)
+    q, k, v, d_o = rand(Hq), rand(1), rand(1), rand(Hq)
+    calls, bwd, out = [], [], []
+    for _ in range(n_calls):
+        o, dq, lse, dkv = torch.zeros_like(q), torch.ones_like(q), torch.zeros(Hq, T, device=dev), torch.zeros(2, T, 1, D, device=dev)
+        f = B.make_fwd_params(q, k, v, o, lse, cu, cu, D ** -0.5)
+        ws = torch.empty(B.cf_attn_bwd_workspace_bytes(f), dtype=torch.uint8, device=dev)
+        calls.append((False, f))
+        bwd.append((True, B.make_bwd_params(f, d_o, dq, dkv[0], dkv[1], ws)))
+        out.append((o, lse, dq, dkv))
+    B.cf_attn_calls(B.make_calls(calls + bwd))
+    torch.cuda.synchronize()
+    score = torch.stack([(q[:, h].float() * k[:, 0].float()).sum(-1) * D ** -0.5 for h in range(Hq)])
+    dv = sum(d_o[:, h].float() for h in range(Hq))
+    for o, lse, dq, dkv in out:
+        assert (o - v).abs().max() <= 2.0 ** -22 * v.abs().max()
+        assert (lse - score).abs().max() <= 64 * 2.0 ** -24 * 8          # a sum of 64 products of a few units each
+        assert dq.abs().max() <= 1e-4 and dkv[0].abs().max() <= 1e-3      # P - 1, rounded, times |dP| ~ 8 (64 heads)
+        assert (dkv[1][:, 0] - dv).abs().max() <= 1e-4                    # 64 terms, rounded
+
+
 @pytest.mark.parametrize("wide", ["q", "kv", "do"])
 def test_strides_beyond_32_bit_offsets(wide):
     """64 rows of 2^25 bf16 elements span 4 GiB, more than the matrix kernels' row offsets: the results of the scalar
