@@ -179,7 +179,7 @@ __device__ __forceinline__ void f32_fwd_body(const cf_attn_fwd_params &p, int id
     const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
     const int G = p.n_q_heads / p.n_kv_heads, kh = id % p.n_kv_heads, h = kh * G + id / p.n_kv_heads % G;
     TileLocation loc;
-    if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, RB, id / p.n_q_heads, loc)) return;
+    if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, p.n_tokens, RB, id / p.n_q_heads, loc)) return;
     const int lq = uniform(loc.len), lk = uniform(loc.other_len), off = lk - lq, q0 = uniform(loc.tile_in_seg) * RB;
     const int rows = min(RB, lq - q0), n_kb = (q0 + rows + off + RB - 1) / RB;
     const float *q = (const float *)p.q + (int64_t)loc.begin * p.q_stride_tok + (int64_t)h * p.q_stride_head;
@@ -309,7 +309,7 @@ __device__ __forceinline__ void f32_dq_body(const cf_attn_bwd_params &b, int id,
     const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
     const int G = p.n_q_heads / p.n_kv_heads, kh = id % p.n_kv_heads, h = kh * G + id / p.n_kv_heads % G;
     TileLocation loc;
-    if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, RB, id / p.n_q_heads, loc)) return;
+    if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, p.n_tokens, RB, id / p.n_q_heads, loc)) return;
     const int lq = uniform(loc.len), lk = uniform(loc.other_len), off = lk - lq, q0 = uniform(loc.tile_in_seg) * RB;
     const int rows = min(RB, lq - q0), n_kb = (q0 + rows + off + RB - 1) / RB;
     const float *k = (const float *)p.k + (int64_t)loc.other_begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head;
@@ -414,7 +414,7 @@ __device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id
     const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
     const int G = p.n_q_heads / p.n_kv_heads, kh = id % p.n_kv_heads;
     TileLocation loc;
-    if (!locate_tile(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, RB, id / p.n_kv_heads, loc)) return;
+    if (!locate_tile(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, p.n_kv_tokens, RB, id / p.n_kv_heads, loc)) return;
     const int lk = uniform(loc.len), lq = uniform(loc.other_len), off = lk - lq;
     // (tiles are numbered from a segment's end; its FIRST key tiles are seen by the most rows: start with those)
     const int k0 = ((lk + RB - 1) / RB - 1 - uniform(loc.tile_in_seg)) * RB, rows = min(RB, lk - k0);

@@ -209,7 +209,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     int seg, kt0, first_pair = 0, n_pairs = 0;
     if (FUSED_HEADS) {
         TileLocation loc;
-        if (!locate_tile(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, BKV, id, loc)) return;
+        if (!locate_tile(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, p.n_kv_tokens, BKV, id, loc)) return;
         seg = loc.seg;
         // locate_tile numbers tiles from the end; the FIRST key tiles of a segment are seen by the most rows, so
         // flip the order inside the segment to start the heaviest tiles first.
@@ -574,7 +574,7 @@ __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__re
         tile_in_seg = t.tile_in_seg, q_seg0 = t.q_begin, lq = t.q_len, k_seg0 = t.k_begin, lk = t.k_len;
     } else {
         TileLocation loc;
-        if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, BM, rank, loc)) return;
+        if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, p.n_tokens, BM, rank, loc)) return;
         // (the same in every lane, but values that leave the search loop do not look that way to the compiler)
         tile_in_seg = uniform(loc.tile_in_seg);
         q_seg0 = uniform(loc.begin), lq = uniform(loc.len), k_seg0 = uniform(loc.other_begin), lk = uniform(loc.other_len);

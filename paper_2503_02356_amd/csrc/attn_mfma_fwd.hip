@@ -65,7 +65,7 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
         tile_in_seg = t.tile_in_seg, q_seg0 = t.q_begin, lq = t.q_len, k_seg0 = t.k_begin, lk = t.k_len;
     } else {
         TileLocation loc;
-        if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, BM, rank, loc)) return;
+        if (!locate_tile(p.cu_seqlens_q, p.cu_seqlens_k, p.n_segments, p.n_tokens, BM, rank, loc)) return;
         // (the same in every lane, but values that leave the search loop do not look that way to the compiler)
         tile_in_seg = uniform(loc.tile_in_seg);
         q_seg0 = uniform(loc.begin), lq = uniform(loc.len), k_seg0 = uniform(loc.other_begin), lk = uniform(loc.other_len);

@@ -330,11 +330,12 @@ __device__ __forceinline__ float sum_with_other_half(float x)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Finds the tile a workgroup owns.  Tiles of `tile` rows are counted per segment over cu[0..n_seg]
-// and numbered from the LAST tile of the LAST segment backwards (the later tiles of a segment see more
-// keys, so the heaviest tiles get the lowest ranks and start first).  Every lane of every wavefront
-// computes the same answer.  Returns false if rank >= number of tiles.
-// The lanes that scan the segment list load its bounds in BOTH lists (cu: the list the tiles are counted
+// Finds the tile a workgroup owns.  Tiles of `tile` rows are counted per segment over cu[0..n_seg], from the LAST tile of the
+// LAST segment backwards (the later tiles of a segment see more keys, so the heaviest tiles get the lowest ranks and start
+// first).  Segment g has ranks for the tiles from cu[g] / tile + g on: at least as many as it needs, so that its place follows
+// from cu[g] alone and is searched for instead of summed up.  Every lane of every wavefront computes the same answer.
+// Returns false for a rank that is no tile; ranks go up to cu[n_seg] / tile + n_seg (n_rows: cu[n_seg]).
+// The lanes that look at the last 64 candidates load their bounds in BOTH lists (cu: the list the tiles are counted
 // over, cu_other: the other one), and the winner's values are handed out by lane reads: the caller gets
 // the segment's four bounds without a second, dependent round of loads.
 struct TileLocation {
@@ -342,7 +343,7 @@ struct TileLocation {
     int begin, len;               // of the segment in cu
     int other_begin, other_len;   // of the segment in cu_other
 };
-__device__ __forceinline__ bool locate_tile(const int32_t *cu, const int32_t *cu_other, int n_seg, int tile, int rank,
+__device__ __forceinline__ bool locate_tile(const int32_t *cu, const int32_t *cu_other, int n_seg, int n_rows, int tile, int rank,
                                             TileLocation &out)
 {
     if (n_seg == 1) {                                // one slice of one sequence: nothing to search
@@ -354,38 +355,25 @@ __device__ __forceinline__ bool locate_tile(const int32_t *cu, const int32_t *cu
         return rank < n;
     }
     const int lane = threadIdx.x & 63;
-    for (int base = 0; base < n_seg; base += 64) {
-        const int gi = n_seg - 1 - (base + lane);
-        int cnt = 0, b0 = 0, b1 = 0, o0 = 0, o1 = 0;
-        if (gi >= 0) {
-            b0 = cu[gi];
-            b1 = cu[gi + 1];
-            o0 = cu_other[gi];
-            o1 = cu_other[gi + 1];
-            cnt = (b1 - b0 + tile - 1) / tile;
-        }
-        int inc = cnt;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_up(inc, o);
-            if (lane >= o) inc += t;
-        }
-        const int total = __shfl(inc, 63);
-        if (rank < total) {
-            const unsigned long long ball = __ballot(inc > rank);
-            const int first = __ffsll((long long)ball) - 1;
-            const int exc = __shfl(inc - cnt, first);
-            const int c = __shfl(cnt, first);
-            out.seg = __builtin_amdgcn_readfirstlane(n_seg - 1 - (base + first));
-            out.tile_in_seg = __builtin_amdgcn_readfirstlane(c - 1 - (rank - exc));
-            out.begin = __builtin_amdgcn_readfirstlane(__shfl(b0, first));
-            out.len = __builtin_amdgcn_readfirstlane(__shfl(b1 - b0, first));
-            out.other_begin = __builtin_amdgcn_readfirstlane(__shfl(o0, first));
-            out.other_len = __builtin_amdgcn_readfirstlane(__shfl(o1 - o0, first));
-            return true;
-        }
-        rank -= total;
+    const int place = n_rows / tile + n_seg - 1 - rank;
+    if (place < 0) return false;
+    int lo = 0, hi = n_seg;                          // the segment is one of [lo, hi): 64 probes at a time
+    while (hi - lo > 64) {
+        const int step = (hi - lo + 63) / 64, g = lo + lane * step;
+        const unsigned long long before = __ballot(g < hi && cu[min(g, hi - 1)] / tile + g <= place);
+        lo += (63 - __clzll((long long)before)) * step;      // (lane 0 always says yes)
+        hi = min(hi, lo + step);
     }
-    return false;
+    const int g = min(lo + lane, hi - 1);
+    const int b0 = cu[g], b1 = cu[g + 1], o0 = cu_other[g], o1 = cu_other[g + 1];
+    const int last = 63 - __clzll((long long)__ballot(lo + lane < hi && b0 / tile + g <= place));
+    out.seg = __builtin_amdgcn_readfirstlane(lo + last);
+    out.begin = __builtin_amdgcn_readfirstlane(__shfl(b0, last));
+    out.len = __builtin_amdgcn_readfirstlane(__shfl(b1 - b0, last));
+    out.other_begin = __builtin_amdgcn_readfirstlane(__shfl(o0, last));
+    out.other_len = __builtin_amdgcn_readfirstlane(__shfl(o1 - o0, last));
+    out.tile_in_seg = __builtin_amdgcn_readfirstlane(place - out.begin / tile - out.seg);
+    return out.tile_in_seg * tile < out.len;
 }
 
 }  // namespace cf

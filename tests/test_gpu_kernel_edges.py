@@ -240,8 +240,12 @@ def test_more_segments_than_one_launch_holds(dtype, T, Hq, n_calls):
         calls.append((False, f))
         bwd.append((True, B.make_bwd_params(f, d_o, dq, dkv[0], dkv[1], ws)))
         out.append((o, lse, dq, dkv))
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    start.record()
     B.cf_attn_calls(B.make_calls(calls + bwd))
+    end.record()
     torch.cuda.synchronize()
+    assert start.elapsed_time(end) < 2500                  # ms; 100 to 400 measured (a search that grows with the segments: up to 15 s)
     score = torch.stack([(q[:, h].float() * k[:, 0].float()).sum(-1) * D ** -0.5 for h in range(Hq)])
     dv = sum(d_o[:, h].float() for h in range(Hq))
     for o, lse, dq, dkv in out:
