@@ -57,29 +57,34 @@ constexpr int BQ = DkvShape<128>::BQ, BKV = DkvShape<128>::BKV;
 // ---- work list of the dK/dV kernel (not used in the fused mode) -------------------------------------------
 // One item = (segment, key tile, range of its (head of the group, query tile) pairs, head by head): the workgroups of one
 // key/value head.  A key tile seen by few query tiles keeps all its pairs in ONE item (one prologue, one epilogue, one set of
-// atomic updates); one with more pairs than the target is cut into equal items.  Where the cuts lie:
-//   A launch ends with its longest item.  A workgroup that has a compute unit to itself takes 2.2 us per pair, one of two 3.6:
-//   an item of 1.6 times what a workgroup slot gets on average (`fair`; 512 slots, `slots` of them when several chunks share
-//   a launch) still ends with the rest, and every item more costs a prologue and an epilogue (some 14 us of its slot).
-//   fair <= kFineMost (few rounds of items): items of `fair` pairs.  Beyond it (long sequences, whose items end evenly
-//   anyway, and whose extra atomic updates cost more than they balance): whole heads, items of half the average but at most
-//   kSplitTarget pairs, except where a whole head is more than `fair`.
-// dK/dV of one packed call, 28 / 4 heads, 8192 tokens around 600: 143 us; items of half the average (twice as many) 196, of
-// 1.0 / 2.0 times the average 177 / 147; 4 / 4 heads, 4000 tokens in one sequence: 70 us, whole heads 147.
+// atomic updates); one with more is cut into equal items.  Where the cuts lie:
+//   A launch ends with its longest item.  A workgroup that has a compute unit to itself takes 2.2 us per pair, one of two 3.6,
+//   so an item of 1.6 times what a workgroup slot gets on average (512 slots, `slots` of them when several chunks share a
+//   launch) still ends with the rest, and every item more costs a prologue and an epilogue (some 14 us of its slot).
+//   - 1.6 averages <= kFineMost pairs (few rounds of items): items of that many pairs.
+//   - Beyond (long sequences, whose items end evenly anyway, and whose extra atomic updates cost more than they balance):
+//     whole heads, items of half the average but at most kSplitTarget pairs, except where a head has more than 1.6 averages.
+//   - A lone call with an average of at most kSmallMost pairs: 2.2 averages, so that its items are about one for each of
+//     the 256 compute units.
+//   - Where single heads of key tiles are about one for each compute unit (over 128, up to 256 in such a call), or one to
+//     one and a half rounds of all slots, they are the items, as long as they are not much longer than that: their different
+//     lengths fill the launch better than equal ones.  Heads of up to three query tiles are never cut.
+// dK/dV of one call, us, against items of half the average of whole heads: 28 / 4 heads, 8192 tokens packed around 600: 145
+// (196; 1.0 / 2.0 averages: 177 / 147); 4 / 4 heads, 4000 tokens in one sequence: 70 (147); 32 / 8 heads, 2048 tokens packed
+// around 200: 43 (71; 1.6 averages: 51); 64 / 8 heads, 500 tokens in one sequence: 37 (37; 1.6 / 2.2 averages: 50 / 41).
 // The list is ordered by DESCENDING duration (pairs; a counting sort): workgroups start in list order, and starting the
 // longest first is what keeps the last compute units from running one long item alone.
 // Workspace layout (ints): [0] = number of items, [64 ...] = the items; an item is int4 {segment, kt0, first pair, pairs}.
-constexpr int kSlots = 512, kSplitTarget = 48, kFineMost = 64, kFineLeast = 3;
-constexpr int kFairNum = 8, kFairDen = 5;             // 1.6
+constexpr int kSlots = 512, kSplitTarget = 48, kFineMost = 64, kSmallMost = 8;
 constexpr int kDurationBuckets = 256;
 
 // sum over segments of ceil(Lk / 128) <= n_kv_tokens / 128 + n_segments
 __host__ __device__ inline int64_t key_tiles_most(const cf_attn_fwd_params &p) { return (int64_t)p.n_kv_tokens / BKV + p.n_segments; }
-// Items of `fair` pairs: one per key tile and, beyond that, as many as one key/value head's pairs hold `fair`, which is at least
-// 1.6 / kSlots of the pairs of all.  Whole heads: G per key tile.
+// Items cut inside heads: one per key tile and, beyond that, as many as one key/value head's pairs hold 1.6 / kSlots of all pairs
+// (2.2: fewer).  Whole heads: G per key tile.
 __host__ __device__ inline int64_t dkv_items_most(const cf_attn_fwd_params &p)
 {
-    const int64_t tiles = key_tiles_most(p), G = p.n_q_heads / p.n_kv_heads, cuts = kSlots * kFairDen / kFairNum / p.n_kv_heads + 1;
+    const int64_t tiles = key_tiles_most(p), G = p.n_q_heads / p.n_kv_heads, cuts = kSlots * 10 / 16 / p.n_kv_heads + 1;
     return tiles * G > tiles + cuts ? tiles * G : tiles + cuts;
 }
 
@@ -91,10 +96,10 @@ __device__ __forceinline__ void build_dkv_worklist(const cf_attn_fwd_params &p, 
 {
     __shared__ int bucket[kDurationBuckets];        // items per duration, then the next free slot of each duration
     __shared__ int seg_lq[256], seg_lk[256];
-    __shared__ int n_items, total;
+    __shared__ int n_items, total, n_tiles;
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
     bucket[tid] = 0;
-    if (tid == 0) total = 0;
+    if (tid == 0) total = n_tiles = 0;
     const int G = p.n_q_heads / p.n_kv_heads;
     auto for_each_tile = [&](auto &&visit) {
         for (int base = 0; base < p.n_segments; base += 256) {
@@ -114,27 +119,29 @@ __device__ __forceinline__ void build_dkv_worklist(const cf_attn_fwd_params &p, 
             }
         }
     };
-    int mine = 0;
-    for_each_tile([&](int, int, int n_qt) { mine += n_qt; });
+    int mine = 0, my_tiles = 0;
+    for_each_tile([&](int, int, int n_qt) { mine += n_qt, ++my_tiles; });
     atomicAdd(&total, mine);
+    atomicAdd(&n_tiles, my_tiles);
     __syncthreads();
     const int64_t all_pairs = (int64_t)total * p.n_q_heads;
-    const int64_t share = (all_pairs * kFairNum + (int64_t)kFairDen * slots - 1) / ((int64_t)kFairDen * slots);
-    const int fair = (int)max((int64_t)kFineLeast, min(share, (int64_t)1 << 30));
-    const int target = fair <= kFineMost ? fair : (int)min((int64_t)kSplitTarget, all_pairs / (2 * slots));
+    // (in floating point: a rounding moves a cut, and no more; 64-bit divisions would take longer than the rest of the list)
+    const float average = (float)all_pairs / (float)slots;      // pairs per slot
+    auto share = [&](float averages) { return (int)fminf(ceilf(average * averages), 1e9f); };
+    const bool large = share(1.6f) > kFineMost, small = slots == kSlots && average <= kSmallMost;
+    const int fair = small ? max(3, share(2.2f)) : share(1.6f);
+    const int64_t head_items = (int64_t)n_tiles * p.n_q_heads;
+    const bool even_heads = small ? head_items > kSlots / 4 && head_items <= kSlots / 2
+                                  : !large && head_items > kSlots && head_items <= kSlots * 3 / 2;
+    const int target = max(2, large || even_heads ? (int)fminf(kSplitTarget, average / 2) : share(1.6f));
     bool cut_heads = true;                           // items may end inside a head's query tiles
     auto for_each_item = [&](auto &&visit) {
         for_each_tile([&](int seg, int kt0, int n_qt) {
-            const int pairs = G * n_qt;
-            if (pairs <= target) {
-                visit(i32x4{seg, kt0, 0, pairs}, min(pairs, kDurationBuckets - 1));
-                return;
-            }
-            const int want = (pairs + target - 1) / target, fairly = (pairs + fair - 1) / fair;
-            const bool heads = !cut_heads || (fair > kFineMost && fairly <= min(G, want));
+            const int pairs = G * n_qt, by_heads = min(G, (pairs + target - 1) / target), fairly = (pairs + fair - 1) / fair;
+            const bool heads = !cut_heads || (large ? fairly <= by_heads : n_qt <= 3 || (even_heads && n_qt <= (small ? fair * 8 / 5 : fair)));
             // equal shares of the heads or of the pairs, the first few with one more
-            const int sp = heads ? min(G, want) : fairly, whole = heads ? G : pairs, unit = heads ? n_qt : 1;
-            const int base = whole / sp, longer = whole - base * sp;
+            const int sp = heads ? by_heads : fairly, whole = heads ? G : pairs, unit = heads ? n_qt : 1;
+            const int base = sp == 1 ? whole : whole / sp, longer = whole - base * sp;
             for (int s = 0; s < sp; ++s) {
                 const int n = (base + (s < longer)) * unit;
                 visit(i32x4{seg, kt0, (s * base + min(s, longer)) * unit, n}, min(n, kDurationBuckets - 1));

@@ -167,12 +167,14 @@ def test_infinities_and_nans_reach_only_the_rows_that_see_them(dtype, D, lens, p
 @pytest.mark.parametrize("lens,prefix,Hq,Hkv,least", [
     ([900, 300, 2100, 37, 128, 640, 1500, 555, 1000, 64, 968], 0, 28, 4, False),   # a packed chunk of 8192 tokens
     ([4000], 0, 4, 4, False),                              # one head per group: nothing to split but its query tiles
-    ([130], 3000, 8, 2, False), ([16384], 0, 8, 1, False), # a short slice behind a prefix; whole heads
+    ([130], 3000, 8, 2, False), ([16384], 0, 8, 1, False), # a short slice behind a prefix; a long sequence
+    ([1500, 200, 40], 100, 14, 2, False), ([1] * 700, 0, 8, 2, False), ([3000] * 3, 0, 28, 4, False),
     ([4000], 0, 4, 4, True), ([1] * 300, 0, 2, 1, True),   # a scratch with room for G items per key tile only
 ])
 def test_dkv_work_list(lens, prefix, Hq, Hkv, least):
     """The list a bf16 backward leaves in its scratch: every (head, query tile) pair of every key tile in exactly one item, longest
-    items first, no item longer than 1.6 times a slot's share (512 slots) nor more items than that asks for."""
+    items first, none longer than 1.6 times what one of 512 slots gets on average (small calls: 1.6 x 2.2) nor more items
+    than that asks for."""
     T, Tk, G, D = sum(lens), sum(lens) + prefix, Hq // Hkv, 128
     t = lambda n, h: torch.randn(n, h, D, device="cuda:0").bfloat16()
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
@@ -205,11 +207,13 @@ def test_dkv_work_list(lens, prefix, Hq, Hkv, least):
     assert seen == pairs
     length = [min(n, 255) for *_, n in items]
     assert length == sorted(length, reverse=True)
-    fair = max(3, -(-sum(pairs.values()) * Hkv * 8 // (5 * 512)))
-    if not least:
-        assert max(n for *_, n in items) <= fair
-        if fair <= 64:
-            assert len(items) <= len(pairs) + 320 // Hkv + 1
+    average = sum(pairs.values()) * Hkv / 512
+    most = max(3, np.ceil(average * 2.2)) * 1.6 if average <= 8 else np.ceil(average * 1.6)
+    if least:
+        assert len(items) <= G * len(pairs)
+    else:
+        assert length[0] <= most or average > 40          # (long sequences: whole heads of up to 255 and more)
+        assert len(items) <= max(G * len(pairs), len(pairs) + 320 // Hkv + 1)
 
 
 def test_d64_backward_without_room_for_a_work_list():
