@@ -23,8 +23,9 @@ WORKLOADS = {                       # name -> inputs.CONFIGS key
 # HBM bytes per launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this
 # command (profiles/bench_<workload>_kernels.txt): FETCH_SIZE x 2.0 KiB + WRITE_SIZE x 1.0 KiB, the factors being
 # what the same counters read for the 512 MiB copy kernel below.  A measured constant of the build the profile was
-# taken on, not something this run re-measures.  (None: the profile mixes shared and single launches.)
-MEASURED_TRAFFIC_BYTES = {"config2_packed_8k": 671e6, "config3_long32k_mixed": None, "config5_long256k_32k": None}
+# taken on, not something this run re-measures: of the launch of a call on its own, as `roofline`.  (None: not a mean
+# over a step's calls.)
+MEASURED_TRAFFIC_BYTES = {"config2_packed_8k": 613e6, "config3_long32k_mixed": None, "config5_long256k_32k": None}
 TRAFFIC_SOURCE = {"config2_packed_8k": "profiles/bench_config2_packed_8k_kernels.txt",
                   "config3_long32k_mixed": "profiles/bench_config3_long32k_mixed_kernels.txt", "config5_long256k_32k": None}
 
@@ -80,12 +81,21 @@ def measure(workload, args, torch, np, B, inputs, ChunkAttention, extras=True):
     pairs = eng.total_pairs
     flop_step = 14.0 * D * Hq * pairs
 
-    # The timed step makes one cf_attn_fwd / cf_attn_bwd call per chunk, as a training loop does (other layers
-    # run between a chunk's attention calls).  The whole-plan launch (cf_attn_*_batch) is timed separately below.
+    # The timed step is the runner's: one forward and one backward call per chunk, handed over as one list per pass
+    # (cf_attn_calls), in which consecutive independent calls share launches: a step of one layer's attention over the
+    # whole batch.  The same calls made one at a time (per_call_step: what a loop reaches that runs other layers between
+    # a chunk's attention calls) and the whole-plan entry points (cf_attn_*_batch) are timed separately below.
     def step(fused=False):
         eng.zero_grads()
         eng.run_forward(fused=fused)
         eng.run_backward(fused=fused)
+
+    def per_call_step():
+        eng.zero_grads()
+        for c in eng.forward_order():
+            B.cf_attn_fwd(eng.chunks[c]["fwd"])
+        for c in eng.backward_order():
+            B.cf_attn_bwd(eng.chunks[c]["bwd"])
 
     for _ in range(args.warmup):
         step()
@@ -119,10 +129,12 @@ def measure(workload, args, torch, np, B, inputs, ChunkAttention, extras=True):
             graph.replay()
             graph_ms = wall_ms(graph.replay, part_reps)
             del graph
+    per_call_step()
+    per_call_ms = wall_ms(per_call_step, part_reps)
     fwd_pass_ms = wall_ms(eng.run_forward, part_reps)
     bwd_pass_ms = wall_ms(bwd_pass, part_reps)
 
-    # ---- per-kernel durations with HIP events on the launch stream (same launches, second pass)
+    # ---- per-kernel durations with HIP events on the launch stream: the launches of the per-call step, not of the timed one
     def kernel_ms(kind):
         evs = []
         order = eng.forward_order() if kind == "fwd" else eng.backward_order()
@@ -139,7 +151,7 @@ def measure(workload, args, torch, np, B, inputs, ChunkAttention, extras=True):
     fwd_ms = np.mean([kernel_ms("fwd") for _ in range(reps)], axis=0)
     bwd_ms = np.mean([kernel_ms("bwd") for _ in range(reps)], axis=0)
     n_chunks = len(eng.chunks)
-    # The dominant kernel is the dK/dV kernel: S = QK^T, dP = dO V^T, dV += P^T dO, dK += dS^T Q, i.e. four of
+    # The dominant kernel is the dK/dV kernel, here as a call of its own launches it, once per chunk: S = QK^T, dP = dO V^T, dV += P^T dO, dK += dS^T Q, i.e. four of
     # the backward's five contractions = 8*D FLOP per unmasked pair and query head.
     bwd_flop_per_launch = 8.0 * D * Hq * pairs / n_chunks          # algorithmic FLOP of an average launch
     bwd_avg_ms = float(np.mean(bwd_ms))
@@ -154,6 +166,7 @@ def measure(workload, args, torch, np, B, inputs, ChunkAttention, extras=True):
                 "traffic": MEASURED_TRAFFIC_BYTES[workload], "traffic_source": TRAFFIC_SOURCE[workload],
                 "algorithmic_bytes": algo_bytes,
                 "avg_launch_ms": bwd_avg_ms, "launches_per_step": n_chunks,
+                "step": "per_call_step (one launch per backward call; the timed step shares launches between calls)",
                 "fwd_kernel": {"kernel": "mfma_fwd_kernel", "avg_launch_ms": fwd_avg_ms,
                                "achieved": 4.0 * D * Hq * pairs / n_chunks / (fwd_avg_ms * 1e-3) / 1e12}}
     out = {"value": tflops, "unit": "TFLOP/s", "ms_per_step": ms_per_step, "steps": args.steps, "warmup": args.warmup,
@@ -165,13 +178,15 @@ def measure(workload, args, torch, np, B, inputs, ChunkAttention, extras=True):
            "fwd_only": {"ms": fwd_pass_ms, "tflops": 4.0 * D * Hq * pairs / (fwd_pass_ms * 1e-3) / 1e12},
            "bwd_only": {"ms": bwd_pass_ms, "tflops": 10.0 * D * Hq * pairs / (bwd_pass_ms * 1e-3) / 1e12,
                         "includes": "zeroing of the dK/dV buffers"},
+           "per_call_step": {"ms_per_step": per_call_ms, "tflops": flop_step / (per_call_ms * 1e-3) / 1e12,
+                             "what": "the same step, every cf_attn_fwd / cf_attn_bwd call on its own"},
            "roofline": roofline}
     if fused_ms is not None:
         out["whole_plan_launch"] = {"ms_per_step": fused_ms, "tflops": flop_step / (fused_ms * 1e-3) / 1e12,
                                     "what": "same step through cf_attn_fwd_batch / cf_attn_bwd_batch"}
     if graph_ms is not None:
         out["graph_replay"] = {"ms_per_step": graph_ms, "tflops": flop_step / (graph_ms * 1e-3) / 1e12,
-                               "what": "the per-chunk step captured in a HIP graph, one replay per step"}
+                               "what": "the timed step captured in a HIP graph, one replay per step"}
     return out, lens, cfg
 
 
