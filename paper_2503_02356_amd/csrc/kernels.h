@@ -7,7 +7,8 @@
 namespace cf {
 
 // Backward scratch inside the caller's workspace:
-//   delta     [Hq][T] fp32 = rowsum(dO * O)
+//   delta     [Hq][T] fp32: rowsum(dO * O) between the scalar kernels, MINUS that between the bf16 matrix kernels (whose dK/dV
+//             kernel starts an accumulator with it)
 //   worklist  bf16 MFMA path only: the dK/dV kernel's work items, written by the first workgroups of the dQ launch
 //             (layout in attn_mfma_bwd.hip); worklist_items = capacity of its item array
 struct BwdWorkspace {

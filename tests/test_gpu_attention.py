@@ -155,7 +155,7 @@ def test_recompute_schedule_gives_same_result():
 @pytest.mark.parametrize("dtype,D,lens,C,Hq,Hkv", [
     ("bf16", 128, [1500, 40, 300, 77, 512, 129, 640, 9, 333, 200, 256, 31, 480, 64, 100, 700, 90, 411], 512, 8, 2),
     ("bf16", 128, [900, 40, 300], 256, 4, 2),
-    ("fp32", 64, [700, 33, 1, 120, 64], 200, 2, 2),          # no MFMA path: the batch call falls back to single launches
+    ("fp32", 64, [700, 33, 1, 120, 64], 200, 2, 2),          # one launch per kernel and independent run of calls
 ])
 def test_whole_plan_launch_matches_per_chunk_calls(dtype, D, lens, C, Hq, Hkv):
     """cf_attn_fwd_batch / cf_attn_bwd_batch (forward and dQ kernels of many chunks as one launch, more chunks

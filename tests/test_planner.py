@@ -319,3 +319,9 @@ def test_pipeline_simulator_errors():
     with pytest.raises(B.CfError):
         B.cf_sim_1f1b_sequences([3, 0], 2)
     assert B.cf_sim_1f1b_sequences([], 3)["makespan"] == 0
+
+
+def test_launch_sharing_limit_is_the_library_s():
+    """The runner lays out one backward workspace per call that shares a launch."""
+    header = open(os.path.join(ROOT, "paper_2503_02356_amd", "csrc", "kernels.h")).read()
+    assert int(re.search(r"CF_BWD_BATCH_MAX = (\d+);", header)[1]) == B.BWD_TOGETHER
