@@ -876,12 +876,13 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
     BwdShape g[CF_BWD_BATCH_MAX];
     int order[CF_BWD_BATCH_MAX];
     int64_t tokens[CF_BWD_BATCH_MAX] = {};           // of the dK/dV launch that a chunk goes into (index: its first chunk)
-    int first_of[CF_BWD_BATCH_MAX];
+    int first_of[CF_BWD_BATCH_MAX], together[CF_BWD_BATCH_MAX] = {};
     for (int c = 0; c < n; ++c) {
         g[c] = bwd_shape(chunks[c].b->f, chunks[c].ws);
         if (!g[c].ok) return hipErrorInvalidConfiguration;
         first_of[c] = c > 0 && chunks[c].dkv_with_previous && (D == 64 || (!g[c].fused && !g[c - 1].fused)) ? first_of[c - 1] : c;
         tokens[first_of[c]] += chunks[c].b->f.n_tokens;
+        ++together[first_of[c]];
         order[c] = c;
     }
     // heaviest first: work ~ queries x keys
@@ -893,7 +894,11 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
     q.n = q.first_block[0] = 0;
     for (int i = 0; i < n; ++i) {
         const int c = order[i];
-        q.slots[i] = (int)max((int64_t)1, kSlots * (int64_t)chunks[c].b->f.n_tokens / tokens[first_of[c]]);
+        // Lists follow each other in a shared launch: the longest items of a late one start late and have to end with what is
+        // left, so that a chunk's share of the slots is taken of the chunks from it on.
+        const int64_t own = chunks[c].b->f.n_tokens;
+        q.slots[i] = (int)max((int64_t)1, min((int64_t)kSlots - (together[first_of[c]] > 1), kSlots * own / tokens[first_of[c]]));
+        tokens[first_of[c]] -= own;
         if (!append(q, *chunks[c].b, chunks[c].ws, g[c], g[c].dq_blocks)) return hipErrorInvalidConfiguration;
     }
     mfma_dq_batch_kernel<D><<<dim3((unsigned)(q.first_block[n] + n)), 256, 0, s>>>(q);
