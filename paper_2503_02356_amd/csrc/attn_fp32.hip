@@ -7,7 +7,7 @@
 // owns 16 query rows of a head (forward, dQ) or 16 key rows of a key/value head (dK/dV), its wavefronts take every 16th
 // block of the other side, and their partial results meet in LDS at the end in a fixed order: no atomics, every result
 // has one writer and is bitwise reproducible.  (32-row units on 32x32x2 MFMAs would leave half the chip idle on a
-// 700-row slice of 6 heads: 132 workgroups.)
+// 700-row slice of 6 heads that is launched on its own: 132 workgroups.)
 // Operands go straight from global memory into registers: a wavefront's blocks are its own, so LDS tiles would not be
 // shared.  What the 16 wavefronts share, the owned rows, is kept in LDS in operand order.
 //
@@ -25,8 +25,9 @@
 // Errors against fp64 are no larger than the scalar kernels' (step of 1 head, D = 64, 1286 tokens, relative: dQ 3.2e-7, dK 3.5e-7,
 // dV 2.6e-7, O 1.8e-7; scalar 3.3e-7, 3.8e-7, 3.2e-7, 2.0e-7).
 //
-// Measured, forward + backward of a whole step: 13 calls of 1286 tokens, 1 head, D = 64: 762 us -> 122 us; 6 / 2 heads,
-// D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 1.24 ms (before: one wavefront per row, scalar loads; attn_simple.hip).
+// Measured, forward + backward of a whole step, calls sharing launches: 6 chunks, 1286 tokens, 1 head, D = 64: 764 us -> 56 us;
+// 6 / 2 heads, D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 0.93 ms (before: one wavefront per row, scalar loads;
+// attn_simple.hip).
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
