@@ -60,17 +60,6 @@ struct Shape {
 template <int D>
 using Acc = f32x4[D / 16];                   // [4 * c + e], register i: column 64 c + 4 * (4 * quarter + i) + e
 
-// Combines over the four lanes that hold the same owned row (lane % 16).
-__device__ __forceinline__ float max_over_quarters(float x)
-{
-    const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return max_with_other_half(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
-}
-__device__ __forceinline__ float sum_over_quarters(float x)
-{
-    const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return sum_with_other_half(__uint_as_float(r[0]) + __uint_as_float(r[1]));
-}
 // Combines over the 16 lanes of a quarter (rotations inside a row of 16 lanes).
 template <int N>
 __device__ __forceinline__ float add_rotated(float x)

@@ -200,12 +200,12 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
                                          const int *__restrict__ wl, char *st0, char *st1)
 {
     using Stage = DkvStage<D>;
-    constexpr int KS = D / 16, DB = D / 32, BLOCK = 32 * 2 * D;
+    using F = Mfma<D>;
+    constexpr int KS = D / F::K, DB = D / 32, N = F::N32, BLOCK = 32 * 2 * D;
     constexpr int QW = DkvShape<D>::QW, BQ = DkvShape<D>::BQ, BKV = DkvShape<D>::BKV;
     static_assert(FUSED_HEADS || QW == 1, "atomic updates are made by the wavefront that owns the keys");
     const cf_attn_fwd_params &p = b.f;
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), key_wave = wave / QW, query_wave = wave % QW;
-    const int half = lane >> 5, col = lane & 31;
 
     // Block id -> (item, key/value head); the key/value head varies fastest (XCD L2 locality, see forward).
     //   fused mode : item = key tile rank, all G heads of the group
@@ -252,16 +252,17 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     const float c2 = scalar(p.softmax_scale * kLog2e);
 
     // B operands kept for the whole kernel: lane = key row, 8 consecutive d per step.
-    bf16x8 kf[KS], vf[KS];
-    {
-        const int64_t at = ((k_seg0 + min(kw0 + col, lk - 1)) * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2 + half * 16;
+    bf16x8 kf[N][KS], vf[N][KS];
+#pragma unroll
+    for (int kb = 0; kb < N; ++kb) {
+        const int64_t from = ((k_seg0 + min(kw0 + F::M * kb + F::column(), lk - 1)) * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2 + F::group() * 16;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            kf[ks] = *(const bf16x8 *)((const char *)p.k + at + ks * 32);
-            vf[ks] = *(const bf16x8 *)((const char *)p.v + at + ks * 32);
+            kf[kb][ks] = *(const bf16x8 *)((const char *)p.k + from + ks * 2 * F::K);
+            vf[kb][ks] = *(const bf16x8 *)((const char *)p.v + from + ks * 2 * F::K);
         }
     }
-    f32x16 dv[DB], dk[DB];
+    f32x16 dv[DB], dk[DB];                           // 32 x 32 blocks: lane % 32 = key, register group j = d 32 db + 8 j + 4 half + 0..3
 #pragma unroll
     for (int i = 0; i < DB; ++i)
 #pragma unroll
@@ -310,63 +311,106 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
         const int q0 = cur_qt * BQ + mb * 32;
         if (q0 + 31 + off < kw0 || (D == 64 && q0 >= lq)) return;     // no row of the block sees a key of this wavefront
         const char *qs = stage, *dos = stage + Stage::tile_bytes;
-        const float *stats = (const float *)(stage + 2 * Stage::tile_bytes) + mb * 32 + (fresh_lane() >> 5) * 4;
-        // The A operands of the block's four products pass through a ring of four fragments, each requested four MFMAs
-        // before its use: 0..KS-1 Q rows, KS..2KS-1 dO rows, then the transposed dO and Q operands (contraction over the
-        // 32 query rows in 2 groups of 16: k-slot 8*half + e of group tq is query row 16*tq + (e/4)*8 + 4*half + e%4).
+        const float *stats = (const float *)(stage + 2 * Stage::tile_bytes) + mb * 32 + fresh_lane() / F::M * 4;
+        // The A operands of the block's four products pass through a ring of four fragments, each requested four uses
+        // before its own: ROWS fragments of Q rows and of dO rows, then the transposed dO and Q operands (contraction over the
+        // 32 query rows in 2 groups of 16).
+        constexpr int ROWS = N * KS, COLS = 2 * DB;
         bf16x8 ring[4];
         auto fetch = [&](int n) {
-            if (n == KS || (n >= 2 * KS && n % DB == 0)) at.forget();
-            if (n < KS) ring[n & 3] = lds_read_b128(qs + at.row(n));
-            else if (n < 2 * KS) ring[n & 3] = lds_read_b128(dos + at.row(n - KS));
-            else if (n < 2 * KS + 4 * DB) {
-                const int m = n - 2 * KS, j = m % DB, tq = m / DB % 2, x = m / (2 * DB);
-                const char *rows = (x ? qs : dos) + tq * (BLOCK / 2);
-                ring[n & 3] = lds_read_tr_pair(rows + at.tr_lo(j), rows + at.tr_hi(j));
+            if (n == ROWS || (n >= 2 * ROWS && n % DB == 0)) at.forget();
+            if (n < 2 * ROWS) {
+                const int m = n % ROWS;
+                ring[n & 3] = lds_read_b128((n < ROWS ? qs : dos) + m % N * (BLOCK / N) + at.row(m / N));
+            } else if (n < 2 * ROWS + 2 * COLS) {
+                const int m = n - 2 * ROWS, db = m % DB, tq = m % COLS / DB;
+                const char *rows = (m / COLS ? qs : dos) + tq * (BLOCK / 2);
+                ring[n & 3] = lds_read_tr_pair(rows + at.tr_lo(db), rows + at.tr_hi(db));
             }
         };
 #pragma unroll
         for (int n = 0; n < 4; ++n) fetch(n);
-        f32x16 s, dp;
-        // register i is query row q0 + (i/4)*8 + 4*half + i%4, column = this lane's key
+        // [query block][key block]; element i of a key block: register i % R of query block i / R, query row q0 + place(i) + 4*group
+        typename F::Acc s[N][N], dp[N][N];
+        constexpr int NS = N * F::R;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+        for (int qb = 0; qb < N; ++qb)
 #pragma unroll
-        for (int n = 0; n < KS; ++n) {
+            for (int kb = 0; kb < N; ++kb) s[qb][kb] = F::zero();
+#pragma unroll
+        for (int n = 0; n < ROWS; ++n) {
             __builtin_amdgcn_sched_barrier(0);
-            s = mfma32(ring[n & 3], kf[n], s);
+#pragma unroll
+            for (int kb = 0; kb < N; ++kb) s[n % N][kb] = F::mul(ring[n & 3], kf[kb][n / N], s[n % N][kb]);
             fetch(n + 4);
         }
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-            const f32x4 d4 = *(const f32x4 *)(stats + BQ + g4 * 8);
+        for (int i = 0; i < NS; i += 4) {
+            const f32x4 d4 = *(const f32x4 *)(stats + BQ + F::place(i));
 #pragma unroll
-            for (int j = 0; j < 4; ++j) dp[g4 * 4 + j] = d4[j];
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int kb = 0; kb < N; ++kb) dp[i / F::R][kb][i % F::R + j] = d4[j];
         }
 #pragma unroll
-        for (int n = KS; n < 2 * KS; ++n) {
+        for (int n = ROWS; n < 2 * ROWS; ++n) {
             __builtin_amdgcn_sched_barrier(0);
-            dp = mfma32(ring[n & 3], vf[n - KS], dp);
+            const int m = n - ROWS;
+#pragma unroll
+            for (int kb = 0; kb < N; ++kb) dp[m % N][kb] = F::mul(ring[n & 3], vf[kb][m / N], dp[m % N][kb]);
             fetch(n + 4);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-            const f32x4 l4 = *(const f32x4 *)(stats + g4 * 8);
+        for (int i = 0; i < NS; i += 4) {
+            const f32x4 l4 = *(const f32x4 *)(stats + F::place(i));
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s[g4 * 4 + j] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[g4 * 4 + j], c2, -l4[j]));
+            for (int kb = 0; kb < N; ++kb)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    s[i / F::R][kb][i % F::R + j] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i / F::R][kb][i % F::R + j], c2, -l4[j]));
         }
         // The causal mask: selects only on a block that crosses the diagonal (its last key lies after its first query).
         if (kw0 + 31 - off - q0 > 0) {
             const int lane_ = fresh_lane();
-            const int lim = kw0 + (lane_ & 31) - off - q0 - (lane_ >> 5) * 4;     // masked iff lim > the constant part of the row
+            const int lim = kw0 + lane_ % F::M - off - q0 - lane_ / F::M * 4;     // masked iff lim > the constant part of the row
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[i] = lim > (i >> 2) * 8 + (i & 3) ? 0.f : s[i];
+            for (int kb = 0; kb < N; ++kb)
+#pragma unroll
+                for (int i = 0; i < NS; ++i) s[i / F::R][kb][i % F::R] = lim > F::place(i) - F::M * kb ? 0.f : s[i / F::R][kb][i % F::R];
         }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) dp[i] *= s[i];
-        auto pack = [](const f32x16 &f, int tq) {
-            return pack8(f[8 * tq + 0], f[8 * tq + 1], f[8 * tq + 2], f[8 * tq + 3], f[8 * tq + 4], f[8 * tq + 5], f[8 * tq + 6], f[8 * tq + 7]);
+        for (int qb = 0; qb < N; ++qb)
+#pragma unroll
+            for (int kb = 0; kb < N; ++kb)
+#pragma unroll
+                for (int i = 0; i < F::R; ++i) dp[qb][kb][i] *= s[qb][kb][i];
+        // B operand of dV_w^T += dO^T P (x = 0) resp. dK_w^T += Q^T dS for the contraction over query rows 16 tq + 0..15, lane % 32 =
+        // key: the bf16 values, or (rest) their rounding residuals.  D = 64: k-slot 8*half + e is row 16 tq + place(e) + 4*half, where
+        // the values stand.  D = 128: a quarter q of the lanes has rows 4 q + 0..3 of both key blocks and keeps those of block
+        // q % 2; the other quarter of its half gets the other ones for its own: k-slot 8*half + e is row 16 tq + 8*half + e.
+        auto value = [&](int x, int i, int kb) { return (x ? dp : s)[i / F::R][kb][i % F::R]; };
+        auto operand = [&](int x, int tq, auto rest) {
+            bf16x8 w;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float f = N == 1 ? value(x, 8 * tq + e, 0) : value(x, 4 * tq + e % 4, e / 4);
+                if (decltype(rest)::value) {
+                    asm volatile("" : "+v"(f));      // (the roundings here are not to be kept for the products below)
+                    f -= (float)(__bf16)f;
+                }
+                w[e] = (__bf16)f;
+            }
+            if (N == 2) {
+                i32x4 u = __builtin_bit_cast(i32x4, w);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const u32x2 r = __builtin_amdgcn_permlane16_swap((unsigned)u[i], (unsigned)u[2 + i], false, false);
+                    u[i] = (int)r[0], u[2 + i] = (int)r[1];
+                }
+                w = __builtin_bit_cast(bf16x8, u);
+            }
+            return w;
         };
         if (D != 64 && residual) {
 #pragma unroll
@@ -374,13 +418,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
 #pragma unroll
                 for (int tq = 0; tq < 2; ++tq) {
                     __builtin_amdgcn_sched_barrier(0);
-                    bf16x8 w;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        float f = x ? dp[8 * tq + e] : s[8 * tq + e];
-                        asm volatile("" : "+v"(f));  // (the roundings here are not to be kept for the products below)
-                        w[e] = (__bf16)(f - (float)(__bf16)f);
-                    }
+                    const bf16x8 w = operand(x, tq, std::true_type());
                     const char *rows = (x ? qs : dos) + tq * (BLOCK / 2);
                     at.forget();
 #pragma unroll
@@ -388,19 +426,24 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
                         accumulate_in_place<D>(x ? dk[j] : dv[j], lds_read_tr_pair(rows + at.tr_lo(j), rows + at.tr_hi(j)), w);
                 }
         }
-        // dV_w^T += dO^T P, then dK_w^T += Q^T dS.  D = 64 splits each fragment of P and dS (three operands) where it is used.
-        bf16x8 w[4], ws[3];
-        if (D != 64) w[0] = pack(s, 0), w[1] = pack(s, 1), w[2] = pack(dp, 0), w[3] = pack(dp, 1);
+        // Each operand is made right before its use (all four at once: 4 registers too many); D = 64 splits it in three.
+        bf16x8 w, ws[3];
 #pragma unroll
-        for (int m = 0; m < 4 * DB; ++m) {
+        for (int m = 0; m < 2 * COLS; ++m) {
             __builtin_amdgcn_sched_barrier(0);
-            const int j = m % DB, g = m / DB, x = g / 2, n = 2 * KS + m;
+            const int j = m % DB, g = m / DB, x = g / 2, n = 2 * ROWS + m;
+            if (D != 64 && j == 0) w = operand(x, g % 2, std::false_type());
             if (D == 64) {
-                if (j == 0) split_exact(x ? dp : s, 8 * (g % 2), ws);
+                if (j == 0) {
+                    float f[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) f[e] = value(x, (8 * (g % 2) + e) % NS, 0);
+                    split_exact(f, ws);
+                }
 #pragma unroll
                 for (int t = 0; t < 3; ++t) accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n & 3], ws[t]);
             } else {
-                accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n & 3], w[g]);
+                accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n & 3], w);
             }
             fetch(n + 4);
         }
@@ -563,10 +606,10 @@ struct KvStage {
 template <int D>
 __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__restrict__ delta, int id, char *stage_a, char *stage_b)
 {
-    constexpr int KS = D / 16, DB = D / 32, KVTILE_BYTES = KvStage<D>::tile_bytes;
+    using F = Mfma<D>;
+    constexpr int KS = D / F::K, DB = D / F::M, N = F::N32, KVTILE_BYTES = KvStage<D>::tile_bytes;
     const cf_attn_fwd_params &p = b.f;
-    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
-    const int half = lane >> 5, col = lane & 31;
+    const int wave = wave_id(), group = F::group(), col = F::column();
 
     const int G = p.n_q_heads / p.n_kv_heads;
     const int kh = id % p.n_kv_heads;
@@ -602,8 +645,7 @@ __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__re
     const int wq0 = q_tile0 + blk * 32;
     const int wave_kmax = min(kmax, wq0 + 32 + off);
     const bool wave_active = wq0 < lq;
-    const int iq = wq0 + col;                        // this lane's query row
-    const int amax = iq + off;                       // last visible key of this lane's row
+    const int amax = wq0 + col + off;                // last visible key of this lane's row (block qb: M qb further)
 
     const int64_t kv_row_bytes = p.kv_stride_tok * 2;
     const char *kbase = uniform((const char *)p.k + ((int64_t)k_seg0 * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2);
@@ -611,43 +653,45 @@ __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__re
     TileDma<BN, D> dma;
     dma.init(kv_row_bytes);
 
-    // Q^T and dO^T fragments (B operands): lane holds row iq, d = 16*ks + 8*half + 0..7
-    bf16x8 qf[KS], dof[KS];
-    float lse2, dlt;
-    const int64_t stat_at = (int64_t)h * p.n_tokens + q_seg0 + min(iq, lq - 1);
-    {
-        const int row = q_seg0 + min(iq, lq - 1);
+    // Q^T and dO^T fragments (B operands): lane holds row wq0 + M*qb + col, d = K*ks + 8*group + 0..7
+    bf16x8 qf[N][KS], dof[N][KS];
+    float lse2[N], dlt[N];
+    auto row_of_block = [&](int qb) { return wq0 + F::M * qb + col; };
+    auto stat_at = [&](int qb) { return (int64_t)h * p.n_tokens + q_seg0 + min(row_of_block(qb), lq - 1); };
+#pragma unroll
+    for (int qb = 0; qb < N; ++qb) {
+        const int iq = row_of_block(qb), row = q_seg0 + min(iq, lq - 1);
         const char *qrow = (const char *)p.q + ((int64_t)row * p.q_stride_tok + (int64_t)h * p.q_stride_head) * 2;
         const char *dorow = (const char *)b.d_o + ((int64_t)row * b.do_stride_tok + (int64_t)h * b.do_stride_head) * 2;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            qf[ks] = *(const bf16x8 *)(qrow + ks * 32 + half * 16);
-            dof[ks] = *(const bf16x8 *)(dorow + ks * 32 + half * 16);
+            qf[qb][ks] = *(const bf16x8 *)(qrow + ks * 2 * F::K + group * 16);
+            dof[qb][ks] = *(const bf16x8 *)(dorow + ks * 2 * F::K + group * 16);
         }
-        lse2 = iq < lq ? p.lse[stat_at] * kLog2e : INFINITY;   // padding rows: P = 0
-        // delta = <dO, O> of this lane's row (section 4.2's backward needs it for dS): each lane half sums its 64 d.
+        lse2[qb] = iq < lq ? p.lse[stat_at(qb)] * kLog2e : INFINITY;   // padding rows: P = 0
+        // delta = <dO, O> of this lane's row (section 4.2's backward needs it for dS): the lanes of a row sum D * M / 64 d each.
         // Published for the dK/dV kernel; head tiles replace it below.
-        dlt = 0.f;
+        dlt[qb] = 0.f;
         if (!head) {
             const char *orow = (const char *)p.o + ((int64_t)row * p.o_stride_tok + (int64_t)h * p.o_stride_head) * 2;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                const bf16x8 of = *(const bf16x8 *)(orow + ks * 32 + half * 16);
+                const bf16x8 of = *(const bf16x8 *)(orow + ks * 2 * F::K + group * 16);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) dlt = __builtin_fmaf((float)of[e], (float)dof[ks][e], dlt);
+                for (int e = 0; e < 8; ++e) dlt[qb] = __builtin_fmaf((float)of[e], (float)dof[qb][ks][e], dlt[qb]);
             }
-            dlt = sum_with_other_half(dlt);
-            if (iq < lq && half == 0) delta[stat_at] = -dlt;
+            dlt[qb] = sum_over_groups<D>(dlt[qb]);
+            if (iq < lq && group == 0) delta[stat_at(qb)] = -dlt[qb];
         }
     }
     const float c2 = p.softmax_scale * kLog2e;
     const LaneOffsets<D> lo = lane_offsets<D>();
 
-    f32x16 dq[DB];
+    RowBlock<D> dq;
 #pragma unroll
     for (int i = 0; i < DB; ++i)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) dq[i][j] = 0.f;
+        for (int qb = 0; qb < N; ++qb) dq[i][qb] = F::zero();
 
     auto issue_tile = [&](int tile_start, char *stage) {
         dma.issue(kbase + (int64_t)tile_start * kv_row_bytes, lk - 1 - tile_start, stage);
@@ -655,7 +699,7 @@ __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__re
     };
 
     // One sweep over the key tiles.  DELTA_PASS: only accumulate sum_j P_j dP_j (this lane's keys) in dsum.
-    float dsum = 0.f;
+    float dsum[N] = {};
     auto sweep = [&](auto delta_pass_tag) {
         constexpr bool DELTA_PASS = decltype(delta_pass_tag)::value;
         issue_tile(0, stage_a);
@@ -669,75 +713,104 @@ __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__re
 
             if (wave_active && tile_start < wave_kmax) {
                 const bool need_mask = tile_start + BN - 1 > wq0 + off;
-                // register i of block mb is key tile_start + 32*mb + (i/4)*8 + 4*half + i%4: masked iff the
-                // compile-time part of that exceeds lim
-                const int lim = amax - tile_start - half * 4;
+                // element i of a query (register i % R of key block i / R) is key tile_start + 32*mb + place(i) + 4*group:
+                // masked iff the compile-time part of that exceeds lim
+                const int lim = amax - tile_start - group * 4;
+                constexpr int NS = N * F::R;
 #pragma unroll
                 for (int mb = 0; mb < 2; ++mb) {
-                    // S^T and dP^T for 32 keys: register i is key tile_start + 32*mb + (i/4)*8 + 4*half + i%4
+                    // S^T and dP^T for 32 keys.
                     // All 16 fragments are requested before the first MFMA: the LDS latency is paid once per
                     // block, not once per MFMA.
-                    f32x16 s, dp;
-                    bf16x8 ka[KS], va[KS];
+                    typename F::Acc s[N][N], dp[N][N];           // [key block][query block]
+                    bf16x8 ka[N][KS], va[N][KS];
 #pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) {
-                        ka[ks] = lds_read_b128(ks_ + mb * (KVTILE_BYTES / 2) + lo.row_unit[ks]);
-                        va[ks] = lds_read_b128(vs_ + mb * (KVTILE_BYTES / 2) + lo.row_unit[ks]);
-                    }
+                    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                        for (int kb = 0; kb < N; ++kb) {
+                            const int at = mb * (KVTILE_BYTES / 2) + kb * (KVTILE_BYTES / 2 / N) + lo.row_unit[ks];
+                            ka[kb][ks] = lds_read_b128(ks_ + at);
+                            va[kb][ks] = lds_read_b128(vs_ + at);
+                        }
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) s[j] = dp[j] = 0.f;
+                    for (int kb = 0; kb < N; ++kb)
 #pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) {
-                        s = mfma32(ka[ks], qf[ks], s);
-                        dp = mfma32(va[ks], dof[ks], dp);
-                    }
+                        for (int qb = 0; qb < N; ++qb) s[kb][qb] = dp[kb][qb] = F::zero();
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                        for (int kb = 0; kb < N; ++kb) {
+#pragma unroll
+                            for (int qb = 0; qb < N; ++qb) s[kb][qb] = F::mul(ka[kb][ks], qf[qb][ks], s[kb][qb]);
+#pragma unroll
+                            for (int qb = 0; qb < N; ++qb) dp[kb][qb] = F::mul(va[kb][ks], dof[qb][ks], dp[kb][qb]);
+                        }
                     // K^T fragments of the dQ contraction: requested now, so that they arrive during the arithmetic
-                    bf16x8 kt[2][DB];
+                    bf16x8 kt[32 / F::K][DB];
                     if (!DELTA_PASS) {
 #pragma unroll
-                        for (int tq = 0; tq < 2; ++tq)
+                        for (int tq = 0; tq < 32 / F::K; ++tq)
 #pragma unroll
                             for (int j = 0; j < DB; ++j) {
-                                const char *ka_ = ks_ + mb * (KVTILE_BYTES / 2) + tq * (KVTILE_BYTES / 4);
-                                kt[tq][j] = lds_read_tr_pair(ka_ + lo.tr_lo[j], ka_ + lo.tr_hi[j]);
+                                const char *ka_ = ks_ + mb * (KVTILE_BYTES / 2) + tq * (F::K * 2 * D);
+                                kt[tq][j] = lds_read_tr_pair(ka_ + lo.tr_lo[j], ka_ + lo.tr_hi(j));
                             }
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     if (!need_mask) {
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], c2, -lse2));
-                            if (DELTA_PASS) dsum += pv * dp[i];
-                            else dp[i] = pv * (dp[i] - dlt);
-                        }
+                        for (int qb = 0; qb < N; ++qb)
+#pragma unroll
+                            for (int i = 0; i < NS; ++i) {
+                                const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i / F::R][qb][i % F::R], c2, -lse2[qb]));
+                                if (DELTA_PASS) dsum[qb] += pv * dp[i / F::R][qb][i % F::R];
+                                else dp[i / F::R][qb][i % F::R] = pv * (dp[i / F::R][qb][i % F::R] - dlt[qb]);
+                            }
                     } else
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], c2, -lse2));
-                        const bool hidden = need_mask && mb * 32 + (i >> 2) * 8 + (i & 3) > lim;
-                        if (hidden) pv = 0.f;
-                        if (DELTA_PASS) dsum += D == 64 && hidden ? 0.f : pv * dp[i];     // (dP of a hidden pair may be anything)
-                        else dp[i] = pv * (dp[i] - dlt);
-                    }
-                    if (DELTA_PASS) continue;
-                    // dQ^T += K^T dS^T : contraction over these 32 keys in 2 groups of 16
+                    for (int qb = 0; qb < N; ++qb)
 #pragma unroll
-                    for (int tq = 0; tq < 2; ++tq) {
-                        bf16x8 dsb[3];
-                        if (D == 64) split_exact(dp, 8 * tq, dsb);
-                        else dsb[0] = pack8(dp[8 * tq + 0], dp[8 * tq + 1], dp[8 * tq + 2], dp[8 * tq + 3],
-                                            dp[8 * tq + 4], dp[8 * tq + 5], dp[8 * tq + 6], dp[8 * tq + 7]);
+                        for (int i = 0; i < NS; ++i) {
+                            float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i / F::R][qb][i % F::R], c2, -lse2[qb]));
+                            const bool hidden = need_mask && mb * 32 + F::place(i) - F::M * qb > lim;
+                            if (hidden) pv = 0.f;
+                            // (dP of a hidden pair may be anything)
+                            if (DELTA_PASS) dsum[qb] += D == 64 && hidden ? 0.f : pv * dp[i / F::R][qb][i % F::R];
+                            else dp[i / F::R][qb][i % F::R] = pv * (dp[i / F::R][qb][i % F::R] - dlt[qb]);
+                        }
+                    if (DELTA_PASS) continue;
+                    // dQ^T += K^T dS^T : contraction over these 32 keys in groups of K
+#pragma unroll
+                    for (int tq = 0; tq < 32 / F::K; ++tq) {
+                        bf16x8 dsb[N][3];
+                        float f[N][8];
+#pragma unroll
+                        for (int qb = 0; qb < N; ++qb) {
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) f[qb][e] = dp[(8 * tq + e) / F::R][qb][(8 * tq + e) % F::R];
+                            if (D == 64) split_exact(f[qb], dsb[qb]);
+                            else dsb[qb][0] = pack8(f[qb]);
+                        }
 #pragma unroll
                         for (int x = 0; x < (D == 64 ? 3 : 1); ++x)
 #pragma unroll
-                            for (int j = 0; j < DB; ++j) dq[j] = mfma32(kt[tq][j], dsb[x], dq[j]);
+                            for (int j = 0; j < DB; ++j)
+#pragma unroll
+                                for (int n = 0; n < N; ++n) {
+                                    const int qb = j & 1 ? N - 1 - n : n;    // (neighbours share an operand)
+                                    dq[j][qb] = F::mul(kt[tq][j], dsb[qb][x], dq[j][qb]);
+                                }
                         if (D != 64 && head) {   // add the bf16 rounding residual of dS
-                            bf16x8 dl;
+                            bf16x8 dl[N];
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) dl[e] = (__bf16)(dp[8 * tq + e] - (float)dsb[0][e]);
+                            for (int qb = 0; qb < N; ++qb)
 #pragma unroll
-                            for (int j = 0; j < DB; ++j) dq[j] = mfma32(kt[tq][j], dl, dq[j]);
+                                for (int e = 0; e < 8; ++e) dl[qb][e] = (__bf16)(f[qb][e] - (float)dsb[qb][0][e]);
+#pragma unroll
+                            for (int j = 0; j < DB; ++j)
+#pragma unroll
+                                for (int qb = 0; qb < N; ++qb) dq[j][qb] = F::mul(kt[tq][j], dl[qb], dq[j][qb]);
                         }
                     }
                 }
@@ -752,24 +825,30 @@ __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__re
     };
     if (head) {
         sweep(std::true_type());
-        dlt = sum_with_other_half(dsum);             // the two lane halves hold different keys of the same row
-        if (wave_active && iq < lq && half == 0) delta[stat_at] = -dlt;
+#pragma unroll
+        for (int qb = 0; qb < N; ++qb) {
+            dlt[qb] = sum_over_groups<D>(dsum[qb]);  // the lanes of a row hold different keys of it
+            if (row_of_block(qb) < lq && group == 0) delta[stat_at(qb)] = -dlt[qb];
+        }
     }
     sweep(std::false_type());
 
     if (wave_active) {
         // dQ rows leave through this wavefront's part of the (now idle) stage buffers, whole rows per store instruction
         char *scratch = (wave < 2 ? stage_a : stage_b) + (wave & 1) * RowScratch<D>::bytes;
-        store_rows_bf16<D>(dq, p.softmax_scale, scratch, lq - wq0, [&](int r) {
+        float scale[N];
+#pragma unroll
+        for (int qb = 0; qb < N; ++qb) scale[qb] = p.softmax_scale;
+        store_rows_bf16<D>(dq, scale, scratch, lq - wq0, [&](int r) {
             return (char *)b.d_q + ((int64_t)(q_seg0 + wq0 + r) * b.dq_stride_tok + (int64_t)h * b.dq_stride_head) * 2;
         });
-        if (D == 64) {
+        if constexpr (D == 64) {
             for_rows_not_finite<D>(dq, p.softmax_scale, lq - wq0, [&](int r) {
                 const int row = q_seg0 + wq0 + r;
                 const unsigned short *qr = row_of<unsigned short>(p.q, row, p.q_stride_tok, h, p.q_stride_head);
                 const unsigned short *dr = row_of<unsigned short>(b.d_o, row, b.do_stride_tok, h, b.do_stride_head);
                 scalar_dq_row<unsigned short, 64, 4>(b, SegmentRows{q_seg0, lq, k_seg0, lk}, row, h, [&](int x) { return ld(qr + x); },
-                                                  [&](int x) { return ld(dr + x); }, __shfl(dlt, r));
+                                                  [&](int x) { return ld(dr + x); }, __shfl(dlt[0], r));
             });
         }
     }

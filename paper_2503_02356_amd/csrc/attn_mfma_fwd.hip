@@ -9,8 +9,9 @@
 // Everything is computed TRANSPOSED so that a lane owns one query:
 //     S^T = K Q^T   (A = K tile rows from LDS, B = Q^T kept in registers for the whole kernel)
 //     O^T += V^T P^T (A = V^T through transposing LDS reads, B = P^T straight from the S^T registers)
-// With the query on the lane axis the row maximum and row sum are in-lane reductions plus one exchange
-// between lane l and lane l^32, the running rescale is one scalar per lane, and P never leaves registers.
+// With the query on the lane axis the row maximum and row sum are in-lane reductions plus an exchange between the
+// lanes of a query (made only where one of them finds a new maximum), the running rescale is a lane scalar, and P never
+// leaves registers.
 // Only tiles that intersect the causal diagonal apply a mask; tiles above it are never visited.
 #include <hip/hip_runtime.h>
 
@@ -40,9 +41,10 @@ struct Stage {
 template <int D>
 __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, char *stage_a, char *stage_b)
 {
-    constexpr int KS = D / 16, DB = D / 32, TILE_BYTES = Stage<D>::tile_bytes;
+    using F = Mfma<D>;
+    constexpr int KS = D / F::K, DB = D / F::M, KB = BN / F::M, QB = F::N32, TILE_BYTES = Stage<D>::tile_bytes;
     const int lane = threadIdx.x & 63, wave = wave_id();
-    const int half = lane >> 5, col = lane & 31;
+    const int group = F::group(), col = F::column();
 
     // Block id -> (tile rank, head).  The key/value head varies fastest so that the workgroups an XCD
     // receives (ids are dealt round-robin over the 8 XCDs) keep re-reading the same K/V head in its L2.
@@ -80,8 +82,7 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     const int wq0 = q_tile0 + blk * 32;              // first row of this wavefront (segment-local)
     const int wave_kmax = min(kmax, wq0 + 32 + off); // keys this wavefront needs (<= 0 rows valid: nothing)
     const bool wave_active = wq0 < lq;
-    const int iq = wq0 + col;                        // this lane's query row
-    const int amax = iq + off;                       // last visible key of this lane's row
+    const int amax = wq0 + col + off;                // last visible key of this lane's row (block qb: M qb further)
 
     const int64_t kv_row_bytes = p.kv_stride_tok * 2;
     const char *kbase = uniform((const char *)p.k + ((int64_t)k_seg0 * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2);
@@ -89,26 +90,29 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     TileDma<BN, D> dma;
     dma.init(kv_row_bytes);
 
-    // Q^T fragments: lane (col, half) holds row iq, d = 16*ks + 8*half + 0..7.
-    bf16x8 qf[KS];
-    {
-        const int row = q_seg0 + min(iq, lq - 1);
+    // Q^T fragments: lane (col, group) holds row wq0 + M*qb + col, d = K*ks + 8*group + 0..7.
+    bf16x8 qf[QB][KS];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int row = q_seg0 + min(wq0 + F::M * qb + col, lq - 1);
         const char *qrow = (const char *)p.q + ((int64_t)row * p.q_stride_tok + (int64_t)h * p.q_stride_head) * 2;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8 *)(qrow + ks * 32 + half * 16);
+        for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *(const bf16x8 *)(qrow + ks * 2 * F::K + group * 16);
     }
     const LaneOffsets<D> lo = lane_offsets<D>();
 
-    f32x16 o_acc[DB];
+    RowBlock<D> o_acc;
 #pragma unroll
-    for (int i = 0; i < DB; ++i)
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) o_acc[i][j] = 0.f;
+        for (int qb = 0; qb < QB; ++qb) o_acc[db][qb] = F::zero();
     // Exponentials: D = 128 in log2 units, the scale folded into them (exp2(s c2 - m), m in those units); D = 64 in the natural
     // units of the scores, exp2((s c2 - m) log2e), where the rounding of log2e only acts on the distance to the maximum.
     constexpr float kLog2e = 1.44269504088896340736f, kUnit = D == 64 ? kLog2e : 1.f;
     const float c2 = p.softmax_scale * (D == 64 ? 1.f : kLog2e);
-    float m_run = -INFINITY, l_run = 0.f;            // running max (those units) and this lane's partial row sum
+    float m_run[QB], l_run[QB];                      // running max (those units) and this lane's partial row sum
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) m_run[qb] = -INFINITY, l_run[qb] = 0.f;
 
     auto issue_tile = [&](int tile_start, char *stage) {
         dma.issue(kbase + (int64_t)tile_start * kv_row_bytes, lk - 1 - tile_start, stage);
@@ -123,91 +127,109 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
         if (t + 1 < n_tiles) issue_tile(tile_start + BN, next_stage);
 
         if (wave_active && tile_start < wave_kmax) {
-            // ---- S^T = K Q^T : two 32-key blocks
-            // All 16 K fragments are requested before the first MFMA: the LDS latency is paid once per tile,
+            // ---- S^T = K Q^T : KB key blocks by QB query blocks
+            // All 16 K fragments (D = 128) are requested before the first MFMA: the LDS latency is paid once per tile,
             // not once per MFMA (the matrix unit then consumes them in arrival order).
-            f32x16 s[2];
-            bf16x8 ka[2][KS];
+            typename F::Acc s[KB][QB];
+            bf16x8 ka[KB][KS];
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb) ka[mb][ks] = lds_read_b128(stage + mb * (TILE_BYTES / 2) + lo.row_unit[ks]);
+                for (int kb = 0; kb < KB; ++kb) ka[kb][ks] = lds_read_b128(stage + kb * (TILE_BYTES / KB) + lo.row_unit[ks]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-                for (int j = 0; j < 16; ++j) s[mb][j] = 0.f;
+                for (int qb = 0; qb < QB; ++qb) s[kb][qb] = F::zero();
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb) s[mb] = mfma32(ka[mb][ks], qf[ks], s[mb]);
+                for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                    for (int x = 0; x < QB; ++x) {
+                        const int qb = kb & 1 ? QB - 1 - x : x;      // (neighbours share an operand)
+                        s[kb][qb] = F::mul(ka[kb][ks], qf[qb][ks], s[kb][qb]);
+                    }
+            // Element i of a query's scores: register i % R of block i / R, key tile_start + place(i) + 4*group.
+            constexpr int NS = KB * F::R;
             // ---- causal mask, only on tiles that cross this wavefront's diagonal
             if (tile_start + BN - 1 > wq0 + off) {
-                // register i of block mb is key tile_start + 32*mb + (i/4)*8 + 4*half + i%4: masked iff the
-                // compile-time part of that exceeds lim (one compare with a constant + one select per element)
-                const int lim = amax - tile_start - half * 4;
+                // masked iff the compile-time part of the key exceeds lim (one compare with a constant + one select per element)
+                const int lim = amax - tile_start - group * 4;
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
+                for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        if (mb * 32 + (i >> 2) * 8 + (i & 3) > lim) s[mb][i] = -INFINITY;
+                    for (int i = 0; i < NS; ++i)
+                        if (F::place(i) - F::M * qb > lim) s[i / F::R][qb][i % F::R] = -INFINITY;
             }
             // ---- online softmax (log2 domain)
-            float mx = s[0][0];
-#pragma unroll
-            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[0][i]);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[1][i]);
-            mx = max_with_other_half(mx);
             // Lazy rescale: the running reference m_run only moves when a row's new maximum exceeds it by more than
             // 2^kLazy; until then P = exp2(s - m_run) <= 2^kLazy, exact enough in the fp32 sums and in bf16 alike,
             // and O needs no rescale.  The final division by l_tot and the LSE absorb whatever reference was used.
-            const float mx2 = mx * c2;
-            const bool grow = mx2 > m_run + kLazy<D>;        // first tile: m_run = -inf
-            if (__builtin_amdgcn_ballot_w64(grow) != 0) {
-                const float m_new = grow ? mx2 : m_run;
-                const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * kUnit);   // first tile: exp2(-inf) = 0
-                m_run = m_new;
-                l_run *= alpha;
+            // The lanes of a query look at their own keys and meet only where one of them has a new maximum.
+            float mx2[QB];
+            bool grow = false;
 #pragma unroll
-                for (int db = 0; db < DB; ++db)
+            for (int qb = 0; qb < QB; ++qb) {
+                float mx = s[0][qb][0];
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) o_acc[db][j] *= alpha;
+                for (int i = 1; i < NS; ++i) mx = fmaxf(mx, s[i / F::R][qb][i % F::R]);
+                mx2[qb] = mx * c2;
+                grow = grow || mx2[qb] > m_run[qb] + kLazy<D>;       // first tile: m_run = -inf
             }
-            // (the row sum in short chains: rounding grows with a chain's length)
+            if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+                    const float mx = max_over_groups<D>(mx2[qb]), m_new = mx > m_run[qb] + kLazy<D> ? mx : m_run[qb];
+                    const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * kUnit);   // first tile: exp2(-inf) = 0
+                    m_run[qb] = m_new;
+                    l_run[qb] *= alpha;
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) o_acc[db][qb] *= alpha;
+                }
+            }
+            // (the row sum in short chains at D = 64: rounding grows with a chain's length)
             constexpr int CHAINS = D == 64 ? 8 : 1;
-            float rs[CHAINS] = {};
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+            for (int qb = 0; qb < QB; ++qb) {
+                float rs[CHAINS] = {};
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    s[mb][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][i], c2, -m_run) * kUnit);
-                    rs[i % CHAINS] += s[mb][i];
+                for (int i = 0; i < NS; ++i) {
+                    const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i / F::R][qb][i % F::R], c2, -m_run[qb]) * kUnit);
+                    s[i / F::R][qb][i % F::R] = pv;
+                    rs[i % CHAINS] += pv;
                 }
 #pragma unroll
-            for (int n = CHAINS / 2; n > 0; n /= 2)
+                for (int n = CHAINS / 2; n > 0; n /= 2)
 #pragma unroll
-                for (int i = 0; i < n; ++i) rs[i] += rs[i + n];
-            l_run += rs[0];
-            // ---- O^T += V^T P^T : contraction over the 64 keys in 4 groups of 16
+                    for (int i = 0; i < n; ++i) rs[i] += rs[i + n];
+                l_run[qb] += rs[0];
+            }
+            // ---- O^T += V^T P^T : contraction over the 64 keys in groups of K
             const char *vst = stage + TILE_BYTES;
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+            for (int t = 0; t < BN / F::K; ++t) {
+                bf16x8 pb[QB][3];
 #pragma unroll
-                for (int tq = 0; tq < 2; ++tq) {
-                    // register 8*tq + j of block mb is key mb*32 + 16*tq + (j/4)*8 + 4*half + j%4
-                    bf16x8 pb[3];
-                    if (D == 64) split_exact(s[mb], 8 * tq, pb);
-                    else pb[0] = pack8(s[mb][8 * tq + 0], s[mb][8 * tq + 1], s[mb][8 * tq + 2], s[mb][8 * tq + 3],
-                                       s[mb][8 * tq + 4], s[mb][8 * tq + 5], s[mb][8 * tq + 6], s[mb][8 * tq + 7]);
-                    const char *va = vst + mb * (TILE_BYTES / 2) + tq * (TILE_BYTES / 4);
+                for (int qb = 0; qb < QB; ++qb) {
+                    float f[8];
 #pragma unroll
-                    for (int j = 0; j < DB; ++j) {
-                        const bf16x8 a = lds_read_tr_pair(va + lo.tr_lo[j], va + lo.tr_hi[j]);
+                    for (int e = 0; e < 8; ++e) f[e] = s[(8 * t + e) / F::R][qb][(8 * t + e) % F::R];
+                    if (D == 64) split_exact(f, pb[qb]);
+                    else pb[qb][0] = pack8(f);
+                }
+                const char *va = vst + t * (TILE_BYTES / (BN / F::K));
 #pragma unroll
-                        for (int t = 0; t < (D == 64 ? 3 : 1); ++t) o_acc[j] = mfma32(a, pb[t], o_acc[j]);
+                for (int db = 0; db < DB; ++db) {
+                    const bf16x8 a = lds_read_tr_pair(va + lo.tr_lo[db], va + lo.tr_hi(db));
+#pragma unroll
+                    for (int x = 0; x < QB; ++x) {
+                        const int qb = db & 1 ? QB - 1 - x : x;
+#pragma unroll
+                        for (int w = 0; w < (D == 64 ? 3 : 1); ++w) o_acc[db][qb] = F::mul(a, pb[qb][w], o_acc[db][qb]);
                     }
                 }
+            }
         }
         wait_lds_dma();
         __syncthreads();
@@ -218,17 +240,26 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     }
 
     if (!wave_active) return;
-    const float l_tot = sum_with_other_half(l_run);
+    float l_tot[QB], scale[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        l_tot[qb] = sum_over_groups<D>(l_run[qb]);
+        scale[qb] = 1.f / l_tot[qb];
+    }
     // O rows leave through this wavefront's part of the (now idle) stage buffers, whole rows per store instruction.
     // The scale of a padding row (l_tot = 0 cannot happen: every real row sees its own key) is never stored.
     char *scratch = (wave < 2 ? stage_a : stage_b) + (wave & 1) * RowScratch<D>::bytes;
-    store_rows_bf16<D>(o_acc, 1.f / l_tot, scratch, lq - wq0, [&](int r) {
+    store_rows_bf16<D>(o_acc, scale, scratch, lq - wq0, [&](int r) {
         return (char *)p.o + ((int64_t)(q_seg0 + wq0 + r) * p.o_stride_tok + (int64_t)h * p.o_stride_head) * 2;
     });
-    if (iq < lq && half == 0)
-        p.lse[(int64_t)h * p.n_tokens + q_seg0 + iq] = m_run * (D == 64 ? 1.f : 0.69314718055994530942f) + __logf(l_tot);
-    if (D == 64) {
-        for_rows_not_finite<D>(o_acc, 1.f / l_tot, lq - wq0, [&](int r) {
+    const int iq = wq0 + (lane & 31);                // lane l < 32 holds the sums of row l, in block l / M
+    if (iq < lq && lane < 32) {
+        const int qb = QB - 1;
+        const float m = lane < F::M ? m_run[0] : m_run[qb], l = lane < F::M ? l_tot[0] : l_tot[qb];
+        p.lse[(int64_t)h * p.n_tokens + q_seg0 + iq] = m * (D == 64 ? 1.f : 0.69314718055994530942f) + __logf(l);
+    }
+    if constexpr (D == 64) {
+        for_rows_not_finite<D>(o_acc, scale[0], lq - wq0, [&](int r) {
             const int row = q_seg0 + wq0 + r;
             const unsigned short *qr = row_of<unsigned short>(p.q, row, p.q_stride_tok, h, p.q_stride_head);
             scalar_fwd_row<unsigned short, 64, 4>(p, SegmentRows{q_seg0, lq, k_seg0, lk}, row, h, [&](int x) { return ld(qr + x); });

@@ -1,9 +1,16 @@
 // Device-side helpers shared by the bf16 MFMA kernels (gfx950).
 //
-// MFMA 32x32x16 bf16 operand layout (lane l of a 64-wide wavefront, half = l / 32):
-//   A (M x K): lane holds row  m = l % 32, k = 8*half + 0..7        (bf16x8)
-//   B (K x N): lane holds col  n = l % 32, k = 8*half + 0..7        (bf16x8)
-//   C/D (M x N, fp32x16): lane holds col n = l % 32, register i <-> row (i/4)*8 + 4*half + i%4
+// MFMA operand layouts, M x M results, K = 512 / M (lane l of a 64-wide wavefront, group = l / M: halves or quarters):
+//   A (M x K): lane holds row  m = l % M, k = 8*group + 0..7        (bf16x8)
+//   B (K x N): lane holds col  n = l % M, k = 8*group + 0..7        (bf16x8)
+//   C/D (M x N, fp32): lane holds col n = l % M, register i <-> row (i/4)*8 + 4*group + i%4
+//                      (M = 32: 16 registers; M = 16: 4 registers, i.e. row 4*group + i)
+// head_dim 128 multiplies with M = 16 (the gradient accumulators of its dK/dV kernel apart): these kernels are limited by the
+// card's power (1.7-1.8 GHz of 2.4 with M = 32 throughout), and on N(0,1) operands the 16x16x32 instruction does more per
+// joule (a sum of 32 products per accumulator update instead of 16): a loop of nothing but MFMAs runs at 1960-2050 TFLOP/s with
+// M = 16 and at 1740-1780 with M = 32.  32768 queries of 64 / 8 heads over 131072 keys: forward 111.9 -> 105.5 ms, dQ 153.5 -> 141.0,
+// dK/dV 207.4 -> 199.5; the clock goes up to 1.98 GHz.  head_dim 64, which splits P and dS into three operands and is
+// bound by vector instructions at 2.2 GHz, keeps M = 32: half as many MFMAs to issue (16 x 16: 2.5 % slower).
 //
 // ds_read_tr16_b64 (transposing LDS read): inside each block of 16 lanes, lane r supplies the address
 // of 4 consecutive 16-bit elements; the 16x4 elements are handed out so that lane i receives
@@ -30,6 +37,32 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 #define CF_LDS __attribute__((address_space(3)))
 
+template <int D>
+struct Mfma {
+    static constexpr int M = D == 64 ? 32 : 16, K = 512 / M;
+    static constexpr int R = M * M / 64;             // registers of a result
+    static constexpr int N32 = 32 / M;               // blocks of M that make 32
+    typedef float Acc __attribute__((ext_vector_type(R)));
+    // The registers of results below each other, read as one array: element i is row place(i) + 4 * group, and elements 8 t .. 8 t + 7
+    // are the operand of contraction group t (rows K t .. K t + K - 1), in the order in which LaneOffsets' transposing reads
+    // fetch the other operand.
+    __host__ __device__ static constexpr int place(int i) { return i / R * M + i % R / 4 * 8 + i % 4; }
+    __device__ __forceinline__ static int group() { return (int)(threadIdx.x & 63) / M; }
+    __device__ __forceinline__ static int column() { return (int)(threadIdx.x & 63) % M; }
+    __device__ __forceinline__ static Acc zero()
+    {
+        Acc a;
+#pragma unroll
+        for (int i = 0; i < R; ++i) a[i] = 0.f;
+        return a;
+    }
+    __device__ __forceinline__ static Acc mul(bf16x8 a, bf16x8 b, Acc c)
+    {
+        if constexpr (M == 32) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+};
+
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -49,7 +82,7 @@ __device__ __forceinline__ void accumulate_in_place(f32x16 &acc, bf16x8 a, bf16x
 // Before the first other use of an accumulator: lets its last MFMA (8 passes) finish.
 __device__ __forceinline__ void accumulator_done(f32x16 &acc) { asm volatile("s_nop 15" : "+v"(acc)); }
 
-// Two transposing reads, 8 rows apart... the caller passes both addresses; result is one bf16x8 operand.
+// Two transposing reads; result is one bf16x8 operand.
 __device__ __forceinline__ bf16x8 lds_read_tr_pair(const char *lo_addr, const char *hi_addr)
 {
     s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((CF_LDS s16x4 *)lo_addr);
@@ -64,23 +97,22 @@ __device__ __forceinline__ bf16x8 lds_read_b128(const char *addr)
 }
 
 // Packs 8 fp32 values into a bf16x8 (round to nearest even; v_cvt_pk_bf16_f32 on gfx950).
-__device__ __forceinline__ bf16x8 pack8(float a0, float a1, float a2, float a3, float a4, float a5, float a6,
-                                        float a7)
+__device__ __forceinline__ bf16x8 pack8(const float (&f)[8])
 {
     bf16x8 r;
-    r[0] = (__bf16)a0; r[1] = (__bf16)a1; r[2] = (__bf16)a2; r[3] = (__bf16)a3;
-    r[4] = (__bf16)a4; r[5] = (__bf16)a5; r[6] = (__bf16)a6; r[7] = (__bf16)a7;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = (__bf16)f[e];
     return r;
 }
 
 // Eight fp32 values as three bf16 operands: x = w[0] + w[1] + w[2] exactly (8 of the 24 significant bits each, taken off by
 // truncation), so that three MFMAs multiply the fp32 value and not its rounding.
-__device__ __forceinline__ void split_exact(const f32x16 &f, int first, bf16x8 (&w)[3])
+__device__ __forceinline__ void split_exact(const float (&f)[8], bf16x8 (&w)[3])
 {
     i32x4 u[3];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        float x0 = f[first + 2 * e], x1 = f[first + 2 * e + 1];
+        float x0 = f[2 * e], x1 = f[2 * e + 1];
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             const unsigned b0 = __float_as_uint(x0), b1 = __float_as_uint(x1);
@@ -95,70 +127,81 @@ __device__ __forceinline__ void split_exact(const f32x16 &f, int first, bf16x8 (
 
 // Swizzled LDS tile with rows of 2 D bytes (D bf16) and no padding: the 16-byte unit u of row r lives at unit
 // u ^ swz(r).  LDS has 64 four-byte banks; a 16-byte row read (ds_read_b128) is served 16 lanes per clock and a
-// transposing 8-byte read (ds_read_b64_tr_b16) 32 lanes per clock.  swz() maps 16 consecutive rows to 16 different
-// bank groups (row reads of one column by 16 rows are conflict free) AND gives the 4 consecutive rows of a transposing
-// read 4 different groups of 4 units (those are conflict free too).  D = 128: a row covers the banks once, so that
-// takes four bits of the row number; D = 64: two rows cover the banks, an even and an odd row never meet, and three
-// bits above the lowest remain, the lowest of them in the place that moves by four units.
+// transposing 8-byte read (ds_read_b64_tr_b16) 32 lanes per clock.  D = 128: a row covers the banks once.  Bits 2, 3 of
+// swz() are the row's lowest two: the 4 consecutive rows of a transposing read lie in 4 different groups of 4 units.  The low
+// two are a function f of a = row / 4 % 4, f = 0, 2, 3, 1:
+//   M = 32  a row read takes one unit of 16 rows at a time (any f that is one to one), a transposing read four units of 4 rows;
+//   M = 16  a row read is served in groups of lanes 0-3, 12-15, 20-23, 24-27 and 4-11, 16-19, 28-31: unit u of the rows with
+//           a = 0, 3 beside unit u + 1 of those with a = 1, 2, and the other way round; f(0), f(3), f(1)^1, f(2)^1 all differ.
+//           A transposing read takes two units of the rows a = 0 beside the same two of a = 1 (2 beside 3): f differs in bit 1.
+// Both are free of conflicts (counted; with f = 0, 2, 1, 3 every row read of M = 16 took twice as long).  D = 64: two rows
+// cover the banks, an even and an odd row never meet, and the row's bit 1 takes the place of its lowest two.
 template <int D>
 __device__ __forceinline__ int swz(int row)
 {
     static_assert(D == 64 || D == 128, "row length");
-    return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+    const int low = (((row >> 2) ^ (row >> 3)) & 1) << 1 | ((row >> 3) & 1);
+    return D == 128 ? ((row & 3) << 2) | low : (((row >> 1) & 1) << 2) | low;
 }
 template <int D>
 __device__ __forceinline__ int tile_off(int row, int unit) { return row * (2 * D) + ((unit ^ swz<D>(row)) << 4); }
 
 // Lane-constant LDS byte offsets into a swizzled tile, computed once per kernel (the XOR of the swizzle
 // cannot be folded into an instruction's immediate offset, so every distinct unit needs its own register;
-// keeping them in D / 8 registers beats recomputing them for each of the ~100 LDS reads per tile).
+// keeping them in registers beats recomputing them for each of the LDS reads of a tile).
 //
 //  row_unit[ks]  operand rows read with ds_read_b128 (MFMA row/col = tile row, contraction along the tile
-//                row): offset of (row = lane % 32, logical unit 2*ks + half).  A 32-row block further down
-//                the tile adds 32 rows (swz() has period 16 rows).
-//  tr_lo[db], tr_hi[db]
+//                row): offset of (row = lane % M, logical unit K / 8 * ks + group).  An M-row block further down
+//                the tile adds M rows (swz() has period 16 rows).
+//  tr_lo[db], tr_hi(db)
 //                operands read with the transposing read (contraction along the tile's ROWS, MFMA
-//                row/col = tile column 32*db + lane % 32): offsets of the two 4-row reads that make one
-//                bf16x8 operand, for contraction rows 4*half + {0..3 by lane group} and 8 rows further.
-//                32 (16) rows further down the tile add 32 (16) row lengths.
+//                row/col = tile column M*db + lane % M): offsets of the two 4-row reads that make one
+//                bf16x8 operand, for contraction rows 4*group + {0..3 by lane} and 8 (M = 32) or 16 rows further.
+//                K rows further down the tile add K row lengths.
 template <int D>
 struct LaneOffsets {
-    int row_unit[D / 16];
-    int tr_lo[D / 32], tr_hi[D / 32];
+    static constexpr int M = Mfma<D>::M, UNITS = Mfma<D>::K / 8;
+    int row_unit[D / 8 / UNITS];
+    int tr_lo[D / M], tr_hi8[M == 32 ? D / M : 1];
+    __device__ __forceinline__ int tr_hi(int db) const { return M == 32 ? tr_hi8[db] : tr_lo[db] + 16 * 2 * D; }
 };
 template <int D>
 __device__ __forceinline__ LaneOffsets<D> lane_offsets()
 {
-    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31, r16 = lane & 15, blk = (lane >> 4) & 1;
+    constexpr int M = Mfma<D>::M, UNITS = LaneOffsets<D>::UNITS;
+    const int lane = threadIdx.x & 63, group = lane / M, r16 = lane & 15, blk = M == 32 ? (lane >> 4) & 1 : 0;
     LaneOffsets<D> o;
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) o.row_unit[ks] = tile_off<D>(col, 2 * ks + half);
-    const int r_lo = 4 * half + (r16 >> 2), u0 = 2 * blk + ((r16 >> 1) & 1), sub = 8 * (r16 & 1);
+    for (int ks = 0; ks < D / 8 / UNITS; ++ks) o.row_unit[ks] = tile_off<D>(lane % M, UNITS * ks + group);
+    const int r_lo = 4 * group + (r16 >> 2), u0 = 2 * blk + ((r16 >> 1) & 1), sub = 8 * (r16 & 1);
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) {
-        o.tr_lo[db] = tile_off<D>(r_lo, 4 * db + u0) + sub;
-        o.tr_hi[db] = tile_off<D>(r_lo + 8, 4 * db + u0) + sub;
+    for (int db = 0; db < D / M; ++db) {
+        o.tr_lo[db] = tile_off<D>(r_lo, M / 8 * db + u0) + sub;
+        if (M == 32) o.tr_hi8[db] = tile_off<D>(r_lo + 8, M / 8 * db + u0) + sub;
     }
     return o;
 }
 
-// The same offsets for a kernel that has no registers to spare: all follow from two bases by XOR (unit 2 ks + half of a
-// row is unit `half` with bits 1.. flipped; 8 rows further flips bit 1 of the swizzle), one instruction per read.
+// The offsets of the dK/dV kernel, which has no registers to spare: all follow from two bases by XOR (a row's units differ in
+// bits above the group's; so do the halves of a transposed operand, of rows FIRST * half + 0..3 and STEP rows further, whose
+// columns are those of M = 32), one instruction per read.
 // forget(): from here on the compiler computes them anew instead of keeping the results of the last use.
 template <int D>
 struct BlockAddress {
+    static constexpr int STEP = D == 64 ? 8 : 4, FIRST = 12 - STEP;
     int row0, tr0;
     __device__ __forceinline__ BlockAddress()
     {
-        const LaneOffsets<D> lo = lane_offsets<D>();
-        row0 = lo.row_unit[0], tr0 = lo.tr_lo[0];
+        const int lane = threadIdx.x & 63, r16 = lane & 15;
+        row0 = lane_offsets<D>().row_unit[0];
+        tr0 = tile_off<D>(FIRST * (lane >> 5) + (r16 >> 2), 2 * ((lane >> 4) & 1) + ((r16 >> 1) & 1)) + 8 * (r16 & 1);
     }
     // to the block `bytes` (a power of two beyond a block's size) further, and back
     __device__ __forceinline__ void flip(int bytes) { row0 ^= bytes, tr0 ^= bytes; }
     __device__ __forceinline__ void forget() { asm volatile("" : "+v"(row0), "+v"(tr0)); }
-    __device__ __forceinline__ int row(int ks) const { return row0 ^ (ks << 5); }
+    __device__ __forceinline__ int row(int ks) const { return row0 ^ (ks * LaneOffsets<D>::UNITS * 16); }
     __device__ __forceinline__ int tr_lo(int db) const { return tr0 ^ (db << 6); }
-    __device__ __forceinline__ int tr_hi(int db) const { return (tr0 ^ (db << 6) ^ (2 << 4)) + 8 * 2 * D; }
+    __device__ __forceinline__ int tr_hi(int db) const { return (tr_lo(db) ^ ((STEP == 8 ? 3 : 2) << 4)) + STEP * 2 * D; }
 };
 
 // Index of this wavefront inside its workgroup, as a value the compiler knows to be wave-uniform.
@@ -263,10 +306,10 @@ __device__ __forceinline__ QTile read_q_tile(const cf_q_tile *table, int rank)
     return QTile{uniform(b[0]), uniform(a[0]), uniform(a[1]), uniform(a[2]), uniform(a[3])};
 }
 
-// Stores a wavefront's 32 x D block of bf16 results (computed transposed: a lane owns one ROW, register group
-// (j, g4) of acc holds its 4 consecutive d starting at 32*j + 8*g4 + 4*half) to global rows of 2 D bytes.
-// A direct store would write 8-byte pieces of 32 different rows per instruction (64 cache lines touched per
-// instruction, 16 instructions); instead the block is turned around in `scratch` (this wavefront's own
+// Stores a wavefront's 32 x D block of bf16 results (computed transposed: a lane owns row M n + lane % M of acc[..][n], four
+// registers are 4 consecutive d) to global rows of 2 D bytes.
+// A direct store would write 8-byte pieces of many different rows per instruction (a cache line touched per
+// lane, 16 instructions); instead the block is turned around in `scratch` (this wavefront's own
 // 32 padded rows of LDS, free at that point) and leaves as D / 16 instructions that each write 512 / D whole rows.
 //   row_ptr(r): global address of row r of the block (r = 0..31), rows >= rows_valid are not written
 template <int D>
@@ -274,20 +317,23 @@ struct RowScratch {
     static constexpr int stride = 2 * D + 16;       // keeps 16-byte alignment, spreads rows over banks
     static constexpr int bytes = 32 * stride;
 };
+template <int D>
+using RowBlock = typename Mfma<D>::Acc[D / Mfma<D>::M][Mfma<D>::N32];
 template <int D, typename RowPtr>
-__device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[D / 32], float scale, char *scratch, int rows_valid,
+__device__ __forceinline__ void store_rows_bf16(const RowBlock<D> &acc, const float (&scale)[Mfma<D>::N32], char *scratch, int rows_valid,
                                                 RowPtr row_ptr)
 {
     constexpr int S = RowScratch<D>::stride, UNITS = D / 8, RPI = 512 / D;
-    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+    using F = Mfma<D>;
+    const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int j = 0; j < D / 32; ++j)
+    for (int n = 0; n < F::N32; ++n)
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
+        for (int i = 0; i < D * F::R / F::M; i += 4) {
             bf16x4 w;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[j][g4 * 4 + e] * scale);
-            *(bf16x4 *)(scratch + col * S + (j * 32 + g4 * 8 + half * 4) * 2) = w;
+            for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[i / F::R][n][i % F::R + e] * scale[n]);
+            *(bf16x4 *)(scratch + (n * F::M + F::column()) * S + (F::place(i) + 4 * F::group()) * 2) = w;
         }
     __builtin_amdgcn_wave_barrier();
     bf16x8 v[D / 16];
@@ -300,16 +346,17 @@ __device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[D / 32], flo
     }
 }
 
-// visit(r), by the whole wavefront, for every row r < rows_valid of a 32 x D block (a lane owns row lane % 32, as above) whose
+// visit(r), by the whole wavefront, for every row r < rows_valid of a 32 x D block (as above, D = 64: a lane owns row lane % 32) whose
 // results, scaled, are not finite.
 template <int D, typename Visit>
-__device__ __forceinline__ void for_rows_not_finite(const f32x16 (&acc)[D / 32], float scale, int rows_valid, Visit visit)
+__device__ __forceinline__ void for_rows_not_finite(const RowBlock<D> &acc, float scale, int rows_valid, Visit visit)
 {
+    static_assert(Mfma<D>::M == 32, "one row per lane");
     float zero = scale * 0.f;                        // stays 0 while everything is finite
 #pragma unroll
     for (int j = 0; j < D / 32; ++j)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) zero = __builtin_fmaf(acc[j][i], 0.f, zero);
+        for (int i = 0; i < 16; ++i) zero = __builtin_fmaf(acc[j][0][i], 0.f, zero);
     const unsigned long long lanes = __ballot(zero != 0.f);
     unsigned rows = (unsigned)lanes | (unsigned)(lanes >> 32);
     if (rows_valid < 32) rows &= (1u << rows_valid) - 1;
@@ -329,6 +376,23 @@ __device__ __forceinline__ float sum_with_other_half(float x)
     const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+
+// Combines over the four lanes l, l ^ 16, l ^ 32, l ^ 48.
+__device__ __forceinline__ float max_over_quarters(float x)
+{
+    const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return max_with_other_half(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float sum_over_quarters(float x)
+{
+    const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return sum_with_other_half(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+// Combines over the lanes of one column of an M x M result.
+template <int D>
+__device__ __forceinline__ float max_over_groups(float x) { return Mfma<D>::M == 32 ? max_with_other_half(x) : max_over_quarters(x); }
+template <int D>
+__device__ __forceinline__ float sum_over_groups(float x) { return Mfma<D>::M == 32 ? sum_with_other_half(x) : sum_over_quarters(x); }
 
 // Finds the tile a workgroup owns.  Tiles of `tile` rows are counted per segment over cu[0..n_seg], from the LAST tile of the
 // LAST segment backwards (the later tiles of a segment see more keys, so the heaviest tiles get the lowest ranks and start
