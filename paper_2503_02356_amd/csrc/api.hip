@@ -285,11 +285,10 @@ int launch_together(const Call *calls, const Touched *t, int n, hipStream_t s, c
     if (calls[0].b && path_of(calls[0]) == kMfma) {
         cf::BwdBatchChunk chunks[cf::CF_BWD_BATCH_MAX];
         for (int c = 0, first = 0; c < n; ++c) {
-            // gradients that several chunks add to grow in the order of the calls: those go into launches of their own
-            bool with_previous = c > 0;
-            for (int a = first; a < c; ++a) with_previous = with_previous && !adds_meet(t[a], t[c]);
-            if (!with_previous) first = c;
-            chunks[c] = {calls[c].b, calls[c].ws, with_previous};
+            bool apart = c > 0;
+            for (int a = first; a < c; ++a) apart = apart && !adds_meet(t[a], t[c]);
+            if (!apart) first = c;
+            chunks[c] = {calls[c].b, calls[c].ws, apart};
         }
         e = cf::launch_mfma_bwd_batch(chunks, n, s);
         return e == hipSuccess ? CF_OK : hip_fail(who, e);

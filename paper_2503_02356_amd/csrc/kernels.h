@@ -55,12 +55,12 @@ constexpr int CF_FWD_BATCH_MAX = 16;
 hipError_t launch_mfma_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s);
 hipError_t launch_mfma_bwd(const cf_attn_bwd_params &p, const BwdWorkspace &ws, hipStream_t s);
 // Backward of 1..CF_BWD_BATCH_MAX chunks: one dQ launch, then the dK/dV kernels, one launch per run of chunks that go with
-// their predecessor.
+// their predecessor: those with work lists, and at head_dim 64 those that add to rows of their own.
 constexpr int CF_BWD_BATCH_MAX = 8;
 struct BwdBatchChunk {
     const cf_attn_bwd_params *b;
     BwdWorkspace ws;
-    bool dkv_with_previous;      // its d_k / d_v rows are no other chunk's of the same dK/dV launch
+    bool rows_of_its_own;        // its d_k / d_v rows are none of its predecessors', back to the last chunk without this
 };
 hipError_t launch_mfma_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s);
 

@@ -5,6 +5,8 @@ import pytest
 import torch
 
 from paper_2503_02356_amd import binding as B
+from paper_2503_02356_amd import inputs
+from paper_2503_02356_amd.runner import ChunkAttention
 from tests import parity as P
 
 pytestmark = pytest.mark.gpu
@@ -91,6 +93,31 @@ def test_gradients_repeat_bitwise(dtype, D, lens, C, Hq, Hkv):
         for sid in got:
             for n in ("dq", "dk", "dv"):
                 assert np.array_equal(got[sid][n], r[sid][n]), (sid, n)
+
+
+@pytest.mark.parametrize("dtype,D,flags,merge", [("bf16", 128, 0, False), ("bf16", 128, 0, True), ("bf16", 128, B.CF_FLAG_DKV_SINGLE_WRITER, False),
+                                                 ("bf16", 64, 0, False), ("fp32", 64, 0, False), ("fp32", 128, 0, True)])
+def test_slices_that_add_to_the_same_rows(dtype, D, flags, merge):
+    """The slices of split sequences add to the same rows of dK and dV, in a list of calls as one by one.  What is added is the same
+    up to the order of fp32 sums: fewer than 64 terms to an element, 64 * 2^-24 = 4e-6."""
+    lens, C, Hq, Hkv = [700, 30, 530, 61, 129, 90], 256, 4, 2
+    plan = B.cf_build_chunks_ex(lens, C, B.CF_PLAN_MERGE_TAILS) if merge else B.cf_build_chunks(lens, C)
+    vals = lambda sid, L: inputs.seq_values(5, sid, L, Hq, Hkv, D, dtype)
+    eng = ChunkAttention(plan, Hq, Hkv, D, dtype, flags=flags).load(vals)
+    results = []
+    for together in (False, True):
+        eng.grad_arena.normal_(generator=torch.Generator(device="cuda:0").manual_seed(1))       # (they are added to)
+        eng.run_forward()
+        if together:
+            eng.run_backward()
+        else:
+            for c in eng.backward_order():
+                B.cf_attn_bwd(eng.chunks[c]["bwd"])
+        torch.cuda.synchronize()
+        results.append((eng.grad_arena.clone(), [ch["d_q"].clone() for ch in eng.chunks]))
+    (g0, q0), (g1, q1) = results
+    assert all(torch.equal(a, b) for a, b in zip(q0, q1))
+    assert ((g0 - g1).norm() / g0.norm()).item() <= 64 * 2.0 ** -24
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
