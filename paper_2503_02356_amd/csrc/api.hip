@@ -265,6 +265,8 @@ bool any_meet(const Range *a, int na, const Range *c, int nc)
     return false;
 }
 bool adds_meet(const Touched &a, const Touched &c) { return any_meet(a.adds, a.n_adds, c.adds, c.n_adds); }
+// Kernels with one writer per gradient row take both calls in one launch.
+bool chains(const Call &a, const Touched &ta, const Call &c, const Touched &tc) { return !adds_meet(ta, tc) || cf::same_key_rows(*a.b, *c.b); }
 // Apart from gradients that both add to, neither reads or writes what the other writes.
 bool independent(const Touched &a, const Touched &c)
 {
@@ -286,24 +288,26 @@ int launch_together(const Call *calls, const Touched *t, int n, hipStream_t s, c
         cf::BwdBatchChunk chunks[cf::CF_BWD_BATCH_MAX];
         for (int c = 0, first = 0; c < n; ++c) {
             bool apart = c > 0;
-            for (int a = first; a < c; ++a) apart = apart && !adds_meet(t[a], t[c]);
+            for (int a = first; a < c; ++a) apart = apart && chains(calls[a], t[a], calls[c], t[c]);
             if (!apart) first = c;
             chunks[c] = {calls[c].b, calls[c].ws, apart};
         }
         e = cf::launch_mfma_bwd_batch(chunks, n, s);
         return e == hipSuccess ? CF_OK : hip_fail(who, e);
     }
+    if (calls[0].b) {
+        const cf_attn_bwd_params *bwd[cf::CF_BWD_BATCH_MAX];
+        for (int c = 0; c < n; ++c) bwd[c] = calls[c].b;
+        e = cf::launch_f32_bwd_batch(bwd, n, s);
+        return e == hipSuccess ? CF_OK : hip_fail(who, e);
+    }
     // heaviest first: the order in which the workgroups are dealt (work ~ queries x keys)
-    int order[cf::CF_FWD_BATCH_MAX];
-    for (int i = 0; i < n; ++i) order[i] = i;
-    std::stable_sort(order, order + n, [&](int x, int y) {
-        return (int64_t)calls[x].f->n_tokens * calls[x].f->n_kv_tokens > (int64_t)calls[y].f->n_tokens * calls[y].f->n_kv_tokens;
-    });
     const cf_attn_fwd_params *fwd[cf::CF_FWD_BATCH_MAX];
-    const cf_attn_bwd_params *bwd[cf::CF_FWD_BATCH_MAX];
-    for (int i = 0; i < n; ++i) fwd[i] = calls[order[i]].f, bwd[i] = calls[order[i]].b;
-    if (calls[0].b) e = cf::launch_f32_bwd_batch(bwd, n, s);
-    else e = path_of(calls[0]) == kMfma ? cf::launch_mfma_fwd_batch(fwd, n, s) : cf::launch_f32_fwd_batch(fwd, n, s);
+    for (int i = 0; i < n; ++i) fwd[i] = calls[i].f;
+    std::stable_sort(fwd, fwd + n, [](const cf_attn_fwd_params *x, const cf_attn_fwd_params *y) {
+        return (int64_t)x->n_tokens * x->n_kv_tokens > (int64_t)y->n_tokens * y->n_kv_tokens;
+    });
+    e = path_of(calls[0]) == kMfma ? cf::launch_mfma_fwd_batch(fwd, n, s) : cf::launch_f32_fwd_batch(fwd, n, s);
     return e == hipSuccess ? CF_OK : hip_fail(who, e);
 }
 
@@ -327,7 +331,7 @@ int launch_calls(const Call *calls, int n, hipStream_t s, const char *who)
                 t[j] = touched(calls[j]);
                 bool apart = true;
                 for (int a = i; a < j && apart; ++a)
-                    apart = independent(t[a], t[j]) && !(path_of(calls[j]) == kF32 && adds_meet(t[a], t[j]));
+                    apart = independent(t[a], t[j]) && (!calls[j].b || path_of(calls[j]) != kF32 || chains(calls[a], t[a], calls[j], t[j]));
                 if (!apart) break;
             }
             if (int rc = launch_together(calls + i, t + i, j - i, s, who)) return rc;

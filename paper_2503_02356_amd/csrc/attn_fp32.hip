@@ -25,8 +25,8 @@
 // Errors against fp64 are no larger than the scalar kernels' (step of 1 head, D = 64, 1286 tokens, relative: dQ 3.2e-7, dK 3.5e-7,
 // dV 2.6e-7, O 1.8e-7; scalar 3.3e-7, 3.8e-7, 3.2e-7, 2.0e-7).
 //
-// Measured, forward + backward of a whole step, calls sharing launches: 6 chunks, 1286 tokens, 1 head, D = 64: 764 us -> 56 us;
-// 6 / 2 heads, D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 0.93 ms (before: one wavefront per row, scalar loads;
+// Measured, forward + backward of a whole step, calls sharing launches: 6 chunks, 1286 tokens, 1 head, D = 64: 764 us -> 51 us;
+// 6 / 2 heads, D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 0.89 ms (before: one wavefront per row, scalar loads;
 // attn_simple.hip).
 #include <hip/hip_runtime.h>
 
@@ -247,11 +247,12 @@ __device__ __forceinline__ void f32_fwd_body(const cf_attn_fwd_params &p, int id
 template <int D>
 __global__ __launch_bounds__(NW * 64) void f32_fwd_kernel(cf_attn_fwd_params p) { f32_fwd_body<D>(p, blockIdx.x); }
 
-// Several chunks in one launch: workgroups [first_block[c], first_block[c + 1]) belong to chunk c.
+// Several chunks in one launch: workgroups [first_block[c], first_block[c + 1]) belong to chunk c, the first dkv_blocks[c] of
+// them to the key rows of c and the chunks chained behind it.
 template <typename Params, int MAX>
 struct Batch {
     int n;
-    int first_block[MAX + 1], dkv_blocks[MAX];
+    int first_block[MAX + 1], dkv_blocks[MAX], next[MAX];
     Params p[MAX];
     __device__ __forceinline__ int chunk_of(int id) const
     {
@@ -259,11 +260,12 @@ struct Batch {
         while (c + 1 < n && id >= first_block[c + 1]) ++c;
         return c;
     }
-    bool append(const Params &chunk, int64_t dkv, int64_t others)
+    bool append(const Params &chunk, int64_t dkv, int64_t others, int next_chunk = -1)
     {
         if (first_block[n] + dkv + others > 0x7fffffffLL) return false;
         p[n] = chunk;
         dkv_blocks[n] = (int)dkv;
+        next[n] = next_chunk;
         first_block[n + 1] = first_block[n] + (int)(dkv + others);
         ++n;
         return true;
@@ -507,22 +509,40 @@ __device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id
 }
 
 template <int D>
-__device__ __forceinline__ void f32_bwd_body(const cf_attn_bwd_params &b, int id, int dkv_blocks)
-{
+struct BwdLds {
     using S = Shape<D>;
-    constexpr int OPERANDS = 2 * S::OPERAND + RB * 4, PARTS = (S::BOTH_MEET ? 2 : 1) * NW * S::PART * 4;
-    __shared__ __attribute__((aligned(16))) char smem[OPERANDS > PARTS ? OPERANDS : PARTS];
+    static constexpr int OPERANDS = 2 * S::OPERAND + RB * 4, PARTS = (S::BOTH_MEET ? 2 : 1) * NW * S::PART * 4;
+    static constexpr int bytes = OPERANDS > PARTS ? OPERANDS : PARTS;
+};
+template <int D>
+__global__ __launch_bounds__(NW * 64) void f32_bwd_kernel(cf_attn_bwd_params b, int dkv_blocks)
+{
+    __shared__ __attribute__((aligned(16))) char smem[BwdLds<D>::bytes];
     __shared__ __attribute__((aligned(16))) float stat[NW][2 * RB];
+    const int id = blockIdx.x;
     if (id < dkv_blocks) f32_dkv_body<D>(b, id, smem, stat);
     else f32_dq_body<D>(b, id - dkv_blocks, smem);
 }
-template <int D>
-__global__ __launch_bounds__(NW * 64) void f32_bwd_kernel(cf_attn_bwd_params b, int dkv_blocks) { f32_bwd_body<D>(b, blockIdx.x, dkv_blocks); }
+// Slices of one sequence add to the same dK/dV rows.  One workgroup adds to 16 of them for all slices of the launch, slice by
+// slice as the calls would, so that a split sequence does not take a launch per slice, each ending with one
+// workgroup's chain on a nearly empty chip (the two steps above, a sequence in 3 slices each: 56.0 -> 51.4 us, 928 -> 889).
 template <int D>
 __global__ __launch_bounds__(NW * 64) void f32_bwd_batch_kernel(BwdBatch q)
 {
-    const int c = q.chunk_of(blockIdx.x);
-    f32_bwd_body<D>(q.p[c], blockIdx.x - q.first_block[c], q.dkv_blocks[c]);
+    __shared__ __attribute__((aligned(16))) char smem[BwdLds<D>::bytes];
+    __shared__ __attribute__((aligned(16))) float stat[NW][2 * RB];
+    int c = q.chunk_of(blockIdx.x);
+    const int id = blockIdx.x - q.first_block[c];
+    if (id >= q.dkv_blocks[c]) {
+        f32_dq_body<D>(q.p[c], id - q.dkv_blocks[c], smem);
+        return;
+    }
+    for (;;) {
+        f32_dkv_body<D>(q.p[c], id, smem, stat);
+        c = q.next[c];
+        if (c < 0) return;
+        __syncthreads();                             // the rows that other wavefronts have written, and LDS
+    }
 }
 
 // Upper bounds on block counts: sum_g ceil(L_g / 16) <= total / 16 + n_segments.
@@ -581,10 +601,17 @@ hipError_t launch_f32_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, 
 hipError_t launch_f32_bwd_batch(const cf_attn_bwd_params *const *chunks, int n, hipStream_t s)
 {
     if (n < 1 || n > CF_BWD_BATCH_MAX) return hipErrorInvalidValue;
+    const CallChains<CF_BWD_BATCH_MAX> chain(n, [&](int c) -> const cf_attn_bwd_params & { return *chunks[c]; });
+    int place[CF_BWD_BATCH_MAX];
+    for (int i = 0; i < n; ++i) place[chain.order[i]] = i;
     BwdBatch q;
     q.n = q.first_block[0] = 0;
-    for (int c = 0; c < n; ++c)
-        if (!q.append(*chunks[c], key_blocks(chunks[c]->f), query_blocks(chunks[c]->f))) return hipErrorInvalidConfiguration;
+    for (int i = 0; i < n; ++i) {
+        const int c = chain.order[i];
+        int64_t dkv = 0;                             // a chain's key rows go with its first call: as many as its longest one has
+        for (int a = c; chain.head[c] == c && a >= 0; a = chain.next[a]) dkv = std::max(dkv, key_blocks(chunks[a]->f));
+        if (!q.append(*chunks[c], dkv, query_blocks(chunks[c]->f), chain.next[c] < 0 ? -1 : place[chain.next[c]])) return hipErrorInvalidConfiguration;
+    }
     const dim3 grid((unsigned)q.first_block[n]);
     if (chunks[0]->f.head_dim == 64) f32_bwd_batch_kernel<64><<<grid, NW * 64, 0, s>>>(q);
     else f32_bwd_batch_kernel<128><<<grid, NW * 64, 0, s>>>(q);

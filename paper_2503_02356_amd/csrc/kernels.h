@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "chunkflow.h"
 
 namespace cf {
@@ -37,9 +39,44 @@ constexpr int64_t kMostWorkItems = 0xffffffffLL;
 // fp32 matrix kernels, head_dim 64 and 128; the backward is one launch and needs no scratch.
 hipError_t launch_f32_fwd(const cf_attn_fwd_params &p, hipStream_t s);
 hipError_t launch_f32_bwd(const cf_attn_bwd_params &p, hipStream_t s);
-// Several chunks of one head_dim as one launch (limits as for the bf16 kernels below); the backward's d_k / d_v disjoint.
+// Several chunks of one head_dim as one launch (limits as for the bf16 kernels below).  Backward: in the order of the calls, those
+// that add to the same rows of d_k / d_v same_key_rows().
 hipError_t launch_f32_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s);
 hipError_t launch_f32_bwd_batch(const cf_attn_bwd_params *const *chunks, int n, hipStream_t s);
+
+// Single slices whose key row r adds to the same rows of d_k and d_v for every r: key tile t of the one is key tile t of the other.
+inline bool same_key_rows(const cf_attn_bwd_params &a, const cf_attn_bwd_params &b)
+{
+    return a.f.n_segments == 1 && b.f.n_segments == 1 && a.d_k == b.d_k && a.d_v == b.d_v && a.dkv_stride_tok == b.dkv_stride_tok &&
+           a.dkv_stride_head == b.dkv_stride_head;
+}
+// Chains of such calls, each in the order of the calls: where one writer per row adds for all slices of a sequence, these share a
+// launch and every workgroup of the chain's first call goes through the chain (which gives the bits of separate launches).
+//   head[c]  first call of c's chain        next[c]  the call behind c in it, -1: none
+//   order    the calls by the work of their chain (queries x keys), heaviest first, a chain's calls next to each other
+template <int MAX>
+struct CallChains {
+    int head[MAX], next[MAX], order[MAX];
+    template <typename CallAt>
+    CallChains(int n, CallAt call)
+    {
+        int64_t work[MAX];
+        for (int c = 0; c < n; ++c) {
+            head[c] = order[c] = c;
+            next[c] = -1;
+            work[c] = (int64_t)call(c).f.n_tokens * call(c).f.n_kv_tokens;
+            for (int a = c - 1; a >= 0 && head[c] == c; --a)
+                if (same_key_rows(call(a), call(c))) {
+                    head[c] = head[a];
+                    next[a] = c;
+                    work[head[c]] += work[c];
+                }
+        }
+        std::stable_sort(order, order + n, [&](int x, int y) {
+            return work[head[x]] != work[head[y]] ? work[head[x]] > work[head[y]] : head[x] < head[y];
+        });
+    }
+};
 
 // Plain scalar kernels: any supported head_dim, fp32 or bf16 storage, fp32 arithmetic.
 hipError_t launch_simple_fwd(const cf_attn_fwd_params &p, hipStream_t s);
@@ -55,12 +92,12 @@ constexpr int CF_FWD_BATCH_MAX = 16;
 hipError_t launch_mfma_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s);
 hipError_t launch_mfma_bwd(const cf_attn_bwd_params &p, const BwdWorkspace &ws, hipStream_t s);
 // Backward of 1..CF_BWD_BATCH_MAX chunks: one dQ launch, then the dK/dV kernels, one launch per run of chunks that go with
-// their predecessor: those with work lists, and at head_dim 64 those that add to rows of their own.
+// their predecessor: those with work lists, and at head_dim 64 those that add to rows of their own or to the same_key_rows().
 constexpr int CF_BWD_BATCH_MAX = 8;
 struct BwdBatchChunk {
     const cf_attn_bwd_params *b;
     BwdWorkspace ws;
-    bool rows_of_its_own;        // its d_k / d_v rows are none of its predecessors', back to the last chunk without this
+    bool chains;                 // its d_k / d_v rows are none of its predecessors' or the same_key_rows(), back to the last chunk without this
 };
 hipError_t launch_mfma_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s);
 

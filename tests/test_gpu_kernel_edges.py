@@ -120,6 +120,33 @@ def test_slices_that_add_to_the_same_rows(dtype, D, flags, merge):
     assert ((g0 - g1).norm() / g0.norm()).item() <= 64 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp32", 64), ("fp32", 128)])
+@pytest.mark.parametrize("backwards", [False, True])
+def test_chains_of_slices_keep_the_bits_of_single_calls(dtype, D, backwards):
+    """Split sequences and packed chunks, 22 backward calls (three launches, chains cut between them): slices that end inside a
+    block of 16 or 32 keys, the first call of a chain its longest or its shortest one.  Same bits as one call at a time."""
+    lens, C, Hq, Hkv = [333, 210, 20, 71, 130, 9, 64, 290, 65, 33, 100], 70, 4, 2
+    plan = B.cf_build_chunks(lens, C)
+    vals = lambda sid, L: inputs.seq_values(8, sid, L, Hq, Hkv, D, dtype)
+    eng = ChunkAttention(plan, Hq, Hkv, D, dtype).load(vals)
+    eng.run_forward()
+    order = eng.backward_order()[::-1] if backwards else eng.backward_order()
+    assert len(order) > 12 and sum(len(plan.group(g)) > 2 for g in eng.groups()) >= 3
+    got = []
+    for together in (False, True):
+        eng.grad_arena.normal_(generator=torch.Generator(device="cuda:0").manual_seed(1))       # (they are added to)
+        if together:
+            ws = [torch.empty_like(eng.workspaces[0]) for _ in order]
+            calls = [B.make_bwd_params(c["fwd"], c["d_o"], c["d_q"], c["dk"], c["dv"], w) for c, w in zip((eng.chunks[c] for c in order), ws)]
+            B.cf_attn_calls(B.make_calls((True, b) for b in calls))
+        else:
+            for c in order:
+                B.cf_attn_bwd(eng.chunks[c]["bwd"])
+        torch.cuda.synchronize()
+        got.append([eng.grad_arena.clone()] + [ch["d_q"].clone() for ch in eng.chunks])
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 def test_calls_that_depend_on_each_other(dtype):
     """The second forward takes the first one's output as its queries; the list stops at a call that is refused."""
