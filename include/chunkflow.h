@@ -310,8 +310,9 @@ int cf_attn_bwd_static(const cf_attn_bwd_params *p, void *hip_stream);
  * forward, 8 backward) that do not touch each other's results becomes ONE launch per kernel, whose workgroups are
  * dealt heaviest chunk first: the last, partly filled wave of workgroups of a big chunk is filled by the next
  * chunk's, and small chunks fill the GPU together.  In the backward, chunks that add to the same dK/dV rows share
- * the dQ launch only (bf16, where each dK/dV row has one writer per launch: head_dim 64, CF_FLAG_DKV_SINGLE_WRITER, many
- * key tiles), both (bf16, where atomic adds are made anyway) or no launch (fp32).
+ * all launches where atomic adds are made anyway (bf16 at head_dim 128) or where the chunks are single slices with the same
+ * d_k, d_v and strides (fp32, head_dim 64: one workgroup adds for all of them, in order); otherwise the dQ launch
+ * only (bf16 with one writer per dK/dV row: also CF_FLAG_DKV_SINGLE_WRITER, many key tiles) or none (fp32).
  *   params  host array [n]; for the backward every chunk needs a workspace of its OWN (they are in use at
  *           the same time; overlapping workspaces -> CF_EINVAL)
  * Errors: as the single-chunk calls, checked for every chunk before anything is enqueued; n == 0 is a no-op.
