@@ -306,8 +306,8 @@ int cf_attn_bwd_static(const cf_attn_bwd_params *p, void *hip_stream);
  * Whole-plan launches: several chunks in one call.  The results are those of calling cf_attn_fwd /
  * cf_attn_bwd for params[0], params[1], ... in that order on the stream (dK/dV that several chunks share --
  * the chunks of one long sequence, section 4.2 -- accumulate in exactly that order).  What changes is the
- * launch shape: a run of consecutive chunks on the same matrix kernels (dtype, head counts, head_dim; up to 16
- * forward, 8 backward) that do not touch each other's results becomes ONE launch per kernel, whose workgroups are
+ * launch shape: a run of consecutive chunks on the same matrix kernels (dtype, head counts, head_dim; up to 16)
+ * that do not touch each other's results becomes ONE launch per kernel, whose workgroups are
  * dealt heaviest chunk first: the last, partly filled wave of workgroups of a big chunk is filled by the next
  * chunk's, and small chunks fill the GPU together.  In the backward, chunks that add to the same dK/dV rows share
  * all launches where atomic adds are made anyway (bf16 at head_dim 128) or where the chunks are single slices with the same

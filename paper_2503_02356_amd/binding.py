@@ -344,7 +344,7 @@ def cf_attn_bwd_batch(params_arr, stream=None):
     _check(lib().cf_attn_bwd_batch(params_arr, n, stream if stream is not None else _stream()))
 
 
-BWD_TOGETHER = 8          # backward calls that cf_attn_calls puts into one launch at most (CF_BWD_BATCH_MAX in csrc/kernels.h)
+BWD_TOGETHER = 16         # backward calls that cf_attn_calls puts into one launch at most (CF_BWD_BATCH_MAX in csrc/kernels.h)
 
 
 def make_calls(ops):

@@ -272,7 +272,8 @@ struct Batch {
     }
 };
 using FwdBatch = Batch<cf_attn_fwd_params, CF_FWD_BATCH_MAX>;
-using BwdBatch = Batch<cf_attn_bwd_params, CF_BWD_BATCH_MAX>;
+using BwdBatch = Batch<BwdArgs, CF_BWD_BATCH_MAX>;
+static_assert(sizeof(BwdBatch) <= 4096 && sizeof(FwdBatch) <= 4096, "kernel arguments");
 template <int D>
 __global__ __launch_bounds__(NW * 64) void f32_fwd_batch_kernel(FwdBatch q)
 {
@@ -291,10 +292,10 @@ __device__ __forceinline__ float probability(float s, float scale, float lse)
 
 // dQ of 16 query rows of one head.
 template <int D>
-__device__ __forceinline__ void f32_dq_body(const cf_attn_bwd_params &b, int id, char *smem)
+__device__ __forceinline__ void f32_dq_body(const BwdArgs &b, int id, char *smem)
 {
     using S = Shape<D>;
-    const cf_attn_fwd_params &p = b.f;
+    const BwdArgs::Fwd &p = b.f;
     f32x4 *qs = (f32x4 *)smem, *dos = (f32x4 *)(smem + S::OPERAND);
     float *del_s = (float *)(smem + 2 * S::OPERAND);
     float *parts = (float *)smem;                    // takes the place of the operands once all wavefronts are done
@@ -397,10 +398,10 @@ __device__ __forceinline__ void f32_dq_body(const cf_attn_bwd_params &b, int id,
 // dK, dV of 16 key rows of one key/value head: (query head of the group, 16-row query block) pairs dealt over the
 // wavefronts.
 template <int D>
-__device__ __forceinline__ void f32_dkv_body(const cf_attn_bwd_params &b, int id, char *smem, float (*stat)[2 * RB])
+__device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *smem, float (*stat)[2 * RB])
 {
     using S = Shape<D>;
-    const cf_attn_fwd_params &p = b.f;
+    const BwdArgs::Fwd &p = b.f;
     f32x4 *ks = (f32x4 *)smem, *vs = (f32x4 *)(smem + S::OPERAND);
     float *parts = (float *)smem;
     const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
@@ -515,7 +516,7 @@ struct BwdLds {
     static constexpr int bytes = OPERANDS > PARTS ? OPERANDS : PARTS;
 };
 template <int D>
-__global__ __launch_bounds__(NW * 64) void f32_bwd_kernel(cf_attn_bwd_params b, int dkv_blocks)
+__global__ __launch_bounds__(NW * 64) void f32_bwd_kernel(BwdArgs b, int dkv_blocks)
 {
     __shared__ __attribute__((aligned(16))) char smem[BwdLds<D>::bytes];
     __shared__ __attribute__((aligned(16))) float stat[NW][2 * RB];

@@ -92,7 +92,7 @@ __host__ __device__ inline int64_t dkv_items_most(const cf_attn_fwd_params &p)
 // of its own).
 // Segment bounds pass through LDS 256 at a time (one coalesced load instead of a chain of dependent ones); a wavefront
 // takes every fourth segment, its lanes the key tiles.
-__device__ __forceinline__ void build_dkv_worklist(const cf_attn_fwd_params &p, int *wl, int capacity, int slots)
+__device__ __forceinline__ void build_dkv_worklist(const BwdArgs::Fwd &p, int *wl, int capacity, int slots)
 {
     __shared__ int bucket[kDurationBuckets];        // items per duration, then the next free slot of each duration
     __shared__ int seg_lq[256], seg_lk[256];
@@ -196,7 +196,7 @@ struct DkvStage {
 // rounding would be the largest error in dK/dV.  At D = 64 P and dS enter every product with all their 24 bits instead, as
 // three bf16 operands.
 template <int D, bool FUSED_HEADS>
-__device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const float *__restrict__ delta, int id,
+__device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restrict__ delta, int id,
                                          const int *__restrict__ wl, char *st0, char *st1)
 {
     using Stage = DkvStage<D>;
@@ -204,7 +204,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
     constexpr int KS = D / F::K, DB = D / 32, N = F::N32, BLOCK = 32 * 2 * D;
     constexpr int QW = DkvShape<D>::QW, BQ = DkvShape<D>::BQ, BKV = DkvShape<D>::BKV;
     static_assert(FUSED_HEADS || QW == 1, "atomic updates are made by the wavefront that owns the keys");
-    const cf_attn_fwd_params &p = b.f;
+    const BwdArgs::Fwd &p = b.f;
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), key_wave = wave / QW, query_wave = wave % QW;
 
     // Block id -> (item, key/value head); the key/value head varies fastest (XCD L2 locality, see forward).
@@ -549,7 +549,7 @@ __device__ __forceinline__ void dkv_body(const cf_attn_bwd_params &b, const floa
 }
 
 template <int D, bool FUSED_HEADS>
-__global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(cf_attn_bwd_params b, const float *__restrict__ delta, const int *__restrict__ wl)
+__global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(BwdArgs b, const float *__restrict__ delta, const int *__restrict__ wl)
 {
     // Separate arrays (not one array with parts): the compiler must see that the direct-to-LDS copy of a coming
     // tile cannot alias the reads of the tile in use, or it waits for the copy too early.
@@ -566,8 +566,9 @@ struct BwdBatch {
     int capacity[CF_BWD_BATCH_MAX], slots[CF_BWD_BATCH_MAX];     // of the work list that is built (see there)
     float *delta[CF_BWD_BATCH_MAX];
     int *wl[CF_BWD_BATCH_MAX];                                   // nullptr: no list (one workgroup per key tile)
-    cf_attn_bwd_params b[CF_BWD_BATCH_MAX];
+    BwdArgs b[CF_BWD_BATCH_MAX];
 };
+static_assert(sizeof(BwdBatch) <= 4096, "kernel arguments");
 __device__ __forceinline__ int chunk_of(const BwdBatch &q, int id)
 {
     int c = 0;
@@ -617,11 +618,11 @@ struct KvStage {
 // LDS, where the first has left them, and no tile's second half is computed where no row sees it.  Steps of 16 packed chunks, 28 / 4
 // heads: 512 tokens around 37 each 297 -> 269 us, 8192 around 600 9.31 -> 9.05 ms; 16 / 4 heads, D = 64, 16.7k tokens 979 -> 940 us.
 template <int D>
-__device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__restrict__ delta, int id, char *stage_a, char *stage_b)
+__device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ delta, int id, char *stage_a, char *stage_b)
 {
     using F = Mfma<D>;
     constexpr int KS = D / F::K, DB = D / F::M, N = F::N32, KVTILE_BYTES = KvStage<D>::tile_bytes;
-    const cf_attn_fwd_params &p = b.f;
+    const BwdArgs::Fwd &p = b.f;
     const int wave = wave_id(), group = F::group(), col = F::column();
 
     const int G = p.n_q_heads / p.n_kv_heads;
@@ -872,7 +873,7 @@ __device__ __forceinline__ void dq_body(const cf_attn_bwd_params &b, float *__re
 
 // wl != nullptr: the launch has one extra workgroup (the first) that builds the dK/dV work list.
 template <int D>
-__global__ __launch_bounds__(256, 2) void mfma_dq_kernel(cf_attn_bwd_params b, float *__restrict__ delta, int *wl, int capacity)
+__global__ __launch_bounds__(256, 2) void mfma_dq_kernel(BwdArgs b, float *__restrict__ delta, int *wl, int capacity)
 {
     // The list builder is workgroup 0: it starts with the first wave of workgroups and is long done when the
     // launch ends (as the last workgroup it would start last and could be what the launch ends with).

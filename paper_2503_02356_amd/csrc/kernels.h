@@ -44,6 +44,42 @@ hipError_t launch_f32_bwd(const cf_attn_bwd_params &p, hipStream_t s);
 hipError_t launch_f32_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s);
 hipError_t launch_f32_bwd_batch(const cf_attn_bwd_params *const *chunks, int n, hipStream_t s);
 
+// What the matrix kernels of the backward read of a call, and what a launch of several calls needs for each of them: 16 of these are a
+// kernel's arguments (4096 bytes; of the calls' own structs 14 would fit).  Names as in cf_attn_bwd_params.  A step of 16 packed chunks of
+// 512 tokens, 28 / 4 heads, in two backward launches per kernel (8 calls each): 269 us, in one: 234; chunks of 8192: no change.
+struct BwdArgs {
+    struct Fwd {
+        float softmax_scale;
+        uint16_t n_q_heads, n_kv_heads;
+        int32_t n_tokens, n_kv_tokens, n_segments, n_q_tiles;
+        const int32_t *cu_seqlens_q, *cu_seqlens_k;
+        const void *q;
+        int64_t q_stride_tok, q_stride_head;
+        const void *k, *v;
+        int64_t kv_stride_tok, kv_stride_head;
+        const void *o;
+        int64_t o_stride_tok, o_stride_head;
+        const float *lse;
+        const cf_q_tile *q_tiles;
+    } f;
+    const void *d_o;
+    int64_t do_stride_tok, do_stride_head;
+    void *d_q;
+    int64_t dq_stride_tok, dq_stride_head;
+    float *d_k, *d_v;
+    int64_t dkv_stride_tok, dkv_stride_head;
+
+    BwdArgs() = default;
+    BwdArgs(const cf_attn_bwd_params &b)
+        : f{b.f.softmax_scale, (uint16_t)b.f.n_q_heads, (uint16_t)b.f.n_kv_heads, b.f.n_tokens, b.f.n_kv_tokens, b.f.n_segments, b.f.n_q_tiles,
+            b.f.cu_seqlens_q, b.f.cu_seqlens_k, b.f.q, b.f.q_stride_tok, b.f.q_stride_head, b.f.k, b.f.v, b.f.kv_stride_tok,
+            b.f.kv_stride_head, b.f.o, b.f.o_stride_tok, b.f.o_stride_head, b.f.lse, b.f.q_tiles},
+          d_o(b.d_o), do_stride_tok(b.do_stride_tok), do_stride_head(b.do_stride_head), d_q(b.d_q), dq_stride_tok(b.dq_stride_tok),
+          dq_stride_head(b.dq_stride_head), d_k(b.d_k), d_v(b.d_v), dkv_stride_tok(b.dkv_stride_tok), dkv_stride_head(b.dkv_stride_head)
+    {
+    }
+};
+
 // Single slices whose key row r adds to the same rows of d_k and d_v for every r: key tile t of the one is key tile t of the other.
 inline bool same_key_rows(const cf_attn_bwd_params &a, const cf_attn_bwd_params &b)
 {
@@ -91,9 +127,9 @@ hipError_t launch_mfma_fwd(const cf_attn_fwd_params &p, hipStream_t s);
 constexpr int CF_FWD_BATCH_MAX = 16;
 hipError_t launch_mfma_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s);
 hipError_t launch_mfma_bwd(const cf_attn_bwd_params &p, const BwdWorkspace &ws, hipStream_t s);
-// Backward of 1..CF_BWD_BATCH_MAX chunks: one dQ launch, then the dK/dV kernels, one launch per run of chunks that go with
+// Backward of 1..CF_BWD_BATCH_MAX (as many as kernel arguments hold) chunks: one dQ launch, then the dK/dV kernels, one launch per run of chunks that go with
 // their predecessor: those with work lists, and at head_dim 64 those that add to rows of their own or to the same_key_rows().
-constexpr int CF_BWD_BATCH_MAX = 8;
+constexpr int CF_BWD_BATCH_MAX = 16;
 struct BwdBatchChunk {
     const cf_attn_bwd_params *b;
     BwdWorkspace ws;

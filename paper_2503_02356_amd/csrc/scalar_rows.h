@@ -2,6 +2,7 @@
 // read.  The scalar kernels are made of these; the matrix kernels that stand in for them take a row from here when its result
 // is not finite: they multiply whole blocks, hidden pairs by zero, and zero times an infinity or a NaN of a later row would
 // reach rows that do not see it.
+//   B  the parameters of a backward call: cf_attn_bwd_params or what a kernel takes of it (BwdArgs)
 //   row operands are passed as functions of the element index (LDS copies, or the global row itself)
 //   UNROLL  of the loops over the elements of a row: small in the matrix kernels, whose registers are not to be spilled for it
 #pragma once
@@ -94,10 +95,10 @@ __device__ inline void scalar_fwd_row(const cf_attn_fwd_params &p, const Segment
 }
 
 // dQ of query row `row` of head h.
-template <typename T, int D, int UNROLL, typename Q, typename DO>
-__device__ inline void scalar_dq_row(const cf_attn_bwd_params &b, const SegmentRows &g, int row, int h, Q q, DO d_o, float delta)
+template <typename T, int D, int UNROLL, typename B, typename Q, typename DO>
+__device__ inline void scalar_dq_row(const B &b, const SegmentRows &g, int row, int h, Q q, DO d_o, float delta)
 {
-    const cf_attn_fwd_params &p = b.f;
+    const auto &p = b.f;
     const int lane = threadIdx.x & 63, kh = h / (p.n_q_heads / p.n_kv_heads);
     const int n_vis = g.lk - g.lq + (row - g.q0) + 1;
     const T *kb = (const T *)p.k + (int64_t)kh * p.kv_stride_head;
@@ -132,11 +133,11 @@ __device__ inline void scalar_dq_row(const cf_attn_bwd_params &b, const SegmentR
 
 // What all query heads of key/value head kh add to dK and dV of key row `krow` (element lane + 64 t; dK without the scale).
 // delta(row, h): of a query row.
-template <typename T, int D, int UNROLL, typename K, typename V, typename Delta>
-__device__ inline void scalar_dkv_row(const cf_attn_bwd_params &b, const SegmentRows &g, int krow, int kh, K k, V v, Delta delta,
+template <typename T, int D, int UNROLL, typename B, typename K, typename V, typename Delta>
+__device__ inline void scalar_dkv_row(const B &b, const SegmentRows &g, int krow, int kh, K k, V v, Delta delta,
                                       float (&dk)[D / 64], float (&dv)[D / 64])
 {
-    const cf_attn_fwd_params &p = b.f;
+    const auto &p = b.f;
     const int lane = threadIdx.x & 63, G = p.n_q_heads / p.n_kv_heads;
     const int j = krow - g.k0, prefix = g.lk - g.lq;
     const int i_first = j > prefix ? j - prefix : 0;  // first query row that sees this key
@@ -174,10 +175,10 @@ __device__ inline void scalar_dkv_row(const cf_attn_bwd_params &b, const Segment
 }
 
 // delta of a query row, formed by each lane for itself: <dO, O>, and for rows that see at most 64 keys sum_j P_j <dO, v_j>.
-template <typename T, int D>
-__device__ inline float scalar_delta(const cf_attn_bwd_params &b, const SegmentRows &g, int row, int h)
+template <typename T, int D, typename B>
+__device__ inline float scalar_delta(const B &b, const SegmentRows &g, int row, int h)
 {
-    const cf_attn_fwd_params &p = b.f;
+    const auto &p = b.f;
     const int n_vis = g.lk - g.lq + (row - g.q0) + 1, kh = h / (p.n_q_heads / p.n_kv_heads);
     const T *d_o = row_of<T>(b.d_o, row, b.do_stride_tok, h, b.do_stride_head);
     float sum = 0.f;

@@ -123,7 +123,7 @@ def test_slices_that_add_to_the_same_rows(dtype, D, flags, merge):
 @pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp32", 64), ("fp32", 128)])
 @pytest.mark.parametrize("backwards", [False, True])
 def test_chains_of_slices_keep_the_bits_of_single_calls(dtype, D, backwards):
-    """Split sequences and packed chunks, 22 backward calls (three launches, chains cut between them): slices that end inside a
+    """Split sequences and packed chunks, 22 backward calls (two launches, a chain cut between them): slices that end inside a
     block of 16 or 32 keys, the first call of a chain its longest or its shortest one.  Same bits as one call at a time."""
     lens, C, Hq, Hkv = [333, 210, 20, 71, 130, 9, 64, 290, 65, 33, 100], 70, 4, 2
     plan = B.cf_build_chunks(lens, C)
