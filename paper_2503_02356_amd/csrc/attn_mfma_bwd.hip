@@ -278,7 +278,7 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     auto issue_tile = [&](char *stage) {
         const int h = nx_h, q0 = nx_qt * BQ, lane_ = fresh_lane();
         const int64_t row0 = q_seg0 + q0;
-        TileDma<BQ, D> dma;
+        TileDma<BQ, D, 4, true> dma;
         dma.init(p.q_stride_tok * 2, wave, lane_);
         dma.issue(uniform((const char *)p.q + (row0 * p.q_stride_tok + (int64_t)h * p.q_stride_head) * 2), lq - 1 - q0, stage);
         dma.init(b.do_stride_tok * 2, wave, lane_);
@@ -309,7 +309,7 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     int cur_qt = qt_start;                           // query tile of the stage in use
     auto do_block = [&](int mb, const char *stage, bool residual) {
         const int q0 = cur_qt * BQ + mb * 32;
-        if (q0 + 31 + off < kw0 || (D == 64 && q0 >= lq)) return;     // no row of the block sees a key of this wavefront
+        if (q0 + 31 + off < kw0 || q0 >= lq) return;     // no row of the block sees a key of this wavefront, or none is a row
         const char *qs = stage, *dos = stage + Stage::tile_bytes;
         const float *stats = (const float *)(stage + 2 * Stage::tile_bytes) + mb * 32 + fresh_lane() / F::M * 4;
         // The A operands of the block's four products pass through a ring of four fragments, each requested four uses
@@ -663,7 +663,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
     const int64_t kv_row_bytes = p.kv_stride_tok * 2;
     const char *kbase = uniform((const char *)p.k + ((int64_t)k_seg0 * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2);
     const char *vbase = uniform((const char *)p.v + ((int64_t)k_seg0 * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2);
-    TileDma<BN, D> dma;
+    TileDma<BN, D, 4, true> dma;
     dma.init(kv_row_bytes);
 
     // Q^T and dO^T fragments (B operands): lane holds row wq0 + M*qb + col, d = K*ks + 8*group + 0..7
