@@ -9,7 +9,10 @@
 // has one writer and is bitwise reproducible.  (32-row units on 32x32x2 MFMAs would leave half the chip idle on a
 // 700-row slice of 6 heads that is launched on its own: 132 workgroups.)
 // Operands go straight from global memory into registers: a wavefront's blocks are its own, so LDS tiles would not be
-// shared.  What the 16 wavefronts share, the owned rows, is kept in LDS in operand order.
+// shared.  What the 16 wavefronts share, the owned rows, is kept in LDS in operand order.  The backward takes a block's rows in
+// two orders, as rows and as columns: they are fetched once, and each wavefront turns them around in a piece of LDS of its own, where
+// its result goes in the end (a second fetch made 40 instead of 24 KB per block of dK/dV at D = 128, 40 bytes per clock and compute
+// unit at the full matrix rate: the two steps below 51.4 -> 45.6 us and 889 -> 790 us, the same bits).
 //
 // Everything is computed with the owned row on the lane axis, as in the bf16 kernels:
 //   forward  S^T = K Q^T              O^T  += V^T P^T           lane % 16 = query
@@ -25,8 +28,8 @@
 // Errors against fp64 are no larger than the scalar kernels' (step of 1 head, D = 64, 1286 tokens, relative: dQ 3.2e-7, dK 3.5e-7,
 // dV 2.6e-7, O 1.8e-7; scalar 3.3e-7, 3.8e-7, 3.2e-7, 2.0e-7).
 //
-// Measured, forward + backward of a whole step, calls sharing launches: 6 chunks, 1286 tokens, 1 head, D = 64: 764 us -> 51 us;
-// 6 / 2 heads, D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 0.89 ms (before: one wavefront per row, scalar loads;
+// Measured, forward + backward of a whole step, calls sharing launches: 6 chunks, 1286 tokens, 1 head, D = 64: 764 us -> 46 us;
+// 6 / 2 heads, D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 0.79 ms (before: one wavefront per row, scalar loads;
 // attn_simple.hip).
 #include <hip/hip_runtime.h>
 
@@ -55,6 +58,7 @@ struct Shape {
     static constexpr int OS = D + 4;         // row stride of a partial result in LDS (spreads float4 rows over the banks)
     static constexpr int PART = RB * OS;     // floats of one wavefront's partial result
     static constexpr int OPERAND = RB * D * 4;   // bytes of 16 staged rows
+    static constexpr int OPERANDS = 2 * OPERAND + RB * 4;    // what the backward stages: two operands, delta
     static constexpr bool BOTH_MEET = D == 64;   // LDS holds the partial results of dK and dV at once
 };
 template <int D>
@@ -112,6 +116,17 @@ __device__ __forceinline__ void load_columns(const float *block, unsigned row_by
         for (int c = 0; c < D / 64; ++c)
             x[i][c] = *(const CF_GLOBAL f32x4 *)(base + ((unsigned)min(4 * quarter + i, last_row) * row_bytes + 16 * m + 256 * c));
 }
+// The same columns of rows that this wavefront already holds (load_row), turned around through its own piece of LDS.  In two
+// parts: the rows may leave their registers in between.
+__device__ __forceinline__ void lds_turn() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"), __builtin_amdgcn_wave_barrier(); }
+template <int D>
+__device__ __forceinline__ void put_rows(const f32x4 (&f)[D / 16], float *piece, int lane)
+{
+    lds_turn();                                      // (what stood there has been read)
+#pragma unroll
+    for (int j = 0; j < D / 16; ++j) *(f32x4 *)(piece + (lane & 15) * Shape<D>::OS + 16 * j + 4 * (lane >> 4)) = f[j];
+    lds_turn();
+}
 // acc^T += X^T w
 template <int D>
 __device__ __forceinline__ void add_column_product(const f32x4 (&x)[4][D / 64], const f32x4 &w, Acc<D> &acc)
@@ -122,6 +137,22 @@ __device__ __forceinline__ void add_column_product(const f32x4 (&x)[4][D / 64], 
         for (int c = 0; c < D / 64; ++c)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[4 * c + e] = mfma_f32(x[i][c][e], w[i], acc[4 * c + e]);
+}
+// acc^T += X^T w, X the rows that stand in this wavefront's piece of LDS
+template <int D>
+__device__ __forceinline__ void add_column_product(const float *piece, int lane, const f32x4 &w, Acc<D> &acc)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (D != 64) __builtin_amdgcn_sched_barrier(0);  // (all of X at once: 34 registers spilled)
+        f32x4 x[D / 64];
+#pragma unroll
+        for (int c = 0; c < D / 64; ++c) x[c] = *(const f32x4 *)(piece + (4 * (lane >> 4) + i) * Shape<D>::OS + 4 * (lane & 15) + 64 * c);
+#pragma unroll
+        for (int c = 0; c < D / 64; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[4 * c + e] = mfma_f32(x[c][e], w[i], acc[4 * c + e]);
+    }
 }
 // A wavefront's transposed result (lane % 16 = owned row) into its part of the LDS scratch.
 template <int D>
@@ -298,7 +329,7 @@ __device__ __forceinline__ void f32_dq_body(const BwdArgs &b, int id, char *smem
     const BwdArgs::Fwd &p = b.f;
     f32x4 *qs = (f32x4 *)smem, *dos = (f32x4 *)(smem + S::OPERAND);
     float *del_s = (float *)(smem + 2 * S::OPERAND);
-    float *parts = (float *)smem;                    // takes the place of the operands once all wavefronts are done
+    float *parts = (float *)(smem + S::OPERANDS);    // of each wavefront: its block's keys, in the end its result
     const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
     const int G = p.n_q_heads / p.n_kv_heads, kh = id % p.n_kv_heads, h = kh * G + id / p.n_kv_heads % G;
     TileLocation loc;
@@ -324,7 +355,6 @@ __device__ __forceinline__ void f32_dq_body(const BwdArgs &b, int id, char *smem
         if (c == 0) del_s[r] = s;
     }
     const float lse = p.lse[(int64_t)h * p.n_tokens + loc.begin + min(q0 + col, lq - 1)];
-    const unsigned kv_row_bytes = (unsigned)p.kv_stride_tok * 4;
     const int amax = q0 + col + off;
     __syncthreads();
     // Rows that see at most 64 keys (large P, large |O|: the rounding of O would be the largest error of dQ) take delta =
@@ -363,11 +393,8 @@ __device__ __forceinline__ void f32_dq_body(const BwdArgs &b, int id, char *smem
         f32x4 kf[S::J], vf[S::J];
         load_row<D>(k + (int64_t)row * p.kv_stride_tok, quarter, kf);
         load_row<D>(v + (int64_t)row * p.kv_stride_tok, quarter, vf);
-        f32x4 x[4][S::NC];
-        auto load_k = [&] { load_columns<D>(k + (int64_t)(kb * RB) * p.kv_stride_tok, kv_row_bytes, lk - 1 - kb * RB, lane, x); };
-        if (D == 64) load_k();
+        put_rows<D>(kf, parts + wave * S::PART, lane);
         const f32x4 s = row_product<D>(kf, qs, lane);
-        if (D != 64) load_k();
         f32x4 dp = row_product<D>(vf, dos, lane);
         const int lim = amax - kb * RB - 4 * quarter;
 #pragma unroll
@@ -375,9 +402,9 @@ __device__ __forceinline__ void f32_dq_body(const BwdArgs &b, int id, char *smem
             const float pv = i > lim ? 0.f : probability(s[i], p.softmax_scale, lse);
             dp[i] = pv * (dp[i] - dlt);
         }
-        add_column_product<D>(x, dp, dq);
+        add_column_product<D>(parts + wave * S::PART, lane, dp, dq);
     }
-    __syncthreads();                                 // the operands have been read for the last time
+    lds_turn();
     if (wave < n_kb) write_part<D>(dq, parts + wave * S::PART, lane);
     __syncthreads();
     const int n = min(NW, n_kb), r = threadIdx.x / (D / 4), c = threadIdx.x % (D / 4);
@@ -403,7 +430,7 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
     using S = Shape<D>;
     const BwdArgs::Fwd &p = b.f;
     f32x4 *ks = (f32x4 *)smem, *vs = (f32x4 *)(smem + S::OPERAND);
-    float *parts = (float *)smem;
+    float *parts = (float *)(smem + S::OPERANDS);    // of each wavefront: its block's rows, in the end its results
     const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
     const int G = p.n_q_heads / p.n_kv_heads, kh = id % p.n_kv_heads;
     TileLocation loc;
@@ -416,8 +443,7 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
     const int n_items = G * n_qb;
     stage_rows<D>((const float *)p.k + (int64_t)loc.begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head, p.kv_stride_tok, k0, lk - 1, ks);
     stage_rows<D>((const float *)p.v + (int64_t)loc.begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head, p.kv_stride_tok, k0, lk - 1, vs);
-    const unsigned q_row_bytes = (unsigned)p.q_stride_tok * 4, do_row_bytes = (unsigned)b.do_stride_tok * 4;
-    float *st = stat[wave];                          // this wavefront's LSE and delta by query row
+    float *piece = parts + wave * S::PART, *st = stat[wave];                          // this wavefront's LSE and delta by query row
     __syncthreads();
 
     Acc<D> dk, dv;
@@ -428,14 +454,12 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
         const float *q = (const float *)p.q + (int64_t)(loc.other_begin + q0) * p.q_stride_tok + (int64_t)h * p.q_stride_head;
         const float *d_o = (const float *)b.d_o + (int64_t)(loc.other_begin + q0) * b.do_stride_tok + (int64_t)h * b.do_stride_head;
         const int last = lq - 1 - q0, row = min(col, last);      // relative to the block's first row
-        // At D = 64 (almost) everything an item reads is requested at once (one latency; short calls are made of those); at
-        // D = 128 there are registers for one or two operands at a time.
-        f32x4 a[S::J], qa[S::J], x[4][S::NC], y[4][S::NC];
+        // At D = 64 everything an item reads is requested at once (one latency; short calls are made of those); at
+        // D = 128 there are registers for one operand at a time.
+        f32x4 a[S::J], qa[S::J];
         load_row<D>(d_o + (int64_t)row * b.do_stride_tok, quarter, a);
         auto load_q_row = [&] { load_row<D>(q + (int64_t)row * p.q_stride_tok, quarter, qa); };
-        auto load_do_columns = [&] { load_columns<D>(d_o, do_row_bytes, last, lane, x); };
-        auto load_q_columns = [&] { load_columns<D>(q, q_row_bytes, last, lane, y); };
-        if (D == 64) load_q_row(), load_do_columns();
+        if (D == 64) load_q_row();
         const float *orow = (const float *)p.o + (int64_t)(loc.other_begin + q0 + row) * p.o_stride_tok + (int64_t)h * p.o_stride_head;
         float dlt = 0.f;
 #pragma unroll
@@ -451,9 +475,9 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
             st[RB + col] = dlt;
         }
         __builtin_amdgcn_wave_barrier();
+        put_rows<D>(a, piece, lane);
         f32x4 dp = row_product<D>(a, vs, lane);
-        if (D == 64) load_q_columns();
-        else load_q_row();
+        if (D != 64) load_q_row();
         f32x4 s = row_product<D>(qa, ks, lane);
         const int lim = k0 + col - off - q0 - 4 * quarter;           // query 4 * quarter + i of the block is masked iff i < lim
         const f32x4 l4 = *(const f32x4 *)(st + 4 * quarter);
@@ -468,9 +492,9 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
 #pragma unroll
         for (int i = 0; i < 4; ++i) dp[i] = s[i] * (dp[i] - d4[i]);
         __builtin_amdgcn_wave_barrier();                             // st is rewritten by the next item
-        if (D != 64) load_do_columns(), load_q_columns();     // (before S: 30 registers spilled)
-        add_column_product<D>(x, s, dv);
-        add_column_product<D>(y, dp, dk);
+        add_column_product<D>(piece, lane, s, dv);
+        put_rows<D>(qa, piece, lane);
+        add_column_product<D>(piece, lane, dp, dk);
     }
     // At D = 64 both results meet in LDS together, at D = 128 there is room for one after the other.
     const int n = min(NW, n_items);
@@ -479,7 +503,8 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
     const int t = threadIdx.x, r = t / (D / 4) % rows, c = t % (D / 4);
     unsigned long long left_out[2 / TOGETHER];       // lanes whose row is not finite
     for (int first = 0; first < 2; first += TOGETHER) {
-        __syncthreads();
+        if (first == 0) lds_turn();
+        else __syncthreads();
         if (wave < n_items) {
             if (first == 0) write_part<D>(dv, parts + wave * S::PART, lane);
             if (first + TOGETHER == 2) write_part<D>(dk, parts + ((TOGETHER - 1) * NW + wave) * S::PART, lane);
@@ -512,8 +537,7 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
 template <int D>
 struct BwdLds {
     using S = Shape<D>;
-    static constexpr int OPERANDS = 2 * S::OPERAND + RB * 4, PARTS = (S::BOTH_MEET ? 2 : 1) * NW * S::PART * 4;
-    static constexpr int bytes = OPERANDS > PARTS ? OPERANDS : PARTS;
+    static constexpr int bytes = S::OPERANDS + (S::BOTH_MEET ? 2 : 1) * NW * S::PART * 4;
 };
 template <int D>
 __global__ __launch_bounds__(NW * 64) void f32_bwd_kernel(BwdArgs b, int dkv_blocks)
