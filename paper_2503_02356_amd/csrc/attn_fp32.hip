@@ -29,7 +29,7 @@
 // dV 2.6e-7, O 1.8e-7; scalar 3.3e-7, 3.8e-7, 3.2e-7, 2.0e-7).
 //
 // Measured, forward + backward of a whole step, calls sharing launches: 6 chunks, 1286 tokens, 1 head, D = 64: 764 us -> 46 us;
-// 6 / 2 heads, D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 0.79 ms (before: one wavefront per row, scalar loads;
+// 6 / 2 heads, D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 0.77 ms (before: one wavefront per row, scalar loads;
 // attn_simple.hip).
 #include <hip/hip_runtime.h>
 
@@ -64,6 +64,12 @@ struct Shape {
 template <int D>
 using Acc = f32x4[D / 16];                   // [4 * c + e], register i: column 64 c + 4 * (4 * quarter + i) + e
 
+// The lane, formed anew at D = 128: there dK/dV fills the 128 registers, and what the compiler keeps of the lane from one use to the next,
+// or over a chain of slices, it makes room for by spilling (26 registers with slices in a chain, reloaded in the loop over blocks:
+// 3 packed chunks of 532 tokens, 4 heads: 67.4 us a step, 60.2 with none; the 4799 tokens below 793 -> 771).
+template <int D>
+__device__ __forceinline__ int lane_of() { return D == 64 ? threadIdx.x & 63 : fresh_lane(); }
+
 // Combines over the 16 lanes of a quarter (rotations inside a row of 16 lanes).
 template <int N>
 __device__ __forceinline__ float add_rotated(float x)
@@ -83,7 +89,7 @@ __device__ __forceinline__ void load_row(const float *row, int quarter, f32x4 (&
 template <int D>
 __device__ __forceinline__ void stage_rows(const float *base, int64_t stride, int row0, int last_row, f32x4 *dst)
 {
-    for (int t = threadIdx.x; t < RB * D / 4; t += NW * 64) {
+    for (int t = wave_id() * 64 + lane_of<D>(); t < RB * D / 4; t += NW * 64) {
         const int r = t / (D / 4), c = t % (D / 4);
         dst[c * RB + r] = *(const f32x4 *)(base + (int64_t)min(row0 + r, last_row) * stride + c * 4);
     }
@@ -431,7 +437,7 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
     const BwdArgs::Fwd &p = b.f;
     f32x4 *ks = (f32x4 *)smem, *vs = (f32x4 *)(smem + S::OPERAND);
     float *parts = (float *)(smem + S::OPERANDS);    // of each wavefront: its block's rows, in the end its results
-    const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
+    const int wave = wave_id();
     const int G = p.n_q_heads / p.n_kv_heads, kh = id % p.n_kv_heads;
     TileLocation loc;
     if (!locate_tile(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, p.n_kv_tokens, RB, id / p.n_kv_heads, loc)) return;
@@ -450,6 +456,7 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
 #pragma unroll
     for (int x = 0; x < D / 16; ++x) dk[x] = dv[x] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int n = wave; n < n_items; n += NW) {
+        const int lane = lane_of<D>(), quarter = lane >> 4, col = lane & 15;
         const int g = n / n_qb, q0 = (qb_first + n - g * n_qb) * RB, h = kh * G + g;
         const float *q = (const float *)p.q + (int64_t)(loc.other_begin + q0) * p.q_stride_tok + (int64_t)h * p.q_stride_head;
         const float *d_o = (const float *)b.d_o + (int64_t)(loc.other_begin + q0) * b.do_stride_tok + (int64_t)h * b.do_stride_head;
@@ -479,9 +486,10 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
         f32x4 dp = row_product<D>(a, vs, lane);
         if (D != 64) load_q_row();
         f32x4 s = row_product<D>(qa, ks, lane);
-        const int lim = k0 + col - off - q0 - 4 * quarter;           // query 4 * quarter + i of the block is masked iff i < lim
-        const f32x4 l4 = *(const f32x4 *)(st + 4 * quarter);
-        f32x4 d4 = *(const f32x4 *)(st + RB + 4 * quarter);
+        const int lane_ = lane_of<D>(), first = lane_ >> 4 << 2;      // (of this lane's queries in the block)
+        const int lim = k0 + (lane_ & 15) - off - q0 - first;        // query first + i of the block is masked iff i < lim
+        const f32x4 l4 = *(const f32x4 *)(st + first);
+        f32x4 d4 = *(const f32x4 *)(st + RB + first);
 #pragma unroll
         for (int i = 0; i < 4; ++i) s[i] = lim > i ? 0.f : probability(s[i], p.softmax_scale, l4[i]);
         if (q0 + off == 0) {
@@ -492,12 +500,12 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
 #pragma unroll
         for (int i = 0; i < 4; ++i) dp[i] = s[i] * (dp[i] - d4[i]);
         __builtin_amdgcn_wave_barrier();                             // st is rewritten by the next item
-        add_column_product<D>(piece, lane, s, dv);
-        put_rows<D>(qa, piece, lane);
-        add_column_product<D>(piece, lane, dp, dk);
+        add_column_product<D>(piece, lane_of<D>(), s, dv);
+        put_rows<D>(qa, piece, lane_of<D>());
+        add_column_product<D>(piece, lane_of<D>(), dp, dk);
     }
     // At D = 64 both results meet in LDS together, at D = 128 there is room for one after the other.
-    const int n = min(NW, n_items);
+    const int n = min(NW, n_items), lane = lane_of<D>();
     constexpr int TOGETHER = S::BOTH_MEET ? 2 : 1;
     static_assert(TOGETHER * RB * (D / 4) <= NW * 64, "one step");
     const int t = threadIdx.x, r = t / (D / 4) % rows, c = t % (D / 4);
@@ -510,7 +518,7 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
             if (first + TOGETHER == 2) write_part<D>(dk, parts + ((TOGETHER - 1) * NW + wave) * S::PART, lane);
         }
         __syncthreads();
-        const int which = first + t / (rows * (D / 4));
+        const int which = TOGETHER == 1 ? first : t / (rows * (D / 4));
         const bool mine = t < TOGETHER * rows * (D / 4);
         f32x4 a = {0.f, 0.f, 0.f, 0.f};
         if (mine) a = sum_parts<D>(parts + (which - first) * NW * S::PART, n, r, c) * (which ? p.softmax_scale : 1.f);
@@ -522,7 +530,7 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
     for (int pass = 0; pass < 2 / TOGETHER; ++pass)
         for_rows_of<D>(left_out[pass], [&](int at) {
             const int first = wave * 64 + at, krow = loc.begin + k0 + first / (D / 4) % rows;
-            const bool is_k = pass + first / (rows * (D / 4)) != 0;
+            const bool is_k = (TOGETHER == 1 ? pass : first / (rows * (D / 4))) != 0;
             const SegmentRows g{loc.other_begin, lq, loc.begin, lk};
             const float *kr = row_of<float>(p.k, krow, p.kv_stride_tok, kh, p.kv_stride_head), *vr = row_of<float>(p.v, krow, p.kv_stride_tok, kh, p.kv_stride_head);
             float gk[D / 64], gv[D / 64];

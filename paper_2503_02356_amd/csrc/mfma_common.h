@@ -421,7 +421,7 @@ __device__ __forceinline__ bool locate_tile(const int32_t *cu, const int32_t *cu
         out.tile_in_seg = n - 1 - rank;
         return rank < n;
     }
-    const int lane = threadIdx.x & 63;
+    const int lane = fresh_lane();
     const int place = n_rows / tile + n_seg - 1 - rank;
     if (place < 0) return false;
     int lo = 0, hi = n_seg;                          // the segment is one of [lo, hi): 64 probes at a time
@@ -435,10 +435,10 @@ __device__ __forceinline__ bool locate_tile(const int32_t *cu, const int32_t *cu
     const int b0 = cu[g], b1 = cu[g + 1], o0 = cu_other[g], o1 = cu_other[g + 1];
     const int last = 63 - __clzll((long long)__ballot(lo + lane < hi && b0 / tile + g <= place));
     out.seg = __builtin_amdgcn_readfirstlane(lo + last);
-    out.begin = __builtin_amdgcn_readfirstlane(__shfl(b0, last));
-    out.len = __builtin_amdgcn_readfirstlane(__shfl(b1 - b0, last));
-    out.other_begin = __builtin_amdgcn_readfirstlane(__shfl(o0, last));
-    out.other_len = __builtin_amdgcn_readfirstlane(__shfl(o1 - o0, last));
+    out.begin = __builtin_amdgcn_readlane(b0, last);
+    out.len = __builtin_amdgcn_readlane(b1 - b0, last);
+    out.other_begin = __builtin_amdgcn_readlane(o0, last);
+    out.other_len = __builtin_amdgcn_readlane(o1 - o0, last);
     out.tile_in_seg = __builtin_amdgcn_readfirstlane(place - out.begin / tile - out.seg);
     return out.tile_in_seg * tile < out.len;
 }

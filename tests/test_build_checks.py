@@ -22,6 +22,16 @@ def test_a_spilled_accumulator_fails_the_build():
     assert len(build.spilled_accumulators(REPORT.format(scratch=8, spill=2))) == 2
 
 
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs hipcc")
+def test_no_fp32_kernel_spills():
+    report = subprocess.run([build.HIPCC] + build.HIP_FLAGS + [build.RESOURCE_REPORT, "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
+                             "--cuda-device-only", "-c", os.path.join(build.CSRC, "attn_fp32.hip"), "-o", os.devnull], check=True,
+                            stderr=subprocess.PIPE, text=True).stderr
+    assert len(re.findall(r"Function Name: \S*f32_bwd_batch_kernel", report)) == 2
+    assert build.spilled_operands(report) == []
+    assert build.spilled_operands(REPORT.format(scratch=8, spill=2))      # (another kernel's spill is seen)
+
+
 def registers(operand):
     m = re.fullmatch(r"v\[(\d+):(\d+)\]|v(\d+)", operand)
     return set() if m is None else {int(m[3])} if m[3] else set(range(int(m[1]), int(m[2]) + 1))
