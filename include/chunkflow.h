@@ -305,14 +305,16 @@ int cf_attn_bwd_static(const cf_attn_bwd_params *p, void *hip_stream);
 /*
  * Whole-plan launches: several chunks in one call.  The results are those of calling cf_attn_fwd /
  * cf_attn_bwd for params[0], params[1], ... in that order on the stream (dK/dV that several chunks share --
- * the chunks of one long sequence, section 4.2 -- accumulate in exactly that order).  What changes is the
+ * the chunks of one long sequence, section 4.2 -- accumulate in exactly that order; only where a chunk's own call adds to a
+ * row several times, in atomic adds of any order -- bf16 at head_dim 128 without CF_FLAG_DKV_SINGLE_WRITER --, may those of
+ * different chunks come in any order too: equal up to the rounding of fp32 sums).  What changes is the
  * launch shape: a run of consecutive chunks on the same matrix kernels (dtype, head counts, head_dim; up to 16)
  * that do not touch each other's results becomes ONE launch per kernel, whose workgroups are
  * dealt heaviest chunk first: the last, partly filled wave of workgroups of a big chunk is filled by the next
  * chunk's, and small chunks fill the GPU together.  In the backward, chunks that add to the same dK/dV rows share
- * all launches where atomic adds are made anyway (bf16 at head_dim 128) or where the chunks are single slices with the same
- * d_k, d_v and strides (fp32, head_dim 64: one workgroup adds for all of them, in order); otherwise the dQ launch
- * only (bf16 with one writer per dK/dV row: also CF_FLAG_DKV_SINGLE_WRITER, many key tiles) or none (fp32).
+ * all launches if they are single slices with the same d_k, d_v and strides and either one workgroup adds for all of them, in order
+ * (fp32, head_dim 64), or each adds several times to the rows they share (bf16 at head_dim 128); otherwise the dQ launch
+ * only (bf16; also CF_FLAG_DKV_SINGLE_WRITER, many key tiles) or none (fp32).
  *   params  host array [n]; for the backward every chunk needs a workspace of its OWN (they are in use at
  *           the same time; overlapping workspaces -> CF_EINVAL)
  * Errors: as the single-chunk calls, checked for every chunk before anything is enqueued; n == 0 is a no-op.
@@ -322,7 +324,8 @@ int cf_attn_bwd_batch(const cf_attn_bwd_params *params, int32_t n, void *hip_str
 
 /*
  * n calls, in order, on one stream: calls[i].backward ? cf_attn_bwd(calls[i].params) : cf_attn_fwd(calls[i].params),
- * with params a cf_attn_bwd_params resp. cf_attn_fwd_params.  Results as of n separate calls, which this saves the way
+ * with params a cf_attn_bwd_params resp. cf_attn_fwd_params.  Results as of n separate calls (dK/dV as in
+ * cf_attn_bwd_batch), which this saves the way
  * into the library (for a caller in an interpreted language longer than the launch itself); calls next to each other
  * that do not touch each other's results -- backward ones with workspaces of their own among them -- share launches as
  * in cf_attn_fwd_batch / cf_attn_bwd_batch.  (cu_seqlens and q_tiles are descriptors: no call of the list writes them.)

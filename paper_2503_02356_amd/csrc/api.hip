@@ -265,8 +265,12 @@ bool any_meet(const Range *a, int na, const Range *c, int nc)
     return false;
 }
 bool adds_meet(const Touched &a, const Touched &c) { return any_meet(a.adds, a.n_adds, c.adds, c.n_adds); }
-// Kernels with one writer per gradient row take both calls in one launch.
-bool chains(const Call &a, const Touched &ta, const Call &c, const Touched &tc) { return !adds_meet(ta, tc) || cf::same_key_rows(*a.b, *c.b); }
+// Backward calls whose dK/dV kernel takes both in one launch: one writer per gradient row goes from slice to slice.
+bool joins(const Call &a, const Touched &ta, const Call &c, const Touched &tc)
+{
+    if (!adds_meet(ta, tc)) return true;
+    return path_of(a) == kMfma && a.f->head_dim == 128 ? cf::dkv_in_any_order(*a.b, a.ws, *c.b, c.ws) : cf::same_key_rows(*a.b, *c.b);
+}
 // Apart from gradients that both add to, neither reads or writes what the other writes.
 bool independent(const Touched &a, const Touched &c)
 {
@@ -288,7 +292,7 @@ int launch_together(const Call *calls, const Touched *t, int n, hipStream_t s, c
         cf::BwdBatchChunk chunks[cf::CF_BWD_BATCH_MAX];
         for (int c = 0, first = 0; c < n; ++c) {
             bool apart = c > 0;
-            for (int a = first; a < c; ++a) apart = apart && chains(calls[a], t[a], calls[c], t[c]);
+            for (int a = first; a < c; ++a) apart = apart && joins(calls[a], t[a], calls[c], t[c]);
             if (!apart) first = c;
             chunks[c] = {calls[c].b, calls[c].ws, apart};
         }
@@ -331,7 +335,7 @@ int launch_calls(const Call *calls, int n, hipStream_t s, const char *who)
                 t[j] = touched(calls[j]);
                 bool apart = true;
                 for (int a = i; a < j && apart; ++a)
-                    apart = independent(t[a], t[j]) && (!calls[j].b || path_of(calls[j]) != kF32 || chains(calls[a], t[a], calls[j], t[j]));
+                    apart = independent(t[a], t[j]) && (!calls[j].b || path_of(calls[j]) != kF32 || joins(calls[a], t[a], calls[j], t[j]));
                 if (!apart) break;
             }
             if (int rc = launch_together(calls + i, t + i, j - i, s, who)) return rc;

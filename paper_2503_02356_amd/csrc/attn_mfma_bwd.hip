@@ -88,6 +88,33 @@ __host__ __device__ inline int64_t dkv_items_most(const cf_attn_fwd_params &p)
     return tiles * G > tiles + cuts ? tiles * G : tiles + cuts;
 }
 
+// The rule above, for a call of `total` (key tile, query tile) pairs of a query head in n_tiles key tiles.
+struct ListCuts {
+    int fair, target;
+    bool large, small, even_heads;
+    __host__ __device__ ListCuts(int total, int n_tiles, int n_q_heads, int slots)
+    {
+        const int64_t all_pairs = (int64_t)total * n_q_heads;
+        // (in floating point: a rounding moves a cut, and no more; 64-bit divisions would take longer than the rest of the list)
+        const float average = (float)all_pairs / (float)slots;      // pairs per slot
+        const int fine = share(average, 1.6f);
+        large = fine > kFineMost, small = slots == kSlots && average <= kSmallMost;
+        fair = small ? max(3, share(average, 2.2f)) : fine;
+        const int64_t head_items = (int64_t)n_tiles * n_q_heads;
+        even_heads = small ? head_items > kSlots / 4 && head_items <= kSlots / 2
+                           : !large && head_items > kSlots && head_items <= kSlots * 3 / 2;
+        target = max(2, large || even_heads ? (int)fminf(kSplitTarget, average / 2) : fine);
+    }
+    __host__ __device__ static int share(float average, float averages) { return (int)fminf(ceilf(average * averages), 1e9f); }
+    // Items of a key tile that n_qt query tiles see.  heads: of whole query heads (of G).  cut_heads: items may end inside one.
+    __host__ __device__ int items(int n_qt, int G, bool cut_heads, bool &heads) const
+    {
+        const int pairs = G * n_qt, by_heads = min(G, (pairs + target - 1) / target), fairly = (pairs + fair - 1) / fair;
+        heads = !cut_heads || (large ? fairly <= by_heads : n_qt <= 3 || (even_heads && n_qt <= (small ? fair * 8 / 5 : fair)));
+        return heads ? by_heads : fairly;
+    }
+};
+
 // Runs in ONE workgroup of 256 threads: among the first of the dQ launch, which the dK/dV kernel follows anyway (no launch
 // of its own).
 // Segment bounds pass through LDS 256 at a time (one coalesced load instead of a chain of dependent ones); a wavefront
@@ -124,23 +151,14 @@ __device__ __forceinline__ void build_dkv_worklist(const BwdArgs::Fwd &p, int *w
     atomicAdd(&total, mine);
     atomicAdd(&n_tiles, my_tiles);
     __syncthreads();
-    const int64_t all_pairs = (int64_t)total * p.n_q_heads;
-    // (in floating point: a rounding moves a cut, and no more; 64-bit divisions would take longer than the rest of the list)
-    const float average = (float)all_pairs / (float)slots;      // pairs per slot
-    auto share = [&](float averages) { return (int)fminf(ceilf(average * averages), 1e9f); };
-    const bool large = share(1.6f) > kFineMost, small = slots == kSlots && average <= kSmallMost;
-    const int fair = small ? max(3, share(2.2f)) : share(1.6f);
-    const int64_t head_items = (int64_t)n_tiles * p.n_q_heads;
-    const bool even_heads = small ? head_items > kSlots / 4 && head_items <= kSlots / 2
-                                  : !large && head_items > kSlots && head_items <= kSlots * 3 / 2;
-    const int target = max(2, large || even_heads ? (int)fminf(kSplitTarget, average / 2) : share(1.6f));
-    bool cut_heads = true;                           // items may end inside a head's query tiles
+    const ListCuts cuts(total, n_tiles, p.n_q_heads, slots);
+    bool cut_heads = true;
     auto for_each_item = [&](auto &&visit) {
         for_each_tile([&](int seg, int kt0, int n_qt) {
-            const int pairs = G * n_qt, by_heads = min(G, (pairs + target - 1) / target), fairly = (pairs + fair - 1) / fair;
-            const bool heads = !cut_heads || (large ? fairly <= by_heads : n_qt <= 3 || (even_heads && n_qt <= (small ? fair * 8 / 5 : fair)));
+            bool heads;
+            const int sp = cuts.items(n_qt, G, cut_heads, heads);
             // equal shares of the heads or of the pairs, the first few with one more
-            const int sp = heads ? by_heads : fairly, whole = heads ? G : pairs, unit = heads ? n_qt : 1;
+            const int whole = heads ? G : G * n_qt, unit = heads ? n_qt : 1;
             const int base = sp == 1 ? whole : whole / sp, longer = whole - base * sp;
             for (int s = 0; s < sp; ++s) {
                 const int n = (base + (s < longer)) * unit;
@@ -976,10 +994,8 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
     for (int c = 0; c < n; ++c) {
         g[c] = bwd_shape(chunks[c].b->f, chunks[c].ws);
         if (!g[c].ok) return hipErrorInvalidConfiguration;
-        // Single writers of the same rows keep the order of the calls in launches of their own.  Work lists add atomically, in any
-        // order, and go together: a step of 28 / 4 heads, 4 slices of 512 tokens and 2 packed chunks 302 -> 234 us, 4 slices of 1024
-        // and 3 packed chunks 720 -> 580 (slices of 8192: no change, their launches end evenly).
-        first_of[c] = c > 0 && (D == 64 ? chunks[c].chains : !g[c].fused && !g[c - 1].fused) ? first_of[c - 1] : c;
+        // Single writers of the same rows keep the order of the calls in launches of their own.
+        first_of[c] = c > 0 && chunks[c].joins && (D == 64 || (!g[c].fused && !g[c - 1].fused)) ? first_of[c - 1] : c;
         tokens[first_of[c]] += chunks[c].b->f.n_tokens;
         ++together[first_of[c]];
         order[c] = c;
@@ -1032,7 +1048,29 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
     return e;
 }
 
+// Slice l (longer) of a call of its own: has every key tile that lies before its own rows more than one item?
+bool cuts_prefix_tiles(const cf_attn_fwd_params &l, const BwdWorkspace &ws)
+{
+    const int64_t prefix = l.n_kv_tokens - l.n_tokens, q_tiles = ((int64_t)l.n_tokens + BQ - 1) / BQ, G = l.n_q_heads / l.n_kv_heads;
+    // key tiles up to the one with the first own row are seen by all query tiles, each one behind by 128 / 64 fewer
+    const int64_t whole = prefix / BKV + 1, first = whole * BKV - prefix, rest = first < l.n_tokens ? (l.n_tokens - first + BKV - 1) / BKV : 0;
+    static_assert(BKV == 2 * BQ, "the sum of the rest");
+    const int64_t total = whole * q_tiles + rest * (q_tiles - first / BQ) - rest * (rest - 1);
+    const ListCuts cuts((int)std::min<int64_t>(total, 0x7fffffff), (int)(whole + rest), l.n_q_heads, kSlots);
+    bool heads;
+    return cuts.items((int)q_tiles, (int)G, true, heads) > 1 &&
+           (ws.worklist_items >= dkv_items_most(l) || cuts.items((int)q_tiles, (int)G, false, heads) > 1);
+}
+
 }  // namespace
+
+bool dkv_in_any_order(const cf_attn_bwd_params &a, const BwdWorkspace &wa, const cf_attn_bwd_params &c, const BwdWorkspace &wc)
+{
+    if (!same_key_rows(a, c)) return false;
+    const bool a_longer = a.f.n_kv_tokens > c.f.n_kv_tokens;
+    const cf_attn_fwd_params &l = a_longer ? a.f : c.f, &s = a_longer ? c.f : a.f;
+    return s.n_kv_tokens <= l.n_kv_tokens - l.n_tokens && cuts_prefix_tiles(l, a_longer ? wa : wc);
+}
 
 int64_t mfma_bwd_blocks(const cf_attn_fwd_params &p)
 {

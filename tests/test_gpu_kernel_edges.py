@@ -120,6 +120,31 @@ def test_slices_that_add_to_the_same_rows(dtype, D, flags, merge):
     assert ((g0 - g1).norm() / g0.norm()).item() <= 64 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("Hq,Hkv,C,merge", [(4, 4, 128, False), (4, 2, 64, False), (4, 4, 128, True)])
+@pytest.mark.parametrize("backwards", [False, True])
+def test_one_work_item_to_a_key_tile_adds_in_the_order_of_the_calls(Hq, Hkv, C, merge, backwards):
+    """bf16, D = 128: where every call adds once to a row of dK and dV, the sums over the slices of a sequence have the bits of
+    separate calls, whatever shares their launches."""
+    lens = [11 * C + 37, 30, 7 * C, 61, 5 * C + 1, 20]
+    plan = B.cf_build_chunks_ex(lens, C, B.CF_PLAN_MERGE_TAILS) if merge else B.cf_build_chunks(lens, C)
+    eng = ChunkAttention(plan, Hq, Hkv, 128, "bf16").load(lambda sid, L: inputs.seq_values(9, sid, L, Hq, Hkv, 128, "bf16"))
+    eng.run_forward()
+    order = eng.backward_order()[::-1] if backwards else eng.backward_order()
+    ws = [torch.empty_like(eng.workspaces[0]) for _ in order]
+    calls = [B.make_bwd_params(c["fwd"], c["d_o"], c["d_q"], c["dk"], c["dv"], w) for c, w in zip((eng.chunks[c] for c in order), ws)]
+    got = []
+    for together in (False, True, True, True):
+        eng.grad_arena.normal_(generator=torch.Generator(device="cuda:0").manual_seed(1))       # (they are added to)
+        if together:
+            B.cf_attn_calls(B.make_calls((True, b) for b in calls))
+        else:
+            for b in calls:
+                B.cf_attn_bwd(b)
+        torch.cuda.synchronize()
+        got.append(eng.grad_arena.clone())
+    assert all(torch.equal(got[0], g) for g in got[1:])
+
+
 @pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp32", 64), ("fp32", 128)])
 @pytest.mark.parametrize("backwards", [False, True])
 def test_chains_of_slices_keep_the_bits_of_single_calls(dtype, D, backwards):
