@@ -312,9 +312,9 @@ int cf_attn_bwd_static(const cf_attn_bwd_params *p, void *hip_stream);
  * that do not touch each other's results becomes ONE launch per kernel, whose workgroups are
  * dealt heaviest chunk first: the last, partly filled wave of workgroups of a big chunk is filled by the next
  * chunk's, and small chunks fill the GPU together.  In the backward, chunks that add to the same dK/dV rows share
- * all launches if they are single slices with the same d_k, d_v and strides and either one workgroup adds for all of them, in order
- * (fp32, head_dim 64), or each adds several times to the rows they share (bf16 at head_dim 128); otherwise the dQ launch
- * only (bf16; also CF_FLAG_DKV_SINGLE_WRITER, many key tiles) or none (fp32).
+ * all launches if they are single slices with the same d_k, d_v and strides and each adds once to a row -- one workgroup adds for
+ * all of them, in order -- or each several times to the rows they share; otherwise the dQ launch only (bf16; also
+ * CF_FLAG_DKV_SINGLE_WRITER and many key tiles at head_dim 128) or none (fp32).
  *   params  host array [n]; for the backward every chunk needs a workspace of its OWN (they are in use at
  *           the same time; overlapping workspaces -> CF_EINVAL)
  * Errors: as the single-chunk calls, checked for every chunk before anything is enqueued; n == 0 is a no-op.

@@ -265,12 +265,8 @@ bool any_meet(const Range *a, int na, const Range *c, int nc)
     return false;
 }
 bool adds_meet(const Touched &a, const Touched &c) { return any_meet(a.adds, a.n_adds, c.adds, c.n_adds); }
-// Backward calls whose dK/dV kernel takes both in one launch: one writer per gradient row goes from slice to slice.
-bool joins(const Call &a, const Touched &ta, const Call &c, const Touched &tc)
-{
-    if (!adds_meet(ta, tc)) return true;
-    return path_of(a) == kMfma && a.f->head_dim == 128 ? cf::dkv_in_any_order(*a.b, a.ws, *c.b, c.ws) : cf::same_key_rows(*a.b, *c.b);
-}
+// The fp32 kernel takes both calls in one launch: one writer per gradient row goes from slice to slice.
+bool chains(const Call &a, const Touched &ta, const Call &c, const Touched &tc) { return !adds_meet(ta, tc) || cf::same_key_rows(*a.b, *c.b); }
 // Apart from gradients that both add to, neither reads or writes what the other writes.
 bool independent(const Touched &a, const Touched &c)
 {
@@ -290,11 +286,9 @@ int launch_together(const Call *calls, const Touched *t, int n, hipStream_t s, c
     }
     if (calls[0].b && path_of(calls[0]) == kMfma) {
         cf::BwdBatchChunk chunks[cf::CF_BWD_BATCH_MAX];
-        for (int c = 0, first = 0; c < n; ++c) {
-            bool apart = c > 0;
-            for (int a = first; a < c; ++a) apart = apart && joins(calls[a], t[a], calls[c], t[c]);
-            if (!apart) first = c;
-            chunks[c] = {calls[c].b, calls[c].ws, apart};
+        for (int c = 0; c < n; ++c) {
+            chunks[c] = {calls[c].b, calls[c].ws, 0};
+            for (int a = 0; a < c; ++a) chunks[c].meets |= (unsigned)adds_meet(t[a], t[c]) << a;
         }
         e = cf::launch_mfma_bwd_batch(chunks, n, s);
         return e == hipSuccess ? CF_OK : hip_fail(who, e);
@@ -335,7 +329,7 @@ int launch_calls(const Call *calls, int n, hipStream_t s, const char *who)
                 t[j] = touched(calls[j]);
                 bool apart = true;
                 for (int a = i; a < j && apart; ++a)
-                    apart = independent(t[a], t[j]) && (!calls[j].b || path_of(calls[j]) != kF32 || joins(calls[a], t[a], calls[j], t[j]));
+                    apart = independent(t[a], t[j]) && (!calls[j].b || path_of(calls[j]) != kF32 || chains(calls[a], t[a], calls[j], t[j]));
                 if (!apart) break;
             }
             if (int rc = launch_together(calls + i, t + i, j - i, s, who)) return rc;

@@ -90,13 +90,14 @@ __host__ __device__ inline int64_t dkv_items_most(const cf_attn_fwd_params &p)
 
 // The rule above, for a call of `total` (key tile, query tile) pairs of a query head in n_tiles key tiles.
 struct ListCuts {
+    float average;                                   // pairs per slot
     int fair, target;
     bool large, small, even_heads;
     __host__ __device__ ListCuts(int total, int n_tiles, int n_q_heads, int slots)
     {
         const int64_t all_pairs = (int64_t)total * n_q_heads;
         // (in floating point: a rounding moves a cut, and no more; 64-bit divisions would take longer than the rest of the list)
-        const float average = (float)all_pairs / (float)slots;      // pairs per slot
+        average = (float)all_pairs / (float)slots;
         const int fine = share(average, 1.6f);
         large = fine > kFineMost, small = slots == kSlots && average <= kSmallMost;
         fair = small ? max(3, share(average, 2.2f)) : fine;
@@ -213,9 +214,10 @@ struct DkvStage {
 // MFMAs the bf16 values of P and dS AND their bf16 rounding residuals: rows that see few keys have large P and dS, whose
 // rounding would be the largest error in dK/dV.  At D = 64 P and dS enter every product with all their 24 bits instead, as
 // three bf16 operands.
-template <int D, bool FUSED_HEADS>
+// RING: operand fragments in flight (below).  wave: of this wavefront.
+template <int D, bool FUSED_HEADS, int RING = 4>
 __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restrict__ delta, int id,
-                                         const int *__restrict__ wl, char *st0, char *st1)
+                                         const int *__restrict__ wl, char *st0, char *st1, int wave = wave_id())
 {
     using Stage = DkvStage<D>;
     using F = Mfma<D>;
@@ -223,7 +225,7 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     constexpr int QW = DkvShape<D>::QW, BQ = DkvShape<D>::BQ, BKV = DkvShape<D>::BKV;
     static_assert(FUSED_HEADS || QW == 1, "atomic updates are made by the wavefront that owns the keys");
     const BwdArgs::Fwd &p = b.f;
-    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), key_wave = wave / QW, query_wave = wave % QW;
+    const int key_wave = wave / QW, query_wave = wave % QW;
 
     // Block id -> (item, key/value head); the key/value head varies fastest (XCD L2 locality, see forward).
     //   fused mode : item = key tile rank, all G heads of the group
@@ -330,24 +332,24 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
         if (q0 + 31 + off < kw0 || q0 >= lq) return;     // no row of the block sees a key of this wavefront, or none is a row
         const char *qs = stage, *dos = stage + Stage::tile_bytes;
         const float *stats = (const float *)(stage + 2 * Stage::tile_bytes) + mb * 32 + fresh_lane() / F::M * 4;
-        // The A operands of the block's four products pass through a ring of four fragments, each requested four uses
+        // The A operands of the block's four products pass through a ring of fragments, each requested RING uses
         // before its own: ROWS fragments of Q rows and of dO rows, then the transposed dO and Q operands (contraction over the
         // 32 query rows in 2 groups of 16).
         constexpr int ROWS = N * KS, COLS = 2 * DB;
-        bf16x8 ring[4];
+        bf16x8 ring[RING];
         auto fetch = [&](int n) {
             if (n == ROWS || (n >= 2 * ROWS && n % DB == 0)) at.forget();
             if (n < 2 * ROWS) {
                 const int m = n % ROWS;
-                ring[n & 3] = lds_read_b128((n < ROWS ? qs : dos) + m % N * (BLOCK / N) + at.row(m / N));
+                ring[n % RING] = lds_read_b128((n < ROWS ? qs : dos) + m % N * (BLOCK / N) + at.row(m / N));
             } else if (n < 2 * ROWS + 2 * COLS) {
                 const int m = n - 2 * ROWS, db = m % DB, tq = m % COLS / DB;
                 const char *rows = (m / COLS ? qs : dos) + tq * (BLOCK / 2);
-                ring[n & 3] = lds_read_tr_pair(rows + at.tr_lo(db), rows + at.tr_hi(db));
+                ring[n % RING] = lds_read_tr_pair(rows + at.tr_lo(db), rows + at.tr_hi(db));
             }
         };
 #pragma unroll
-        for (int n = 0; n < 4; ++n) fetch(n);
+        for (int n = 0; n < RING; ++n) fetch(n);
         // [query block][key block]; element i of a key block: register i % R of query block i / R, query row q0 + place(i) + 4*group
         typename F::Acc s[N][N], dp[N][N];
         constexpr int NS = N * F::R;
@@ -359,8 +361,8 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
         for (int n = 0; n < ROWS; ++n) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int kb = 0; kb < N; ++kb) s[n % N][kb] = F::mul(ring[n & 3], kf[kb][n / N], s[n % N][kb]);
-            fetch(n + 4);
+            for (int kb = 0; kb < N; ++kb) s[n % N][kb] = F::mul(ring[n % RING], kf[kb][n / N], s[n % N][kb]);
+            fetch(n + RING);
         }
 #pragma unroll
         for (int i = 0; i < NS; i += 4) {
@@ -375,8 +377,8 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
             __builtin_amdgcn_sched_barrier(0);
             const int m = n - ROWS;
 #pragma unroll
-            for (int kb = 0; kb < N; ++kb) dp[m % N][kb] = F::mul(ring[n & 3], vf[kb][m / N], dp[m % N][kb]);
-            fetch(n + 4);
+            for (int kb = 0; kb < N; ++kb) dp[m % N][kb] = F::mul(ring[n % RING], vf[kb][m / N], dp[m % N][kb]);
+            fetch(n + RING);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -459,11 +461,11 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
                     split_exact(f, ws);
                 }
 #pragma unroll
-                for (int t = 0; t < 3; ++t) accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n & 3], ws[t]);
+                for (int t = 0; t < 3; ++t) accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n % RING], ws[t]);
             } else {
-                accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n & 3], w);
+                accumulate_in_place<D>(x ? dk[j] : dv[j], ring[n % RING], w);
             }
-            fetch(n + 4);
+            fetch(n + RING);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -595,18 +597,21 @@ __device__ __forceinline__ int chunk_of(const BwdBatch &q, int id)
 }
 
 // Chunks with work lists: they follow each other, each longest first, and the last workgroups of one chunk run beside the first of
-// the next.  Or (D = 64) chunks of disjoint dK/dV rows and chains of slices that add to the same ones, one workgroup to a row: 16 / 4
-// heads, 16.7k tokens, a sequence in 2 slices: 1014 -> 979 us a step (a launch per slice before).
-template <int D>
+// the next.  CHAINS: chunks of disjoint dK/dV rows and chains of slices that add to the same ones, one workgroup to a row: D = 64, 16 / 4
+// heads, 16.7k tokens, a sequence in 2 slices: 1014 -> 979 us a step (a launch per slice before); D = 128: run_bwd_batch.  (D = 128
+// has one register less then, and four to a fragment.)
+template <int D, bool CHAINS>
 __global__ __launch_bounds__(256, 2) void mfma_dkv_batch_kernel(BwdBatch q)
 {
     __shared__ __attribute__((aligned(16))) char st0[DkvStage<D>::bytes];
     __shared__ __attribute__((aligned(16))) char st1[DkvStage<D>::bytes];
+    const int wave = wave_id();
     int c = chunk_of(q, blockIdx.x);
     const int id = blockIdx.x - q.first_block[c];
     for (;;) {
-        dkv_body<D, D == 64>(q.b[c], q.delta[c], id, q.wl[c], st0, st1);
-        if (D != 64) return;
+        if constexpr (D == 128 && CHAINS) dkv_body<D, true, 3>(q.b[c], q.delta[c], id, nullptr, st0, st1, wave);
+        else dkv_body<D, CHAINS>(q.b[c], q.delta[c], id, q.wl[c], st0, st1);
+        if (!CHAINS) return;
         c = q.next[c];
         if (c < 0) return;
         __syncthreads();                             // LDS has been read for the last time
@@ -984,6 +989,41 @@ bool append(BwdBatch &q, const cf_attn_bwd_params &b, const BwdWorkspace &ws, co
     return true;
 }
 
+// How a chunk's dK/dV goes out.  Calls that add to the same rows do so in the order of the calls where each of them adds to a row once.
+//   kList   a list that cuts key tiles into several items, which meet in atomic adds in any order; the lists of several slices then go
+//           together, in any order too: a step of 28 / 4 heads, 4 slices of 512 tokens and 2 packed chunks 302 -> 234 us, 4 slices
+//           of 1024 and 3 packed chunks 720 -> 580 (slices of 8192: no change, their launches end evenly)
+//   kChain  one writer per row (D = 64), or a list of one item to a key tile: the slices of a sequence go from one to the next in the
+//           workgroup of a key tile.  32 / 32 heads, 4000 tokens in slices of 512 and 2 packed chunks: 868 us a step, 1040 with a launch per
+//           slice (lists in any order: 869); 8 / 8 heads, 20000 tokens in slices of 1000: 4190, 4600 (3810)
+//   kAlone  a launch of its own, in order: one writer per row by the flag or for many key tiles; and lists of one item to a key tile whose
+//           launches end evenly (32 / 32 heads, 16000 tokens in slices of 2000, up to 240 pairs a slot: 8.98 ms a step, as a chain 9.16)
+enum DkvKind { kAlone, kList, kChain };
+constexpr float kChainMost = 96;      // pairs a slot
+// Of a call with a work list.  Are the key tiles that all its query tiles see cut into several items, in a launch of its own?
+// (Several segments: their lengths are not known here; such a call shares rows with no other in a launch.)
+DkvKind kind_of_list(const cf_attn_fwd_params &p, const BwdWorkspace &ws)
+{
+    if (p.n_segments > 1) return kList;
+    const int64_t prefix = p.n_kv_tokens - p.n_tokens, q_tiles = ((int64_t)p.n_tokens + BQ - 1) / BQ;
+    // key tiles up to the one with the first own row are seen by all query tiles, each one behind by 128 / 64 fewer
+    const int64_t whole = prefix / BKV + 1, first = whole * BKV - prefix, rest = first < p.n_tokens ? (p.n_tokens - first + BKV - 1) / BKV : 0;
+    static_assert(BKV == 2 * BQ, "the sum of the rest");
+    const int64_t total = whole * q_tiles + rest * (q_tiles - first / BQ) - rest * (rest - 1);
+    const int G = p.n_q_heads / p.n_kv_heads;
+    const ListCuts cuts((int)std::min<int64_t>(total, 0x7fffffff), (int)(whole + rest), p.n_q_heads, kSlots);
+    bool heads;
+    if (cuts.items((int)q_tiles, G, true, heads) > 1 && (ws.worklist_items >= dkv_items_most(p) || cuts.items((int)q_tiles, G, false, heads) > 1)) return kList;
+    return cuts.average <= kChainMost ? kChain : kAlone;
+}
+// Slices whose lists may add to the rows that they share in any order: all of these lie before the longer one's own rows, where its
+// key tiles are cut.
+bool any_order(const cf_attn_bwd_params &a, const cf_attn_bwd_params &c)
+{
+    const cf_attn_fwd_params &l = a.f.n_kv_tokens > c.f.n_kv_tokens ? a.f : c.f, &s = &l == &a.f ? c.f : a.f;
+    return same_key_rows(a, c) && s.n_kv_tokens <= l.n_kv_tokens - l.n_tokens;
+}
+
 template <int D>
 hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
 {
@@ -991,15 +1031,23 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
     int order[CF_BWD_BATCH_MAX];
     int64_t tokens[CF_BWD_BATCH_MAX] = {};           // of the dK/dV launch that a chunk goes into (index: its first chunk)
     int first_of[CF_BWD_BATCH_MAX], together[CF_BWD_BATCH_MAX] = {};
+    DkvKind kind[CF_BWD_BATCH_MAX];
+    unsigned shares = 0;                             // bit c: chunk c adds to rows that another one adds to
+    for (int c = 0; c < n; ++c)
+        if (chunks[c].meets != 0) shares |= chunks[c].meets | 1u << c;
     for (int c = 0; c < n; ++c) {
         g[c] = bwd_shape(chunks[c].b->f, chunks[c].ws);
         if (!g[c].ok) return hipErrorInvalidConfiguration;
-        // Single writers of the same rows keep the order of the calls in launches of their own.
-        first_of[c] = c > 0 && chunks[c].joins && (D == 64 || (!g[c].fused && !g[c - 1].fused)) ? first_of[c - 1] : c;
-        tokens[first_of[c]] += chunks[c].b->f.n_tokens;
-        ++together[first_of[c]];
+        kind[c] = D == 64 ? kChain : g[c].fused ? kAlone : shares >> c & 1 ? kind_of_list(chunks[c].b->f, chunks[c].ws) : kList;
+        first_of[c] = c > 0 && kind[c] == kind[c - 1] && kind[c] != kAlone ? first_of[c - 1] : c;
+        for (int a = first_of[c]; a < c; ++a)
+            if ((chunks[c].meets >> a & 1) && !(kind[c] == kChain ? same_key_rows : any_order)(*chunks[a].b, *chunks[c].b)) first_of[c] = c;
         order[c] = c;
     }
+    for (int c = 0; c < n; ++c) tokens[first_of[c]] += chunks[c].b->f.n_tokens, ++together[first_of[c]];
+    for (int c = 0; D == 128 && c < n; ++c)          // (a chain needs no list, and has a workgroup for each key tile)
+        if (kind[c] == kChain && together[first_of[c]] > 1)
+            g[c].fused = true, g[c].dkv_blocks = kv_tiles_most(chunks[c].b->f) * chunks[c].b->f.n_kv_heads;
     // heaviest first: work ~ queries x keys
     std::stable_sort(order, order + n, [&](int x, int y) {
         const cf_attn_fwd_params &a = chunks[x].b->f, &b = chunks[y].b->f;
@@ -1025,7 +1073,7 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
             continue;
         }
         q.n = 0;
-        if constexpr (D == 64) {
+        if (kind[first] == kChain) {
             const CallChains<CF_BWD_BATCH_MAX> chain(end - first, [&](int c) -> const cf_attn_bwd_params & { return *chunks[first + c].b; });
             int place[CF_BWD_BATCH_MAX];
             for (int i = 0; i < end - first; ++i) place[chain.order[i]] = i;
@@ -1042,35 +1090,15 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
                 if (first_of[c] == first && !append(q, *chunks[c].b, chunks[c].ws, g[c], g[c].dkv_blocks)) return hipErrorInvalidConfiguration;
             }
         }
-        mfma_dkv_batch_kernel<D><<<dim3((unsigned)q.first_block[q.n]), 256, 0, s>>>(q);
+        const dim3 grid((unsigned)q.first_block[q.n]);
+        if (kind[first] == kChain) mfma_dkv_batch_kernel<D, true><<<grid, 256, 0, s>>>(q);
+        else if constexpr (D == 128) mfma_dkv_batch_kernel<D, false><<<grid, 256, 0, s>>>(q);
         e = hipGetLastError();
     }
     return e;
 }
 
-// Slice l (longer) of a call of its own: has every key tile that lies before its own rows more than one item?
-bool cuts_prefix_tiles(const cf_attn_fwd_params &l, const BwdWorkspace &ws)
-{
-    const int64_t prefix = l.n_kv_tokens - l.n_tokens, q_tiles = ((int64_t)l.n_tokens + BQ - 1) / BQ, G = l.n_q_heads / l.n_kv_heads;
-    // key tiles up to the one with the first own row are seen by all query tiles, each one behind by 128 / 64 fewer
-    const int64_t whole = prefix / BKV + 1, first = whole * BKV - prefix, rest = first < l.n_tokens ? (l.n_tokens - first + BKV - 1) / BKV : 0;
-    static_assert(BKV == 2 * BQ, "the sum of the rest");
-    const int64_t total = whole * q_tiles + rest * (q_tiles - first / BQ) - rest * (rest - 1);
-    const ListCuts cuts((int)std::min<int64_t>(total, 0x7fffffff), (int)(whole + rest), l.n_q_heads, kSlots);
-    bool heads;
-    return cuts.items((int)q_tiles, (int)G, true, heads) > 1 &&
-           (ws.worklist_items >= dkv_items_most(l) || cuts.items((int)q_tiles, (int)G, false, heads) > 1);
-}
-
 }  // namespace
-
-bool dkv_in_any_order(const cf_attn_bwd_params &a, const BwdWorkspace &wa, const cf_attn_bwd_params &c, const BwdWorkspace &wc)
-{
-    if (!same_key_rows(a, c)) return false;
-    const bool a_longer = a.f.n_kv_tokens > c.f.n_kv_tokens;
-    const cf_attn_fwd_params &l = a_longer ? a.f : c.f, &s = a_longer ? c.f : a.f;
-    return s.n_kv_tokens <= l.n_kv_tokens - l.n_tokens && cuts_prefix_tiles(l, a_longer ? wa : wc);
-}
 
 int64_t mfma_bwd_blocks(const cf_attn_fwd_params &p)
 {

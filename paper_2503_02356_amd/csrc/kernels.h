@@ -128,20 +128,13 @@ constexpr int CF_FWD_BATCH_MAX = 16;
 hipError_t launch_mfma_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, hipStream_t s);
 hipError_t launch_mfma_bwd(const cf_attn_bwd_params &p, const BwdWorkspace &ws, hipStream_t s);
 // Backward of 1..CF_BWD_BATCH_MAX (as many as kernel arguments hold) chunks: one dQ launch, then the dK/dV kernels, one launch per
-// run of chunks that join their predecessor.
+// run of chunks that can share it (run_bwd_batch).
 constexpr int CF_BWD_BATCH_MAX = 16;
 struct BwdBatchChunk {
     const cf_attn_bwd_params *b;
     BwdWorkspace ws;
-    bool joins;                  // its d_k / d_v rows are none of its predecessors', back to the last chunk without this, or
-                                 // the same_key_rows() (head_dim 64) resp. dkv_in_any_order() (128)
+    unsigned meets;              // bit a: its d_k / d_v rows may be rows of chunk a before it
 };
-// head_dim 128, work lists: may the two calls add to the rows they share in one launch?  Where a call's list has one item for a key
-// tile, its sum over slices has the bits of the order of the calls, and keeps them in launches of their own.  Where it has several,
-// they meet in atomic adds, in any order in a launch of their own too, and the calls go together: a step of 28 / 4 heads, 4 slices of
-// 512 tokens and 2 packed chunks 302 -> 234 us, 4 slices of 1024 and 3 packed chunks 720 -> 580 (slices of 8192: no change, their launches
-// end evenly).  Two slices of a sequence share rows that lie before the longer one's own, so that its list decides.
-bool dkv_in_any_order(const cf_attn_bwd_params &a, const BwdWorkspace &wa, const cf_attn_bwd_params &c, const BwdWorkspace &wc);
 hipError_t launch_mfma_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s);
 
 }  // namespace cf

@@ -60,7 +60,7 @@ def test_nothing_else_touches_an_accumulator_in_the_loop(tmp_path):
                    "-S", os.path.join(build.CSRC, "attn_mfma_bwd.hip"), "-o", out], check=True, stderr=subprocess.DEVNULL)
     text = open(out).read()
     kernels = re.findall(r"^(\S*mfma_dkv\S*ILi128E\S*):.*?\n(.*?)^\.Lfunc_end", text, re.M | re.S)
-    assert len(kernels) == 3
+    assert len(kernels) == 4
     for name, body in kernels:
         n, regs, faults = accumulator_faults(body)
         assert n > 0 and regs == 128 and faults == [], (name, n, regs, faults[:5])

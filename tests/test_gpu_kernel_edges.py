@@ -120,7 +120,7 @@ def test_slices_that_add_to_the_same_rows(dtype, D, flags, merge):
     assert ((g0 - g1).norm() / g0.norm()).item() <= 64 * 2.0 ** -24
 
 
-@pytest.mark.parametrize("Hq,Hkv,C,merge", [(4, 4, 128, False), (4, 2, 64, False), (4, 4, 128, True)])
+@pytest.mark.parametrize("Hq,Hkv,C,merge", [(4, 4, 128, False), (4, 2, 64, False), (4, 4, 128, True), (8, 8, 100, False)])
 @pytest.mark.parametrize("backwards", [False, True])
 def test_one_work_item_to_a_key_tile_adds_in_the_order_of_the_calls(Hq, Hkv, C, merge, backwards):
     """bf16, D = 128: where every call adds once to a row of dK and dV, the sums over the slices of a sequence have the bits of
@@ -145,31 +145,84 @@ def test_one_work_item_to_a_key_tile_adds_in_the_order_of_the_calls(Hq, Hkv, C, 
     assert all(torch.equal(got[0], g) for g in got[1:])
 
 
+def _together_and_apart(calls, grads):
+    """Gradient buffers and dQ of backward calls in one list and one at a time, on the same start values."""
+    got = []
+    for together in (False, True):
+        for i, g in enumerate(grads):
+            g.normal_(generator=torch.Generator(device="cuda:0").manual_seed(i))        # (they are added to)
+        if together:
+            B.cf_attn_calls(B.make_calls((True, b) for b in calls))
+        else:
+            for b in calls:
+                B.cf_attn_bwd(b)
+        torch.cuda.synchronize()
+        got.append([g.clone() for g in grads] + [b._keepalive[2].clone() for b in calls])
+    return got
+
+
+def _calls_of(eng, order, grads=lambda ch: (ch["dk"], ch["dv"])):
+    ch = [eng.chunks[c] for c in order]
+    return [B.make_bwd_params(c["fwd"], c["d_o"], c["d_q"], *grads(c), torch.empty_like(eng.workspaces[0])) for c in ch]
+
+
 @pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp32", 64), ("fp32", 128)])
 @pytest.mark.parametrize("backwards", [False, True])
-def test_chains_of_slices_keep_the_bits_of_single_calls(dtype, D, backwards):
+@pytest.mark.parametrize("merge", [False, True])
+def test_chains_of_slices_keep_the_bits_of_single_calls(dtype, D, backwards, merge):
     """Split sequences and packed chunks, 22 backward calls (two launches, a chain cut between them): slices that end inside a
-    block of 16 or 32 keys, the first call of a chain its longest or its shortest one.  Same bits as one call at a time."""
+    block of 16 or 32 keys, the first call of a chain its longest or its shortest one, last slices in packed chunks (which add to
+    rows of a chain and are none of it).  Same bits as one call at a time."""
     lens, C, Hq, Hkv = [333, 210, 20, 71, 130, 9, 64, 290, 65, 33, 100], 70, 4, 2
-    plan = B.cf_build_chunks(lens, C)
+    plan = B.cf_build_chunks_ex(lens, C, B.CF_PLAN_MERGE_TAILS) if merge else B.cf_build_chunks(lens, C)
     vals = lambda sid, L: inputs.seq_values(8, sid, L, Hq, Hkv, D, dtype)
     eng = ChunkAttention(plan, Hq, Hkv, D, dtype).load(vals)
     eng.run_forward()
     order = eng.backward_order()[::-1] if backwards else eng.backward_order()
-    assert len(order) > 12 and sum(len(plan.group(g)) > 2 for g in eng.groups()) >= 3
-    got = []
-    for together in (False, True):
-        eng.grad_arena.normal_(generator=torch.Generator(device="cuda:0").manual_seed(1))       # (they are added to)
-        if together:
-            ws = [torch.empty_like(eng.workspaces[0]) for _ in order]
-            calls = [B.make_bwd_params(c["fwd"], c["d_o"], c["d_q"], c["dk"], c["dv"], w) for c, w in zip((eng.chunks[c] for c in order), ws)]
-            B.cf_attn_calls(B.make_calls((True, b) for b in calls))
-        else:
-            for c in order:
-                B.cf_attn_bwd(eng.chunks[c]["bwd"])
-        torch.cuda.synchronize()
-        got.append([eng.grad_arena.clone()] + [ch["d_q"].clone() for ch in eng.chunks])
-    assert all(torch.equal(a, b) for a, b in zip(*got))
+    assert len(order) > B.BWD_TOGETHER and sum(len(plan.group(g)) > 2 for g in eng.groups()) >= 3
+    first = (len(order) + 1) // 2                    # (two launches of equal size, where nothing else ends the first one)
+    assert merge or any(set(plan.group(g)) & set(order[:first]) and set(plan.group(g)) & set(order[first:]) for g in eng.groups())
+    assert merge == any(ch["merged"] for ch in eng.chunks)
+    apart, together = _together_and_apart(_calls_of(eng, order), [eng.grad_arena])
+    assert all(torch.equal(a, b) for a, b in zip(apart, together))
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp32", 64), ("fp32", 128)])
+@pytest.mark.parametrize("name,value", [("q", float("nan")), ("d_o", float("inf")), ("v", float("-inf")), ("k", float("nan"))])
+def test_chains_take_rows_again_that_are_not_finite(dtype, D, name, value):
+    """A value that is not finite in the third of five slices, dK and dV as views into one buffer: the rows that the matrix product
+    leaves out of a slice's gradients are added pair by pair between two slices of the chain.  Same bits as one call at a time."""
+    L, C, Hq, Hkv = 333, 70, 4, 2
+    plan = B.cf_build_chunks([L], C)
+    eng = ChunkAttention(plan, Hq, Hkv, D, dtype).load(lambda sid, n: inputs.seq_values(8, sid, n, Hq, Hkv, D, dtype))
+    where = eng.chunks[2]
+    (where[name][where["P"] + 33] if name in "kv" else where[name][33])[1, 5] = value
+    eng.run_forward()
+    both = torch.empty(L, Hkv, 2, D, device="cuda:0")
+    calls = _calls_of(eng, eng.backward_order(), lambda ch: tuple(both[:len(ch["k"]), :, i] for i in (0, 1)))
+    apart, together = _together_and_apart(calls, [both])
+    bad = ~torch.isfinite(apart[0])
+    assert bad.any() and not bad.all()
+    for a, b in zip(apart, together):
+        assert torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(nan=0.), b.nan_to_num(nan=0.))
+
+
+@pytest.mark.parametrize("Hq,Hkv,C", [(4, 4, 128), (8, 2, 256)])
+def test_single_writers_among_work_lists(Hq, Hkv, C):
+    """bf16, D = 128, slices of one sequence: calls with one writer per dK/dV row next to calls with work lists.  One head per
+    group: every call adds once to a row, same bits as one call at a time; else up to the order of fp32 sums (as above)."""
+    plan = B.cf_build_chunks([6 * C + 50, 40, 5 * C, 61], C)
+    eng = ChunkAttention(plan, Hq, Hkv, 128, "bf16").load(lambda sid, L: inputs.seq_values(7, sid, L, Hq, Hkv, 128, "bf16"))
+    eng.run_forward()
+    calls = _calls_of(eng, eng.backward_order())
+    for i, b in enumerate(calls):
+        b.f.flags = B.CF_FLAG_DKV_SINGLE_WRITER if i % 3 == 1 else 0
+    apart, together = _together_and_apart(calls, [eng.grad_arena])
+    assert all(torch.equal(a, b) for a, b in zip(apart[1:], together[1:]))
+    if Hq == Hkv:
+        assert torch.equal(apart[0], together[0])
+    else:
+        assert ((apart[0] - together[0]).norm() / apart[0].norm()).item() <= 64 * 2.0 ** -24
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
