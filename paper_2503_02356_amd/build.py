@@ -42,8 +42,8 @@ def spilled_accumulators(report):
 
 def spilled_operands(report):
     """Matrix kernels that spill vector registers: their blocks are laid out to fit, and a few reloads in the loop over blocks
-    take what the layout gained (fp32 backward of 3 packed chunks of 532 tokens, 4 heads, D = 128: 67.1 us with 26 spilled, 64.5
-    with none).  -> [(kernel, what)]"""
+    take what the layout gained (fp32 step of 3 packed chunks of 532 tokens, 4 heads, D = 128: 79 us with 26 spilled in the
+    backward, 71 with none).  -> [(kernel, what)]"""
     return [(k, f"{what}: {n}") for k, what, n in _resources(report)
             if what == "VGPRs Spill" and n != 0 and re.search(r"\d(mfma|f32)_\w+_kernel", k)]
 

@@ -29,7 +29,7 @@
 // dV 2.6e-7, O 1.8e-7; scalar 3.3e-7, 3.8e-7, 3.2e-7, 2.0e-7).
 //
 // Measured, forward + backward of a whole step, calls sharing launches: 6 chunks, 1286 tokens, 1 head, D = 64: 764 us -> 46 us;
-// 6 / 2 heads, D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 0.77 ms (before: one wavefront per row, scalar loads;
+// 6 / 2 heads, D = 128, 4799 tokens in 6 chunks: 13.7 ms -> 0.76 ms (before: one wavefront per row, scalar loads;
 // attn_simple.hip).
 #include <hip/hip_runtime.h>
 
@@ -64,11 +64,14 @@ struct Shape {
 template <int D>
 using Acc = f32x4[D / 16];                   // [4 * c + e], register i: column 64 c + 4 * (4 * quarter + i) + e
 
-// The lane, formed anew at D = 128: there dK/dV fills the 128 registers, and what the compiler keeps of the lane from one use to the next,
-// or over a chain of slices, it makes room for by spilling (26 registers with slices in a chain, reloaded in the loop over blocks:
-// 3 packed chunks of 532 tokens, 4 heads: 67.4 us a step, 60.2 with none; the 4799 tokens below 793 -> 771).
-template <int D>
-__device__ __forceinline__ int lane_of() { return D == 64 ? threadIdx.x & 63 : fresh_lane(); }
+// The lane, as a value that the compiler does not know to be the same for every item: what follows from it is formed where it is used.
+template <int USE>
+__device__ __forceinline__ int lane_again(int lane, int item)
+{
+    int x;
+    asm("; lane %c3" : "=v"(x) : "0"(lane), "s"(item), "n"(USE));
+    return x;
+}
 
 // Combines over the 16 lanes of a quarter (rotations inside a row of 16 lanes).
 template <int N>
@@ -86,10 +89,10 @@ __device__ __forceinline__ void load_row(const float *row, int quarter, f32x4 (&
     for (int j = 0; j < D / 16; ++j) f[j] = *(const f32x4 *)(row + 16 * j + 4 * quarter);
 }
 // The 16 owned rows into LDS, in operand order: piece c (floats 4 c .. 4 c + 3) of row r at [c * 16 + r].
-template <int D>
+template <int D, bool ANEW = false>
 __device__ __forceinline__ void stage_rows(const float *base, int64_t stride, int row0, int last_row, f32x4 *dst)
 {
-    for (int t = wave_id() * 64 + lane_of<D>(); t < RB * D / 4; t += NW * 64) {
+    for (int t = ANEW ? wave_id() * 64 + fresh_lane() : threadIdx.x; t < RB * D / 4; t += NW * 64) {
         const int r = t / (D / 4), c = t % (D / 4);
         dst[c * RB + r] = *(const f32x4 *)(base + (int64_t)min(row0 + r, last_row) * stride + c * 4);
     }
@@ -430,25 +433,29 @@ __device__ __forceinline__ void f32_dq_body(const BwdArgs &b, int id, char *smem
 
 // dK, dV of 16 key rows of one key/value head: (query head of the group, 16-row query block) pairs dealt over the
 // wavefronts.
-template <int D>
+template <int D, bool CHAINS>
 __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *smem, float (*stat)[2 * RB])
 {
     using S = Shape<D>;
+    // In D = 128's kernel of chains dK/dV fills the 128 registers, and what the compiler keeps of the lane from one use to the next, or over
+    // a chain of slices, it makes room for by spilling (26 registers, reloaded in the loop over blocks: 3 packed chunks of 532 tokens, 4 heads,
+    // 79 us a step, 71 with none; the 4799 tokens above 791 -> 757).
+    constexpr bool ANEW = CHAINS && D == 128;
     const BwdArgs::Fwd &p = b.f;
     f32x4 *ks = (f32x4 *)smem, *vs = (f32x4 *)(smem + S::OPERAND);
     float *parts = (float *)(smem + S::OPERANDS);    // of each wavefront: its block's rows, in the end its results
-    const int wave = wave_id();
+    const int lane = threadIdx.x & 63, wave = wave_id(), quarter = lane >> 4, col = lane & 15;
     const int G = p.n_q_heads / p.n_kv_heads, kh = id % p.n_kv_heads;
     TileLocation loc;
-    if (!locate_tile(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, p.n_kv_tokens, RB, id / p.n_kv_heads, loc)) return;
+    if (!locate_tile<ANEW>(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, p.n_kv_tokens, RB, id / p.n_kv_heads, loc)) return;
     const int lk = uniform(loc.len), lq = uniform(loc.other_len), off = lk - lq;
     // (tiles are numbered from a segment's end; its FIRST key tiles are seen by the most rows: start with those)
     const int k0 = ((lk + RB - 1) / RB - 1 - uniform(loc.tile_in_seg)) * RB, rows = min(RB, lk - k0);
     const int qb_first = max(0, k0 - off) / RB, n_qb = (lq + RB - 1) / RB - qb_first;
     if (n_qb <= 0) return;
     const int n_items = G * n_qb;
-    stage_rows<D>((const float *)p.k + (int64_t)loc.begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head, p.kv_stride_tok, k0, lk - 1, ks);
-    stage_rows<D>((const float *)p.v + (int64_t)loc.begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head, p.kv_stride_tok, k0, lk - 1, vs);
+    stage_rows<D, ANEW>((const float *)p.k + (int64_t)loc.begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head, p.kv_stride_tok, k0, lk - 1, ks);
+    stage_rows<D, ANEW>((const float *)p.v + (int64_t)loc.begin * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head, p.kv_stride_tok, k0, lk - 1, vs);
     float *piece = parts + wave * S::PART, *st = stat[wave];                          // this wavefront's LSE and delta by query row
     __syncthreads();
 
@@ -456,40 +463,40 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
 #pragma unroll
     for (int x = 0; x < D / 16; ++x) dk[x] = dv[x] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int n = wave; n < n_items; n += NW) {
-        const int lane = lane_of<D>(), quarter = lane >> 4, col = lane & 15;
+        const int row_lane = ANEW ? lane_again<0>(lane, n) : lane, quarter_ = ANEW ? row_lane >> 4 : quarter, col_ = ANEW ? row_lane & 15 : col;
         const int g = n / n_qb, q0 = (qb_first + n - g * n_qb) * RB, h = kh * G + g;
         const float *q = (const float *)p.q + (int64_t)(loc.other_begin + q0) * p.q_stride_tok + (int64_t)h * p.q_stride_head;
         const float *d_o = (const float *)b.d_o + (int64_t)(loc.other_begin + q0) * b.do_stride_tok + (int64_t)h * b.do_stride_head;
-        const int last = lq - 1 - q0, row = min(col, last);      // relative to the block's first row
+        const int last = lq - 1 - q0, row = min(col_, last);      // relative to the block's first row
         // At D = 64 everything an item reads is requested at once (one latency; short calls are made of those); at
         // D = 128 there are registers for one operand at a time.
         f32x4 a[S::J], qa[S::J];
-        load_row<D>(d_o + (int64_t)row * b.do_stride_tok, quarter, a);
-        auto load_q_row = [&] { load_row<D>(q + (int64_t)row * p.q_stride_tok, quarter, qa); };
+        load_row<D>(d_o + (int64_t)row * b.do_stride_tok, quarter_, a);
+        auto load_q_row = [&] { load_row<D>(q + (int64_t)row * p.q_stride_tok, quarter_, qa); };
         if (D == 64) load_q_row();
         const float *orow = (const float *)p.o + (int64_t)(loc.other_begin + q0 + row) * p.o_stride_tok + (int64_t)h * p.o_stride_head;
         float dlt = 0.f;
 #pragma unroll
         for (int j = 0; j < S::J; ++j) {
-            const f32x4 y = *(const f32x4 *)(orow + 16 * j + 4 * quarter);
+            const f32x4 y = *(const f32x4 *)(orow + 16 * j + 4 * quarter_);
 #pragma unroll
             for (int e = 0; e < 4; ++e) dlt = __builtin_fmaf(a[j][e], y[e], dlt);
         }
         dlt = sum_over_quarters(dlt);
         const float lse = p.lse[(int64_t)h * p.n_tokens + loc.other_begin + q0 + row];
-        if (quarter == 0) {
-            st[col] = col <= last ? lse : kNoRow;
-            st[RB + col] = dlt;
+        if (quarter_ == 0) {
+            st[col_] = col_ <= last ? lse : kNoRow;
+            st[RB + col_] = dlt;
         }
         __builtin_amdgcn_wave_barrier();
-        put_rows<D>(a, piece, lane);
-        f32x4 dp = row_product<D>(a, vs, lane);
+        put_rows<D>(a, piece, row_lane);
+        f32x4 dp = row_product<D>(a, vs, row_lane);
         if (D != 64) load_q_row();
-        f32x4 s = row_product<D>(qa, ks, lane);
-        const int lane_ = lane_of<D>(), first = lane_ >> 4 << 2;      // (of this lane's queries in the block)
-        const int lim = k0 + (lane_ & 15) - off - q0 - first;        // query first + i of the block is masked iff i < lim
-        const f32x4 l4 = *(const f32x4 *)(st + first);
-        f32x4 d4 = *(const f32x4 *)(st + RB + first);
+        f32x4 s = row_product<D>(qa, ks, row_lane);
+        const int sum_lane = ANEW ? lane_again<1>(lane, n) : lane, q4 = ANEW ? sum_lane >> 4 : quarter, key = ANEW ? sum_lane & 15 : col;
+        const int lim = k0 + key - off - q0 - 4 * q4;                // query 4 * q4 + i of the block is masked iff i < lim
+        const f32x4 l4 = *(const f32x4 *)(st + 4 * q4);
+        f32x4 d4 = *(const f32x4 *)(st + RB + 4 * q4);
 #pragma unroll
         for (int i = 0; i < 4; ++i) s[i] = lim > i ? 0.f : probability(s[i], p.softmax_scale, l4[i]);
         if (q0 + off == 0) {
@@ -500,12 +507,12 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
 #pragma unroll
         for (int i = 0; i < 4; ++i) dp[i] = s[i] * (dp[i] - d4[i]);
         __builtin_amdgcn_wave_barrier();                             // st is rewritten by the next item
-        add_column_product<D>(piece, lane_of<D>(), s, dv);
-        put_rows<D>(qa, piece, lane_of<D>());
-        add_column_product<D>(piece, lane_of<D>(), dp, dk);
+        add_column_product<D>(piece, sum_lane, s, dv);
+        put_rows<D>(qa, piece, sum_lane);
+        add_column_product<D>(piece, sum_lane, dp, dk);
     }
     // At D = 64 both results meet in LDS together, at D = 128 there is room for one after the other.
-    const int n = min(NW, n_items), lane = lane_of<D>();
+    const int n = min(NW, n_items), end_lane = D == 128 ? fresh_lane() : lane;
     constexpr int TOGETHER = S::BOTH_MEET ? 2 : 1;
     static_assert(TOGETHER * RB * (D / 4) <= NW * 64, "one step");
     const int t = threadIdx.x, r = t / (D / 4) % rows, c = t % (D / 4);
@@ -514,8 +521,8 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
         if (first == 0) lds_turn();
         else __syncthreads();
         if (wave < n_items) {
-            if (first == 0) write_part<D>(dv, parts + wave * S::PART, lane);
-            if (first + TOGETHER == 2) write_part<D>(dk, parts + ((TOGETHER - 1) * NW + wave) * S::PART, lane);
+            if (first == 0) write_part<D>(dv, parts + wave * S::PART, end_lane);
+            if (first + TOGETHER == 2) write_part<D>(dk, parts + ((TOGETHER - 1) * NW + wave) * S::PART, end_lane);
         }
         __syncthreads();
         const int which = TOGETHER == 1 ? first : t / (rows * (D / 4));
@@ -524,7 +531,7 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
         if (mine) a = sum_parts<D>(parts + (which - first) * NW * S::PART, n, r, c) * (which ? p.softmax_scale : 1.f);
         const unsigned long long bad = __ballot(!finite(a));
         left_out[first / TOGETHER] = bad;
-        if (mine && (bad & lanes_of_row<D>(lane)) == 0)
+        if (mine && (bad & lanes_of_row<D>(end_lane)) == 0)
             *(f32x4 *)((which ? b.d_k : b.d_v) + (int64_t)(loc.begin + k0 + r) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head + c * 4) += a;
     }
     for (int pass = 0; pass < 2 / TOGETHER; ++pass)
@@ -538,7 +545,7 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
                                         [&](int row, int h) { return scalar_delta<float, D>(b, g, row, h); }, gk, gv);
             float *dst = (is_k ? b.d_k : b.d_v) + (int64_t)krow * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head;
 #pragma unroll
-            for (int x = 0; x < D / 64; ++x) dst[lane + 64 * x] += is_k ? gk[x] * p.softmax_scale : gv[x];
+            for (int x = 0; x < D / 64; ++x) dst[end_lane + 64 * x] += is_k ? gk[x] * p.softmax_scale : gv[x];
         });
 }
 
@@ -553,7 +560,7 @@ __global__ __launch_bounds__(NW * 64) void f32_bwd_kernel(BwdArgs b, int dkv_blo
     __shared__ __attribute__((aligned(16))) char smem[BwdLds<D>::bytes];
     __shared__ __attribute__((aligned(16))) float stat[NW][2 * RB];
     const int id = blockIdx.x;
-    if (id < dkv_blocks) f32_dkv_body<D>(b, id, smem, stat);
+    if (id < dkv_blocks) f32_dkv_body<D, false>(b, id, smem, stat);
     else f32_dq_body<D>(b, id - dkv_blocks, smem);
 }
 // Slices of one sequence add to the same dK/dV rows.  One workgroup adds to 16 of them for all slices of the launch, slice by
@@ -571,7 +578,7 @@ __global__ __launch_bounds__(NW * 64) void f32_bwd_batch_kernel(BwdBatch q)
         return;
     }
     for (;;) {
-        f32_dkv_body<D>(q.p[c], id, smem, stat);
+        f32_dkv_body<D, true>(q.p[c], id, smem, stat);
         c = q.next[c];
         if (c < 0) return;
         __syncthreads();                             // the rows that other wavefronts have written, and LDS

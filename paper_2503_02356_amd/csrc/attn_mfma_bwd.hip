@@ -236,7 +236,7 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     int seg, kt0, first_pair = 0, n_pairs = 0;
     if (FUSED_HEADS) {
         TileLocation loc;
-        if (!locate_tile(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, p.n_kv_tokens, BKV, id, loc)) return;
+        if (!locate_tile<RING == 3>(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, p.n_kv_tokens, BKV, id, loc)) return;
         seg = loc.seg;
         // locate_tile numbers tiles from the end; the FIRST key tiles of a segment are seen by the most rows, so
         // flip the order inside the segment to start the heaviest tiles first.

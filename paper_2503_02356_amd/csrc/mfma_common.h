@@ -410,6 +410,8 @@ struct TileLocation {
     int begin, len;               // of the segment in cu
     int other_begin, other_len;   // of the segment in cu_other
 };
+// ANEW: nothing of the lane is kept for it (kernels with no register to spare).
+template <bool ANEW = false>
 __device__ __forceinline__ bool locate_tile(const int32_t *cu, const int32_t *cu_other, int n_seg, int n_rows, int tile, int rank,
                                             TileLocation &out)
 {
@@ -421,7 +423,7 @@ __device__ __forceinline__ bool locate_tile(const int32_t *cu, const int32_t *cu
         out.tile_in_seg = n - 1 - rank;
         return rank < n;
     }
-    const int lane = fresh_lane();
+    const int lane = ANEW ? fresh_lane() : threadIdx.x & 63;
     const int place = n_rows / tile + n_seg - 1 - rank;
     if (place < 0) return false;
     int lo = 0, hi = n_seg;                          // the segment is one of [lo, hi): 64 probes at a time
@@ -434,11 +436,12 @@ __device__ __forceinline__ bool locate_tile(const int32_t *cu, const int32_t *cu
     const int g = min(lo + lane, hi - 1);
     const int b0 = cu[g], b1 = cu[g + 1], o0 = cu_other[g], o1 = cu_other[g + 1];
     const int last = 63 - __clzll((long long)__ballot(lo + lane < hi && b0 / tile + g <= place));
+    auto of_last = [&](int x) { return ANEW ? __builtin_amdgcn_readlane(x, last) : __builtin_amdgcn_readfirstlane(__shfl(x, last)); };
     out.seg = __builtin_amdgcn_readfirstlane(lo + last);
-    out.begin = __builtin_amdgcn_readlane(b0, last);
-    out.len = __builtin_amdgcn_readlane(b1 - b0, last);
-    out.other_begin = __builtin_amdgcn_readlane(o0, last);
-    out.other_len = __builtin_amdgcn_readlane(o1 - o0, last);
+    out.begin = of_last(b0);
+    out.len = of_last(b1 - b0);
+    out.other_begin = of_last(o0);
+    out.other_len = of_last(o1 - o0);
     out.tile_in_seg = __builtin_amdgcn_readfirstlane(place - out.begin / tile - out.seg);
     return out.tile_in_seg * tile < out.len;
 }

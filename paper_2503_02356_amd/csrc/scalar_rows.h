@@ -9,7 +9,6 @@
 #include <hip/hip_runtime.h>
 
 #include "chunkflow.h"
-#include "mfma_common.h"
 
 namespace cf {
 
@@ -60,7 +59,7 @@ __device__ inline const T *row_of(const void *base, int row, int64_t stride_tok,
 template <typename T, int D, int UNROLL, typename Q>
 __device__ inline void scalar_fwd_row(const cf_attn_fwd_params &p, const SegmentRows &g, int row, int h, Q q)
 {
-    const int lane = fresh_lane(), kh = h / (p.n_q_heads / p.n_kv_heads);
+    const int lane = threadIdx.x & 63, kh = h / (p.n_q_heads / p.n_kv_heads);
     const int n_vis = g.lk - g.lq + (row - g.q0) + 1;
     const T *kb = (const T *)p.k + (int64_t)kh * p.kv_stride_head;
     const T *vb = (const T *)p.v + (int64_t)kh * p.kv_stride_head;
@@ -100,7 +99,7 @@ template <typename T, int D, int UNROLL, typename B, typename Q, typename DO>
 __device__ inline void scalar_dq_row(const B &b, const SegmentRows &g, int row, int h, Q q, DO d_o, float delta)
 {
     const auto &p = b.f;
-    const int lane = fresh_lane(), kh = h / (p.n_q_heads / p.n_kv_heads);
+    const int lane = threadIdx.x & 63, kh = h / (p.n_q_heads / p.n_kv_heads);
     const int n_vis = g.lk - g.lq + (row - g.q0) + 1;
     const T *kb = (const T *)p.k + (int64_t)kh * p.kv_stride_head;
     const T *vb = (const T *)p.v + (int64_t)kh * p.kv_stride_head;
@@ -139,7 +138,7 @@ __device__ inline void scalar_dkv_row(const B &b, const SegmentRows &g, int krow
                                       float (&dk)[D / 64], float (&dv)[D / 64])
 {
     const auto &p = b.f;
-    const int lane = fresh_lane(), G = p.n_q_heads / p.n_kv_heads;
+    const int lane = threadIdx.x & 63, G = p.n_q_heads / p.n_kv_heads;
     const int j = krow - g.k0, prefix = g.lk - g.lq;
     const int i_first = j > prefix ? j - prefix : 0;  // first query row that sees this key
     constexpr int DPL = D / 64;
