@@ -24,6 +24,14 @@ def schedule_memory(plan, K, n_q_heads, n_kv_heads, head_dim, elem_bytes=2):
                 state_bytes=st["state_tokens"] * per_state_token)
 
 
+def calls_together(ws_bytes):
+    """Backward calls of a single stream that a runner gives workspaces of their own, so that they can share launches: as many as a
+    launch takes while these are small, else half of it.  16 packed chunks, a step with 8 / 16 workspaces: 28 / 4 heads, chunks of 512
+    tokens (57 KB each) 259 / 220 us, 4096 (451 KB) 2611 / 2576, 8192 (903 KB) 8.52 / 8.61 ms; 64 / 8 heads, 2048 (514 KB) 1995 / 1943 us,
+    4096 (1 MB) 5686 / 5708."""
+    return B.BWD_TOGETHER if ws_bytes * B.BWD_TOGETHER <= 12 << 20 else B.BWD_TOGETHER // 2
+
+
 class ChunkAttention:
     def __init__(self, plan, n_q_heads, n_kv_heads, head_dim, dtype, scale=None, device="cuda:0", flags=0,
                  n_streams=1, fused_launch=False, only_groups=None, tile_tables=True):
@@ -174,7 +182,7 @@ class ChunkAttention:
         # as backward calls share a launch.
         self.workspaces = [torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
                            for _ in range(0 if self.fused_launch else self.n_streams if self.n_streams > 1 else
-                                          min(B.BWD_TOGETHER, len(self.chunks)))]
+                                          min(calls_together(ws_bytes), len(self.chunks)))]
         self.streams = [torch.cuda.Stream(device=dev) for _ in range(self.n_streams)] if self.n_streams > 1 else []
         # groups go, in plan order, to the stream with the least work so far (work = unmasked pairs)
         load, lane_of = [0] * self.n_streams, {}

@@ -325,3 +325,11 @@ def test_launch_sharing_limit_is_the_library_s():
     """The runner lays out one backward workspace per call that shares a launch."""
     header = open(os.path.join(ROOT, "paper_2503_02356_amd", "csrc", "kernels.h")).read()
     assert int(re.search(r"CF_BWD_BATCH_MAX = (\d+);", header)[1]) == B.BWD_TOGETHER
+
+
+def test_a_runner_s_workspaces_stay_small():
+    """One per call that shares a launch where launches are short; large chunks, whose launches gain nothing from it, hold half as many."""
+    from paper_2503_02356_amd.runner import calls_together
+    need = lambda T, heads: heads * T * 4            # (delta; the work list adds some KB)
+    assert calls_together(need(512, 28)) == calls_together(need(4096, 28)) == calls_together(need(2048, 64)) == B.BWD_TOGETHER
+    assert calls_together(need(8192, 28)) == calls_together(need(32768, 64)) == 8
