@@ -16,7 +16,7 @@
 //                  items of similar length, longest first; the items of one key/value head meet in dK/dV
 //                  through fp32 atomic adds (once per workgroup, at the end).
 //
-//  dq kernel   Same shape as the forward kernel: a workgroup owns 128 query rows of one head, key/value
+//  dq kernel   Same shape as the forward kernel: a workgroup owns four units of 32 query rows and a head, key/value
 //              tiles of 64 rows go through LDS, everything transposed so that a lane owns one query:
 //                  S^T = K Q^T   dP^T = V dO^T   dS^T = P^T (dP^T - delta)   dQ^T += K^T dS^T
 //              LSE and delta are one scalar per lane; dS^T feeds the last product straight from registers.
@@ -220,7 +220,8 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
                                          const int *__restrict__ wl, char *st0, char *st1, int wave = wave_id())
 {
     using Stage = DkvStage<D>;
-    using F = Mfma<D>;
+    constexpr int M = D == 64 ? 32 : 16;
+    using F = Mfma<M>;
     constexpr int KS = D / F::K, DB = D / 32, N = F::N32, BLOCK = 32 * 2 * D;
     constexpr int QW = DkvShape<D>::QW, BQ = DkvShape<D>::BQ, BKV = DkvShape<D>::BKV;
     static_assert(FUSED_HEADS || QW == 1, "atomic updates are made by the wavefront that owns the keys");
@@ -287,7 +288,7 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     for (int i = 0; i < DB; ++i)
 #pragma unroll
         for (int j = 0; j < 16; ++j) dv[i][j] = dk[i][j] = 0.f;
-    BlockAddress<D> at;                              // of the block in use
+    BlockAddress<D, M> at;                              // of the block in use
     at.flip(query_wave * BLOCK);
 
     // Tile staging: Q and dO rows, LSE and -delta go straight from global memory into an LDS stage; once they have landed,
@@ -581,6 +582,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(BwdArgs b, const float
 // Several chunks' backward in one launch: workgroups [first_block[c], first_block[c + 1]) belong to chunk c.
 struct BwdBatch {
     int n;
+    unsigned wide;                                               // bit c: chunk c's dQ multiplies with M = 32
     int first_block[CF_BWD_BATCH_MAX + 1];
     int next[CF_BWD_BATCH_MAX];                                  // chunk whose dK/dV rows are done behind this one's, by the same workgroups
     int capacity[CF_BWD_BATCH_MAX], slots[CF_BWD_BATCH_MAX];     // of the work list that is built (see there)
@@ -640,10 +642,10 @@ struct KvStage {
 // the others (one query head per workgroup left the wavefronts without rows idle), the second run takes one or two key tiles from
 // LDS, where the first has left them, and no tile's second half is computed where no row sees it.  Steps of 16 packed chunks, 28 / 4
 // heads: 512 tokens around 37 each 297 -> 269 us, 8192 around 600 9.31 -> 9.05 ms; 16 / 4 heads, D = 64, 16.7k tokens 979 -> 940 us.
-template <int D>
+template <int D, int M>
 __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ delta, int id, char *stage_a, char *stage_b)
 {
-    using F = Mfma<D>;
+    using F = Mfma<M>;
     constexpr int KS = D / F::K, DB = D / F::M, N = F::N32, KVTILE_BYTES = KvStage<D>::tile_bytes;
     const BwdArgs::Fwd &p = b.f;
     const int wave = wave_id(), group = F::group(), col = F::column();
@@ -716,14 +718,14 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
 #pragma unroll
                 for (int e = 0; e < 8; ++e) dlt[qb] = __builtin_fmaf((float)of[e], (float)dof[qb][ks][e], dlt[qb]);
             }
-            dlt[qb] = sum_over_groups<D>(dlt[qb]);
+            dlt[qb] = sum_over_groups<M>(dlt[qb]);
             if (iq < lq && group == 0) delta[stat_at(qb)] = -dlt[qb];
         }
     }
     const float c2 = p.softmax_scale * kLog2e;
-    const LaneOffsets<D> lo = lane_offsets<D>();
+    const LaneOffsets<D, M> lo = lane_offsets<D, M>();
 
-    RowBlock<D> dq;
+    RowBlock<D, M> dq;
 #pragma unroll
     for (int i = 0; i < DB; ++i)
 #pragma unroll
@@ -783,8 +785,11 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
                         for (int kb = 0; kb < N; ++kb) {
 #pragma unroll
                             for (int qb = 0; qb < N; ++qb) s[kb][qb] = F::mul(ka[kb][ks], qf[qb][ks], s[kb][qb]);
+                            // (M = 32: S and dP are one chain each; two MFMAs of a chain in a row would wait.  LDS reads may pass.)
+                            if (M == 32) __builtin_amdgcn_sched_barrier(0x180);
 #pragma unroll
                             for (int qb = 0; qb < N; ++qb) dp[kb][qb] = F::mul(va[kb][ks], dof[qb][ks], dp[kb][qb]);
+                            if (M == 32) __builtin_amdgcn_sched_barrier(0x180);
                         }
                     // K^T fragments of the dQ contraction: requested now, so that they arrive during the arithmetic
                     bf16x8 kt[32 / F::K][DB];
@@ -867,7 +872,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
         sweep(std::true_type(), 0);
 #pragma unroll
         for (int qb = 0; qb < N; ++qb) {
-            dlt[qb] = sum_over_groups<D>(dsum[qb]);  // the lanes of a row hold different keys of it
+            dlt[qb] = sum_over_groups<M>(dsum[qb]);  // the lanes of a row hold different keys of it
             if (row_of_block(qb) < lq && group == 0) delta[stat_at(qb)] = -dlt[qb];
         }
     }
@@ -879,7 +884,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
         float scale[N];
 #pragma unroll
         for (int qb = 0; qb < N; ++qb) scale[qb] = p.softmax_scale;
-        store_rows_bf16<D>(dq, scale, scratch, lq - wq0, [&](int r) {
+        store_rows_bf16<D, M>(dq, scale, scratch, lq - wq0, [&](int r) {
             return (char *)b.d_q + ((int64_t)(q_seg0 + wq0 + r) * b.dq_stride_tok + (int64_t)h * b.dq_stride_head) * 2;
         });
         if constexpr (D == 64) {
@@ -895,7 +900,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
 }
 
 // wl != nullptr: the launch has one extra workgroup (the first) that builds the dK/dV work list.
-template <int D>
+template <int D, int M>
 __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(BwdArgs b, float *__restrict__ delta, int *wl, int capacity)
 {
     // The list builder is workgroup 0: it starts with the first wave of workgroups and is long done when the
@@ -908,13 +913,14 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(BwdArgs b, float *__res
     // loads of the next tile cannot alias the reads of the current one, or it waits for them too early.
     __shared__ __attribute__((aligned(16))) char stage_a[KvStage<D>::bytes];
     __shared__ __attribute__((aligned(16))) char stage_b[KvStage<D>::bytes];
-    dq_body<D>(b, delta, (int)blockIdx.x - (wl != nullptr ? 1 : 0), stage_a, stage_b);
+    dq_body<D, M>(b, delta, (int)blockIdx.x - (wl != nullptr ? 1 : 0), stage_a, stage_b);
 }
 
 // Several chunks, heaviest first: dQ and delta of a chunk depend on nothing another chunk's backward writes, so the last,
 // partly filled wave of workgroups of a big chunk can be filled by the next chunk's.  The first q.n workgroups build the
 // chunks' dK/dV work lists.
-template <int D>
+// M = 0: chunks with either M.
+template <int D, int M>
 __global__ __launch_bounds__(256, 2) void mfma_dq_batch_kernel(BwdBatch q)
 {
     if ((int)blockIdx.x < q.n) {
@@ -925,7 +931,8 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_batch_kernel(BwdBatch q)
     __shared__ __attribute__((aligned(16))) char stage_a[KvStage<D>::bytes];
     __shared__ __attribute__((aligned(16))) char stage_b[KvStage<D>::bytes];
     const int id = (int)blockIdx.x - q.n, c = chunk_of(q, id);
-    dq_body<D>(q.b[c], q.delta[c], id - q.first_block[c], stage_a, stage_b);
+    if (M == 32 || (M == 0 && (q.wide >> c & 1))) dq_body<D, 32>(q.b[c], q.delta[c], id - q.first_block[c], stage_a, stage_b);
+    else if constexpr (M != 32) dq_body<D, 16>(q.b[c], q.delta[c], id - q.first_block[c], stage_a, stage_b);
 }
 
 // Launch geometry of one chunk's backward.
@@ -970,7 +977,9 @@ hipError_t run_bwd(const cf_attn_bwd_params &b, const BwdWorkspace &ws, hipStrea
     // dQ first: it also produces delta, which the dK/dV kernel reads; its first workgroup builds the dK/dV work list
     // where one is needed.
     int *wl = g.fused ? nullptr : ws.worklist;
-    mfma_dq_kernel<D><<<dim3((unsigned)(g.dq_blocks + (wl ? 1 : 0))), 256, 0, s>>>(b, ws.delta, wl, (int)ws.worklist_items);
+    const dim3 dq_grid((unsigned)(g.dq_blocks + (wl ? 1 : 0)));
+    if (D == 64 || wide_mfma(b.f)) mfma_dq_kernel<D, 32><<<dq_grid, 256, 0, s>>>(b, ws.delta, wl, (int)ws.worklist_items);
+    else if constexpr (D == 128) mfma_dq_kernel<D, 16><<<dq_grid, 256, 0, s>>>(b, ws.delta, wl, (int)ws.worklist_items);
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : launch_dkv<D>(b, ws, g, take_profile_hook(), s);
 }
@@ -984,6 +993,7 @@ bool append(BwdBatch &q, const cf_attn_bwd_params &b, const BwdWorkspace &ws, co
     q.capacity[i] = (int)ws.worklist_items;
     q.delta[i] = ws.delta;
     q.wl[i] = g.fused ? nullptr : ws.worklist;
+    q.wide = (i == 0 ? 0 : q.wide) | (unsigned)wide_mfma(b.f) << i;
     q.b[i] = b;
     ++q.n;
     return true;
@@ -1064,7 +1074,12 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
         tokens[first_of[c]] -= own;
         if (!append(q, *chunks[c].b, chunks[c].ws, g[c], g[c].dq_blocks)) return hipErrorInvalidConfiguration;
     }
-    mfma_dq_batch_kernel<D><<<dim3((unsigned)(q.first_block[n] + n)), 256, 0, s>>>(q);
+    const dim3 dq_grid((unsigned)(q.first_block[n] + n));
+    if (D == 64 || q.wide == (1u << n) - 1) mfma_dq_batch_kernel<D, 32><<<dq_grid, 256, 0, s>>>(q);
+    else if constexpr (D == 128) {
+        if (q.wide == 0) mfma_dq_batch_kernel<D, 16><<<dq_grid, 256, 0, s>>>(q);
+        else mfma_dq_batch_kernel<D, 0><<<dq_grid, 256, 0, s>>>(q);
+    }
     hipError_t e = hipGetLastError();
     for (int first = 0, end; first < n && e == hipSuccess; first = end) {
         for (end = first + 1; end < n && first_of[end] == first;) ++end;

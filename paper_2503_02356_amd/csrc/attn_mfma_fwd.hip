@@ -38,10 +38,10 @@ struct Stage {
 // id: index of the workgroup among those of this chunk
 // D = 64 keeps what the scalar kernels keep in fp32: the second product takes P with all its 24 bits, as three bf16 operands
 // (three MFMAs), exponentials and row sums are formed so that the errors of O and LSE against fp64 are no larger than theirs.
-template <int D>
+template <int D, int M>
 __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, char *stage_a, char *stage_b)
 {
-    using F = Mfma<D>;
+    using F = Mfma<M>;
     constexpr int KS = D / F::K, DB = D / F::M, KB = BN / F::M, QB = F::N32, TILE_BYTES = Stage<D>::tile_bytes;
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int group = F::group(), col = F::column();
@@ -99,9 +99,9 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *(const bf16x8 *)(qrow + ks * 2 * F::K + group * 16);
     }
-    const LaneOffsets<D> lo = lane_offsets<D>();
+    const LaneOffsets<D, M> lo = lane_offsets<D, M>();
 
-    RowBlock<D> o_acc;
+    RowBlock<D, M> o_acc;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -180,7 +180,7 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
             if (__builtin_amdgcn_ballot_w64(grow) != 0) {
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) {
-                    const float mx = max_over_groups<D>(mx2[qb]), m_new = mx > m_run[qb] + kLazy<D> ? mx : m_run[qb];
+                    const float mx = max_over_groups<M>(mx2[qb]), m_new = mx > m_run[qb] + kLazy<D> ? mx : m_run[qb];
                     const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * kUnit);   // first tile: exp2(-inf) = 0
                     m_run[qb] = m_new;
                     l_run[qb] *= alpha;
@@ -243,20 +243,21 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     float l_tot[QB], scale[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        l_tot[qb] = sum_over_groups<D>(l_run[qb]);
+        l_tot[qb] = sum_over_groups<M>(l_run[qb]);
         scale[qb] = 1.f / l_tot[qb];
     }
     // O rows leave through this wavefront's part of the (now idle) stage buffers, whole rows per store instruction.
     // The scale of a padding row (l_tot = 0 cannot happen: every real row sees its own key) is never stored.
     char *scratch = (wave < 2 ? stage_a : stage_b) + (wave & 1) * RowScratch<D>::bytes;
-    store_rows_bf16<D>(o_acc, scale, scratch, lq - wq0, [&](int r) {
+    store_rows_bf16<D, M>(o_acc, scale, scratch, lq - wq0, [&](int r) {
         return (char *)p.o + ((int64_t)(q_seg0 + wq0 + r) * p.o_stride_tok + (int64_t)h * p.o_stride_head) * 2;
     });
     const int iq = wq0 + (lane & 31);                // lane l < 32 holds the sums of row l, in block l / M
     if (iq < lq && lane < 32) {
         const int qb = QB - 1;
         const float m = lane < F::M ? m_run[0] : m_run[qb], l = lane < F::M ? l_tot[0] : l_tot[qb];
-        p.lse[(int64_t)h * p.n_tokens + q_seg0 + iq] = m * (D == 64 ? 1.f : 0.69314718055994530942f) + __logf(l);
+        // One rounding in every kernel: where a product and a sum end up in different blocks, the compiler rounds both.
+        p.lse[(int64_t)h * p.n_tokens + q_seg0 + iq] = __builtin_fmaf(m, D == 64 ? 1.f : 0.69314718055994530942f, __logf(l));
     }
     if constexpr (D == 64) {
         for_rows_not_finite<D>(o_acc, scale[0], lq - wq0, [&](int r) {
@@ -267,14 +268,14 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     }
 }
 
-template <int D>
+template <int D, int M>
 __global__ __launch_bounds__(256, 2) void mfma_fwd_kernel(cf_attn_fwd_params p)
 {
     // Two separate arrays (not one array with two halves): the compiler must see that the direct-to-LDS
     // loads of the next tile cannot alias the reads of the current one, or it waits for them too early.
     __shared__ __attribute__((aligned(16))) char stage_a[Stage<D>::bytes];
     __shared__ __attribute__((aligned(16))) char stage_b[Stage<D>::bytes];
-    fwd_body<D>(p, blockIdx.x, stage_a, stage_b);
+    fwd_body<D, M>(p, blockIdx.x, stage_a, stage_b);
 }
 
 // Several chunks in one launch: workgroups [first_block[c], first_block[c+1]) belong to chunk c.  The host
@@ -282,10 +283,12 @@ __global__ __launch_bounds__(256, 2) void mfma_fwd_kernel(cf_attn_fwd_params p)
 // the next chunk's workgroups instead of leaving compute units idle.
 struct FwdBatch {
     int n;
+    unsigned wide;                // bit c: chunk c multiplies with M = 32
     int first_block[CF_FWD_BATCH_MAX + 1];
     cf_attn_fwd_params p[CF_FWD_BATCH_MAX];
 };
-template <int D>
+// M = 0: chunks with either M.
+template <int D, int M>
 __global__ __launch_bounds__(256, 2) void mfma_fwd_batch_kernel(FwdBatch b)
 {
     __shared__ __attribute__((aligned(16))) char stage_a[Stage<D>::bytes];
@@ -293,7 +296,8 @@ __global__ __launch_bounds__(256, 2) void mfma_fwd_batch_kernel(FwdBatch b)
     const int id = blockIdx.x;
     int c = 0;
     while (c + 1 < b.n && id >= b.first_block[c + 1]) ++c;
-    fwd_body<D>(b.p[c], id - b.first_block[c], stage_a, stage_b);
+    if (M == 32 || (M == 0 && (b.wide >> c & 1))) fwd_body<D, 32>(b.p[c], id - b.first_block[c], stage_a, stage_b);
+    else if constexpr (M != 32) fwd_body<D, 16>(b.p[c], id - b.first_block[c], stage_a, stage_b);
 }
 
 // Upper bound on the number of 128-row tiles: sum_g ceil(Lq_g / BM) <= T / BM + n_segments.
@@ -311,16 +315,21 @@ hipError_t launch_mfma_fwd_batch(const cf_attn_fwd_params *const *chunks, int n,
     if (n < 1 || n > CF_FWD_BATCH_MAX) return hipErrorInvalidValue;
     FwdBatch b;
     b.n = n;
+    b.wide = 0;
     int64_t total = 0;
     for (int c = 0; c < n; ++c) {
         b.first_block[c] = (int)total;
         b.p[c] = *chunks[c];
+        b.wide |= (unsigned)wide_mfma(*chunks[c]) << c;
         total += fwd_blocks(*chunks[c]);
         if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     }
     b.first_block[n] = (int)total;
-    if (chunks[0]->head_dim == 64) mfma_fwd_batch_kernel<64><<<dim3((unsigned)total), 256, 0, s>>>(b);
-    else mfma_fwd_batch_kernel<128><<<dim3((unsigned)total), 256, 0, s>>>(b);
+    const dim3 grid((unsigned)total);
+    if (chunks[0]->head_dim == 64) mfma_fwd_batch_kernel<64, 32><<<grid, 256, 0, s>>>(b);
+    else if (b.wide == 0) mfma_fwd_batch_kernel<128, 16><<<grid, 256, 0, s>>>(b);
+    else if (b.wide == (1u << n) - 1) mfma_fwd_batch_kernel<128, 32><<<grid, 256, 0, s>>>(b);
+    else mfma_fwd_batch_kernel<128, 0><<<grid, 256, 0, s>>>(b);
     return hipGetLastError();
 }
 
@@ -330,8 +339,10 @@ hipError_t launch_mfma_fwd(const cf_attn_fwd_params &p, hipStream_t s)
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const ProfileHook hook = take_profile_hook();
     if (hook.start) (void)hipEventRecord(hook.start, s);
-    if (p.head_dim == 64) mfma_fwd_kernel<64><<<dim3((unsigned)blocks), 256, 0, s>>>(p);
-    else mfma_fwd_kernel<128><<<dim3((unsigned)blocks), 256, 0, s>>>(p);
+    const dim3 grid((unsigned)blocks);
+    if (p.head_dim == 64) mfma_fwd_kernel<64, 32><<<grid, 256, 0, s>>>(p);
+    else if (wide_mfma(p)) mfma_fwd_kernel<128, 32><<<grid, 256, 0, s>>>(p);
+    else mfma_fwd_kernel<128, 16><<<grid, 256, 0, s>>>(p);
     const hipError_t e = hipGetLastError();
     if (hook.stop) (void)hipEventRecord(hook.stop, s);
     return e;

@@ -121,6 +121,14 @@ hipError_t launch_simple_bwd(const cf_attn_bwd_params &p, const BwdWorkspace &ws
 // delta[h][t] = sum_d dO[t][h][d] * O[t][h][d].
 hipError_t launch_delta(const cf_attn_bwd_params &p, const BwdWorkspace &ws, hipStream_t s);
 
+// head_dim 128, forward and dQ: 32x32x16 MFMAs instead of 16x16x32 (mfma_common.h)?  A launch that fills the chip is limited by power and
+// gains 2-7 % from the smaller ones.  On a chip that is mostly empty a wavefront is alone on its SIMD, and the time to issue twice as many
+// is added to its chain: forwards of up to 1000 rows behind 3000-50000 keys 3.2-3.7 % slower, backwards 1 %.  What shares a call's launch
+// may not decide, since its bits depend on the choice; so the line lies where 16 calls, the most of a launch, have no more workgroups (of 128
+// rows and a head) than the chip holds, 512.  8000 tokens of 8 / 2 heads in slices of 512, all forwards in a launch: 228 us with
+// 16x16x32, 219 with 32x32x16; in slices of 1000: 160 and 162.
+inline bool wide_mfma(const cf_attn_fwd_params &p) { return p.head_dim == 64 || (int64_t)p.n_tokens * p.n_q_heads <= 32 * 128; }
+
 // bf16 MFMA kernels, head_dim 64 and 128 (one head_dim per batch).
 hipError_t launch_mfma_fwd(const cf_attn_fwd_params &p, hipStream_t s);
 // Forward of 1..CF_FWD_BATCH_MAX chunks as one launch, workgroups dealt in the order of `chunks`.

@@ -5,12 +5,12 @@
 //   B (K x N): lane holds col  n = l % M, k = 8*group + 0..7        (bf16x8)
 //   C/D (M x N, fp32): lane holds col n = l % M, register i <-> row (i/4)*8 + 4*group + i%4
 //                      (M = 32: 16 registers; M = 16: 4 registers, i.e. row 4*group + i)
-// head_dim 128 multiplies with M = 16 (the gradient accumulators of its dK/dV kernel apart): these kernels are limited by the
-// card's power (1.7-1.8 GHz of 2.4 with M = 32 throughout), and on N(0,1) operands the 16x16x32 instruction does more per
-// joule (a sum of 32 products per accumulator update instead of 16): a loop of nothing but MFMAs runs at 1960-2050 TFLOP/s with
-// M = 16 and at 1740-1780 with M = 32.  32768 queries of 64 / 8 heads over 131072 keys: forward 111.9 -> 105.5 ms, dQ 153.5 -> 141.0,
-// dK/dV 207.4 -> 199.5; the clock goes up to 1.98 GHz.  head_dim 64, which splits P and dS into three operands and is
-// bound by vector instructions at 2.2 GHz, keeps M = 32: half as many MFMAs to issue (16 x 16: 2.5 % slower).
+// head_dim 128 multiplies with M = 16 (the gradient accumulators of its dK/dV kernel apart, and small calls, wide_mfma()): launches
+// that fill the chip are limited by the card's power, and on N(0,1) operands the 16x16x32 instruction does more per joule (a sum of
+// 32 products per accumulator update instead of 16): a loop of nothing but MFMAs runs at 1990-2030 TFLOP/s with M = 16 and at 1800 with
+// M = 32.  32768 queries of 64 / 8 heads over 131072 keys: forward 111.9 -> 105.5 ms, dQ 153.5 -> 141.0, dK/dV 207.4 -> 199.5.
+// head_dim 64, which splits P and dS into three operands and is bound by vector instructions, keeps M = 32: half as many MFMAs to
+// issue (16 x 16: 2.5 % slower).
 //
 // ds_read_tr16_b64 (transposing LDS read): inside each block of 16 lanes, lane r supplies the address
 // of 4 consecutive 16-bit elements; the 16x4 elements are handed out so that lane i receives
@@ -37,9 +37,9 @@ typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 #define CF_LDS __attribute__((address_space(3)))
 
-template <int D>
+template <int SIZE>
 struct Mfma {
-    static constexpr int M = D == 64 ? 32 : 16, K = 512 / M;
+    static constexpr int M = SIZE, K = 512 / M;
     static constexpr int R = M * M / 64;             // registers of a result
     static constexpr int N32 = 32 / M;               // blocks of M that make 32
     typedef float Acc __attribute__((ext_vector_type(R)));
@@ -158,19 +158,19 @@ __device__ __forceinline__ int tile_off(int row, int unit) { return row * (2 * D
 //                row/col = tile column M*db + lane % M): offsets of the two 4-row reads that make one
 //                bf16x8 operand, for contraction rows 4*group + {0..3 by lane} and 8 (M = 32) or 16 rows further.
 //                K rows further down the tile add K row lengths.
-template <int D>
+template <int D, int M>
 struct LaneOffsets {
-    static constexpr int M = Mfma<D>::M, UNITS = Mfma<D>::K / 8;
+    static constexpr int UNITS = Mfma<M>::K / 8;
     int row_unit[D / 8 / UNITS];
     int tr_lo[D / M], tr_hi8[M == 32 ? D / M : 1];
     __device__ __forceinline__ int tr_hi(int db) const { return M == 32 ? tr_hi8[db] : tr_lo[db] + 16 * 2 * D; }
 };
-template <int D>
-__device__ __forceinline__ LaneOffsets<D> lane_offsets()
+template <int D, int M>
+__device__ __forceinline__ LaneOffsets<D, M> lane_offsets()
 {
-    constexpr int M = Mfma<D>::M, UNITS = LaneOffsets<D>::UNITS;
+    constexpr int UNITS = LaneOffsets<D, M>::UNITS;
     const int lane = threadIdx.x & 63, group = lane / M, r16 = lane & 15, blk = M == 32 ? (lane >> 4) & 1 : 0;
-    LaneOffsets<D> o;
+    LaneOffsets<D, M> o;
 #pragma unroll
     for (int ks = 0; ks < D / 8 / UNITS; ++ks) o.row_unit[ks] = tile_off<D>(lane % M, UNITS * ks + group);
     const int r_lo = 4 * group + (r16 >> 2), u0 = 2 * blk + ((r16 >> 1) & 1), sub = 8 * (r16 & 1);
@@ -186,20 +186,20 @@ __device__ __forceinline__ LaneOffsets<D> lane_offsets()
 // bits above the group's; so do the halves of a transposed operand, of rows FIRST * half + 0..3 and STEP rows further, whose
 // columns are those of M = 32), one instruction per read.
 // forget(): from here on the compiler computes them anew instead of keeping the results of the last use.
-template <int D>
+template <int D, int M>
 struct BlockAddress {
-    static constexpr int STEP = D == 64 ? 8 : 4, FIRST = 12 - STEP;
+    static constexpr int STEP = M == 32 ? 8 : 4, FIRST = 12 - STEP;
     int row0, tr0;
     __device__ __forceinline__ BlockAddress()
     {
         const int lane = threadIdx.x & 63, r16 = lane & 15;
-        row0 = lane_offsets<D>().row_unit[0];
+        row0 = lane_offsets<D, M>().row_unit[0];
         tr0 = tile_off<D>(FIRST * (lane >> 5) + (r16 >> 2), 2 * ((lane >> 4) & 1) + ((r16 >> 1) & 1)) + 8 * (r16 & 1);
     }
     // to the block `bytes` (a power of two beyond a block's size) further, and back
     __device__ __forceinline__ void flip(int bytes) { row0 ^= bytes, tr0 ^= bytes; }
     __device__ __forceinline__ void forget() { asm volatile("" : "+v"(row0), "+v"(tr0)); }
-    __device__ __forceinline__ int row(int ks) const { return row0 ^ (ks * LaneOffsets<D>::UNITS * 16); }
+    __device__ __forceinline__ int row(int ks) const { return row0 ^ (ks * LaneOffsets<D, M>::UNITS * 16); }
     __device__ __forceinline__ int tr_lo(int db) const { return tr0 ^ (db << 6); }
     __device__ __forceinline__ int tr_hi(int db) const { return (tr_lo(db) ^ ((STEP == 8 ? 3 : 2) << 4)) + STEP * 2 * D; }
 };
@@ -320,14 +320,14 @@ struct RowScratch {
     static constexpr int stride = 2 * D + 16;       // keeps 16-byte alignment, spreads rows over banks
     static constexpr int bytes = 32 * stride;
 };
-template <int D>
-using RowBlock = typename Mfma<D>::Acc[D / Mfma<D>::M][Mfma<D>::N32];
-template <int D, typename RowPtr>
-__device__ __forceinline__ void store_rows_bf16(const RowBlock<D> &acc, const float (&scale)[Mfma<D>::N32], char *scratch, int rows_valid,
+template <int D, int M>
+using RowBlock = typename Mfma<M>::Acc[D / M][Mfma<M>::N32];
+template <int D, int M, typename RowPtr>
+__device__ __forceinline__ void store_rows_bf16(const RowBlock<D, M> &acc, const float (&scale)[Mfma<M>::N32], char *scratch, int rows_valid,
                                                 RowPtr row_ptr)
 {
     constexpr int S = RowScratch<D>::stride, UNITS = D / 8, RPI = 512 / D;
-    using F = Mfma<D>;
+    using F = Mfma<M>;
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int n = 0; n < F::N32; ++n)
@@ -352,9 +352,8 @@ __device__ __forceinline__ void store_rows_bf16(const RowBlock<D> &acc, const fl
 // visit(r), by the whole wavefront, for every row r < rows_valid of a 32 x D block (as above, D = 64: a lane owns row lane % 32) whose
 // results, scaled, are not finite.
 template <int D, typename Visit>
-__device__ __forceinline__ void for_rows_not_finite(const RowBlock<D> &acc, float scale, int rows_valid, Visit visit)
+__device__ __forceinline__ void for_rows_not_finite(const RowBlock<D, 32> &acc, float scale, int rows_valid, Visit visit)
 {
-    static_assert(Mfma<D>::M == 32, "one row per lane");
     float zero = scale * 0.f;                        // stays 0 while everything is finite
 #pragma unroll
     for (int j = 0; j < D / 32; ++j)
@@ -392,10 +391,10 @@ __device__ __forceinline__ float sum_over_quarters(float x)
     return sum_with_other_half(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 // Combines over the lanes of one column of an M x M result.
-template <int D>
-__device__ __forceinline__ float max_over_groups(float x) { return Mfma<D>::M == 32 ? max_with_other_half(x) : max_over_quarters(x); }
-template <int D>
-__device__ __forceinline__ float sum_over_groups(float x) { return Mfma<D>::M == 32 ? sum_with_other_half(x) : sum_over_quarters(x); }
+template <int M>
+__device__ __forceinline__ float max_over_groups(float x) { return M == 32 ? max_with_other_half(x) : max_over_quarters(x); }
+template <int M>
+__device__ __forceinline__ float sum_over_groups(float x) { return M == 32 ? sum_with_other_half(x) : sum_over_quarters(x); }
 
 // Finds the tile a workgroup owns.  Tiles of `tile` rows are counted per segment over cu[0..n_seg], from the LAST tile of the
 // LAST segment backwards (the later tiles of a segment see more keys, so the heaviest tiles get the lowest ranks and start

@@ -68,3 +68,16 @@ def test_nothing_else_touches_an_accumulator_in_the_loop(tmp_path):
         last = list(re.finditer(r"s_nop 1\n\s*(v_mfma_f32_32x32x16_bf16 .*)\n", body))[-1]
         planted = body[:last.start()] + f"v_mov_b32_e32 v0, v{min(registers(operands(last[1])[0]))}\n\t" + body[last.start():]
         assert accumulator_faults(planted)[2]
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs hipcc")
+def test_products_of_dq_alternate(tmp_path):
+    """S and dP are one chain of 32x32x16 MFMAs each: no two in a row add to the same accumulator, which would have to wait."""
+    out = str(tmp_path / "bwd.s")
+    subprocess.run([build.HIPCC] + build.HIP_FLAGS + ["-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC, "--cuda-device-only",
+                   "-S", os.path.join(build.CSRC, "attn_mfma_bwd.hip"), "-o", out], check=True, stderr=subprocess.DEVNULL)
+    kernels = re.findall(r"^(\S*mfma_dq_\S+):.*?\n(.*?)^\.Lfunc_end", open(out).read(), re.M | re.S)
+    assert len(kernels) >= 4
+    for name, body in kernels:
+        mfma = [operands(l.strip())[0] for l in body.splitlines() if l.strip().startswith("v_mfma")]
+        assert len(mfma) > 100 and all(a != b for a, b in zip(mfma, mfma[1:])), name

@@ -225,6 +225,33 @@ def test_single_writers_among_work_lists(Hq, Hkv, C):
         assert ((apart[0] - together[0]).norm() / apart[0].norm()).item() <= 64 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("Hq,Hkv,C", [(8, 2, 512), (8, 2, 513), (4, 4, 1024), (28, 4, 146), (28, 4, 147)])
+def test_both_sizes_of_mfma(Hq, Hkv, C):
+    """bf16, D = 128: calls of up to 4096 (query row, head) pairs use 32x32x16 MFMAs in the forward and dQ, others 16x16x32.  Lists of calls
+    with the one, the other and both give the bits of single calls, and match the oracle."""
+    lens = [2 * C + 45, 30, C - 1, 61, 20]
+    plan = B.cf_build_chunks(lens, C)
+    vals = lambda sid, L: inputs.seq_values(6, sid, L, Hq, Hkv, 128, "bf16")
+    eng = ChunkAttention(plan, Hq, Hkv, 128, "bf16").load(vals)
+    small = [ch["T"] * Hq <= 4096 for ch in eng.chunks]
+    assert any(small) and all(small) == (C * Hq <= 4096)
+    res = []
+    for one_by_one in (True, False):
+        eng.zero_grads()
+        if one_by_one:
+            for c in eng.forward_order():
+                B.cf_attn_fwd(eng.chunks[c]["fwd"])
+            for c in eng.backward_order():
+                B.cf_attn_bwd(eng.chunks[c]["bwd"])
+        else:
+            eng.run_forward(), eng.run_backward()
+        res.append(eng.results())
+        P.check(res[-1], P.run_oracle(lens, Hq, Hkv, 128, "bf16", seed=6), "bf16", f"one by one: {one_by_one}")
+    for sid in res[0]:
+        for n in ("o", "lse", "dq"):
+            assert np.array_equal(res[0][sid][n], res[1][sid][n]), (sid, n)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 def test_calls_that_depend_on_each_other(dtype):
     """The second forward takes the first one's output as its queries; the list stops at a call that is refused."""
