@@ -198,7 +198,7 @@ int bwd_one(const cf_attn_bwd_params *b, const cf::BwdWorkspace &ws, hipStream_t
 // ---- several calls at once --------------------------------------------------------------------------------------
 // Small chunks leave most of the chip idle and large ones end with a partly filled wave of workgroups: consecutive calls
 // of one kind that do not touch each other's results go out as ONE launch (backward: one per kernel).  A step of 16
-// chunks of 512 tokens, 28 / 4 heads: 755 us in 48 launches, 341 us in 5; 16 chunks of 8192 tokens: 10.44 -> 9.39 ms.
+// chunks of 512 tokens, 28 / 4 heads: 769 us in 48 launches, 218 us in 3; 16 chunks of 8192 tokens: 9.43 -> 8.95 ms.
 // A checked call: fwd for a forward (b NULL), else the backward's parameters and its scratch.
 struct Call {
     const cf_attn_fwd_params *f;
