@@ -299,12 +299,9 @@ int launch_together(const Call *calls, const Touched *t, int n, hipStream_t s, c
         e = cf::launch_f32_bwd_batch(bwd, n, s);
         return e == hipSuccess ? CF_OK : hip_fail(who, e);
     }
-    // heaviest first: the order in which the workgroups are dealt (work ~ queries x keys)
     const cf_attn_fwd_params *fwd[cf::CF_FWD_BATCH_MAX];
     for (int i = 0; i < n; ++i) fwd[i] = calls[i].f;
-    std::stable_sort(fwd, fwd + n, [](const cf_attn_fwd_params *x, const cf_attn_fwd_params *y) {
-        return (int64_t)x->n_tokens * x->n_kv_tokens > (int64_t)y->n_tokens * y->n_kv_tokens;
-    });
+    std::stable_sort(fwd, fwd + n, [](const cf_attn_fwd_params *x, const cf_attn_fwd_params *y) { return cf::starts_before(*x, *y); });
     e = path_of(calls[0]) == kMfma ? cf::launch_mfma_fwd_batch(fwd, n, s) : cf::launch_f32_fwd_batch(fwd, n, s);
     return e == hipSuccess ? CF_OK : hip_fail(who, e);
 }

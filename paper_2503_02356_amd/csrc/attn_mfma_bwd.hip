@@ -1038,7 +1038,7 @@ template <int D>
 hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
 {
     BwdShape g[CF_BWD_BATCH_MAX];
-    int order[CF_BWD_BATCH_MAX];
+    int order[CF_BWD_BATCH_MAX], dq_order[CF_BWD_BATCH_MAX], slots[CF_BWD_BATCH_MAX];
     int64_t tokens[CF_BWD_BATCH_MAX] = {};           // of the dK/dV launch that a chunk goes into (index: its first chunk)
     int first_of[CF_BWD_BATCH_MAX], together[CF_BWD_BATCH_MAX] = {};
     DkvKind kind[CF_BWD_BATCH_MAX];
@@ -1052,26 +1052,29 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
         first_of[c] = c > 0 && kind[c] == kind[c - 1] && kind[c] != kAlone ? first_of[c - 1] : c;
         for (int a = first_of[c]; a < c; ++a)
             if ((chunks[c].meets >> a & 1) && !(kind[c] == kChain ? same_key_rows : any_order)(*chunks[a].b, *chunks[c].b)) first_of[c] = c;
-        order[c] = c;
+        order[c] = dq_order[c] = c;
     }
     for (int c = 0; c < n; ++c) tokens[first_of[c]] += chunks[c].b->f.n_tokens, ++together[first_of[c]];
     for (int c = 0; D == 128 && c < n; ++c)          // (a chain needs no list, and has a workgroup for each key tile)
         if (kind[c] == kChain && together[first_of[c]] > 1)
             g[c].fused = true, g[c].dkv_blocks = kv_tiles_most(chunks[c].b->f) * chunks[c].b->f.n_kv_heads;
-    // heaviest first: work ~ queries x keys
-    std::stable_sort(order, order + n, [&](int x, int y) {
-        const cf_attn_fwd_params &a = chunks[x].b->f, &b = chunks[y].b->f;
-        return (int64_t)a.n_tokens * a.n_kv_tokens > (int64_t)b.n_tokens * b.n_kv_tokens;
-    });
-    BwdBatch q;
-    q.n = q.first_block[0] = 0;
+    // dK/dV: heaviest first (the items of a list have no chains to speak of: by longest chain 28 / 4 heads, four packed chunks of 2048
+    // tokens take 214 us, 208 so)
+    std::stable_sort(order, order + n, [&](int x, int y) { return work_of(chunks[x].b->f) > work_of(chunks[y].b->f); });
+    std::stable_sort(dq_order, dq_order + n, [&](int x, int y) { return starts_before(chunks[x].b->f, chunks[y].b->f); });
     for (int i = 0; i < n; ++i) {
         const int c = order[i];
         // Lists follow each other in a shared launch: the longest items of a late one start late and have to end with what is
         // left, so that a chunk's share of the slots is taken of the chunks from it on.
         const int64_t own = chunks[c].b->f.n_tokens;
-        q.slots[i] = (int)max((int64_t)1, min((int64_t)kSlots - (together[first_of[c]] > 1), kSlots * own / tokens[first_of[c]]));
+        slots[c] = (int)max((int64_t)1, min((int64_t)kSlots - (together[first_of[c]] > 1), kSlots * own / tokens[first_of[c]]));
         tokens[first_of[c]] -= own;
+    }
+    BwdBatch q;
+    q.n = q.first_block[0] = 0;
+    for (int i = 0; i < n; ++i) {
+        const int c = dq_order[i];
+        q.slots[i] = slots[c];
         if (!append(q, *chunks[c].b, chunks[c].ws, g[c], g[c].dq_blocks)) return hipErrorInvalidConfiguration;
     }
     const dim3 dq_grid((unsigned)(q.first_block[n] + n));

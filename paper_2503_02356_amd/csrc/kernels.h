@@ -80,6 +80,25 @@ struct BwdArgs {
     }
 };
 
+// Order of the calls of a list in a launch that they share, whose workgroups start in that order, for kernels whose workgroups run over
+// the keys of some query rows: does a's longest chain of key tiles come before c's (then by queries x keys)?  A launch ends with its
+// longest chain, so the chunk that has it goes first, however little work it is.  Of a chunk of several sequences only the mean length is
+// known here; the longest is taken for four times that (ten lengths of a lognormal distribution, sigma 0.9), and a prefix is one
+// sequence's.  Against the order by queries x keys, us a step: 16 / 4 heads, D = 64, five chunks of 4096 tokens, one of them 904 rows behind
+// 4096 keys: 935 -> 758 (compute units idle half of forward and dQ before); 28 / 4 heads, four packed chunks of 2048: 409 -> 384; eight chunks
+// of 8192: no change.
+inline int64_t longest_chain(const cf_attn_fwd_params &p)
+{
+    const int64_t own = p.n_segments == 1 ? p.n_tokens : std::min<int64_t>(p.n_tokens, 4 * (int64_t)p.n_tokens / p.n_segments);
+    return p.n_kv_tokens - p.n_tokens + own;
+}
+inline int64_t work_of(const cf_attn_fwd_params &p) { return (int64_t)p.n_tokens * p.n_kv_tokens; }
+inline bool starts_before(const cf_attn_fwd_params &a, const cf_attn_fwd_params &c)
+{
+    const int64_t la = longest_chain(a), lc = longest_chain(c);
+    return la != lc ? la > lc : work_of(a) > work_of(c);
+}
+
 // Single slices whose key row r adds to the same rows of d_k and d_v for every r: key tile t of the one is key tile t of the other.
 inline bool same_key_rows(const cf_attn_bwd_params &a, const cf_attn_bwd_params &b)
 {
@@ -100,7 +119,7 @@ struct CallChains {
         for (int c = 0; c < n; ++c) {
             head[c] = order[c] = c;
             next[c] = -1;
-            work[c] = (int64_t)call(c).f.n_tokens * call(c).f.n_kv_tokens;
+            work[c] = work_of(call(c).f);
             for (int a = c - 1; a >= 0 && head[c] == c; --a)
                 if (same_key_rows(call(a), call(c))) {
                     head[c] = head[a];

@@ -252,6 +252,27 @@ def test_both_sizes_of_mfma(Hq, Hkv, C):
             assert np.array_equal(res[0][sid][n], res[1][sid][n]), (sid, n)
 
 
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("fp32", 64)])
+def test_the_longest_chain_of_a_list_starts_first(dtype, D):
+    """Forward and dQ start with the chunk of the longest chain, dK/dV with the one of most work: here the last slice of the split
+    sequence (20 rows behind 600 keys) and the packed chunks.  Same bits of O, LSE and dQ as one call at a time, and the oracle's results."""
+    lens, C, Hq, Hkv = [620, 150, 140, 10, 130, 100, 70], 300, 4, 2
+    got, eng = P.run_gpu(lens, C, Hq, Hkv, D, dtype, seed=35)
+    work = {c: ch["T"] * (ch["P"] + ch["T"]) for c, ch in enumerate(eng.chunks)}
+    tail = [c for c, ch in enumerate(eng.chunks) if ch["P"] == 600]
+    assert len(tail) == 1 and work[tail[0]] == min(work.values())
+    P.check(got, P.run_oracle(lens, Hq, Hkv, D, dtype, seed=35), dtype, "list")
+    eng.zero_grads()
+    for c in eng.forward_order():
+        B.cf_attn_fwd(eng.chunks[c]["fwd"])
+    for c in eng.backward_order():
+        B.cf_attn_bwd(eng.chunks[c]["bwd"])
+    one = eng.results()
+    for sid in got:
+        for n in ("o", "lse", "dq"):
+            assert np.array_equal(got[sid][n], one[sid][n]), (sid, n)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 def test_calls_that_depend_on_each_other(dtype):
     """The second forward takes the first one's output as its queries; the list stops at a call that is refused."""
