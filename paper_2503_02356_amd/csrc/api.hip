@@ -196,7 +196,7 @@ int bwd_one(const cf_attn_bwd_params *b, const cf::BwdWorkspace &ws, hipStream_t
 }
 
 // ---- several calls at once --------------------------------------------------------------------------------------
-// Small chunks leave most of the chip idle and large ones end with a partly filled wave of workgroups: consecutive calls
+// Small chunks leave most of the chip idle and large ones end with a partly filled wave of workgroups: calls
 // of one kind that do not touch each other's results go out as ONE launch (backward: one per kernel).  A step of 16
 // chunks of 512 tokens, 28 / 4 heads: 769 us in 48 launches, 218 us in 3; 16 chunks of 8192 tokens: 9.43 -> 8.95 ms.
 // A checked call: fwd for a forward (b NULL), else the backward's parameters and its scratch.
@@ -306,10 +306,45 @@ int launch_together(const Call *calls, const Touched *t, int n, hipStream_t s, c
     return e == hipSuccess ? CF_OK : hip_fail(who, e);
 }
 
-// Launches n <= kWindow checked calls, in order.
-int launch_calls(const Call *calls, int n, hipStream_t s, const char *who)
+// Brings calls of one kernel together: a call moves forward, behind the last one of the run that it joins, past calls of other kernels that
+// it has nothing to do with (neither reads or writes what the other writes, no common gradient rows).  order: of t, from the first call to
+// the last; calls of one kernel keep theirs.  Algorithm 2's second half asks for forward and backward in turns (one kept chunk: a slice's
+// forward again, its backward, the slice before it, ...): launches of one slice each, which fill the chip in part.  Steps, us: one sequence
+// of 32768 in slices of 2048, 28 / 4 heads, one kept chunk: 36510 -> 34690; 9000 in slices of 1024, two kept: 3564 -> 2648; 8000 in slices
+// of 512, 8 / 2 heads, one kept: 3738 -> 1080.
+void bring_together(const Call *calls, const Touched *t, int n, int *order)
 {
-    Touched t[kWindow];
+    bool placed[kWindow] = {};
+    for (int at = 0, first = 0; at < n;) {
+        while (placed[first]) ++first;
+        order[at++] = first;
+        placed[first] = true;
+        for (int j = first + 1; j < n; ++j) {
+            if (placed[j] || !same_kernel(calls[first], calls[j])) continue;
+            bool free = true;                        // of all that stay behind it and were before it
+            for (int a = first + 1; a < j && free; ++a) free = placed[a] || (independent(t[a], t[j]) && !adds_meet(t[a], t[j]));
+            if (!free) break;
+            order[at++] = j;
+            placed[j] = true;
+        }
+    }
+}
+
+// Launches n <= kWindow checked calls, in an order that gives the results of theirs.
+int launch_calls(const Call *in, int n, hipStream_t s, const char *who)
+{
+    Touched touches[kWindow], t[kWindow];
+    Call calls[kWindow];
+    int order[kWindow];
+    bool keep = true;                                // the order: one kernel, or a call that may be refused by its launch
+    for (int i = 0; i < n; ++i) {
+        touches[i] = touched(in[i]);
+        order[i] = i;
+        keep = keep && same_kernel(in[0], in[i]);
+    }
+    for (int i = 0; i < n && !keep; ++i) keep = path_of(in[i]) != kScalar && launch_size(in[i]) > cf::kMostWorkItems;
+    if (!keep) bring_together(in, touches, n, order);
+    for (int i = 0; i < n; ++i) calls[i] = in[order[i]], t[i] = touches[order[i]];
     for (int i = 0; i < n;) {
         int end = i + 1;
         while (end < n && same_kernel(calls[i], calls[end])) ++end;
@@ -317,13 +352,11 @@ int launch_calls(const Call *calls, int n, hipStream_t s, const char *who)
         const int most = calls[i].b ? cf::CF_BWD_BATCH_MAX : cf::CF_FWD_BATCH_MAX;
         const int launches = (end - i + most - 1) / most, size = (end - i + launches - 1) / launches;
         while (i < end) {
-            t[i] = touched(calls[i]);
             int64_t work_items = launch_size(calls[i]);
             int j = i + 1;
             for (; j < end && j - i < size; ++j) {
                 work_items += launch_size(calls[j]);
                 if (work_items > cf::kMostWorkItems) break;
-                t[j] = touched(calls[j]);
                 bool apart = true;
                 for (int a = i; a < j && apart; ++a)
                     apart = independent(t[a], t[j]) && (!calls[j].b || path_of(calls[j]) != kF32 || chains(calls[a], t[a], calls[j], t[j]));

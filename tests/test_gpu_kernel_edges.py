@@ -273,6 +273,48 @@ def test_the_longest_chain_of_a_list_starts_first(dtype, D):
             assert np.array_equal(got[sid][n], one[sid][n]), (sid, n)
 
 
+@pytest.mark.parametrize("dtype,D,one_slot", [("bf16", 128, False), ("bf16", 128, True), ("bf16", 64, True), ("fp32", 64, False), ("fp32", 64, True)])
+def test_forward_and_backward_in_turns(dtype, D, one_slot):
+    """Algorithm 2 with one kept chunk, as a list: calls move past others that they have nothing to do with.  Same results as one call at
+    a time (dK/dV: up to the order of at most 40 fp32 sums where items meet in atomic adds), also where all chunks share one O and one LSE,
+    so that each backward has to come between its forward and the next one.  Two heads' sizes: the kernels alternate too."""
+    C, results = 130, []
+    engines = []
+    for Hq, lens in ((4, [700, 60, 129, 40, 30]), (2, [390, 131])):
+        plan = B.cf_build_chunks(lens, C)
+        eng = ChunkAttention(plan, Hq, 2, D, dtype).load(lambda sid, L: inputs.seq_values(11, sid, L, Hq, 2, D, dtype))
+        engines.append((plan, eng, [(op == B.CF_OP_BWD, c) for op, c in plan.schedule(1)]))
+    if one_slot:
+        for plan, eng, _ in engines:
+            for c in range(plan.n_chunks):
+                ch = eng.chunks[c]
+                o, lse = eng.chunks[0]["o"], eng.chunks[0]["lse"]
+                assert ch["T"] <= o.shape[0]
+                ch["o"], ch["lse"] = o[:ch["T"]], lse.view(-1)[:lse.shape[0] * ch["T"]].view(lse.shape[0], ch["T"])
+                ch["fwd"] = B.make_fwd_params(ch["q"], ch["k"], ch["v"], ch["o"], ch["lse"], ch["cu_q"], ch["cu_k"], eng.scale)
+                ch["bwd"] = B.make_bwd_params(ch["fwd"], ch["d_o"], ch["d_q"], ch["dk"], ch["dv"], torch.empty_like(eng.workspaces[0]))
+    (_, e0, ops0), (_, e1, ops1) = engines
+    ops = [(e, *op) for pair in zip(ops0, ops1) for e, op in zip((e0, e1), pair)] + [(e0, *op) for op in ops0[len(ops1):]]
+    assert len(ops1) <= len(ops0) and len(ops) < 64 and sum(bwd for _, bwd, _ in ops) > 8
+    calls = [(bwd, e.chunks[c]["bwd" if bwd else "fwd"]) for e, bwd, c in ops]
+    for together in (False, True, True):
+        for e in (e0, e1):
+            e.grad_arena.zero_()
+            for ch in e.chunks:
+                ch["o"].fill_(float("nan")), ch["lse"].fill_(float("nan")), ch["d_q"].fill_(float("nan"))
+        if together:
+            B.cf_attn_calls(B.make_calls(calls))
+        else:
+            for bwd, params in calls:
+                (B.cf_attn_bwd if bwd else B.cf_attn_fwd)(params)
+        torch.cuda.synchronize()
+        results.append([t.clone() for e in (e0, e1) for ch in e.chunks for t in (ch["d_q"], ch["o"], ch["lse"])] + [e.grad_arena.clone() for e in (e0, e1)])
+    for got in results[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(results[0][:-2], got[:-2]))
+        for a, b in zip(results[0][-2:], got[-2:]):
+            assert torch.equal(a, b) if (dtype, D) != ("bf16", 128) else ((a - b).norm() / a.norm()).item() <= 40 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 def test_calls_that_depend_on_each_other(dtype):
     """The second forward takes the first one's output as its queries; the list stops at a call that is refused."""
