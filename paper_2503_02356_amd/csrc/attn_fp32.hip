@@ -40,8 +40,6 @@
 namespace cf {
 namespace {
 
-#define CF_GLOBAL __attribute__((address_space(1)))
-
 constexpr int NW = 16;           // wavefronts per workgroup
 constexpr int RB = 16;           // rows per block
 constexpr int kExactDeltaKeys = 64;      // rows that see at most so many keys: dQ takes delta from P and dP (as the scalar kernels do)
@@ -287,27 +285,20 @@ __device__ __forceinline__ void f32_fwd_body(const cf_attn_fwd_params &p, int id
 template <int D>
 __global__ __launch_bounds__(NW * 64) void f32_fwd_kernel(cf_attn_fwd_params p) { f32_fwd_body<D>(p, blockIdx.x); }
 
-// Several chunks in one launch: workgroups [first_block[c], first_block[c + 1]) belong to chunk c, the first dkv_blocks[c] of
-// them to the key rows of c and the chunks chained behind it.
+// Several chunks in one launch; of a chunk's workgroups the first dkv_blocks[c] belong to its key rows and those of the chunks chained behind
+// it.
 template <typename Params, int MAX>
 struct Batch {
-    int n;
-    int first_block[MAX + 1], dkv_blocks[MAX], next[MAX];
+    Blocks<MAX> blocks;
+    int dkv_blocks[MAX], next[MAX];
     Params p[MAX];
-    __device__ __forceinline__ int chunk_of(int id) const
-    {
-        int c = 0;
-        while (c + 1 < n && id >= first_block[c + 1]) ++c;
-        return c;
-    }
     bool append(const Params &chunk, int64_t dkv, int64_t others, int next_chunk = -1)
     {
-        if (first_block[n] + dkv + others > 0x7fffffffLL) return false;
-        p[n] = chunk;
-        dkv_blocks[n] = (int)dkv;
-        next[n] = next_chunk;
-        first_block[n + 1] = first_block[n] + (int)(dkv + others);
-        ++n;
+        const int i = blocks.n;
+        if (!blocks.append(dkv + others)) return false;
+        p[i] = chunk;
+        dkv_blocks[i] = (int)dkv;
+        next[i] = next_chunk;
         return true;
     }
 };
@@ -317,8 +308,9 @@ static_assert(sizeof(BwdBatch) <= 4096 && sizeof(FwdBatch) <= 4096, "kernel argu
 template <int D>
 __global__ __launch_bounds__(NW * 64) void f32_fwd_batch_kernel(FwdBatch q)
 {
-    const int c = q.chunk_of(blockIdx.x);
-    f32_fwd_body<D>(q.p[c], blockIdx.x - q.first_block[c]);
+    int id = blockIdx.x;
+    const int c = q.blocks.chunk_of(id);
+    f32_fwd_body<D>(q.p[c], id);
 }
 
 // exp(s scale - lse).  The scores keep their natural units, in which LSE is exact, and the rounding of the product with log2e
@@ -571,8 +563,7 @@ __global__ __launch_bounds__(NW * 64) void f32_bwd_batch_kernel(BwdBatch q)
 {
     __shared__ __attribute__((aligned(16))) char smem[BwdLds<D>::bytes];
     __shared__ __attribute__((aligned(16))) float stat[NW][2 * RB];
-    int c = q.chunk_of(blockIdx.x);
-    const int id = blockIdx.x - q.first_block[c];
+    int id = blockIdx.x, c = q.blocks.chunk_of(id);
     if (id >= q.dkv_blocks[c]) {
         f32_dq_body<D>(q.p[c], id - q.dkv_blocks[c], smem);
         return;
@@ -629,10 +620,10 @@ hipError_t launch_f32_fwd_batch(const cf_attn_fwd_params *const *chunks, int n, 
 {
     if (n < 1 || n > CF_FWD_BATCH_MAX) return hipErrorInvalidValue;
     FwdBatch q;
-    q.n = q.first_block[0] = 0;
+    q.blocks.clear();
     for (int c = 0; c < n; ++c)
         if (!q.append(*chunks[c], 0, query_blocks(*chunks[c]))) return hipErrorInvalidConfiguration;
-    const dim3 grid((unsigned)q.first_block[n]);
+    const dim3 grid((unsigned)q.blocks.end);
     if (chunks[0]->head_dim == 64) f32_fwd_batch_kernel<64><<<grid, NW * 64, 0, s>>>(q);
     else f32_fwd_batch_kernel<128><<<grid, NW * 64, 0, s>>>(q);
     return hipGetLastError();
@@ -645,14 +636,14 @@ hipError_t launch_f32_bwd_batch(const cf_attn_bwd_params *const *chunks, int n, 
     int place[CF_BWD_BATCH_MAX];
     for (int i = 0; i < n; ++i) place[chain.order[i]] = i;
     BwdBatch q;
-    q.n = q.first_block[0] = 0;
+    q.blocks.clear();
     for (int i = 0; i < n; ++i) {
         const int c = chain.order[i];
         int64_t dkv = 0;                             // a chain's key rows go with its first call: as many as its longest one has
         for (int a = c; chain.head[c] == c && a >= 0; a = chain.next[a]) dkv = std::max(dkv, key_blocks(chunks[a]->f));
         if (!q.append(*chunks[c], dkv, query_blocks(chunks[c]->f), chain.next[c] < 0 ? -1 : place[chain.next[c]])) return hipErrorInvalidConfiguration;
     }
-    const dim3 grid((unsigned)q.first_block[n]);
+    const dim3 grid((unsigned)q.blocks.end);
     if (chunks[0]->f.head_dim == 64) f32_bwd_batch_kernel<64><<<grid, NW * 64, 0, s>>>(q);
     else f32_bwd_batch_kernel<128><<<grid, NW * 64, 0, s>>>(q);
     return hipGetLastError();

@@ -203,6 +203,29 @@ struct DkvStage {
     static_assert(bytes >= 2 * scratch_bytes, "two wavefronts turn their results around in a stage");
 };
 
+// As RowArgs (mfma_common.h), for this kernel.
+struct KeyArgs {
+    const char *k, *v, *q, *d_o;
+    const int32_t *cu_q, *cu_k;
+    int64_t kv_tok, kv_head, q_tok, q_head, do_tok, do_head;
+    int n_q_heads, n_kv_heads;
+    const int *wl;
+    // together: not in chains, which have no registers to keep them in; there each is loaded where it is used.
+    __device__ __forceinline__ KeyArgs(const BwdArgs &b, const int *worklist, bool together)
+        : kv_tok(b.f.kv_stride_tok), kv_head(b.f.kv_stride_head), q_tok(b.f.q_stride_tok), q_head(b.f.q_stride_head), do_tok(b.do_stride_tok),
+          do_head(b.do_stride_head), n_q_heads(b.f.n_q_heads), n_kv_heads(b.f.n_kv_heads)
+    {
+        auto k_ = (const CF_GLOBAL char *)b.f.k, v_ = (const CF_GLOBAL char *)b.f.v, q_ = (const CF_GLOBAL char *)b.f.q, do_ = (const CF_GLOBAL char *)b.d_o;
+        auto cu_q_ = (const CF_CONSTANT int32_t *)b.f.cu_seqlens_q, cu_k_ = (const CF_CONSTANT int32_t *)b.f.cu_seqlens_k;
+        auto wl_ = (const CF_CONSTANT int *)worklist;
+        if (together)
+            asm("" : "+s"(k_), "+s"(v_), "+s"(q_), "+s"(do_), "+s"(cu_q_), "+s"(cu_k_), "+s"(kv_tok), "+s"(kv_head), "+s"(q_tok), "+s"(q_head),
+                     "+s"(do_tok), "+s"(do_head), "+s"(n_q_heads), "+s"(n_kv_heads), "+s"(wl_));
+        k = (const char *)k_, v = (const char *)v_, q = (const char *)q_, d_o = (const char *)do_;
+        cu_q = (const int32_t *)cu_q_, cu_k = (const int32_t *)cu_k_, wl = (const int *)wl_;
+    }
+};
+
 // A wavefront owns 32 key rows: K_w, V_w (operands) and dV_w^T, dK_w^T (fp32) stay in its
 // registers for the whole kernel, 192 of them at D = 128.  Per 32-row block of queries:
 //     S = Q K_w^T    P = exp2(S c - LSE)    dP' = dO V_w^T - delta (the accumulator starts at -delta)    dS = P dP'
@@ -231,32 +254,33 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     // Block id -> (item, key/value head); the key/value head varies fastest (XCD L2 locality, see forward).
     //   fused mode : item = key tile rank, all G heads of the group
     //   otherwise  : item = entry of the work list
-    const int G = p.n_q_heads / p.n_kv_heads;
-    const int kh = id % p.n_kv_heads;
-    id /= p.n_kv_heads;
-    int seg, kt0, first_pair = 0, n_pairs = 0;
+    const KeyArgs first(b, wl, RING != 3);
+    auto args = [&] { return RING == 3 ? KeyArgs(b, wl, false) : first; };
+    const int G = args().n_q_heads / args().n_kv_heads;
+    const int kh = id % args().n_kv_heads;
+    id /= args().n_kv_heads;
+    int kt0, first_pair = 0, n_pairs = 0, q_seg0, lq, k_seg0, lk;
+    // (all of this is the same in every lane, but values that leave locate_tile's search loop do not look that way to
+    // the compiler: say so, or everything derived from them lives in vector registers.)
     if (FUSED_HEADS) {
         TileLocation loc;
-        if (!locate_tile<RING == 3>(p.cu_seqlens_k, p.cu_seqlens_q, p.n_segments, p.n_kv_tokens, BKV, id, loc)) return;
-        seg = loc.seg;
+        if (!locate_tile<RING == 3>(args().cu_k, args().cu_q, p.n_segments, p.n_kv_tokens, BKV, id, loc)) return;
+        q_seg0 = uniform(loc.other_begin), lq = uniform(loc.other_len), k_seg0 = uniform(loc.begin), lk = uniform(loc.len);
         // locate_tile numbers tiles from the end; the FIRST key tiles of a segment are seen by the most rows, so
         // flip the order inside the segment to start the heaviest tiles first.
-        kt0 = ((loc.len + BKV - 1) / BKV - 1 - loc.tile_in_seg) * BKV;
+        kt0 = uniform(((loc.len + BKV - 1) / BKV - 1 - loc.tile_in_seg) * BKV);
     } else {
-        if (id >= wl[0]) return;
-        const i32x4 *items = (const i32x4 *)(wl + 64);
-        const i32x4 item = items[id];
-        seg = item[0];
-        kt0 = item[1];
-        first_pair = uniform(item[2]);
-        n_pairs = uniform(item[3]);
+        // (the item and the count at once: there is room for an item of every workgroup)
+        const i32x4 item = ((const i32x4 *)(args().wl + 64))[id];
+        int n_items = args().wl[0], seg = item[0];
+        kt0 = item[1], first_pair = item[2], n_pairs = item[3];
+        asm("" : "+s"(n_items), "+s"(seg), "+s"(kt0), "+s"(first_pair), "+s"(n_pairs));
+        if (id >= n_items) return;
+        int q_seg1 = args().cu_q[seg + 1], k_seg1 = args().cu_k[seg + 1];
+        q_seg0 = args().cu_q[seg], k_seg0 = args().cu_k[seg];
+        asm("" : "+s"(q_seg0), "+s"(q_seg1), "+s"(k_seg0), "+s"(k_seg1));        // (at once)
+        lq = q_seg1 - q_seg0, lk = k_seg1 - k_seg0;
     }
-    // (seg, kt0 are the same in every lane, but values that leave locate_tile's search loop do not look that way to
-    // the compiler: say so, or everything derived from them lives in vector registers.)
-    seg = uniform(seg);
-    kt0 = uniform(kt0);
-    const int q_seg0 = p.cu_seqlens_q[seg], lq = p.cu_seqlens_q[seg + 1] - q_seg0;
-    const int k_seg0 = p.cu_seqlens_k[seg], lk = p.cu_seqlens_k[seg + 1] - k_seg0;
     const int off = lk - lq;
     const int qt_first = max(0, kt0 - off) / BQ;     // first query tile with a row that sees any key of this tile
     const int qt_end = (lq + BQ - 1) / BQ;
@@ -276,11 +300,11 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     bf16x8 kf[N][KS], vf[N][KS];
 #pragma unroll
     for (int kb = 0; kb < N; ++kb) {
-        const int64_t from = ((k_seg0 + min(kw0 + F::M * kb + F::column(), lk - 1)) * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2 + F::group() * 16;
+        const int64_t from = ((k_seg0 + min(kw0 + F::M * kb + F::column(), lk - 1)) * args().kv_tok + (int64_t)kh * args().kv_head) * 2 + F::group() * 16;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            kf[kb][ks] = *(const bf16x8 *)((const char *)p.k + from + ks * 2 * F::K);
-            vf[kb][ks] = *(const bf16x8 *)((const char *)p.v + from + ks * 2 * F::K);
+            kf[kb][ks] = *(const bf16x8 *)(args().k + from + ks * 2 * F::K);
+            vf[kb][ks] = *(const bf16x8 *)(args().v + from + ks * 2 * F::K);
         }
     }
     f32x16 dv[DB], dk[DB];                           // 32 x 32 blocks: lane % 32 = key, register group j = d 32 db + 8 j + 4 half + 0..3
@@ -300,10 +324,10 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
         const int h = nx_h, q0 = nx_qt * BQ, lane_ = fresh_lane();
         const int64_t row0 = q_seg0 + q0;
         TileDma<BQ, D, 4, true> dma;
-        dma.init(p.q_stride_tok * 2, wave, lane_);
-        dma.issue(uniform((const char *)p.q + (row0 * p.q_stride_tok + (int64_t)h * p.q_stride_head) * 2), lq - 1 - q0, stage);
-        dma.init(b.do_stride_tok * 2, wave, lane_);
-        dma.issue(uniform((const char *)b.d_o + (row0 * b.do_stride_tok + (int64_t)h * b.do_stride_head) * 2), lq - 1 - q0,
+        dma.init(args().q_tok * 2, wave, lane_);
+        dma.issue(uniform(args().q + (row0 * args().q_tok + (int64_t)h * args().q_head) * 2), lq - 1 - q0, stage);
+        dma.init(args().do_tok * 2, wave, lane_);
+        dma.issue(uniform(args().d_o + (row0 * args().do_tok + (int64_t)h * args().do_head) * 2), lq - 1 - q0,
                   stage + Stage::tile_bytes);
         constexpr int PER = BQ / 64;                 // wavefronts that fetch LSE resp. -delta, 64 rows each
         if (wave < 2 * PER)
@@ -579,11 +603,10 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_kernel(BwdArgs b, const float
     dkv_body<D, FUSED_HEADS>(b, delta, blockIdx.x, wl, st0, st1);
 }
 
-// Several chunks' backward in one launch: workgroups [first_block[c], first_block[c + 1]) belong to chunk c.
+// Several chunks' backward in one launch.
 struct BwdBatch {
-    int n;
     unsigned wide;                                               // bit c: chunk c's dQ multiplies with M = 32
-    int first_block[CF_BWD_BATCH_MAX + 1];
+    Blocks<CF_BWD_BATCH_MAX> blocks;
     int next[CF_BWD_BATCH_MAX];                                  // chunk whose dK/dV rows are done behind this one's, by the same workgroups
     int capacity[CF_BWD_BATCH_MAX], slots[CF_BWD_BATCH_MAX];     // of the work list that is built (see there)
     float *delta[CF_BWD_BATCH_MAX];
@@ -591,12 +614,6 @@ struct BwdBatch {
     BwdArgs b[CF_BWD_BATCH_MAX];
 };
 static_assert(sizeof(BwdBatch) <= 4096, "kernel arguments");
-__device__ __forceinline__ int chunk_of(const BwdBatch &q, int id)
-{
-    int c = 0;
-    while (c + 1 < q.n && id >= q.first_block[c + 1]) ++c;
-    return c;
-}
 
 // Chunks with work lists: they follow each other, each longest first, and the last workgroups of one chunk run beside the first of
 // the next.  CHAINS: chunks of disjoint dK/dV rows and chains of slices that add to the same ones, one workgroup to a row: D = 64, 16 / 4
@@ -608,8 +625,7 @@ __global__ __launch_bounds__(256, 2) void mfma_dkv_batch_kernel(BwdBatch q)
     __shared__ __attribute__((aligned(16))) char st0[DkvStage<D>::bytes];
     __shared__ __attribute__((aligned(16))) char st1[DkvStage<D>::bytes];
     const int wave = wave_id();
-    int c = chunk_of(q, blockIdx.x);
-    const int id = blockIdx.x - q.first_block[c];
+    int id = blockIdx.x, c = q.blocks.chunk_of(id);
     for (;;) {
         if constexpr (D == 128 && CHAINS) dkv_body<D, true, 3>(q.b[c], q.delta[c], id, nullptr, st0, st1, wave);
         else dkv_body<D, CHAINS>(q.b[c], q.delta[c], id, q.wl[c], st0, st1);
@@ -653,17 +669,18 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
     constexpr bool FROM_DELTA = M == 16;
     const BwdArgs::Fwd &p = b.f;
     const int wave = wave_id(), group = F::group(), col = F::column();
+    const RowArgs a(p);
 
-    const int G = p.n_q_heads / p.n_kv_heads;
-    const int kh = id % p.n_kv_heads;
-    id /= p.n_kv_heads;
+    const int G = a.n_q_heads / a.n_kv_heads;
+    const int kh = id % a.n_kv_heads;
+    id /= a.n_kv_heads;
     const int j = id % G;                            // which of the G workgroups of this (tile, key/value head)
     const int rank = id / G;
 
     int tile_in_seg, q_seg0, lq, k_seg0, lk;
-    if (p.q_tiles != nullptr) {
-        if (rank >= p.n_q_tiles) return;
-        const QTile t = read_q_tile(p.q_tiles, rank);
+    if (a.tiles != nullptr) {
+        if (rank >= a.n_tiles) return;
+        const QTile t = read_q_tile(a.tiles, rank);
         tile_in_seg = t.tile_in_seg, q_seg0 = t.q_begin, lq = t.q_len, k_seg0 = t.k_begin, lk = t.k_len;
     } else {
         TileLocation loc;
@@ -689,9 +706,9 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
     const bool wave_active = wq0 < lq;
     const int amax = wq0 + col + off;                // last visible key of this lane's row (block qb: M qb further)
 
-    const int64_t kv_row_bytes = p.kv_stride_tok * 2;
-    const char *kbase = uniform((const char *)p.k + ((int64_t)k_seg0 * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2);
-    const char *vbase = uniform((const char *)p.v + ((int64_t)k_seg0 * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2);
+    const int64_t kv_row_bytes = a.kv_tok * 2;
+    const char *kbase = uniform(a.k + ((int64_t)k_seg0 * a.kv_tok + (int64_t)kh * a.kv_head) * 2);
+    const char *vbase = uniform(a.v + ((int64_t)k_seg0 * a.kv_tok + (int64_t)kh * a.kv_head) * 2);
     TileDma<BN, D, 4, true> dma;
     dma.init(kv_row_bytes);
 
@@ -703,7 +720,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
 #pragma unroll
     for (int qb = 0; qb < N; ++qb) {
         const int iq = row_of_block(qb), row = q_seg0 + min(iq, lq - 1);
-        const char *qrow = (const char *)p.q + ((int64_t)row * p.q_stride_tok + (int64_t)h * p.q_stride_head) * 2;
+        const char *qrow = a.q + ((int64_t)row * a.q_tok + (int64_t)h * a.q_head) * 2;
         const char *dorow = (const char *)b.d_o + ((int64_t)row * b.do_stride_tok + (int64_t)h * b.do_stride_head) * 2;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -931,16 +948,17 @@ __global__ __launch_bounds__(256, 2) void mfma_dq_kernel(BwdArgs b, float *__res
 template <int D, int M>
 __global__ __launch_bounds__(256, 2) void mfma_dq_batch_kernel(BwdBatch q)
 {
-    if ((int)blockIdx.x < q.n) {
+    int id = (int)blockIdx.x - q.blocks.n;
+    if (id < 0) {
         const int c = blockIdx.x;
         if (D == 128 && q.wl[c] != nullptr) build_dkv_worklist(q.b[c].f, q.wl[c], q.capacity[c], q.slots[c]);
         return;
     }
     __shared__ __attribute__((aligned(16))) char stage_a[KvStage<D>::bytes];
     __shared__ __attribute__((aligned(16))) char stage_b[KvStage<D>::bytes];
-    const int id = (int)blockIdx.x - q.n, c = chunk_of(q, id);
-    if (M == 32 || (M == 0 && (q.wide >> c & 1))) dq_body<D, 32>(q.b[c], q.delta[c], id - q.first_block[c], stage_a, stage_b);
-    else if constexpr (M != 32) dq_body<D, 16>(q.b[c], q.delta[c], id - q.first_block[c], stage_a, stage_b);
+    const int c = q.blocks.chunk_of(id);
+    if (M == 32 || (M == 0 && (q.wide >> c & 1))) dq_body<D, 32>(q.b[c], q.delta[c], id, stage_a, stage_b);
+    else if constexpr (M != 32) dq_body<D, 16>(q.b[c], q.delta[c], id, stage_a, stage_b);
 }
 
 // Launch geometry of one chunk's backward.
@@ -995,15 +1013,13 @@ hipError_t run_bwd(const cf_attn_bwd_params &b, const BwdWorkspace &ws, hipStrea
 // Adds a chunk's part to a batch launch.
 bool append(BwdBatch &q, const cf_attn_bwd_params &b, const BwdWorkspace &ws, const BwdShape &g, int64_t blocks)
 {
-    const int i = q.n;
-    if (q.first_block[i] + blocks > 0x7fffffffLL - CF_BWD_BATCH_MAX) return false;
-    q.first_block[i + 1] = q.first_block[i] + (int)blocks;
+    const int i = q.blocks.n;
+    if (!q.blocks.append(blocks)) return false;
     q.capacity[i] = (int)ws.worklist_items;
     q.delta[i] = ws.delta;
     q.wl[i] = g.fused ? nullptr : ws.worklist;
     q.wide = (i == 0 ? 0 : q.wide) | (unsigned)wide_mfma(b.f) << i;
     q.b[i] = b;
-    ++q.n;
     return true;
 }
 
@@ -1079,13 +1095,13 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
         tokens[first_of[c]] -= own;
     }
     BwdBatch q;
-    q.n = q.first_block[0] = 0;
+    q.blocks.clear();
     for (int i = 0; i < n; ++i) {
         const int c = dq_order[i];
         q.slots[i] = slots[c];
         if (!append(q, *chunks[c].b, chunks[c].ws, g[c], g[c].dq_blocks)) return hipErrorInvalidConfiguration;
     }
-    const dim3 dq_grid((unsigned)(q.first_block[n] + n));
+    const dim3 dq_grid((unsigned)(q.blocks.end + n));
     if (D == 64 || q.wide == (1u << n) - 1) mfma_dq_batch_kernel<D, 32><<<dq_grid, 256, 0, s>>>(q);
     else if constexpr (D == 128) {
         if (q.wide == 0) mfma_dq_batch_kernel<D, 16><<<dq_grid, 256, 0, s>>>(q);
@@ -1098,7 +1114,7 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
             e = launch_dkv<D>(*chunks[first].b, chunks[first].ws, g[first], ProfileHook(), s);
             continue;
         }
-        q.n = 0;
+        q.blocks.clear();
         if (kind[first] == kChain) {
             const CallChains<CF_BWD_BATCH_MAX> chain(end - first, [&](int c) -> const cf_attn_bwd_params & { return *chunks[first + c].b; });
             int place[CF_BWD_BATCH_MAX];
@@ -1116,7 +1132,7 @@ hipError_t run_bwd_batch(const BwdBatchChunk *chunks, int n, hipStream_t s)
                 if (first_of[c] == first && !append(q, *chunks[c].b, chunks[c].ws, g[c], g[c].dkv_blocks)) return hipErrorInvalidConfiguration;
             }
         }
-        const dim3 grid((unsigned)q.first_block[q.n]);
+        const dim3 grid((unsigned)q.blocks.end);
         if (kind[first] == kChain) mfma_dkv_batch_kernel<D, true><<<grid, 256, 0, s>>>(q);
         else if constexpr (D == 128) mfma_dkv_batch_kernel<D, false><<<grid, 256, 0, s>>>(q);
         e = hipGetLastError();

@@ -45,12 +45,13 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     constexpr int KS = D / F::K, DB = D / F::M, KB = BN / F::M, QB = F::N32, TILE_BYTES = Stage<D>::tile_bytes;
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int group = F::group(), col = F::column();
+    const RowArgs a(p);
 
     // Block id -> (tile rank, head).  The key/value head varies fastest so that the workgroups an XCD
     // receives (ids are dealt round-robin over the 8 XCDs) keep re-reading the same K/V head in its L2.
-    const int G = p.n_q_heads / p.n_kv_heads;
-    const int kh = id % p.n_kv_heads;
-    id /= p.n_kv_heads;
+    const int G = a.n_q_heads / a.n_kv_heads;
+    const int kh = id % a.n_kv_heads;
+    id /= a.n_kv_heads;
     const int j = id % G;                            // which of the G workgroups of this (tile, key/value head)
     const int rank = id / G;
     // The tile's 4 G units (32-row block, query head of the group) are dealt out four at a time, block-major:
@@ -61,9 +62,9 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     const int h = kh * G + (unit - blk * G);
 
     int tile_in_seg, q_seg0, lq, k_seg0, lk;
-    if (p.q_tiles != nullptr) {
-        if (rank >= p.n_q_tiles) return;
-        const QTile t = read_q_tile(p.q_tiles, rank);
+    if (a.tiles != nullptr) {
+        if (rank >= a.n_tiles) return;
+        const QTile t = read_q_tile(a.tiles, rank);
         tile_in_seg = t.tile_in_seg, q_seg0 = t.q_begin, lq = t.q_len, k_seg0 = t.k_begin, lk = t.k_len;
     } else {
         TileLocation loc;
@@ -84,9 +85,9 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     const bool wave_active = wq0 < lq;
     const int amax = wq0 + col + off;                // last visible key of this lane's row (block qb: M qb further)
 
-    const int64_t kv_row_bytes = p.kv_stride_tok * 2;
-    const char *kbase = uniform((const char *)p.k + ((int64_t)k_seg0 * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2);
-    const char *vbase = uniform((const char *)p.v + ((int64_t)k_seg0 * p.kv_stride_tok + (int64_t)kh * p.kv_stride_head) * 2);
+    const int64_t kv_row_bytes = a.kv_tok * 2;
+    const char *kbase = uniform(a.k + ((int64_t)k_seg0 * a.kv_tok + (int64_t)kh * a.kv_head) * 2);
+    const char *vbase = uniform(a.v + ((int64_t)k_seg0 * a.kv_tok + (int64_t)kh * a.kv_head) * 2);
     TileDma<BN, D> dma;
     dma.init(kv_row_bytes);
 
@@ -95,7 +96,7 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const int row = q_seg0 + min(wq0 + F::M * qb + col, lq - 1);
-        const char *qrow = (const char *)p.q + ((int64_t)row * p.q_stride_tok + (int64_t)h * p.q_stride_head) * 2;
+        const char *qrow = a.q + ((int64_t)row * a.q_tok + (int64_t)h * a.q_head) * 2;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *(const bf16x8 *)(qrow + ks * 2 * F::K + group * 16);
     }
@@ -278,13 +279,12 @@ __global__ __launch_bounds__(256, 2) void mfma_fwd_kernel(cf_attn_fwd_params p)
     fwd_body<D, M>(p, blockIdx.x, stage_a, stage_b);
 }
 
-// Several chunks in one launch: workgroups [first_block[c], first_block[c+1]) belong to chunk c.  The host
+// Several chunks in one launch.  The host
 // puts the heaviest chunk first, so the last, partly filled wave of workgroups of a big chunk is filled by
 // the next chunk's workgroups instead of leaving compute units idle.
 struct FwdBatch {
-    int n;
     unsigned wide;                // bit c: chunk c multiplies with M = 32
-    int first_block[CF_FWD_BATCH_MAX + 1];
+    Blocks<CF_FWD_BATCH_MAX> blocks;
     cf_attn_fwd_params p[CF_FWD_BATCH_MAX];
 };
 // M = 0: chunks with either M.
@@ -293,11 +293,10 @@ __global__ __launch_bounds__(256, 2) void mfma_fwd_batch_kernel(FwdBatch b)
 {
     __shared__ __attribute__((aligned(16))) char stage_a[Stage<D>::bytes];
     __shared__ __attribute__((aligned(16))) char stage_b[Stage<D>::bytes];
-    const int id = blockIdx.x;
-    int c = 0;
-    while (c + 1 < b.n && id >= b.first_block[c + 1]) ++c;
-    if (M == 32 || (M == 0 && (b.wide >> c & 1))) fwd_body<D, 32>(b.p[c], id - b.first_block[c], stage_a, stage_b);
-    else if constexpr (M != 32) fwd_body<D, 16>(b.p[c], id - b.first_block[c], stage_a, stage_b);
+    int id = blockIdx.x;
+    const int c = b.blocks.chunk_of(id);
+    if (M == 32 || (M == 0 && (b.wide >> c & 1))) fwd_body<D, 32>(b.p[c], id, stage_a, stage_b);
+    else if constexpr (M != 32) fwd_body<D, 16>(b.p[c], id, stage_a, stage_b);
 }
 
 // Upper bound on the number of 128-row tiles: sum_g ceil(Lq_g / BM) <= T / BM + n_segments.
@@ -314,18 +313,14 @@ hipError_t launch_mfma_fwd_batch(const cf_attn_fwd_params *const *chunks, int n,
 {
     if (n < 1 || n > CF_FWD_BATCH_MAX) return hipErrorInvalidValue;
     FwdBatch b;
-    b.n = n;
     b.wide = 0;
-    int64_t total = 0;
+    b.blocks.clear();
     for (int c = 0; c < n; ++c) {
-        b.first_block[c] = (int)total;
         b.p[c] = *chunks[c];
         b.wide |= (unsigned)wide_mfma(*chunks[c]) << c;
-        total += fwd_blocks(*chunks[c]);
-        if (total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+        if (!b.blocks.append(fwd_blocks(*chunks[c]))) return hipErrorInvalidConfiguration;
     }
-    b.first_block[n] = (int)total;
-    const dim3 grid((unsigned)total);
+    const dim3 grid((unsigned)b.blocks.end);
     if (chunks[0]->head_dim == 64) mfma_fwd_batch_kernel<64, 32><<<grid, 256, 0, s>>>(b);
     else if (b.wide == 0) mfma_fwd_batch_kernel<128, 16><<<grid, 256, 0, s>>>(b);
     else if (b.wide == (1u << n) - 1) mfma_fwd_batch_kernel<128, 32><<<grid, 256, 0, s>>>(b);

@@ -36,6 +36,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 #define CF_LDS __attribute__((address_space(3)))
+#define CF_GLOBAL __attribute__((address_space(1)))
+#define CF_CONSTANT __attribute__((address_space(4)))
 
 template <int SIZE>
 struct Mfma {
@@ -296,6 +298,29 @@ __device__ __forceinline__ float scalar(float x)
     return r;
 }
 __device__ __forceinline__ void wait_lds_dma() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+
+// What a workgroup needs of its chunk's arguments to find its rows and to ask for them, loaded together: the compiler fetches an argument
+// where it is first used, each time with a wait of its own, eight or nine in a row before the first row was asked for, now three or four.  Steps, with KeyArgs (dK/dV):
+// 16 packed chunks of 512 tokens, 28 / 4 heads 213 -> 210 us; 16 / 4 heads, D = 64, five chunks of 4096 749 -> 742; 16 packed chunks of 8192
+// 8.87 -> 8.83 ms.
+struct RowArgs {
+    const char *q, *k, *v;
+    int64_t q_tok, q_head, kv_tok, kv_head;          // strides, in elements
+    const cf_q_tile *tiles;
+    int n_tiles, n_q_heads, n_kv_heads;
+    template <typename Params>
+    __device__ __forceinline__ explicit RowArgs(const Params &p)
+        : q_tok(p.q_stride_tok), q_head(p.q_stride_head), kv_tok(p.kv_stride_tok), kv_head(p.kv_stride_head), n_tiles(p.n_q_tiles),
+          n_q_heads(p.n_q_heads), n_kv_heads(p.n_kv_heads)
+    {
+        // (one instruction that all of them go through; the pointers as ones to global and to constant memory, or flat loads would follow)
+        auto q_ = (const CF_GLOBAL char *)p.q, k_ = (const CF_GLOBAL char *)p.k, v_ = (const CF_GLOBAL char *)p.v;
+        auto tiles_ = (const CF_CONSTANT cf_q_tile *)p.q_tiles;
+        asm("" : "+s"(q_), "+s"(k_), "+s"(v_), "+s"(q_tok), "+s"(q_head), "+s"(kv_tok), "+s"(kv_head), "+s"(tiles_), "+s"(n_tiles),
+                 "+s"(n_q_heads), "+s"(n_kv_heads));
+        q = (const char *)q_, k = (const char *)k_, v = (const char *)v_, tiles = (const cf_q_tile *)tiles_;
+    }
+};
 
 // The 128-row query tile of workgroup rank `rank` from the caller's table (cf_attn_q_tiles: heaviest tile first,
 // each record carries its segment's bounds): one uniform 32-byte read instead of the search of locate_tile.
