@@ -510,6 +510,13 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
     const int t = threadIdx.x, r = t / (D / 4) % rows, c = t % (D / 4);
     unsigned long long left_out[2 / TOGETHER];       // lanes whose row is not finite
     for (int first = 0; first < 2; first += TOGETHER) {
+        // (what the gradients hold already is fetched while the partial results meet: fetched behind that, steps of 13 small calls, 1 head and 4
+        // heads, D = 64, took 45.1 and 46.1 us instead of 44.1 and 44.8, of 3 packed chunks of 600 tokens, 4 heads, D = 128, 88.6 instead of 87.7)
+        const int which = TOGETHER == 1 ? first : t / (rows * (D / 4));
+        const bool mine = t < TOGETHER * rows * (D / 4);
+        f32x4 *to = (f32x4 *)((which ? b.d_k : b.d_v) + (int64_t)(loc.begin + k0 + r) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head + c * 4);
+        f32x4 held = {0.f, 0.f, 0.f, 0.f}, a = held;
+        if (mine) held = *to;
         if (first == 0) lds_turn();
         else __syncthreads();
         if (wave < n_items) {
@@ -517,14 +524,10 @@ __device__ __forceinline__ void f32_dkv_body(const BwdArgs &b, int id, char *sme
             if (first + TOGETHER == 2) write_part<D>(dk, parts + ((TOGETHER - 1) * NW + wave) * S::PART, end_lane);
         }
         __syncthreads();
-        const int which = TOGETHER == 1 ? first : t / (rows * (D / 4));
-        const bool mine = t < TOGETHER * rows * (D / 4);
-        f32x4 a = {0.f, 0.f, 0.f, 0.f};
         if (mine) a = sum_parts<D>(parts + (which - first) * NW * S::PART, n, r, c) * (which ? p.softmax_scale : 1.f);
         const unsigned long long bad = __ballot(!finite(a));
         left_out[first / TOGETHER] = bad;
-        if (mine && (bad & lanes_of_row<D>(end_lane)) == 0)
-            *(f32x4 *)((which ? b.d_k : b.d_v) + (int64_t)(loc.begin + k0 + r) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head + c * 4) += a;
+        if (mine && (bad & lanes_of_row<D>(end_lane)) == 0) *to = held + a;
     }
     for (int pass = 0; pass < 2 / TOGETHER; ++pass)
         for_rows_of<D>(left_out[pass], [&](int at) {
