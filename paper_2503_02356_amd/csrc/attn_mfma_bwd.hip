@@ -536,6 +536,18 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     const int end_lane = fresh_lane(), end_half = end_lane >> 5, end_col = end_lane & 31;
     unsigned not_finite[2] = {0, 0};                 // rows of dV and dK that this wavefront has left out (D = 64; see scalar_rows.h)
     auto add_rows = [&](const f32x16 (&acc)[DB], float scale, float *g, unsigned &left_out) {
+        float *const rows = g + ((int64_t)(k_seg0 + kw0) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head);
+        // FUSED_HEADS: what 8 rows hold already is fetched together, for the first 8 while the results are turned around.  (Row by row, behind
+        // each one's test, it was a latency for each of the 64 rows of dV and dK.  Steps, us: 32 / 32 heads, 4000 tokens in slices of 512 and 2
+        // packed chunks 873 -> 774; 8 / 8 heads, 20000 in slices of 1000 4165 -> 3933; 16 / 4 heads, D = 64, five chunks of 4096 731 -> 718.)
+        float held[8][D / 64];
+        auto fetch_held = [&](int r0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int c = 0; c < D / 64; ++c) held[e][c] = rows[(int64_t)min(r0 + e, rows_valid - 1) * b.dkv_stride_tok + end_lane + 64 * c];
+        };
+        if (FUSED_HEADS && rows_valid > 8 * query_wave) fetch_held(8 * query_wave);
 #pragma unroll
         for (int j = 0; j < DB; ++j)
 #pragma unroll
@@ -546,7 +558,6 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
                 *(f32x4 *)(tr + end_col * D + (((j * 8 + g4 * 2 + end_half) ^ (end_col & 15)) << 2)) = a;
             }
         meet();
-        g += (int64_t)(k_seg0 + kw0) * b.dkv_stride_tok + (int64_t)kh * b.dkv_stride_head;
         // 8 rows per step: all LDS reads first, then the global updates (one LDS latency per step)
         for (int r0 = 8 * query_wave; r0 < rows_valid; r0 += 8 * QW) {
             float v[8][D / 64];
@@ -564,14 +575,15 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
                 const bool leave = D == 64 && __ballot(!finite(v[e][0])) != 0;
                 if (leave && r0 + e < rows_valid) left_out |= 1u << (r0 + e);
                 if (!leave && r0 + e < rows_valid) {
-                    float *row = g + (int64_t)(r0 + e) * b.dkv_stride_tok + end_lane;
+                    float *row = rows + (int64_t)(r0 + e) * b.dkv_stride_tok + end_lane;
 #pragma unroll
                     for (int c = 0; c < D / 64; ++c) {
-                        if (FUSED_HEADS) row[64 * c] += v[e][c];
+                        if (FUSED_HEADS) row[64 * c] = held[e][c] + v[e][c];
                         else unsafeAtomicAdd(row + 64 * c, v[e][c]);
                     }
                 }
             }
+            if (FUSED_HEADS && r0 + 8 * QW < rows_valid) fetch_held(r0 + 8 * QW);
         }
         meet();
     };
@@ -1028,8 +1040,8 @@ bool append(BwdBatch &q, const cf_attn_bwd_params &b, const BwdWorkspace &ws, co
 //           together, in any order too: a step of 28 / 4 heads, 4 slices of 512 tokens and 2 packed chunks 302 -> 234 us, 4 slices
 //           of 1024 and 3 packed chunks 720 -> 580 (slices of 8192: no change, their launches end evenly)
 //   kChain  one writer per row (D = 64), or a list of one item to a key tile: the slices of a sequence go from one to the next in the
-//           workgroup of a key tile.  32 / 32 heads, 4000 tokens in slices of 512 and 2 packed chunks: 868 us a step, 1040 with a launch per
-//           slice (lists in any order: 869); 8 / 8 heads, 20000 tokens in slices of 1000: 4190, 4600 (3810)
+//           workgroup of a key tile.  32 / 32 heads, 4000 tokens in slices of 512 and 2 packed chunks: 774 us a step, 1040 with a launch per
+//           slice (lists in any order: 869); 8 / 8 heads, 20000 tokens in slices of 1000: 3933, 4600 (3810)
 //   kAlone  a launch of its own, in order: one writer per row by the flag or for many key tiles; and lists of one item to a key tile whose
 //           launches end evenly (32 / 32 heads, 16000 tokens in slices of 2000, up to 240 pairs a slot: 8.98 ms a step, as a chain 9.16)
 enum DkvKind { kAlone, kList, kChain };
