@@ -142,26 +142,31 @@ inline bool same_key_rows(const cf_attn_bwd_params &a, const cf_attn_bwd_params 
 // Chains of such calls, each in the order of the calls: where one writer per row adds for all slices of a sequence, these share a
 // launch and every workgroup of the chain's first call goes through the chain (which gives the bits of separate launches).
 //   head[c]  first call of c's chain        next[c]  the call behind c in it, -1: none
-//   order    the calls by the work of their chain (queries x keys), heaviest first, a chain's calls next to each other
+//   order    the calls by the query rows that the first keys of their chain see (of a chunk of several sequences: longest_chain), in steps of
+//            512, then by its work (queries x keys), a chain's calls next to each other.  A launch ends with the workgroup of the most rows:
+//            16 / 4 heads, D = 64, five chunks of 4096, a sequence in two slices among them: by work alone 748 us a step, so 724; four
+//            packed chunks of 4096: 593, 567; where all rows are short, in steps of 1 instead of 512, 1-2 % slower
 template <int MAX>
 struct CallChains {
     int head[MAX], next[MAX], order[MAX];
     template <typename CallAt>
     CallChains(int n, CallAt call)
     {
-        int64_t work[MAX];
+        int64_t work[MAX], longest[MAX];
         for (int c = 0; c < n; ++c) {
             head[c] = order[c] = c;
             next[c] = -1;
             work[c] = work_of(call(c).f);
+            longest[c] = (call(c).f.n_segments == 1 ? call(c).f.n_tokens : longest_chain(call(c).f)) / 512;
             for (int a = c - 1; a >= 0 && head[c] == c; --a)
                 if (same_key_rows(call(a), call(c))) {
                     head[c] = head[a];
                     next[a] = c;
-                    work[head[c]] += work[c];
+                    work[head[c]] += work[c], longest[head[c]] += longest[c];
                 }
         }
         std::stable_sort(order, order + n, [&](int x, int y) {
+            if (longest[head[x]] != longest[head[y]]) return longest[head[x]] > longest[head[y]];
             return work[head[x]] != work[head[y]] ? work[head[x]] > work[head[y]] : head[x] < head[y];
         });
     }
