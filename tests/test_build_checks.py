@@ -81,3 +81,10 @@ def test_products_of_dq_alternate(tmp_path):
     for name, body in kernels:
         mfma = [operands(l.strip())[0] for l in body.splitlines() if l.strip().startswith("v_mfma")]
         assert len(mfma) > 100 and all(a != b for a, b in zip(mfma, mfma[1:])), name
+
+
+def test_lane_reads_in_assembly_wait_for_their_register():
+    """A lane read needs a wait state behind the instruction that wrote its register; the compiler puts none before inline assembly."""
+    reads = [line for name in sorted(os.listdir(build.CSRC)) if name.endswith((".hip", ".h"))
+             for line in open(os.path.join(build.CSRC, name)) if re.search(r"asm.*v_read(first)?lane", line)]
+    assert reads and all(re.search(r'"s_nop \d+\\n\\tv_readfirstlane_b32 [^\\]*"', line) for line in reads), reads
