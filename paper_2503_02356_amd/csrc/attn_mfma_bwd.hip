@@ -38,19 +38,24 @@ constexpr float kLog2e = 1.44269504088896340736f;
 // =====================================================================================================
 // dK / dV
 // =====================================================================================================
-// How the four wavefronts of a workgroup divide a tile: KW groups of 32 keys, QW wavefronts each that take every QW-th 32-row
-// block of the query tile (their partial results meet in LDS at the end, in a fixed order).
-// D = 128: 128 keys per workgroup; query heads are split over work items where that fills the chip, through atomic adds.
-// D = 64: every dK/dV row has one writer, so no workgroup may share its keys with another: few keys and a long query tile
-// shorten the chain that one workgroup is.  Step of 16 / 4 heads, 16.7k tokens: 0.99 ms with 32 keys x 128 rows a tile, 1.03
-// with 64 x 128, 1.06 with 64 x 64, 1.32 with 128 x 64 (0.95 with split heads and atomic adds).
+// How the four wavefronts of a workgroup divide its work: KW groups of 32 keys, QW wavefronts each.
+// D = 128: 128 keys per workgroup, whose wavefronts read the same query tiles; query heads are split over work items where that fills
+// the chip, through atomic adds.
+// D = 64: every dK/dV row has one writer, so no workgroup may share its keys with another: few keys shorten the chain that one workgroup
+// is.  The four wavefronts take the 32-row blocks of all the group's heads in turn, one each, and add up in LDS at the end, in a fixed
+// order.  No two of them read the same rows, so that each copies its own into its own part of LDS (OWN) and waits for nobody until
+// the end.  Steps, us, against tiles of 128 rows of a head that the four copied together, with a barrier for each (wavefronts without rows
+// at a head's end waited there): 16 / 4 heads, five chunks of 4096 697 -> 686; 8 / 2 heads, 4500 tokens in slices of 2048 and 3 packed
+// chunks 405 -> 393; 6 / 2 heads, 2700 in slices of 1000 and 3 packed chunks 226 -> 218; one head, 700 in slices of 256 59.8 -> 58.4.
+// (Eight wavefronts to 32 keys, one workgroup a compute unit: 710, 339, 194, 59.8, but 4 / 4 heads packed around 50 40 for 36: half of them
+// have nothing to do in a short sequence.  64 or 128 keys took 4-30 % longer than 32, split heads with atomic adds 4 % less.)
 template <int D>
 struct DkvShape {
     static constexpr int KW = D == 64 ? 1 : 4, QW = 4 / KW;
     static constexpr int BKV = 32 * KW;               // key rows per workgroup
-    static constexpr int BQ = D == 64 ? 128 : 64;    // query rows per tile
-    static constexpr int BLOCKS = BQ / 32 / QW;       // of a tile, per wavefront
-    static_assert(BLOCKS == 1 || BLOCKS == 2, "do_tile");
+    static constexpr bool OWN = QW > 1;               // every wavefront has tiles of its own
+    static constexpr int BQ = OWN ? 32 : 64;          // query rows per tile
+    static constexpr int BLOCKS = BQ / 32;
 };
 constexpr int BQ = DkvShape<128>::BQ, BKV = DkvShape<128>::BKV;
 
@@ -193,14 +198,15 @@ __device__ __forceinline__ void build_dkv_worklist(const BwdArgs::Fwd &p, int *w
     if (tid == 0) wl[0] = min(n_items, capacity);
 }
 
-// One stage: Q tile, dO tile, LSE[64] (log2 units), -delta[64] (the dQ kernel stores it negated).  Two stages also hold the end-of-kernel transpose
-// scratch (32 rows of D floats per wavefront).
+// One stage: Q tile, dO tile, LSE[64] (log2 units), -delta[64] (the dQ kernel stores it negated); OWN: one for each wavefront.  Two stages
+// (OWN: a wavefront's part of the first) also hold the end-of-kernel transpose scratch (32 rows of D floats per wavefront).
 template <int D>
 struct DkvStage {
     static constexpr int BQ = DkvShape<D>::BQ;
-    static constexpr int tile_bytes = BQ * 2 * D, bytes = 2 * tile_bytes + 2 * BQ * 4;
+    static constexpr bool OWN = DkvShape<D>::OWN;
+    static constexpr int tile_bytes = BQ * 2 * D, one = 2 * tile_bytes + 2 * 64 * 4, bytes = DkvShape<D>::QW * one;
     static constexpr int scratch_bytes = 32 * D * 4;
-    static_assert(bytes >= 2 * scratch_bytes, "two wavefronts turn their results around in a stage");
+    static_assert(OWN ? one >= scratch_bytes : bytes >= 2 * scratch_bytes, "wavefronts turn their results around in a stage");
 };
 
 // As RowArgs (mfma_common.h), for this kernel.
@@ -247,6 +253,7 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     using F = Mfma<M>;
     constexpr int KS = D / F::K, DB = D / 32, N = F::N32, BLOCK = 32 * 2 * D;
     constexpr int QW = DkvShape<D>::QW, BQ = DkvShape<D>::BQ, BKV = DkvShape<D>::BKV;
+    constexpr bool OWN = DkvShape<D>::OWN;
     static_assert(FUSED_HEADS || QW == 1, "atomic updates are made by the wavefront that owns the keys");
     const BwdArgs::Fwd &p = b.f;
     const int key_wave = wave / QW, query_wave = wave % QW;
@@ -286,9 +293,17 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     const int qt_end = (lq + BQ - 1) / BQ;
     if (qt_first >= qt_end) return;                  // whole workgroup leaves before any barrier
     if (FUSED_HEADS) n_pairs = G * (qt_end - qt_first);
-    const int n_tiles = n_pairs;                     // (head, query tile) pairs, head by head
-    const int head_first = FUSED_HEADS ? 0 : first_pair / (qt_end - qt_first);
-    const int qt_start = qt_first + first_pair - head_first * (qt_end - qt_first);
+    // (head, query tile) pairs, head by head; OWN: this wavefront's, every QW-th
+    const int n_tiles = OWN ? (n_pairs - query_wave + QW - 1) / QW : n_pairs;
+    int head_first = FUSED_HEADS ? 0 : first_pair / (qt_end - qt_first), qt_start = qt_first + first_pair - head_first * (qt_end - qt_first);
+    auto go_on = [&](int &qt, int &h, int by) {      // to the pair that is `by` further
+        qt += by;
+        while (qt >= qt_end) qt -= qt_end - qt_first, ++h;
+    };
+    if (OWN) {
+        go_on(qt_start, head_first, query_wave);
+        st0 += query_wave * Stage::one, st1 += query_wave * Stage::one;
+    }
     // query tiles below qt_head are RESIDUAL ones for this key tile
     const int qt_head = kt0 == 0 && off < 128 ? (128 - off + BQ - 1) / BQ : 0;
 
@@ -313,43 +328,56 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
 #pragma unroll
         for (int j = 0; j < 16; ++j) dv[i][j] = dk[i][j] = 0.f;
     BlockAddress<D, M> at;                              // of the block in use
-    at.flip(query_wave * BLOCK);
 
     // Tile staging: Q and dO rows, LSE and -delta go straight from global memory into an LDS stage; once they have landed,
-    // wavefront 0 turns LSE into log2 units (+inf for rows past the segment, so that P = 0).  What the copies need of the
+    // wavefront 0 (OWN: each) turns LSE into log2 units (+inf for rows past the segment, so that P = 0).  What the copies need of the
     // lane is made anew per tile: every register counts (a spilled one would be reloaded behind the copies in flight,
     // and the wait for it would be a wait for them).
     int nx_h = kh * G + head_first, nx_qt = qt_start;            // the tile the next copy fetches (advances by additions only)
     auto issue_tile = [&](char *stage) {
         const int h = nx_h, q0 = nx_qt * BQ, lane_ = fresh_lane();
         const int64_t row0 = q_seg0 + q0;
-        TileDma<BQ, D, 4, true> dma;
-        dma.init(args().q_tok * 2, wave, lane_);
+        TileDma<BQ, D, OWN ? 1 : 4, true> dma;
+        dma.init(args().q_tok * 2, OWN ? 0 : wave, lane_);
         dma.issue(uniform(args().q + (row0 * args().q_tok + (int64_t)h * args().q_head) * 2), lq - 1 - q0, stage);
-        dma.init(args().do_tok * 2, wave, lane_);
+        dma.init(args().do_tok * 2, OWN ? 0 : wave, lane_);
         dma.issue(uniform(args().d_o + (row0 * args().do_tok + (int64_t)h * args().do_head) * 2), lq - 1 - q0,
                   stage + Stage::tile_bytes);
-        constexpr int PER = BQ / 64;                 // wavefronts that fetch LSE resp. -delta, 64 rows each
-        if (wave < 2 * PER)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(TileDma<BQ, D>::descriptor((const char *)uniform((wave < PER ? p.lse : delta) + (int64_t)h * p.n_tokens + row0)),
-                                                     (CF_LDS void *)(stage + 2 * Stage::tile_bytes + wave * 256), 4,
-                                                     min(wave % PER * 64 + lane_, lq - 1 - q0) * 4, 0, 0, 0);
-        if (++nx_qt == qt_end) {
-            nx_qt = qt_first;
-            ++nx_h;
+        // LSE and -delta of 64 rows (OWN: the tile's and what lies behind them in the segment)
+        auto issue_stats = [&](const float *from, int which) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(TileDma<64, D>::descriptor((const char *)uniform(from + (int64_t)h * p.n_tokens + row0)),
+                                                     (CF_LDS void *)(stage + 2 * Stage::tile_bytes + which * 256), 4,
+                                                     min(lane_, lq - 1 - q0) * 4, 0, 0, 0);
+        };
+        if (OWN) {
+            issue_stats(p.lse, 0);
+            issue_stats(delta, 1);
+            go_on(nx_qt, nx_h, QW);
+        } else {
+            if (wave < 2) issue_stats(wave < 1 ? p.lse : delta, wave);
+            if (++nx_qt == qt_end) {
+                nx_qt = qt_first;
+                ++nx_h;
+            }
         }
     };
     auto finish_tile = [&](char *stage, int rows) {  // rows: of the segment, in this tile
         wait_lds_dma();
-        if (wave < BQ / 64) {
-            const int row = wave * 64 + fresh_lane();
+        if (OWN || wave == 0) {
+            const int row = fresh_lane();
             float *l = (float *)(stage + 2 * Stage::tile_bytes) + row;
             *l = row < rows ? *l * kLog2e : INFINITY;
         }
     };
-    issue_tile(st0);
-    finish_tile(st0, lq - qt_start * BQ);
-    __syncthreads();
+    auto publish_tile = [] {
+        if (OWN) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        else __syncthreads();
+    };
+    if (!OWN || n_tiles > 0) {
+        issue_tile(st0);
+        finish_tile(st0, lq - qt_start * BQ);
+    }
+    publish_tile();
 
     int cur_qt = qt_start;                           // query tile of the stage in use
     auto do_block = [&](int mb, const char *stage, bool residual) {
@@ -391,7 +419,7 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
         }
 #pragma unroll
         for (int i = 0; i < NS; i += 4) {
-            const f32x4 d4 = *(const f32x4 *)(stats + BQ + F::place(i));
+            const f32x4 d4 = *(const f32x4 *)(stats + 64 + F::place(i));
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -500,13 +528,18 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
             const bool residual = cur_qt < qt_head;
 #pragma unroll 1
             for (int i = 0; i < DkvShape<D>::BLOCKS; ++i) {
-                do_block(query_wave + i * QW, stage, residual);
-                if (DkvShape<D>::BLOCKS == 2) at.flip(QW * BLOCK);
+                do_block(i, stage, residual);
+                if (DkvShape<D>::BLOCKS == 2) at.flip(BLOCK);
             }
         }
-        if (++cur_qt == qt_end) cur_qt = qt_first;
+        if (OWN) {
+            int h = 0;
+            go_on(cur_qt, h, QW);
+        } else if (++cur_qt == qt_end) {
+            cur_qt = qt_first;
+        }
         if (t + 1 < n_tiles) finish_tile(next_stage, lq - cur_qt * BQ);
-        __syncthreads();
+        publish_tile();
     };
     for (int t = 0; t < n_tiles; t += 2) {
         do_tile(t, st0, st1);
@@ -527,7 +560,9 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
         accumulator_done(dv[j]);
         accumulator_done(dk[j]);
     }
-    auto scratch_of = [&](int w) { return (float *)((w < 2 ? st0 : st1) + (w & 1) * Stage::scratch_bytes); };
+    auto scratch_of = [&](int w) {
+        return (float *)(OWN ? st0 + (w - query_wave) * Stage::one : (w < 2 ? st0 : st1) + (w & 1) * Stage::scratch_bytes);
+    };
     auto meet = [] {
         if (QW == 1) __builtin_amdgcn_wave_barrier();
         else __syncthreads();

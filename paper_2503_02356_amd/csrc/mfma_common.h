@@ -224,8 +224,8 @@ __device__ __forceinline__ int fresh_lane()
 // A tile takes ROWS / (RPI * WAVES) instructions per wavefront (PARTS); each costs the issuing wavefront some 30-45 clocks
 // wherever it is placed (measured), so they are simply issued together at the start of a tile.
 // Addressing is the buffer form on purpose: the tile's first row is a wave-uniform pointer that becomes the
-// base of a buffer descriptor (scalar arithmetic), the lane's place inside a tile is ONE register computed
-// at init, and a part adds a scalar offset, so a full tile costs no vector address arithmetic at all.  Only
+// base of a buffer descriptor (scalar arithmetic), the lane's place inside a tile is ONE register (two where a part is half a
+// swizzle period) computed at init, and a part adds a scalar offset, so a full tile costs no vector address arithmetic at all.  Only
 // a ragged tile (rows beyond last_row, relative to src, re-read last_row; the caller masks them) computes
 // clamped per-lane offsets.  The descriptor's size field is left at its maximum: nothing relies on the
 // hardware's out-of-range behaviour.
@@ -236,11 +236,13 @@ template <int ROWS, int D, int WAVES = 4, bool BLOCKS = false>
 struct TileDma {
     static constexpr int RPI = 512 / D, UNITS = D / 8;      // rows per instruction, 16-byte units per row
     static constexpr int PARTS = ROWS / (RPI * WAVES);
-    static_assert(PARTS >= 1 && (RPI * WAVES) % 16 == 0, "a part must cover whole swizzle periods");
-    unsigned row_bytes, unit16;   // unit16: byte offset of this lane's 16-byte unit inside its row (same for all parts)
+    static constexpr int KINDS = (RPI * WAVES) % 16 == 0 ? 1 : 2;     // parts of half a swizzle period: even and odd ones
+    static_assert(PARTS >= 1 && (RPI * WAVES) % 8 == 0, "a part must cover whole swizzle periods or halves");
+    unsigned row_bytes;
+    unsigned unit16[KINDS];       // byte offset of this lane's 16-byte unit inside its row
     int r0;                       // this lane's row in part 0; part c adds RPI * WAVES rows
     int wv;                       // index of this wavefront among the copying ones
-    unsigned lane_off;            // r0 * row_bytes + unit16: this lane's offset in part 0 of a full tile
+    unsigned lane_off[KINDS];     // r0 * row_bytes + unit16: this lane's offset in a part of a full tile, from the part's first row
 
     // wave: index of the calling wavefront among the WAVES that copy (wave-uniform)
     __device__ __forceinline__ void init(int64_t row_bytes_, int wave, int lane)
@@ -248,8 +250,11 @@ struct TileDma {
         row_bytes = (unsigned)row_bytes_;
         wv = wave;
         r0 = RPI * wave + lane / UNITS;
-        unit16 = ((lane % UNITS) ^ swz<D>(r0)) * 16; // swz() has period 16 rows
-        lane_off = (unsigned)r0 * row_bytes + unit16;
+#pragma unroll
+        for (int i = 0; i < KINDS; ++i) {            // swz() has period 16 rows
+            unit16[i] = ((lane % UNITS) ^ swz<D>(r0 + RPI * WAVES * i)) * 16;
+            lane_off[i] = (unsigned)r0 * row_bytes + unit16[i];
+        }
     }
     __device__ __forceinline__ void init(int64_t row_bytes_) { init(row_bytes_, wave_id(), threadIdx.x & 63); }
     __device__ __forceinline__ CF_LDS void *part_dst(char *lds_tile, int c) const { return (CF_LDS void *)(lds_tile + (c * WAVES + wv) * 1024); }
@@ -259,12 +264,12 @@ struct TileDma {
     }
     __device__ __forceinline__ void full_part(__amdgpu_buffer_rsrc_t rsrc, char *lds_tile, int c) const
     {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, part_dst(lds_tile, c), 16, (int)lane_off, (int)(RPI * WAVES * c * row_bytes), 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, part_dst(lds_tile, c), 16, (int)lane_off[c % KINDS], (int)(RPI * WAVES * c * row_bytes), 0, 0);
     }
     __device__ __forceinline__ void ragged_part(__amdgpu_buffer_rsrc_t rsrc, int last_row, char *lds_tile, int c) const
     {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, part_dst(lds_tile, c), 16,
-                                                 (int)((unsigned)min(r0 + RPI * WAVES * c, last_row) * row_bytes + unit16), 0, 0, 0);
+                                                 (int)((unsigned)min(r0 + RPI * WAVES * c, last_row) * row_bytes + unit16[c % KINDS]), 0, 0, 0);
     }
     // last_row is wave-uniform, so the branch below is a scalar one.
     __device__ __forceinline__ void issue(const char *src, int last_row, char *lds_tile) const

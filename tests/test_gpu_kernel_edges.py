@@ -41,6 +41,15 @@ def test_bf16_blocks(D, lens, C, Hq, Hkv, flags):
     P.check(got, ref, "bf16", f"lens={lens[:9]} C={C} D={D} flags={flags}")
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(1, 1), (3, 1), (5, 1), (14, 2)])
+@pytest.mark.parametrize("lens,C", [([1, 31, 32, 33, 64, 65, 96, 97, 129, 161], 709), ([333], 100)])
+def test_blocks_of_a_group_dealt_to_four_wavefronts(lens, C, Hq, Hkv):
+    """dK/dV at D = 64: the 32-row blocks of all heads of a group go round four wavefronts: fewer blocks than wavefronts, heads of fewer
+    blocks than a round, a last block of one row, slices whose blocks start behind the keys."""
+    got, _ = P.run_gpu(lens, C, Hq, Hkv, 64, "bf16", seed=37)
+    P.check(got, P.run_oracle(lens, Hq, Hkv, 64, "bf16", seed=37), "bf16", f"lens={lens} C={C} heads={Hq}/{Hkv}")
+
+
 @pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp32", 64), ("fp32", 128)])
 @pytest.mark.parametrize("lens,C,Hq,Hkv", [([300, 41, 700, 64, 9, 150], 256, 4, 2), ([40] * 30 + [130] * 5, 600, 2, 2)])
 def test_errors_are_no_larger_than_the_scalar_kernels(dtype, D, lens, C, Hq, Hkv):
