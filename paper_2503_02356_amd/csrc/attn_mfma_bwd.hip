@@ -47,8 +47,10 @@ constexpr float kLog2e = 1.44269504088896340736f;
 // the end.  Steps, us, against tiles of 128 rows of a head that the four copied together, with a barrier for each (wavefronts without rows
 // at a head's end waited there): 16 / 4 heads, five chunks of 4096 697 -> 686; 8 / 2 heads, 4500 tokens in slices of 2048 and 3 packed
 // chunks 405 -> 393; 6 / 2 heads, 2700 in slices of 1000 and 3 packed chunks 226 -> 218; one head, 700 in slices of 256 59.8 -> 58.4.
-// (Eight wavefronts to 32 keys, one workgroup a compute unit: 710, 339, 194, 59.8, but 4 / 4 heads packed around 50 40 for 36: half of them
-// have nothing to do in a short sequence.  64 or 128 keys took 4-30 % longer than 32, split heads with atomic adds 4 % less.)
+// (Eight wavefronts to 32 keys, one workgroup a compute unit, halve the chain: calls of one slice take 4-25 % less, packed chunks 2-10 %
+// more, since short sequences leave half of them idle.  By a rule on the call, as the bits have to follow from it alone, a step's slices and
+// packed chunks need a launch each, and that costs more than it gives: 705 -> 743, 401 -> 403, 219 -> 219, 58.6 -> 66.0.
+// 64 or 128 keys took 4-30 % longer than 32, split heads with atomic adds 4 % less.)
 template <int D>
 struct DkvShape {
     static constexpr int KW = D == 64 ? 1 : 4, QW = 4 / KW;
