@@ -45,7 +45,9 @@ __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, ch
     constexpr int KS = D / F::K, DB = D / F::M, KB = BN / F::M, QB = F::N32, TILE_BYTES = Stage<D>::tile_bytes;
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int group = F::group(), col = F::column();
-    const RowArgs a(p);
+    // (not where M = 32 at D = 128: few workgroups with long chains, whose loop, of the same instructions, then takes other registers: 8 / 2
+    // heads, 250 rows behind 100000 keys 1642 us for 1596)
+    const RowArgs a(p, D == 64 || M == 16);
 
     // Block id -> (tile rank, head).  The key/value head varies fastest so that the workgroups an XCD
     // receives (ids are dealt round-robin over the 8 XCDs) keep re-reading the same K/V head in its L2.

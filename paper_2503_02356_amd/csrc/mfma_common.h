@@ -316,14 +316,15 @@ struct RowArgs {
     const cf_q_tile *tiles;
     int n_tiles, n_q_heads, n_kv_heads;
     template <typename Params>
-    __device__ __forceinline__ explicit RowArgs(const Params &p)
+    __device__ __forceinline__ explicit RowArgs(const Params &p, bool together = true)
         : q_tok(p.q_stride_tok), q_head(p.q_stride_head), kv_tok(p.kv_stride_tok), kv_head(p.kv_stride_head), n_tiles(p.n_q_tiles),
           n_q_heads(p.n_q_heads), n_kv_heads(p.n_kv_heads)
     {
         // (one instruction that all of them go through; the pointers as ones to global and to constant memory, or flat loads would follow)
         auto q_ = (const CF_GLOBAL char *)p.q, k_ = (const CF_GLOBAL char *)p.k, v_ = (const CF_GLOBAL char *)p.v;
         auto tiles_ = (const CF_CONSTANT cf_q_tile *)p.q_tiles;
-        asm("" : "+s"(q_), "+s"(k_), "+s"(v_), "+s"(q_tok), "+s"(q_head), "+s"(kv_tok), "+s"(kv_head), "+s"(tiles_), "+s"(n_tiles),
+        if (together)
+            asm("" : "+s"(q_), "+s"(k_), "+s"(v_), "+s"(q_tok), "+s"(q_head), "+s"(kv_tok), "+s"(kv_head), "+s"(tiles_), "+s"(n_tiles),
                  "+s"(n_q_heads), "+s"(n_kv_heads));
         q = (const char *)q_, k = (const char *)k_, v = (const char *)v_, tiles = (const cf_q_tile *)tiles_;
     }
