@@ -712,10 +712,6 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
 {
     using F = Mfma<M>;
     constexpr int KS = D / F::K, DB = D / F::M, N = F::N32, KVTILE_BYTES = KvStage<D>::tile_bytes;
-    // dP's accumulators start at -delta, one for the four registers of a query (M = 32: sixteen, which there is no room for): a subtraction
-    // less per element.  32768-token sequence in slices of 8192 and 8 packed chunks, 28 / 4 heads: 33.25 -> 32.95 ms a step; a call
-    // of 8192 rows behind 24576 keys: 9.76 -> 9.60.
-    constexpr bool FROM_DELTA = M == 16;
     const BwdArgs::Fwd &p = b.f;
     const int wave = wave_id(), group = F::group(), col = F::column();
     const RowArgs a(p);
@@ -848,11 +844,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
 #pragma unroll
                     for (int kb = 0; kb < N; ++kb)
 #pragma unroll
-                        for (int qb = 0; qb < N; ++qb) {
-                            s[kb][qb] = F::zero();
-#pragma unroll
-                            for (int i = 0; i < F::R; ++i) dp[kb][qb][i] = FROM_DELTA && !DELTA_PASS ? -dlt[qb] : 0.f;
-                        }
+                        for (int qb = 0; qb < N; ++qb) s[kb][qb] = dp[kb][qb] = F::zero();
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -884,7 +876,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
                             for (int i = 0; i < NS; ++i) {
                                 const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i / F::R][qb][i % F::R], c2, -lse2[qb]));
                                 if (DELTA_PASS) dsum[qb] += pv * dp[i / F::R][qb][i % F::R];
-                                else dp[i / F::R][qb][i % F::R] = pv * (dp[i / F::R][qb][i % F::R] - (FROM_DELTA ? 0.f : dlt[qb]));
+                                else dp[i / F::R][qb][i % F::R] = pv * (dp[i / F::R][qb][i % F::R] - dlt[qb]);
                             }
                     } else
 #pragma unroll
@@ -896,7 +888,7 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
                             if (hidden) pv = 0.f;
                             // (dP of a hidden pair may be anything)
                             if (DELTA_PASS) dsum[qb] += D == 64 && hidden ? 0.f : pv * dp[i / F::R][qb][i % F::R];
-                            else dp[i / F::R][qb][i % F::R] = pv * (dp[i / F::R][qb][i % F::R] - (FROM_DELTA ? 0.f : dlt[qb]));
+                            else dp[i / F::R][qb][i % F::R] = pv * (dp[i / F::R][qb][i % F::R] - dlt[qb]);
                         }
                     if (DELTA_PASS) continue;
                     // dQ^T += K^T dS^T : contraction over these 32 keys in groups of K

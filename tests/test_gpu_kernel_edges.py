@@ -324,6 +324,35 @@ def test_forward_and_backward_in_turns(dtype, D, one_slot):
             assert torch.equal(a, b) if (dtype, D) != ("bf16", 128) else ((a - b).norm() / a.norm()).item() <= 40 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("Hq,T", [(32, 130), (4, 130), (32, 300)])
+@pytest.mark.parametrize("together", [False, True])
+def test_dp_is_summed_before_delta_is_taken_off(Hq, T, together):
+    """dQ at D = 128, both sizes of MFMA: of delta = -1 and dP = 2^-8 + 4 x 2^-25, a 2^-25 from every 32 columns, dP - delta is
+    1 + 2^-8 + 2^-23, which fp32 holds and which rounds up to the bf16 1 + 2^-7.  A sum that starts at -delta loses each 2^-25 and is left
+    with 1 + 2^-8, half way, which rounds to 1.  Q = 0 and LSE = 0 make every P 1, one key's K = 1 brings its dS into dQ; the rows are far
+    enough from the start of the sequence for delta to be <dO, O>."""
+    D, prefix, bf16 = 128, 200, torch.bfloat16
+    dev = lambda *shape, dtype=bf16, value=0: torch.full(shape, value, dtype=dtype, device="cuda:0")
+    q, o, d_o, k, v = dev(T, Hq, D), dev(T, Hq, D), dev(T, Hq, D, value=1), dev(prefix + T, 4, D), dev(prefix + T, 4, D)
+    o[:, :, 0] = -1
+    k[5, :, 0] = 1
+    v[5, :, 0] = 2.0 ** -8
+    v[5, :, 1::32] = 2.0 ** -25
+    lse, dq, dkv = dev(Hq, T, dtype=torch.float32), dev(T, Hq, D), dev(2, prefix + T, 4, D, dtype=torch.float32)
+    cu = [torch.tensor([0, n], dtype=torch.int32, device="cuda:0") for n in (T, prefix + T)]
+    f = B.make_fwd_params(q, k, v, o, lse, *cu, 1.0)
+    calls = []
+    for _ in range(2 if together else 1):
+        ws = torch.empty(B.cf_attn_bwd_workspace_bytes(f), dtype=torch.uint8, device="cuda:0")
+        calls.append((True, B.make_bwd_params(f, d_o, torch.full_like(dq, float("nan")), dkv[0], dkv[1], ws)))
+    B.cf_attn_calls(B.make_calls(calls))
+    torch.cuda.synchronize()
+    want = dev(T, Hq, D)
+    want[:, :, 0] = 1 + 2.0 ** -7
+    for _, b in calls:
+        assert torch.equal(b._keepalive[2], want)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 def test_calls_that_depend_on_each_other(dtype):
     """The second forward takes the first one's output as its queries; the list stops at a call that is refused."""
