@@ -35,19 +35,22 @@ struct Stage {
     static constexpr int bytes = 2 * tile_bytes;     // K then V
 };
 
-// id: index of the workgroup among those of this chunk
+// id: index of the workgroup among those of this chunk; SHARED: of several chunks in a launch
 // D = 64 keeps what the scalar kernels keep in fp32: the second product takes P with all its 24 bits, as three bf16 operands
 // (three MFMAs), exponentials and row sums are formed so that the errors of O and LSE against fp64 are no larger than theirs.
-template <int D, int M>
+template <int D, int M, bool SHARED>
 __device__ __forceinline__ void fwd_body(const cf_attn_fwd_params &p, int id, char *stage_a, char *stage_b)
 {
     using F = Mfma<M>;
     constexpr int KS = D / F::K, DB = D / F::M, KB = BN / F::M, QB = F::N32, TILE_BYTES = Stage<D>::tile_bytes;
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int group = F::group(), col = F::column();
-    // (not where M = 32 at D = 128: few workgroups with long chains, whose loop, of the same instructions, then takes other registers: 8 / 2
-    // heads, 250 rows behind 100000 keys 1642 us for 1596)
-    const RowArgs a(p, D == 64 || M == 16);
+    // (Not at D = 128 for a call alone or where M = 32: the main loop then begins 8 or 16 bytes elsewhere in its cache line, which costs
+    // long calls more than their start gains, also with the very same registers in the loop.  Calls alone, us, together and now: 28 / 4
+    // heads, 250 rows behind 100000 keys 1700 and 1684; 4 / 4, one sequence of 10006 179.1 and 177.3; 14 / 2, 7749 207.7 and 206.9; short
+    // calls 0.1 us the other way, 32 / 32, 182 rows 7.6 and 7.7.  M = 32: 8 / 2 heads, 250 rows behind 100000 keys 1642 and 1596.  D = 64,
+    // alone: 16 / 4 heads, 4096 packed around 300 19.5 together, 19.9 not; 6 / 2, 500 rows behind 9000 keys 172.7 and 174.0.)
+    const RowArgs a(p, D == 64 || (SHARED && M == 16));
 
     // Block id -> (tile rank, head).  The key/value head varies fastest so that the workgroups an XCD
     // receives (ids are dealt round-robin over the 8 XCDs) keep re-reading the same K/V head in its L2.
@@ -278,7 +281,7 @@ __global__ __launch_bounds__(256, 2) void mfma_fwd_kernel(cf_attn_fwd_params p)
     // loads of the next tile cannot alias the reads of the current one, or it waits for them too early.
     __shared__ __attribute__((aligned(16))) char stage_a[Stage<D>::bytes];
     __shared__ __attribute__((aligned(16))) char stage_b[Stage<D>::bytes];
-    fwd_body<D, M>(p, blockIdx.x, stage_a, stage_b);
+    fwd_body<D, M, false>(p, blockIdx.x, stage_a, stage_b);
 }
 
 // Several chunks in one launch.  The host
@@ -297,8 +300,8 @@ __global__ __launch_bounds__(256, 2) void mfma_fwd_batch_kernel(FwdBatch b)
     __shared__ __attribute__((aligned(16))) char stage_b[Stage<D>::bytes];
     int id = blockIdx.x;
     const int c = b.blocks.chunk_of(id);
-    if (M == 32 || (M == 0 && (b.wide >> c & 1))) fwd_body<D, 32>(b.p[c], id, stage_a, stage_b);
-    else if constexpr (M != 32) fwd_body<D, 16>(b.p[c], id, stage_a, stage_b);
+    if (M == 32 || (M == 0 && (b.wide >> c & 1))) fwd_body<D, 32, true>(b.p[c], id, stage_a, stage_b);
+    else if constexpr (M != 32) fwd_body<D, 16, true>(b.p[c], id, stage_a, stage_b);
 }
 
 // Upper bound on the number of 128-row tiles: sum_g ceil(Lq_g / BM) <= T / BM + n_segments.
