@@ -295,14 +295,13 @@ __device__ __forceinline__ T *uniform(T *p)
 }
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 // A float that is the same in every lane, in a scalar register (what the vector unit computed would stay in a vector
-// register: scalar float arithmetic does not exist here, and a readfirstlane of a uniform value is folded away).  The wait state that a
-// lane read of a just written register needs is part of the assembly: the compiler puts none before what it cannot see into, and the
-// read then takes what the register held before.
+// register: scalar float arithmetic does not exist here, and a readfirstlane of a uniform value is folded away, so the value passes
+// through assembly of no instruction first).  The read itself is the compiler's: it needs a wait state behind the instruction that wrote
+// its register, and what uses its result up to five behind it, which the compiler keeps for its own instructions only.
 __device__ __forceinline__ float scalar(float x)
 {
-    float r;
-    asm("s_nop 0\n\tv_readfirstlane_b32 %0, %1" : "=s"(r) : "v"(x));
-    return r;
+    asm("" : "+v"(x));
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
 }
 __device__ __forceinline__ void wait_lds_dma() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
