@@ -157,7 +157,7 @@ struct CallChains {
             head[c] = order[c] = c;
             next[c] = -1;
             work[c] = work_of(call(c).f);
-            longest[c] = (call(c).f.n_segments == 1 ? call(c).f.n_tokens : longest_chain(call(c).f)) / 512;
+            longest[c] = call(c).f.n_segments == 1 ? call(c).f.n_tokens : longest_chain(call(c).f);
             for (int a = c - 1; a >= 0 && head[c] == c; --a)
                 if (same_key_rows(call(a), call(c))) {
                     head[c] = head[a];
@@ -166,7 +166,8 @@ struct CallChains {
                 }
         }
         std::stable_sort(order, order + n, [&](int x, int y) {
-            if (longest[head[x]] != longest[head[y]]) return longest[head[x]] > longest[head[y]];
+            const int64_t lx = longest[head[x]] / 512, ly = longest[head[y]] / 512;      // (of the whole chain: its slices may be shorter than a step)
+            if (lx != ly) return lx > ly;
             return work[head[x]] != work[head[y]] ? work[head[x]] > work[head[y]] : head[x] < head[y];
         });
     }
