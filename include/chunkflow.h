@@ -324,13 +324,14 @@ int cf_attn_bwd_batch(const cf_attn_bwd_params *params, int32_t n, void *hip_str
 
 /*
  * n calls, as if in order, on one stream: calls[i].backward ? cf_attn_bwd(calls[i].params) : cf_attn_fwd(calls[i].params),
- * with params a cf_attn_bwd_params resp. cf_attn_fwd_params.  Results as of n separate calls (dK/dV as in
- * cf_attn_bwd_batch), which this saves the way
- * into the library (for a caller in an interpreted language longer than the launch itself); calls
- * that do not touch each other's results -- backward ones with workspaces of their own among them -- share launches as
- * in cf_attn_fwd_batch / cf_attn_bwd_batch, and for that a call is enqueued before others that it has nothing to do with.  (cu_seqlens and q_tiles are descriptors: no call of the list writes them.)
- * Stops at the first call that fails and returns its error; the calls before it have been enqueued.  n < 0, NULL calls
- * with n > 0 -> CF_EINVAL.
+ * with params a cf_attn_bwd_params resp. cf_attn_fwd_params.  Results as of n separate calls (dK/dV as in cf_attn_bwd_batch), which
+ * this saves the way into the library (for a caller in an interpreted language longer than the launch itself); calls that do not
+ * touch each other's results -- backward ones with workspaces of their own among them -- share launches as in cf_attn_fwd_batch /
+ * cf_attn_bwd_batch, and for that a call is enqueued before others that it has nothing to do with.  (cu_seqlens and q_tiles are
+ * descriptors: no call of the list writes them.)
+ * Stops at the first call that fails its checks, or that asks for more than a launch holds, and returns its error; the calls before
+ * it have been enqueued, those behind it have not.  After any other CF_EHIP (an error of the device, say) any of the 64 calls around
+ * the one that failed may have been enqueued or not.  n < 0, NULL calls with n > 0 -> CF_EINVAL.
  */
 typedef struct {
     const void *params;

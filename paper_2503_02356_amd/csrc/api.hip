@@ -210,7 +210,7 @@ struct Call {
     cf::BwdWorkspace ws;
     Path path;
     uint64_t kernel;             // the same in calls that can share launches; 0: it shares none
-    int64_t size;                // work-items of its largest launch (on the matrix kernels)
+    int64_t size;                // work-items of its largest launch
 
     Call() = default;
     explicit Call(const cf_attn_fwd_params *fwd)
@@ -223,7 +223,10 @@ private:
     {
         return path == kScalar ? 0 : (uint64_t)path << 48 | (uint64_t)(b != nullptr) << 40 | (uint64_t)f->head_dim << 32 | (uint64_t)f->n_q_heads << 16 | (uint64_t)f->n_kv_heads;
     }
-    int64_t size_of() const { return path == kMfma ? cf::mfma_launch_size(*f, b != nullptr) : cf::f32_launch_size(*f, b != nullptr); }
+    int64_t size_of() const
+    {
+        return path == kMfma ? cf::mfma_launch_size(*f, b != nullptr) : path == kF32 ? cf::f32_launch_size(*f, b != nullptr) : cf::simple_launch_size(*f, b != nullptr);
+    }
 };
 bool same_kernel(const Call &a, const Call &c) { return a.kernel != 0 && a.kernel == c.kernel; }
 
@@ -350,7 +353,7 @@ int launch_calls(const Call *in, int n, hipStream_t s, const char *who)
         order[i] = i;
         keep = keep && same_kernel(in[0], in[i]);
     }
-    for (int i = 0; i < n && !keep; ++i) keep = in[i].path != kScalar && in[i].size > cf::kMostWorkItems;
+    for (int i = 0; i < n && !keep; ++i) keep = in[i].size > cf::kMostWorkItems;
     if (!keep) bring_together(in, touches, n, order);
     for (int i = 0; i < n; ++i) calls[i] = in[order[i]], t[i] = touches[order[i]];
     for (int i = 0; i < n;) {

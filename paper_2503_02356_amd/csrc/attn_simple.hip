@@ -15,7 +15,7 @@
 namespace cf {
 namespace {
 
-constexpr int kWaves = 4;  // wavefronts per workgroup
+constexpr int kWaves = kScalarWaves;  // wavefronts per workgroup
 
 // Largest g in [0, n) with cu[g] <= row  (cu non-decreasing, cu[0] = 0, zero-length segments skipped).
 __device__ inline int find_segment(const int32_t *cu, int n, int row)

@@ -35,6 +35,15 @@ int64_t f32_launch_size(const cf_attn_fwd_params &p, bool backward);
 int64_t mfma_launch_size(const cf_attn_fwd_params &p, bool backward);
 int64_t mfma_bwd_blocks(const cf_attn_fwd_params &p);
 constexpr int64_t kMostWorkItems = 0xffffffffLL;
+// On the scalar kernels, the last resort, where the runtime refuses a call of more: the work-items of the longest row of workgroups, a
+// wavefront to a row of Q or of K, to each of the first 64 rows of a segment (delta of the rows with few keys) or to four deltas.
+constexpr int kScalarWaves = 4;      // wavefronts per workgroup
+inline int64_t simple_launch_size(const cf_attn_fwd_params &p, bool backward)
+{
+    auto of = [](int64_t wavefronts) { return (wavefronts + kScalarWaves - 1) / kScalarWaves * (kScalarWaves * 64); };
+    if (!backward) return of(p.n_tokens);
+    return std::max({of(p.n_kv_tokens), of((int64_t)p.n_segments * 64), of(((int64_t)p.n_tokens * p.n_q_heads + 3) / 4)});
+}
 
 // fp32 matrix kernels, head_dim 64 and 128; the backward is one launch and needs no scratch.
 hipError_t launch_f32_fwd(const cf_attn_fwd_params &p, hipStream_t s);
