@@ -320,9 +320,10 @@ int launch_together(const Call *calls, const Touched *t, int n, hipStream_t s, c
 // Brings calls of one kernel together: a call moves forward, behind the last one of the run that it joins, past calls of other kernels that
 // it has nothing to do with (neither reads or writes what the other writes, no common gradient rows).  order: of t, from the first call to
 // the last; calls of one kernel keep theirs.  Algorithm 2's second half asks for forward and backward in turns (one kept chunk: a slice's
-// forward again, its backward, the slice before it, ...): launches of one slice each, which fill the chip in part.  Steps, us: one sequence
-// of 32768 in slices of 2048, 28 / 4 heads, one kept chunk: 36510 -> 34690; 9000 in slices of 1024, two kept: 3564 -> 2648; 8000 in slices
-// of 512, 8 / 2 heads, one kept: 3738 -> 1080.
+// forward again, its backward, the slice before it, ...): launches of one slice each, which fill the chip in part.  Steps, us: a sequence
+// of 32768 in slices of 2048 and a packed chunk, 28 / 4 heads, one kept chunk: 35590 -> 33920 (host time of the list 145-210 -> 24: its 34
+// launches become 4); 9000 in slices of 1024 and 2 packed chunks, two kept: 3524 -> 2605; 8000 in slices of 512 and 2 packed chunks, 8 / 2
+// heads, one kept: 3737 -> 1071.
 void bring_together(const Call *calls, const Touched *t, int n, int *order)
 {
     bool placed[kWindow] = {};

@@ -45,8 +45,8 @@ constexpr float kLog2e = 1.44269504088896340736f;
 // is.  The four wavefronts take the 32-row blocks of all the group's heads in turn, one each, and add up in LDS at the end, in a fixed
 // order.  No two of them read the same rows, so that each copies its own into its own part of LDS (OWN) and waits for nobody until
 // the end.  Steps, us, against tiles of 128 rows of a head that the four copied together, with a barrier for each (wavefronts without rows
-// at a head's end waited there): 16 / 4 heads, five chunks of 4096 697 -> 686; 8 / 2 heads, 4500 tokens in slices of 2048 and 3 packed
-// chunks 405 -> 393; 6 / 2 heads, 2700 in slices of 1000 and 3 packed chunks 226 -> 218; one head, 700 in slices of 256 59.8 -> 58.4.
+// at a head's end waited there): 16 / 4 heads, five chunks of 4096 686 -> 675; 8 / 2 heads, 4500 tokens in slices of 2048 and 3 packed
+// chunks 405 -> 394; 6 / 2 heads, 2700 in slices of 1000 and 3 packed chunks 225 -> 218; one head, 700 in slices of 256 60.2 -> 58.8.
 // (Eight wavefronts to 32 keys, one workgroup a compute unit, halve the chain: calls of one slice take 4-25 % less, packed chunks 2-10 %
 // more, since short sequences leave half of them idle.  By a rule on the call, as the bits have to follow from it alone, a step's slices and
 // packed chunks need a launch each, and that costs more than it gives: 705 -> 743, 401 -> 403, 219 -> 219, 58.6 -> 66.0.
@@ -549,9 +549,10 @@ __device__ __forceinline__ void dkv_body(const BwdArgs &b, const float *__restri
     }
 
     // dK, dV: lane = key row; register group g4 of accumulator j = 4 consecutive d starting at 32*j + 8*g4 + 4*half.
-    // Each wavefront turns its 32 x D blocks around in LDS (its own half of a stage, free after the loop's last
-    // barrier; unit u of row r at u ^ (r & 15)) and then updates whole rows, 64 lanes = 64 consecutive floats: a
-    // lane-per-row update would touch 64 cache lines per instruction.
+    // Each wavefront turns its 32 x D blocks around in LDS (unit u of row r at u ^ (r & 15)) and then updates whole rows, 64 lanes = 64
+    // consecutive floats: a lane-per-row update would touch 64 cache lines per instruction.  The room for it is the wavefront's half of a
+    // stage, free after the loop's last barrier; OWN: its own part of the first stage, which no other wavefront touches before meet(), and
+    // which it has read for the last time itself.
     //   FUSED_HEADS : this workgroup is the only writer of these rows in this launch: plain load, add, store.
     //   otherwise   : the query heads of a group add into the same rows: fp32 atomic adds.
     // QW > 1: the partial results of a key group's wavefronts are added in their order, each of them writes every QW-th group of 8 rows.
@@ -714,6 +715,8 @@ __device__ __forceinline__ void dq_body(const BwdArgs &b, float *__restrict__ de
     constexpr int KS = D / F::K, DB = D / F::M, N = F::N32, KVTILE_BYTES = KvStage<D>::tile_bytes;
     const BwdArgs::Fwd &p = b.f;
     const int wave = wave_id(), group = F::group(), col = F::column();
+    // (calls alone, us, against arguments loaded where they are used: 28 / 4 heads, 512 packed around 37 37.2 -> 36.4; 14 / 2, 1747 around 73
+    // 51.6 -> 50.9; 28 / 4, 8192 around 600 227.0 -> 227.5; long ones within 0.3 %)
     const RowArgs a(p);
 
     const int G = a.n_q_heads / a.n_kv_heads;

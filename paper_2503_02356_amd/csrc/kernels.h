@@ -129,7 +129,9 @@ struct Blocks {
 // known here; the longest is taken for four times that (ten lengths of a lognormal distribution, sigma 0.9), and a prefix is one
 // sequence's.  Against the order by queries x keys, us a step: 16 / 4 heads, D = 64, five chunks of 4096 tokens, one of them 904 rows behind
 // 4096 keys: 935 -> 758 (compute units idle half of forward and dQ before); 28 / 4 heads, four packed chunks of 2048: 409 -> 384; eight chunks
-// of 8192: no change.
+// of 8192: no change.  Other spreads, 28 / 4 heads, chunks of 2048: all sequences of 500 or all of 100 242.0 and 275.5 either way; one of 1500
+// and ten of 50 in every chunk 399.2 and 399.9; D = 64, a sequence of 5000 in slices and thirty of 400 762 -> 573; where the estimate errs, two
+// chunks of one of 1800 and six of 40 beside two of four of 500, 369 -> 383.
 inline int64_t longest_chain(const cf_attn_fwd_params &p)
 {
     const int64_t own = p.n_segments == 1 ? p.n_tokens : std::min<int64_t>(p.n_tokens, 4 * (int64_t)p.n_tokens / p.n_segments);

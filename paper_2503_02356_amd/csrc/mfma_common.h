@@ -306,9 +306,9 @@ __device__ __forceinline__ float scalar(float x)
 __device__ __forceinline__ void wait_lds_dma() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
 // What a workgroup needs of its chunk's arguments to find its rows and to ask for them, loaded together: the compiler fetches an argument
-// where it is first used, each time with a wait of its own, eight or nine in a row before the first row was asked for, now three or four.  Steps, with KeyArgs (dK/dV):
-// 16 packed chunks of 512 tokens, 28 / 4 heads 213 -> 210 us; 16 / 4 heads, D = 64, five chunks of 4096 749 -> 742; 16 packed chunks of 8192
-// 8.87 -> 8.83 ms.
+// where it is first used, each time with a wait of its own, eight or nine in a row before the first row was asked for, now three or four.
+// Steps, with KeyArgs (dK/dV): 16 packed chunks of 512 tokens, 28 / 4 heads 213 -> 210 us; 16 / 4 heads, D = 64, five chunks of 4096 749 -> 742;
+// packed chunks of 8192 as before, within the 0.5-1 % that runs of one side differ.
 struct RowArgs {
     const char *q, *k, *v;
     int64_t q_tok, q_head, kv_tok, kv_head;          // strides, in elements

@@ -262,9 +262,9 @@ def test_both_sizes_of_mfma(Hq, Hkv, C):
 
 
 @pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("fp32", 64)])
-def test_the_longest_chain_of_a_list_starts_first(dtype, D):
-    """Forward and dQ start with the chunk of the longest chain, dK/dV with the one of most work: here the last slice of the split
-    sequence (20 rows behind 600 keys) and the packed chunks.  Same bits of O, LSE and dQ as one call at a time, and the oracle's results."""
+def test_results_do_not_depend_on_the_order_in_a_launch(dtype, D):
+    """A list whose launches start with its last call (tests/test_launch_order.py): the last slice of the split sequence, 20 rows behind 600
+    keys, has the longest chain and the least work.  Same bits of O, LSE and dQ as one call at a time, and the oracle's results."""
     lens, C, Hq, Hkv = [620, 150, 140, 10, 130, 100, 70], 300, 4, 2
     got, eng = P.run_gpu(lens, C, Hq, Hkv, D, dtype, seed=35)
     work = {c: ch["T"] * (ch["P"] + ch["T"]) for c, ch in enumerate(eng.chunks)}
